@@ -1568,7 +1568,7 @@ static hipError_t launch_spec_layout(const GemmParams& p, const GemmArgs& a, int
 // 128 x 128), whose co-resident workgroups overlap each other's fill and epilogue.  So long-K GEMMs
 // with few tiles prefer the big tiles, short-K weight gradients the co-resident ones, and a GEMM
 // whose 256 x 256 tile count fills the last round badly a shape that divides better.
-static int compute_units() {
+int compute_units() {
     static int cus = 0;
     if (cus == 0) {
         int dev = 0;

@@ -1,0 +1,335 @@
+// float GEMM for gfx950: C[M,N] = epi(opA(A) opB(B)) on the matrix cores (MFMA 32x32x2 f32: float operands, float
+// accumulation, so nothing is rounded that the generic kernel did not round; only the order of the sums differs).
+//
+// What bounds it.  A 32x32x2 instruction is 64 cycles for two operand registers per lane, so LDS and global bandwidth
+// are far from their limits at any tile and the kernel is bound by the matrix pipe where there is work for all of it,
+// by latency where there is not.  Hence three tiles that differ only in how much of the output one workgroup takes:
+//   128 x 128   2 x 2 wavefronts of 64 x 64                     (many tiles)
+//    64 x 64    2 x 2 wavefronts of 32 x 32
+//    32 x 32    4 wavefronts on the same block, each a quarter of every k-step, added through LDS in wavefront order
+// and K cut into shares (one workgroup per tile and share, float partial sums in the workspace added in share order by
+// gemm_f32_sum_kernel) where even those leave compute units idle.
+//
+// Measured (floor: flops at the 154 TFLOP/s of a large float product): 4096 x 2048 x 2048 262 us (floor 223) on the
+// 128-wide tile, 276 and 318 on the narrower ones; 2048 x 1024 x 1024 41 us (28) on the 64-wide, 44 and 47 on the others;
+// 256 x 512 x 256 4.2 us, a launch's least, on the 32-wide, where the generic kernel with its 64 x 64 tiles of vector
+// arithmetic took 46; 384 x 384 x 16384 55 us (31) in 16 shares of 32-wide tiles.  The estimate in f32_plan is within 5 %
+// of the best (tile, shares) on 33 of 34 such shapes.
+//
+// Pipeline.  K in steps of 32 through an LDS ring filled by buffer_load ... lds (128-byte rows: whole cache lines;
+// everything outside the matrix reads zero), one barrier per step, the loads of step kt + STAGES - 1 issued right after
+// the barrier of step kt.  Operands stay in the layout they have in memory:
+//   K contiguous      rows of 32 k; a lane reads 4 consecutive k of its row (16 bytes)
+//   M or N contiguous rows of the tile's width per k; a lane reads one float per k
+// A k-group is 8 k: instruction j of a group takes k = j from lanes 0..31 and k = 4 + j from lanes 32..63, which is what
+// the 16-byte read of a K-contiguous row delivers.
+#include <hip/hip_runtime.h>
+
+#include <algorithm>
+#include <type_traits>
+
+#include "device_math.h"
+#include "kernels.h"
+#include "lds_dma.h"
+
+namespace tpl {
+
+typedef __attribute__((ext_vector_type(16))) float f32x16;
+
+constexpr int FK = 32;                          // k per stage
+constexpr unsigned F_OOB = 0x80000000u;         // past any operand this kernel takes (below 2 GiB)
+
+template <int WM_, int WN_, int TM_, int TN_, int KW_, int STAGES_>
+struct F32Tile {
+    static constexpr int WM = WM_, WN = WN_, TM = TM_, TN = TN_, KW = KW_, STAGES = STAGES_;
+    static_assert(WM * WN * KW == 4, "four wavefronts");
+    static constexpr int BM = WM * TM * 32, BN = WN * TN * 32;
+    static constexpr int LA = BM / 32, LB = BN / 32;                     // direct loads per thread and stage
+    static constexpr int A_BYTES = BM * FK * 4, STAGE_BYTES = (BM + BN) * FK * 4;
+    static constexpr int LDS_BYTES = STAGES * STAGE_BYTES > (KW > 1 ? 16384 : 0) ? STAGES * STAGE_BYTES : 16384;
+};
+
+struct GemmF32Params {
+    const float* A; const float* B; float* C;
+    const float* bias; const float* resid; float* aux;
+    int M, N, K, lda, ldb, epi;
+    int tiles_m, tiles_n, nk, nk_total;         // nk: k-steps of one share
+    float* partial;                             // [share][M][N], or null
+};
+
+// LDS position (in 16-byte chunks) of the stage tile of an operand of R rows.  K contiguous: chunk c of row r at
+// 8 r + (c ^ (r / 2 % 8)), so 16 rows read at one k lie on all banks.  M/N contiguous: row k holds R / 4 chunks; the two
+// lane halves read rows k and k + 4, which are kept in different halves of the 256-byte bank line.
+template <bool KMAJ, int R> __device__ __forceinline__ void f32_chunk_src(int p, int& row, int& chunk) {
+    if (KMAJ) {
+        row = p >> 3;
+        chunk = (p & 7) ^ ((row >> 1) & 7);
+    } else {
+        constexpr int CPR = R / 4;
+        const int pr = p / CPR, c = p % CPR;
+        if (CPR >= 16) { row = pr; chunk = c ^ (((pr >> 2) & 1) << 3); }
+        else { row = (pr & ~7) | ((pr & 1) << 2) | ((pr >> 1) & 3); chunk = c; }   // physical rows 2 j, 2 j + 1 = k j, j + 4
+    }
+}
+template <bool KMAJ, int R> __device__ __forceinline__ int f32_mn_addr(int k, int mn) {   // byte address, M/N contiguous
+    constexpr int CPR = R / 4;
+    if (CPR >= 16) return k * (R * 4) + ((((mn >> 2) ^ (((k >> 2) & 1) << 3))) << 4) + (mn & 3) * 4;
+    const int pr = (k & ~7) | ((k & 3) << 1) | ((k >> 2) & 1);
+    return pr * (R * 4) + mn * 4;
+}
+
+template <typename T, bool A_KMAJ, bool B_KMAJ>
+__global__ __launch_bounds__(256) void gemm_f32_kernel(GemmF32Params p) {
+    extern __shared__ __attribute__((aligned(16))) char smem[];
+    constexpr int TM = T::TM, TN = T::TN, BM = T::BM, BN = T::BN, LA = T::LA, LB = T::LB, S = T::STAGES;
+    const int t = threadIdx.x, lane = t & 63, half = lane >> 5;
+    const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
+    const int wk = T::KW > 1 ? wave : 0, wm = T::KW > 1 ? 0 : wave / T::WN, wn = T::KW > 1 ? 0 : wave % T::WN;
+    const int ntiles = p.tiles_m * p.tiles_n;
+    const int share = blockIdx.x / ntiles, tile = blockIdx.x - share * ntiles;
+    const int m0 = (tile % p.tiles_m) * BM, n0 = (tile / p.tiles_m) * BN;
+    const int kt0 = share * p.nk;
+    const int nk = p.nk_total - kt0 < p.nk ? p.nk_total - kt0 : p.nk;
+
+    const i32x4 ra = make_rsrc(p.A, (unsigned)((int64_t)(A_KMAJ ? p.M : p.K) * p.lda * 4));
+    const i32x4 rb = make_rsrc(p.B, (unsigned)((int64_t)(B_KMAJ ? p.N : p.K) * p.ldb * 4));
+    const unsigned lds0 = (unsigned)(uintptr_t)(lds_void_ptr)smem;
+    unsigned offa[LA], offb[LB];
+    int ka[LA], kb[LB];                          // k of the chunk inside a stage (K contiguous), 0 otherwise
+#pragma unroll
+    for (int i = 0; i < LA; ++i) {
+        int r, c;
+        f32_chunk_src<A_KMAJ, BM>(t + 256 * i, r, c);
+        const bool ok = A_KMAJ ? m0 + r < p.M : m0 + 4 * c < p.M;
+        offa[i] = ok ? (unsigned)(A_KMAJ ? ((int64_t)(m0 + r) * p.lda + 4 * c) * 4 : ((int64_t)r * p.lda + m0 + 4 * c) * 4) : F_OOB;
+        ka[i] = A_KMAJ ? 4 * c : 0;
+    }
+#pragma unroll
+    for (int i = 0; i < LB; ++i) {
+        int r, c;
+        f32_chunk_src<B_KMAJ, BN>(t + 256 * i, r, c);
+        const bool ok = B_KMAJ ? n0 + r < p.N : n0 + 4 * c < p.N;
+        offb[i] = ok ? (unsigned)(B_KMAJ ? ((int64_t)(n0 + r) * p.ldb + 4 * c) * 4 : ((int64_t)r * p.ldb + n0 + 4 * c) * 4) : F_OOB;
+        kb[i] = B_KMAJ ? 4 * c : 0;
+    }
+    const unsigned sa = A_KMAJ ? 4u : (unsigned)p.lda * 4u, sb = B_KMAJ ? 4u : (unsigned)p.ldb * 4u;   // bytes per k
+    // Stages past the end of the share read through a descriptor of no records, so that the number of loads in flight
+    // never changes.  Rows k >= K of an M/N-contiguous operand lie past its buffer; K-contiguous chunks past K are
+    // checked (they would be the next row's).
+    auto fetch = [&](int s) {
+        const unsigned buf = lds0 + (unsigned)(s % S) * T::STAGE_BYTES + (unsigned)wave * 1024u;
+        const int k0 = (kt0 + s) * FK;
+        i32x4 r = ra;
+        r[2] = __builtin_amdgcn_readfirstlane(s < nk ? ra[2] : 0);
+#pragma unroll
+        for (int i = 0; i < LA; ++i)
+            buffer_load_lds_b128(r, buf + i * 4096, k0 + ka[i] < p.K ? offa[i] + (unsigned)k0 * sa : F_OOB);
+        r = rb;
+        r[2] = __builtin_amdgcn_readfirstlane(s < nk ? rb[2] : 0);
+#pragma unroll
+        for (int i = 0; i < LB; ++i)
+            buffer_load_lds_b128(r, buf + T::A_BYTES + i * 4096, k0 + kb[i] < p.K ? offb[i] + (unsigned)k0 * sb : F_OOB);
+    };
+
+    f32x16 acc[TM][TN];
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.0f;
+
+    auto frag = [&](float (&f)[4], const char* st, int mn, int g, auto kmaj, auto rows) {
+        constexpr bool KM = decltype(kmaj)::value;
+        constexpr int R = decltype(rows)::value;
+        const int row = mn + (lane & 31);
+        if (KM) {
+            const int c = 2 * g + half;
+            const float4 v = *reinterpret_cast<const float4*>(st + row * 128 + ((c ^ ((row >> 1) & 7)) << 4));
+            f[0] = v.x; f[1] = v.y; f[2] = v.z; f[3] = v.w;
+        } else {
+#pragma unroll
+            for (int j = 0; j < 4; ++j) f[j] = *reinterpret_cast<const float*>(st + f32_mn_addr<KM, R>(8 * g + 4 * half + j, row));
+        }
+    };
+    auto group = [&](const char* st, int g) {                     // 8 k: TM TN x 4 matrix instructions
+        float fa[TM][4], fb[TN][4];
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+            frag(fa[i], st, (wm * TM + i) * 32, g, std::integral_constant<bool, A_KMAJ>{}, std::integral_constant<int, BM>{});
+#pragma unroll
+        for (int j = 0; j < TN; ++j)
+            frag(fb[j], st + T::A_BYTES, (wn * TN + j) * 32, g, std::integral_constant<bool, B_KMAJ>{}, std::integral_constant<int, BN>{});
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+#pragma unroll
+            for (int i = 0; i < TM; ++i)
+#pragma unroll
+                for (int j = 0; j < TN; ++j)
+                    acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(fa[i][e], fb[j][e], acc[i][j], 0, 0, 0);
+    };
+
+#pragma unroll
+    for (int s = 0; s < S - 1; ++s) fetch(s);
+    for (int kt = 0; kt < nk; ++kt) {
+        asm volatile("s_waitcnt vmcnt(%0)" :: "n"((S - 2) * (LA + LB)) : "memory");   // stage kt has landed (this wavefront's part)
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");                           // reads of stage kt - 1 are done
+        __builtin_amdgcn_s_barrier();
+        __builtin_amdgcn_sched_barrier(0);
+        fetch(kt + S - 1);                                        // into the slot of stage kt - 1
+        const char* st = smem + (kt % S) * T::STAGE_BYTES;
+        if (T::KW > 1) {
+            group(st, wk);
+        } else {
+#pragma unroll
+            for (int g = 0; g < 4; ++g) group(st, g);
+        }
+    }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+
+    // Epilogue straight from the accumulators: register v of a block is row 8 (v / 4) + 4 half + v % 4, column lane % 32,
+    // so a store covers two rows of 128 bytes.
+    const bool split = p.partial != nullptr;
+    auto emit = [&](int gm, int gn, float v, float bias) {
+        if (gm >= p.M || gn >= p.N) return;
+        const int64_t idx = (int64_t)gm * p.N + gn;
+        if (split) { p.partial[(int64_t)share * p.M * p.N + idx] = v; return; }
+        v += bias;
+        if (p.resid) v += p.resid[idx];
+        if (p.epi == EPI_GELU) { p.aux[idx] = v; v = gelu_f(v); }
+        else if (p.epi == EPI_DGELU) v *= gelu_grad_f(p.aux[idx]);
+        p.C[idx] = v;
+    };
+    if (T::KW > 1) {
+        // four partial sums of one block: each wavefront adds the four, in wavefront order, for a quarter of the rows
+        float* red = reinterpret_cast<float*>(smem);              // [wavefront][register][lane]
+        __syncthreads();
+#pragma unroll
+        for (int v = 0; v < 16; ++v) red[(wave * 16 + v) * 64 + lane] = acc[0][0][v];
+        __syncthreads();
+        const int gn = n0 + (lane & 31);
+        const float bias = (p.bias && !split && gn < p.N) ? p.bias[gn] : 0.0f;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const int v = wave * 4 + q;
+            const float s = ((red[v * 64 + lane] + red[(16 + v) * 64 + lane]) + red[(32 + v) * 64 + lane]) + red[(48 + v) * 64 + lane];
+            emit(m0 + 8 * wave + 4 * half + q, gn, s, bias);
+        }
+        return;
+    }
+#pragma unroll
+    for (int j = 0; j < TN; ++j) {
+        const int gn = n0 + (wn * TN + j) * 32 + (lane & 31);
+        const float bias = (p.bias && !split && gn < p.N) ? p.bias[gn] : 0.0f;
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) emit(m0 + (wm * TM + i) * 32 + 8 * (v >> 2) + 4 * half + (v & 3), gn, acc[i][j][v], bias);
+    }
+}
+
+// Sum of the K shares in share order, then the epilogue; 4 columns per thread.
+__global__ __launch_bounds__(256) void gemm_f32_sum_kernel(GemmF32Params p, int shares) {
+    const int64_t idx = ((int64_t)blockIdx.x * 256 + threadIdx.x) * 4, mn = (int64_t)p.M * p.N;
+    if (idx >= mn) return;
+    float v[4] = {0, 0, 0, 0};
+    auto add4 = [&](const float* q) {
+        const float4 x = *reinterpret_cast<const float4*>(q);
+        v[0] += x.x; v[1] += x.y; v[2] += x.z; v[3] += x.w;
+    };
+    for (int s = 0; s < shares; ++s) add4(p.partial + s * mn + idx);
+    if (p.bias) add4(p.bias + idx % p.N);
+    if (p.resid) add4(p.resid + idx);
+    if (p.epi == EPI_GELU) {
+        *reinterpret_cast<float4*>(p.aux + idx) = make_float4(v[0], v[1], v[2], v[3]);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) v[e] = gelu_f(v[e]);
+    } else if (p.epi == EPI_DGELU) {
+        const float4 u = *reinterpret_cast<const float4*>(p.aux + idx);
+        v[0] *= gelu_grad_f(u.x); v[1] *= gelu_grad_f(u.y); v[2] *= gelu_grad_f(u.z); v[3] *= gelu_grad_f(u.w);
+    }
+    *reinterpret_cast<float4*>(p.C + idx) = make_float4(v[0], v[1], v[2], v[3]);
+}
+
+bool gemm_f32_supported(const GemmArgs& a) {
+    if (a.dtype != F32 || a.N % 4 || (a.trans_a ? a.M : a.K) % 4 || (a.trans_b && a.K % 4)) return false;
+    // 32-bit buffer offsets
+    return a.M * a.K * 4 < 0x7FFFFFFFll && a.N * a.K * 4 < 0x7FFFFFFFll && ((a.M + 31) / 32) * ((a.N + 31) / 32) < (1 << 24) &&
+           a.K < (1 << 24);
+}
+
+// Tile and K shares by a time estimate.  Compute units share a launch's workgroups evenly and the workgroups of one unit
+// share its matrix pipes, so a launch takes (workgroups per unit, rounded up) x (matrix cycles of one) at least; one
+// workgroup alone cannot run a k-step in less than its load latency over the loads in flight, and every launch has a
+// fixed start and end.  Cutting K costs the partial sums' traffic and a second launch.
+struct F32Plan { int variant, shares, nk; };
+static F32Plan f32_plan(int64_t M, int64_t N, int64_t K) {
+    static const int bm[3] = {128, 64, 32};
+    static const double step_us[3] = {1.95, 0.49, 0.125};         // matrix cycles of a k-step
+    static const double alone_us[3] = {2.2, 0.65, 0.45};          // a k-step of a workgroup that has its unit to itself
+    const int cus = compute_units();
+    const int nk = (int)((K + FK - 1) / FK);
+    F32Plan best{0, 1, nk};
+    double best_us = -1;
+    for (int v = 0; v < 3; ++v) {
+        const int64_t tiles = ((M + bm[v] - 1) / bm[v]) * ((N + bm[v] - 1) / bm[v]);
+        for (int want = 1; want <= 16; want *= 2) {
+            const int per = (nk + want - 1) / want, shares = (nk + per - 1) / per;
+            if (want > 1 && (shares != want || per < 4 || tiles * (want / 2) >= 4 * cus)) continue;
+            const int64_t wgs = tiles * shares;
+            const double rounds = (double)((wgs + cus - 1) / cus);
+            double us = std::max(rounds * step_us[v], alone_us[v]) * per + 3.0;
+            if (shares > 1) us += 4.5 + (double)M * N * 8.0 * shares / 3.0e6;
+            if (best_us < 0 || us < best_us) { best = F32Plan{v, shares, per}; best_us = us; }
+        }
+    }
+    return best;
+}
+
+size_t gemm_f32_workspace_bytes(int64_t M, int64_t N, int64_t K) {
+    const F32Plan pl = f32_plan(M, N, K);
+    return pl.shares > 1 ? (size_t)pl.shares * (size_t)M * (size_t)N * sizeof(float) : 0;
+}
+
+template <typename T, bool AK, bool BK>
+static hipError_t launch_f32(GemmF32Params p, int shares, hipStream_t s) {
+    static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_f32_kernel<T, AK, BK>),
+                                                       hipFuncAttributeMaxDynamicSharedMemorySize, T::LDS_BYTES);
+    if (attr != hipSuccess) return attr;
+    p.tiles_m = (p.M + T::BM - 1) / T::BM;
+    p.tiles_n = (p.N + T::BN - 1) / T::BN;
+    hipLaunchKernelGGL((gemm_f32_kernel<T, AK, BK>), dim3((unsigned)(p.tiles_m * p.tiles_n * shares)), dim3(256), T::LDS_BYTES, s, p);
+    return hipGetLastError();
+}
+template <typename T>
+static hipError_t launch_f32_layout(const GemmF32Params& p, const GemmArgs& a, int shares) {
+    if (!a.trans_a) return a.trans_b ? launch_f32<T, true, true>(p, shares, a.stream) : launch_f32<T, true, false>(p, shares, a.stream);
+    return a.trans_b ? launch_f32<T, false, true>(p, shares, a.stream) : launch_f32<T, false, false>(p, shares, a.stream);
+}
+
+hipError_t gemm_f32(const GemmArgs& a) {
+    GemmF32Params p{};
+    p.A = (const float*)a.A; p.B = (const float*)a.B; p.C = (float*)a.C;
+    p.bias = (const float*)a.bias; p.resid = (const float*)a.resid; p.aux = (float*)a.aux;
+    p.M = (int)a.M; p.N = (int)a.N; p.K = (int)a.K; p.epi = a.epi;
+    p.lda = a.trans_a ? p.M : p.K;
+    p.ldb = a.trans_b ? p.K : p.N;
+    const F32Plan pl = f32_plan(a.M, a.N, a.K);
+    p.nk = pl.nk;
+    p.nk_total = (p.K + FK - 1) / FK;
+    if (pl.shares > 1) {
+        if (!a.ws || a.ws_bytes < (size_t)pl.shares * (size_t)a.M * (size_t)a.N * sizeof(float)) return hipErrorInvalidValue;
+        p.partial = (float*)a.ws;
+    }
+    hipError_t e;
+    switch (pl.variant) {
+        case 0: e = launch_f32_layout<F32Tile<2, 2, 2, 2, 1, 2>>(p, a, pl.shares); break;
+        case 1: e = launch_f32_layout<F32Tile<2, 2, 1, 1, 1, 3>>(p, a, pl.shares); break;
+        default: e = launch_f32_layout<F32Tile<1, 1, 1, 1, 4, 4>>(p, a, pl.shares); break;
+    }
+    if (e != hipSuccess || pl.shares == 1) return e;
+    hipLaunchKernelGGL(gemm_f32_sum_kernel, dim3((unsigned)((a.M * a.N / 4 + 255) / 256)), dim3(256), 0, a.stream, p, pl.shares);
+    return hipGetLastError();
+}
+
+}  // namespace tpl

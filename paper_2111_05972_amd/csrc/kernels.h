@@ -66,7 +66,10 @@ struct AttnArgs {
     hipStream_t stream;
 };
 
-// Generic kernels (any shape; the only path for float).
+// Compute units of the current device (256 where there is none).
+int compute_units();
+
+// Generic kernels (any shape): what the matrix-core kernels do not take.
 hipError_t gemm_simple(const GemmArgs& a);
 hipError_t attn_simple_fwd(const AttnArgs& a);
 hipError_t attn_simple_bwd(const AttnArgs& a);
@@ -118,6 +121,14 @@ size_t ln_dist_scratch_bytes(int64_t M, int64_t Hs);
 hipError_t slice_epilogue_fwd(int dtype, bool gelu, int64_t M, int64_t N, const void* in, const void* bias,
                               const void* resid, void* u, void* out, hipStream_t s);
 hipError_t gelu_bwd(int dtype, int64_t M, int64_t N, const void* dg, const void* u, void* du, hipStream_t s);
+
+// float MFMA kernels for gfx950.
+bool gemm_f32_supported(const GemmArgs& a);
+size_t gemm_f32_workspace_bytes(int64_t M, int64_t N, int64_t K);
+hipError_t gemm_f32(const GemmArgs& a);
+bool attn_f32_supported(const AttnArgs& a);
+hipError_t attn_f32_fwd(const AttnArgs& a);
+hipError_t attn_f32_bwd(const AttnArgs& a);
 
 // bf16 MFMA kernels for gfx950.
 bool gemm_bf16_supported(const GemmArgs& a);

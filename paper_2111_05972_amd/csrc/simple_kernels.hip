@@ -1,5 +1,5 @@
 // Generic kernels: any shape, float or bfloat16 storage, float accumulation.
-// They are the only path for float tensors and cover bfloat16 shapes the MFMA kernels do not take.
+// They cover the shapes the MFMA kernels do not take (head sizes above 128, operands of 2 GiB and more).
 #include <hip/hip_runtime.h>
 
 #include <mutex>

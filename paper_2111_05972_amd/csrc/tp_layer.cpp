@@ -107,7 +107,7 @@ void saved_layout(const Dims& x, tp_layer_saved_layout* L) {
 }
 
 size_t gemm_ws(int dtype, int64_t M, int64_t N, int64_t K) {
-    return dtype == TPL_BF16 ? up(gemm_bf16_workspace_bytes(M, N, K)) : 0;
+    return up(dtype == TPL_BF16 ? gemm_bf16_workspace_bytes(M, N, K) : gemm_f32_workspace_bytes(M, N, K));
 }
 
 // Backward scratch: dU, dO, dQKV, D, and per chain (attention, MLP) column-sum partials and GEMM scratch.
@@ -234,6 +234,7 @@ int run_gemm(GemmArgs& g) {
     }
     g.colsum_done = false;
     if (g.dtype == BF16 && gemm_bf16_supported(g)) e = gemm_bf16(g, &g.colsum_done);
+    else if (gemm_f32_supported(g)) e = gemm_f32(g);
     else e = gemm_simple(g);
     if (slot >= 0 && hipEventRecord(g_prof.stop[slot], g.stream) != hipSuccess) return TPL_EHIP;
     return e == hipSuccess ? TPL_OK : TPL_EHIP;
@@ -242,6 +243,7 @@ int run_gemm(GemmArgs& g) {
 int run_attn(AttnArgs& a, bool bwd) {
     hipError_t e;
     if (a.dtype == BF16 && attn_bf16_supported(a)) e = bwd ? attn_bf16_bwd(a) : attn_bf16_fwd(a);
+    else if (attn_f32_supported(a)) e = bwd ? attn_f32_bwd(a) : attn_f32_fwd(a);
     else e = bwd ? attn_simple_bwd(a) : attn_simple_fwd(a);
     return e == hipSuccess ? TPL_OK : TPL_EHIP;
 }
