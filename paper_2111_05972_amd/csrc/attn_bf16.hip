@@ -1,4 +1,8 @@
-// bf16 flash-style softmax attention for gfx950 (head size 64 or 128), forward and backward.
+// bf16 flash-style softmax attention for gfx950, forward and backward, head sizes that are a multiple of 8 up to 128.
+//
+// DH is the head size rounded up to 32, 64, 96 or 128: tiles, fragments and accumulators are DH wide, columns past the
+// head size dh read as zero (they must not be the next head's) and are not stored.  (8 heads x 3 x 1001 tokens x 80: the
+// training step around it took 3.52 ms with one wavefront per row on vector arithmetic, 0.54 ms on the 96-wide kernels.)
 //
 // qkv is [B*S, 3*nl*dh] with columns (q | k | v, local head, dh); o is [B*S, nl*dh].  The S x S
 // score matrix is never stored: scores are recomputed tile by tile on the matrix cores (MFMA
@@ -61,12 +65,12 @@ constexpr float RESCALE_LAG = 8.0f;  // forward: how far (log2) the row maximum 
 // bits that separate the 4 rows of a transposing read move the 64-byte column group, the remaining
 // row bits move the chunk inside it.
 template <int DH> __device__ __forceinline__ int swz(int row) {
-    return DH == 64 ? ((((row >> 1) & 1) << 2) | ((row >> 2) & 3))     // 128-byte rows, 8 chunks
-                    : (((row & 3) << 2) | ((row >> 2) & 3));           // 256-byte rows, 16 chunks
+    return DH == 64    ? ((((row >> 1) & 1) << 2) | ((row >> 2) & 3))     // 128-byte rows, 8 chunks
+           : DH == 128 ? (((row & 3) << 2) | ((row >> 2) & 3))            // 256-byte rows, 16 chunks
+                       : ((row >> 2) & 3);    // 64- and 192-byte rows: 4 rows already start in 4 different column groups
 }
 template <int DH> constexpr int tile_bytes() { return TILE * DH * 2; }
-template <int DH, int NT> constexpr int NCHUNKS = TILE * DH / 8 / NT;     // 16-byte chunks per thread and tile
-template <int DH> constexpr int chunks_per_thread() { return NCHUNKS<DH, ATHREADS>; }
+template <int DH, int NT> constexpr int NCHUNKS = (TILE * DH / 8 + NT - 1) / NT;   // 16-byte chunks per thread and tile (at most)
 
 // ---- global -> LDS without passing through registers ---------------------------------------------
 // A tile is TILE rows x DH bf16 = TILE*DH/8 chunks of 16 bytes; a buffer load with the LDS flag writes the 64
@@ -74,18 +78,18 @@ template <int DH> constexpr int chunks_per_thread() { return NCHUNKS<DH, ATHREAD
 // hold chunk (slot ^ swz(row)) of its row, so the swizzle is applied to the global offset each lane requests.
 // Offsets are relative to row 0 of this (batch, head); the descriptor ends after the head's slice of row S-1,
 // which makes rows >= S read as zero.
+constexpr unsigned HEAD_OOB = 0x80000000u;      // past every slice (below 2 GiB), also with a row offset added
 template <int DH, int NT>
-__device__ __forceinline__ void dma_offsets(unsigned (&off)[(NCHUNKS<DH, NT>)], int64_t ld, int t) {
+__device__ __forceinline__ void dma_offsets(unsigned (&off)[(NCHUNKS<DH, NT>)], int64_t ld, int dh, int t) {
     constexpr int NC = DH / 8;
 #pragma unroll
     for (int i = 0; i < NCHUNKS<DH, NT>; ++i) {
         const int p = t + NT * i, row = p / NC, c = (p % NC) ^ swz<DH>(row);
-        off[i] = (unsigned)row * (unsigned)(ld * 2) + (unsigned)c * 16u;
+        off[i] = c * 8 < dh ? (unsigned)row * (unsigned)(ld * 2) + (unsigned)c * 16u : HEAD_OOB;
     }
 }
-template <int DH>
-__device__ __forceinline__ i32x4 head_rsrc(const bf16_t* base, int64_t ld, int S) {
-    return make_rsrc(base, (unsigned)(((int64_t)(S - 1) * ld + DH) * 2));
+__device__ __forceinline__ i32x4 head_rsrc(const bf16_t* base, int64_t ld, int S, int dh) {
+    return make_rsrc(base, (unsigned)(((int64_t)(S - 1) * ld + dh) * 2));
 }
 // rows [row0, row0 + TILE) -> LDS tile at byte address lds_tile; wave = wavefront index (uniform)
 template <int DH, int NT>
@@ -93,7 +97,8 @@ __device__ __forceinline__ void tile_dma(i32x4 rsrc, unsigned lds_tile, const un
                                          unsigned row0_bytes, int wave) {
 #pragma unroll
     for (int i = 0; i < NCHUNKS<DH, NT>; ++i)
-        buffer_load_lds_b128(rsrc, lds_tile + (unsigned)(i * NT + wave * 64) * 16u, off[i] + row0_bytes);
+        if ((i + 1) * NT <= TILE * DH / 8 || i * NT + wave * 64 < TILE * DH / 8)   // the last round may need some wavefronts only
+            buffer_load_lds_b128(rsrc, lds_tile + (unsigned)(i * NT + wave * 64) * 16u, off[i] + row0_bytes);
 }
 // A use of v that the compiler must order after the load that produces v: placed before a streaming loop, it
 // makes the compiler wait for prologue loads there, instead of inside the loop at their first use, where the
@@ -159,13 +164,12 @@ template <int IMM> __device__ __forceinline__ bf16x8 lds_frag_t(unsigned addr0, 
 }
 template <typename T> __device__ __forceinline__ void keep_in_register(T& v) { asm volatile("" : "+v"(v)); }
 // The same operand straight from global memory (loop-invariant fragments kept in registers).
-template <int DH>
-__device__ __forceinline__ bf16x8 frag_k_global(const bf16_t* base, int64_t ld, int row, int nrows,
+__device__ __forceinline__ bf16x8 frag_k_global(const bf16_t* base, int64_t ld, int row, int nrows, int dh,
                                                 int ks, int lane) {
     bf16x8 z;
 #pragma unroll
     for (int e = 0; e < 8; ++e) z[e] = (bf16_t)0.0f;
-    if (row >= nrows) return z;
+    if (row >= nrows || 16 * ks + 8 * (lane >> 5) >= dh) return z;
     return *reinterpret_cast<const bf16x8*>(base + (int64_t)row * ld + 16 * ks + 8 * (lane >> 5));
 }
 __device__ __forceinline__ bf16x8 pack_regs(const f32x16& a, int first) {
@@ -278,9 +282,9 @@ template <int DH> constexpr int fwd_lds_bytes() {
 }
 
 template <int DH, bool CAUSAL>
-__global__ __launch_bounds__(FTHREADS, DH == 64 ? 4 : 2) void attn_fwd_kernel(const bf16_t* __restrict__ qkv,
+__global__ __launch_bounds__(FTHREADS, DH <= 64 ? 4 : 2) void attn_fwd_kernel(const bf16_t* __restrict__ qkv,
                                                             bf16_t* __restrict__ o,
-                                                            float* __restrict__ lse, int S, int nl, int BH,
+                                                            float* __restrict__ lse, int S, int nl, int dh, int BH,
                                                             float* __restrict__ part, ChunkLen ch) {
     extern __shared__ __attribute__((aligned(16))) char smem[];
     constexpr int TB = tile_bytes<DH>();
@@ -291,17 +295,17 @@ __global__ __launch_bounds__(FTHREADS, DH == 64 ? 4 : 2) void attn_fwd_kernel(co
     const Chunk ck = find_chunk(CAUSAL, false, S, ch, slot, 0);
     const int qb = ck.blk;
     const int b = bh / nl, h = bh % nl;
-    const int64_t ld = 3LL * nl * DH;
-    const bf16_t* qbase = qkv + (int64_t)b * S * ld + (int64_t)h * DH;
-    const bf16_t* kbase = qbase + (int64_t)nl * DH;
-    const bf16_t* vbase = kbase + (int64_t)nl * DH;
+    const int64_t ld = 3LL * nl * dh;
+    const bf16_t* qbase = qkv + (int64_t)b * S * ld + (int64_t)h * dh;
+    const bf16_t* kbase = qbase + (int64_t)nl * dh;
+    const bf16_t* vbase = kbase + (int64_t)nl * dh;
     const int q0 = qb * BLK + qs * 32;                    // first query of this wavefront
     const int q = q0 + (lane & 31);                       // this lane's query
-    const float c2 = LOG2E / sqrtf((float)DH);
+    const float c2 = LOG2E / sqrtf((float)dh);
 
     bf16x8 qf[DH / 16];
 #pragma unroll
-    for (int ks = 0; ks < DH / 16; ++ks) qf[ks] = frag_k_global<DH>(qbase, ld, q, S, ks, lane);
+    for (int ks = 0; ks < DH / 16; ++ks) qf[ks] = frag_k_global(qbase, ld, q, S, dh, ks, lane);
 
     f32x16 oacc[DH / 32];
 #pragma unroll
@@ -312,9 +316,9 @@ __global__ __launch_bounds__(FTHREADS, DH == 64 ? 4 : 2) void attn_fwd_kernel(co
     const int tile0 = ck.t0, ntiles = ck.t1;
     const unsigned lds0 = (unsigned)(uintptr_t)(lds_void_ptr)smem;
     const int wave_u = __builtin_amdgcn_readfirstlane(wave);
-    const i32x4 desc_k = head_rsrc<DH>(kbase, ld, S), desc_v = head_rsrc<DH>(vbase, ld, S);
+    const i32x4 desc_k = head_rsrc(kbase, ld, S, dh), desc_v = head_rsrc(vbase, ld, S, dh);
     unsigned off[NCH];
-    dma_offsets<DH, FTHREADS>(off, ld, t);
+    dma_offsets<DH, FTHREADS>(off, ld, dh, t);
     auto fetch_tile = [&](int kt, unsigned stage) {       // K and V rows of tile kt -> LDS stage
         const unsigned r0 = (unsigned)kt * TILE * (unsigned)(ld * 2);
         tile_dma<DH, FTHREADS>(desc_k, stage, off, r0, wave_u);
@@ -445,7 +449,7 @@ __global__ __launch_bounds__(FTHREADS, DH == 64 ? 4 : 2) void attn_fwd_kernel(co
                 }
             if (half == 0) { pp[BLK * DH + ql] = mn; pp[BLK * DH + BLK + ql] = ltot; }
         } else if (q < S) {
-            bf16_t* op = o + ((int64_t)b * S + q) * ((int64_t)nl * DH) + (int64_t)h * DH;
+            bf16_t* op = o + ((int64_t)b * S + q) * ((int64_t)nl * dh) + (int64_t)h * dh;
 #pragma unroll
             for (int dt = 0; dt < DH / 32; ++dt)
 #pragma unroll
@@ -454,20 +458,23 @@ __global__ __launch_bounds__(FTHREADS, DH == 64 ? 4 : 2) void attn_fwd_kernel(co
 #pragma unroll
                     for (int j = 0; j < 4; ++j)
                         r[j] = (oacc[dt][4 * i + j] * f0 + mg[(2 + dt * 16 + 4 * i + j) * 64] * f1) * inv;
-                    store4(op + dt * 32 + 8 * i + 4 * half, r[0], r[1], r[2], r[3]);
+                    if (dt * 32 + 8 * i + 4 * half < dh) store4(op + dt * 32 + 8 * i + 4 * half, r[0], r[1], r[2], r[3]);
                 }
             if (half == 0) lse[((int64_t)b * nl + h) * S + q] = (mn + log2f(ltot)) * LN2;
         }
     }
 }
 
+// Threads per row of the combine kernels, four columns each: a power of two.
+template <int DH> constexpr int combine_tpr() { return DH == 96 ? 32 : DH / 4; }
+
 // Forward, second kernel: merges the chunks of every strip that was cut (max, rescale, add, in chunk order),
-// normalises and writes O and LSE.  Workgroup = (256 / (DH/4) query rows of a block, batch*head); DH/4 threads per row.
+// normalises and writes O and LSE.  Workgroup = (256 / TPR query rows of a block, batch*head), TPR threads per row.
 template <int DH, bool CAUSAL>
 __global__ __launch_bounds__(256) void attn_fwd_combine_kernel(const float* __restrict__ part, bf16_t* __restrict__ o,
-                                                               float* __restrict__ lse, int S, int nl, int BH, ChunkLen ch,
+                                                               float* __restrict__ lse, int S, int nl, int dh, int BH, ChunkLen ch,
                                                                int blk0) {
-    constexpr int TPR = DH / 4, PSZ = BLK * (DH + 2), RPW = 256 / TPR, WPB = BLK / RPW;
+    constexpr int TPR = combine_tpr<DH>(), PSZ = BLK * (DH + 2), RPW = 256 / TPR, WPB = BLK / RPW;
     const Chunk ck = find_chunk(CAUSAL, false, S, ch, -1, blk0 + (int)blockIdx.x / WPB);
     if (ck.nch == 1) return;
     const int bh = blockIdx.y, b = bh / nl, h = bh % nl;
@@ -475,7 +482,7 @@ __global__ __launch_bounds__(256) void attn_fwd_combine_kernel(const float* __re
     {
         const int ql = ((int)blockIdx.x % WPB) * RPW + threadIdx.x / TPR;
         const int q = ck.blk * BLK + ql;
-        if (q >= S) return;
+        if (q >= S || 4 * tc >= dh) return;
         const float* p0 = part + ((int64_t)ck.slot0 * BH + bh) * PSZ;
         float mtot = -INFINITY;
         for (int c = 0; c < ck.nch; ++c) mtot = fmaxf(mtot, p0[(int64_t)c * BH * PSZ + BLK * DH + ql]);
@@ -489,7 +496,7 @@ __global__ __launch_bounds__(256) void attn_fwd_combine_kernel(const float* __re
             a0 = fmaf(v.x, f, a0); a1 = fmaf(v.y, f, a1); a2 = fmaf(v.z, f, a2); a3 = fmaf(v.w, f, a3);
         }
         const float inv = ltot > 0.0f ? 1.0f / ltot : 0.0f;
-        store4(o + ((int64_t)b * S + q) * ((int64_t)nl * DH) + (int64_t)h * DH + 4 * tc, a0 * inv, a1 * inv, a2 * inv,
+        store4(o + ((int64_t)b * S + q) * ((int64_t)nl * dh) + (int64_t)h * dh + 4 * tc, a0 * inv, a1 * inv, a2 * inv,
                a3 * inv);
         if (tc == 0) lse[((int64_t)b * nl + h) * S + q] = (mtot + log2f(ltot)) * LN2;
     }
@@ -497,14 +504,14 @@ __global__ __launch_bounds__(256) void attn_fwd_combine_kernel(const float* __re
 
 // Backward, last kernel: dQ, dK, dV of every strip that was cut = sum of its chunks' partials in chunk order.
 // blockIdx.z = 0: dQ (query-block strips), 1: dK, 2: dV (key-block strips; a slot holds [dK | dV]); workgroup =
-// (256 / (DH/4) rows of a block, batch*head), DH/4 threads per row.
+// (256 / TPR rows of a block, batch*head), TPR threads per row.
 template <int DH, bool CAUSAL>
 __global__ __launch_bounds__(256) void attn_bwd_combine_kernel(const float* __restrict__ part_q,
                                                                const float* __restrict__ part_kv,
-                                                               bf16_t* __restrict__ dqkv, int S, int nl, int BH,
+                                                               bf16_t* __restrict__ dqkv, int S, int nl, int dh, int BH,
                                                                ChunkLen ch_q, ChunkLen ch_kv,
                                                                int blk0_q, int ncut_q, int blk0_kv, int ncut_kv) {
-    constexpr int TPR = DH / 4, RPW = 256 / TPR, WPB = BLK / RPW;
+    constexpr int TPR = combine_tpr<DH>(), RPW = 256 / TPR, WPB = BLK / RPW;
     const int which = blockIdx.z;
     if ((int)blockIdx.x / WPB >= (which == 0 ? ncut_q : ncut_kv)) return;
     const Chunk ck = find_chunk(CAUSAL, which != 0, S, which == 0 ? ch_q : ch_kv, -1,
@@ -513,48 +520,46 @@ __global__ __launch_bounds__(256) void attn_bwd_combine_kernel(const float* __re
     const int bh = blockIdx.y, b = bh / nl, h = bh % nl;
     const int psz = which == 0 ? BLK * DH : 2 * BLK * DH;
     const float* p0 = (which == 0 ? part_q : part_kv) + ((int64_t)ck.slot0 * BH + bh) * psz + (which == 2 ? BLK * DH : 0);
-    const float f = which == 2 ? 1.0f : 1.0f / sqrtf((float)DH);
-    const int64_t ld = 3LL * nl * DH;
+    const float f = which == 2 ? 1.0f : 1.0f / sqrtf((float)dh);
+    const int64_t ld = 3LL * nl * dh;
     const int tc = threadIdx.x % TPR;
     {
         const int rl = ((int)blockIdx.x % WPB) * RPW + threadIdx.x / TPR;
         const int row = ck.blk * BLK + rl;
-        if (row >= S) return;
+        if (row >= S || 4 * tc >= dh) return;
         float a0 = 0.0f, a1 = 0.0f, a2 = 0.0f, a3 = 0.0f;
         for (int c = 0; c < ck.nch; ++c) {
             const float4 v = *reinterpret_cast<const float4*>(p0 + (int64_t)c * BH * psz + rl * DH + 4 * tc);
             a0 += v.x; a1 += v.y; a2 += v.z; a3 += v.w;
         }
-        store4(dqkv + ((int64_t)b * S + row) * ld + (int64_t)which * nl * DH + (int64_t)h * DH + 4 * tc, a0 * f, a1 * f,
+        store4(dqkv + ((int64_t)b * S + row) * ld + (int64_t)which * nl * dh + (int64_t)h * dh + 4 * tc, a0 * f, a1 * f,
                a2 * f, a3 * f);
     }
 }
 
 // =================================================================================================
-// D[b,h,s] = sum_d dO[s,d] * O[s,d]   (one wavefront per token row, 8 elements per lane per pass)
+// D[b,h,s] = sum_d dO[s,d] * O[s,d]: LPH lanes per (token, head), 8 elements each; reads dO and O once, coalesced.
 // =================================================================================================
 template <int DH>
 __global__ __launch_bounds__(256) void attn_dsum_kernel(const bf16_t* __restrict__ o,
                                                         const bf16_t* __restrict__ d_o,
-                                                        float* __restrict__ dsum, int B, int S, int nl) {
-    const int lane = threadIdx.x & 63;
-    const int64_t row = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-    if (row >= (int64_t)B * S) return;
-    const int b = (int)(row / S), s = (int)(row % S);
-    const int Hl = nl * DH;
-    constexpr int LPH = DH / 8;     // lanes per head
-    for (int c0 = 0; c0 < Hl; c0 += 512) {
-        int c = c0 + lane * 8;
-        float acc = 0.0f;
-        if (c < Hl) {
-            bf16x8 a = *reinterpret_cast<const bf16x8*>(o + row * Hl + c);
-            bf16x8 g = *reinterpret_cast<const bf16x8*>(d_o + row * Hl + c);
+                                                        float* __restrict__ dsum, int B, int S, int nl, int dh) {
+    constexpr int LPH = DH <= 32 ? 4 : DH == 64 ? 8 : 16;
+    const int64_t item = ((int64_t)blockIdx.x * 256 + threadIdx.x) / LPH, items = (int64_t)B * S * nl;   // token-major, then head
+    const int c = (threadIdx.x % LPH) * 8;
+    float acc = 0.0f;
+    if (item < items && c < dh) {
+        const bf16x8 a = *reinterpret_cast<const bf16x8*>(o + item * dh + c);
+        const bf16x8 g = *reinterpret_cast<const bf16x8*>(d_o + item * dh + c);
 #pragma unroll
-            for (int e = 0; e < 8; ++e) acc = fmaf((float)a[e], (float)g[e], acc);
-        }
+        for (int e = 0; e < 8; ++e) acc = fmaf((float)a[e], (float)g[e], acc);
+    }
 #pragma unroll
-        for (int off = LPH / 2; off > 0; off >>= 1) acc += __shfl_xor(acc, off, 64);
-        if (c < Hl && (lane % LPH) == 0) dsum[((int64_t)b * nl + c / DH) * S + s] = acc;
+    for (int off = LPH / 2; off > 0; off >>= 1) acc += __shfl_xor(acc, off, 64);
+    if (item < items && c == 0) {
+        const int64_t row = item / nl;
+        const int h = (int)(item - row * nl), b = (int)(row / S), s = (int)(row - (int64_t)b * S);
+        dsum[((int64_t)b * nl + h) * S + s] = acc;
     }
 }
 
@@ -570,30 +575,30 @@ template <int DH, bool CAUSAL, bool DK_ROLE>
 __device__ __forceinline__ void attn_dkv_body(char* smem, const bf16_t* __restrict__ qkv,
                                               const bf16_t* __restrict__ d_o, const float* __restrict__ lse,
                                               const float* __restrict__ dsum, bf16_t* __restrict__ dqkv,
-                                              int S, int nl, int bh, const Chunk& ck, float* __restrict__ pslot) {
+                                              int S, int nl, int dh, int bh, const Chunk& ck, float* __restrict__ pslot) {
     constexpr int TB = tile_bytes<DH>();
     constexpr int NCH = NCHUNKS<DH, FTHREADS>;
     constexpr int STAGE = 2 * TB + 2 * TILE * 4;          // Q tile, dO tile, LSE*log2e, D
     const int t = threadIdx.x, lane = t & 63, wave = t >> 6, half = lane >> 5;
     const int kb = ck.blk;
     const int b = bh / nl, h = bh % nl;
-    const int64_t ld = 3LL * nl * DH, ldo = (int64_t)nl * DH;
-    const bf16_t* qbase = qkv + (int64_t)b * S * ld + (int64_t)h * DH;
-    const bf16_t* kbase = qbase + (int64_t)nl * DH;
-    const bf16_t* vbase = kbase + (int64_t)nl * DH;
-    const bf16_t* dobase = d_o + (int64_t)b * S * ldo + (int64_t)h * DH;
+    const int64_t ld = 3LL * nl * dh, ldo = (int64_t)nl * dh;
+    const bf16_t* qbase = qkv + (int64_t)b * S * ld + (int64_t)h * dh;
+    const bf16_t* kbase = qbase + (int64_t)nl * dh;
+    const bf16_t* vbase = kbase + (int64_t)nl * dh;
+    const bf16_t* dobase = d_o + (int64_t)b * S * ldo + (int64_t)h * dh;
     const float* lrow = lse + ((int64_t)b * nl + h) * S;
     const float* drow = dsum + ((int64_t)b * nl + h) * S;
     const int k0 = kb * BLK + (wave & 3) * 32;
     const int kv = k0 + (lane & 31);
-    const float scale = 1.0f / sqrtf((float)DH);
+    const float scale = 1.0f / sqrtf((float)dh);
     const float c2 = LOG2E * scale;
 
     bf16x8 kf[DH / 16], vf[DK_ROLE ? DH / 16 : 1];
 #pragma unroll
     for (int ks = 0; ks < DH / 16; ++ks) {
-        kf[ks] = frag_k_global<DH>(kbase, ld, kv, S, ks, lane);
-        if (DK_ROLE) vf[ks] = frag_k_global<DH>(vbase, ld, kv, S, ks, lane);
+        kf[ks] = frag_k_global(kbase, ld, kv, S, dh, ks, lane);
+        if (DK_ROLE) vf[ks] = frag_k_global(vbase, ld, kv, S, dh, ks, lane);
     }
     f32x16 acc[DH / 32];                                   // dK (DK_ROLE) or dV
 #pragma unroll
@@ -602,10 +607,10 @@ __device__ __forceinline__ void attn_dkv_body(char* smem, const bf16_t* __restri
     const int qt0 = ck.t0, ntiles = ck.t1;                // query tiles of this chunk (the strip starts at the diagonal)
     const unsigned lds0 = (unsigned)(uintptr_t)(lds_void_ptr)smem;
     const int wave_u = __builtin_amdgcn_readfirstlane(wave);
-    const i32x4 desc_q = head_rsrc<DH>(qbase, ld, S), desc_do = head_rsrc<DH>(dobase, ldo, S);
+    const i32x4 desc_q = head_rsrc(qbase, ld, S, dh), desc_do = head_rsrc(dobase, ldo, S, dh);
     unsigned off_q[NCH], off_do[NCH];
-    dma_offsets<DH, FTHREADS>(off_q, ld, t);
-    dma_offsets<DH, FTHREADS>(off_do, ldo, t);
+    dma_offsets<DH, FTHREADS>(off_q, ld, dh, t);
+    dma_offsets<DH, FTHREADS>(off_do, ldo, dh, t);
     float rl = 0.0f, rd = 0.0f;
     // Q and dO rows of tile qt straight into LDS; LSE and D of its rows through registers (r2s stores them)
     auto g2r = [&](int qt, unsigned stage) {
@@ -647,7 +652,7 @@ __device__ __forceinline__ void attn_dkv_body(char* smem, const bf16_t* __restri
             // Fragments of all MFMA phases (Q for S, dO for dP in the dK role, then Q or dO transposed) through a
             // rolling window of W registers, as in the dQ kernel.
             f32x16 s = zero16(), dp = zero16();
-            constexpr int NF = DH / 16, W = DH == 64 ? NF : NF / 2, NP = DK_ROLE ? 2 * NF : NF;
+            constexpr int NF = DH / 16, W = DH <= 64 ? NF : NF / 2, NP = DK_ROLE ? 2 * NF : NF;
             bf16x8 fr[W];
             const char* src = DK_ROLE ? qs : dos;                          // dK += dS^T Q ; dV += P^T dO
             auto fetch = [&](int i) {
@@ -716,14 +721,15 @@ __device__ __forceinline__ void attn_dkv_body(char* smem, const bf16_t* __restri
                 store_f4(pp + dt * 32 + 8 * i + 4 * half, acc[dt][4 * i], acc[dt][4 * i + 1], acc[dt][4 * i + 2],
                          acc[dt][4 * i + 3]);
     } else if (kv < S) {
-        bf16_t* outp = dqkv + ((int64_t)b * S + kv) * ld + (int64_t)(DK_ROLE ? 1 : 2) * nl * DH + (int64_t)h * DH;
+        bf16_t* outp = dqkv + ((int64_t)b * S + kv) * ld + (int64_t)(DK_ROLE ? 1 : 2) * nl * dh + (int64_t)h * dh;
         const float f = DK_ROLE ? scale : 1.0f;
 #pragma unroll
         for (int dt = 0; dt < DH / 32; ++dt)
 #pragma unroll
             for (int i = 0; i < 4; ++i)
-                store4(outp + dt * 32 + 8 * i + 4 * half, acc[dt][4 * i] * f, acc[dt][4 * i + 1] * f,
-                       acc[dt][4 * i + 2] * f, acc[dt][4 * i + 3] * f);
+                if (dt * 32 + 8 * i + 4 * half < dh)
+                    store4(outp + dt * 32 + 8 * i + 4 * half, acc[dt][4 * i] * f, acc[dt][4 * i + 1] * f,
+                           acc[dt][4 * i + 2] * f, acc[dt][4 * i + 3] * f);
     }
 }
 
@@ -731,14 +737,14 @@ __device__ __forceinline__ void attn_dkv_body(char* smem, const bf16_t* __restri
 template <int DH, bool CAUSAL>
 __device__ __forceinline__ void attn_dkv_wg(char* smem, const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ d_o,
                                             const float* __restrict__ lse, const float* __restrict__ dsum,
-                                            bf16_t* __restrict__ dqkv, int S, int nl, int BH,
+                                            bf16_t* __restrict__ dqkv, int S, int nl, int dh, int BH,
                                             float* __restrict__ part, ChunkLen ch, int wg) {
     const int bh = wg % BH, slot = wg / BH;
     const Chunk ck = find_chunk(CAUSAL, true, S, ch, slot, 0);
     float* pslot = part + ((int64_t)slot * BH + bh) * (2 * BLK * DH);
     // the role is uniform per wavefront; both bodies run the same loop and the same barriers
-    if ((threadIdx.x >> 6) < 4) attn_dkv_body<DH, CAUSAL, false>(smem, qkv, d_o, lse, dsum, dqkv, S, nl, bh, ck, pslot);
-    else attn_dkv_body<DH, CAUSAL, true>(smem, qkv, d_o, lse, dsum, dqkv, S, nl, bh, ck, pslot);
+    if ((threadIdx.x >> 6) < 4) attn_dkv_body<DH, CAUSAL, false>(smem, qkv, d_o, lse, dsum, dqkv, S, nl, dh, bh, ck, pslot);
+    else attn_dkv_body<DH, CAUSAL, true>(smem, qkv, d_o, lse, dsum, dqkv, S, nl, dh, bh, ck, pslot);
 }
 
 // =================================================================================================
@@ -756,7 +762,7 @@ template <int DH> constexpr int dq_lds_bytes() {
 template <int DH, bool CAUSAL>
 __device__ __forceinline__ void attn_dq_wg(char* smem, const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ d_o,
                                            const float* __restrict__ lse, const float* __restrict__ dsum,
-                                           bf16_t* __restrict__ dqkv, int S, int nl, int BH,
+                                           bf16_t* __restrict__ dqkv, int S, int nl, int dh, int BH,
                                            float* __restrict__ part, ChunkLen ch, int wg) {
     constexpr int TB = tile_bytes<DH>();
     constexpr int NCH = NCHUNKS<DH, FTHREADS>;
@@ -766,14 +772,14 @@ __device__ __forceinline__ void attn_dq_wg(char* smem, const bf16_t* __restrict_
     const Chunk ck = find_chunk(CAUSAL, false, S, ch, slot, 0);
     const int qb = ck.blk;
     const int b = bh / nl, h = bh % nl;
-    const int64_t ld = 3LL * nl * DH, ldo = (int64_t)nl * DH;
-    const bf16_t* qbase = qkv + (int64_t)b * S * ld + (int64_t)h * DH;
-    const bf16_t* kbase = qbase + (int64_t)nl * DH;
-    const bf16_t* vbase = kbase + (int64_t)nl * DH;
-    const bf16_t* dobase = d_o + (int64_t)b * S * ldo + (int64_t)h * DH;
+    const int64_t ld = 3LL * nl * dh, ldo = (int64_t)nl * dh;
+    const bf16_t* qbase = qkv + (int64_t)b * S * ld + (int64_t)h * dh;
+    const bf16_t* kbase = qbase + (int64_t)nl * dh;
+    const bf16_t* vbase = kbase + (int64_t)nl * dh;
+    const bf16_t* dobase = d_o + (int64_t)b * S * ldo + (int64_t)h * dh;
     const int q0 = qb * BLK + qs * 32;
     const int q = q0 + (lane & 31);
-    const float scale = 1.0f / sqrtf((float)DH);
+    const float scale = 1.0f / sqrtf((float)dh);
     const float c2 = LOG2E * scale;
     const float l2 = q < S ? lse[((int64_t)b * nl + h) * S + q] * LOG2E : 0.0f;
     const float dq_d = q < S ? dsum[((int64_t)b * nl + h) * S + q] : 0.0f;
@@ -781,8 +787,8 @@ __device__ __forceinline__ void attn_dq_wg(char* smem, const bf16_t* __restrict_
     bf16x8 qf[DH / 16], dof[DH / 16];
 #pragma unroll
     for (int ks = 0; ks < DH / 16; ++ks) {
-        qf[ks] = frag_k_global<DH>(qbase, ld, q, S, ks, lane);
-        dof[ks] = frag_k_global<DH>(dobase, ldo, q, S, ks, lane);
+        qf[ks] = frag_k_global(qbase, ld, q, S, dh, ks, lane);
+        dof[ks] = frag_k_global(dobase, ldo, q, S, dh, ks, lane);
     }
     f32x16 dq[DH / 32];
 #pragma unroll
@@ -792,9 +798,9 @@ __device__ __forceinline__ void attn_dq_wg(char* smem, const bf16_t* __restrict_
     const int tile0 = ck.t0, ntiles = ck.t1;
     const unsigned lds0 = (unsigned)(uintptr_t)(lds_void_ptr)smem;
     const int wave_u = __builtin_amdgcn_readfirstlane(wave);
-    const i32x4 desc_k = head_rsrc<DH>(kbase, ld, S), desc_v = head_rsrc<DH>(vbase, ld, S);
+    const i32x4 desc_k = head_rsrc(kbase, ld, S, dh), desc_v = head_rsrc(vbase, ld, S, dh);
     unsigned off[NCH];
-    dma_offsets<DH, FTHREADS>(off, ld, t);
+    dma_offsets<DH, FTHREADS>(off, ld, dh, t);
     auto fetch_tile = [&](int kt, unsigned stage) {       // K and V rows of tile kt -> LDS stage
         const unsigned r0 = (unsigned)kt * TILE * (unsigned)(ld * 2);
         tile_dma<DH, FTHREADS>(desc_k, stage, off, r0, wave_u);
@@ -818,7 +824,7 @@ __device__ __forceinline__ void attn_dq_wg(char* smem, const bf16_t* __restrict_
             // is read through a rolling window of W registers: fragment i + W is requested right after the MFMA
             // that used fragment i, so LDS latency hides under W MFMAs instead of being paid before every one.
             f32x16 s = zero16(), dp = zero16();
-            constexpr int NF = DH / 16, W = DH == 64 ? NF : NF / 2;
+            constexpr int NF = DH / 16, W = DH <= 64 ? NF : NF / 2;
             bf16x8 fr[W];
             auto fetch = [&](int i) {                       // i is a compile-time constant after unrolling
                 if (i < NF) return frag_k<DH>(ks_, kvh * 32, i, lane);
@@ -885,7 +891,7 @@ __device__ __forceinline__ void attn_dq_wg(char* smem, const bf16_t* __restrict_
                 store_f4(pp + dt * 32 + 8 * i + 4 * half, r[0], r[1], r[2], r[3]);
             }
     } else if (kvh == 0 && q < S) {
-        bf16_t* dqp = dqkv + ((int64_t)b * S + q) * ld + (int64_t)h * DH;
+        bf16_t* dqp = dqkv + ((int64_t)b * S + q) * ld + (int64_t)h * dh;
 #pragma unroll
         for (int dt = 0; dt < DH / 32; ++dt)
 #pragma unroll
@@ -893,7 +899,7 @@ __device__ __forceinline__ void attn_dq_wg(char* smem, const bf16_t* __restrict_
                 float r[4];
 #pragma unroll
                 for (int j = 0; j < 4; ++j) r[j] = (dq[dt][4 * i + j] + mg[(dt * 16 + 4 * i + j) * 64]) * scale;
-                store4(dqp + dt * 32 + 8 * i + 4 * half, r[0], r[1], r[2], r[3]);
+                if (dt * 32 + 8 * i + 4 * half < dh) store4(dqp + dt * 32 + 8 * i + 4 * half, r[0], r[1], r[2], r[3]);
             }
     }
 }
@@ -909,20 +915,20 @@ __global__ __launch_bounds__(FTHREADS, 2) void attn_bwd_kernel(const bf16_t* __r
                                                                const bf16_t* __restrict__ d_o,
                                                                const float* __restrict__ lse,
                                                                const float* __restrict__ dsum,
-                                                               bf16_t* __restrict__ dqkv, int S, int nl, int BH,
+                                                               bf16_t* __restrict__ dqkv, int S, int nl, int dh, int BH,
                                                                float* __restrict__ part_kv, float* __restrict__ part_q,
                                                                ChunkLen ch_kv, ChunkLen ch_q, int wgs_kv) {
     extern __shared__ __attribute__((aligned(16))) char smem[];
     const int wg = blockIdx.x;                               // uniform: one kind per workgroup, its own barriers
-    if (wg < wgs_kv) attn_dkv_wg<DH, CAUSAL>(smem, qkv, d_o, lse, dsum, dqkv, S, nl, BH, part_kv, ch_kv, wg);
-    else attn_dq_wg<DH, CAUSAL>(smem, qkv, d_o, lse, dsum, dqkv, S, nl, BH, part_q, ch_q, wg - wgs_kv);
+    if (wg < wgs_kv) attn_dkv_wg<DH, CAUSAL>(smem, qkv, d_o, lse, dsum, dqkv, S, nl, dh, BH, part_kv, ch_kv, wg);
+    else attn_dq_wg<DH, CAUSAL>(smem, qkv, d_o, lse, dsum, dqkv, S, nl, dh, BH, part_q, ch_q, wg - wgs_kv);
 }
 
 // ---- host side ----------------------------------------------------------------------------------
 bool attn_bf16_supported(const AttnArgs& a) {
     // tile loads address a (batch, head) slice with 32-bit byte offsets
-    return a.dtype == BF16 && (a.dh == 64 || a.dh == 128) && a.S >= 1 && (int64_t)a.B * a.nl <= 65535 &&
-           (int64_t)a.S * 3 * a.nl * a.dh * 2 < (1LL << 31);
+    return a.dtype == BF16 && a.dh % 8 == 0 && a.dh <= 128 && a.S >= 1 && (int64_t)a.B * a.nl <= 65535 &&
+           ((int64_t)a.S + TILE) * 3 * a.nl * a.dh * 2 < (1LL << 31);
 }
 
 template <typename K>
@@ -988,14 +994,15 @@ static int chunk_tiles_bwd(const AttnArgs& a, bool kv_side) {
     }
     return NEVER_CUT;
 }
+static int padded_dh(int dh) { return (dh + 31) / 32 * 32; }
 static size_t part_bytes_fwd(const AttnArgs& a, ChunkLen ch) {
-    return (size_t)strip_slots(a.causal, false, a.S, ch) * a.B * a.nl * BLK * (a.dh + 2) * sizeof(float);
+    return (size_t)strip_slots(a.causal, false, a.S, ch) * a.B * a.nl * BLK * (padded_dh(a.dh) + 2) * sizeof(float);
 }
 static size_t part_bytes_dq(const AttnArgs& a, ChunkLen ch) {
-    return (size_t)strip_slots(a.causal, false, a.S, ch) * a.B * a.nl * BLK * a.dh * sizeof(float);
+    return (size_t)strip_slots(a.causal, false, a.S, ch) * a.B * a.nl * BLK * padded_dh(a.dh) * sizeof(float);
 }
 static size_t part_bytes_dkv(const AttnArgs& a, ChunkLen ch) {
-    return (size_t)strip_slots(a.causal, true, a.S, ch) * a.B * a.nl * BLK * 2 * a.dh * sizeof(float);
+    return (size_t)strip_slots(a.causal, true, a.S, ch) * a.B * a.nl * BLK * 2 * padded_dh(a.dh) * sizeof(float);
 }
 // Blocks whose strips are cut: a contiguous range (strip length is monotonic in the block index).
 static void cut_range(const AttnArgs& a, bool kv_side, ChunkLen ch, int* blk0, int* n) {
@@ -1038,12 +1045,12 @@ static hipError_t fwd_t(const AttnArgs& a) {
     if (wgs > 0x7fffffffLL) return hipErrorInvalidValue;
     float* part = static_cast<float*>(a.ws);
     hipLaunchKernelGGL((attn_fwd_kernel<DH, CAUSAL>), dim3((unsigned)wgs), dim3(FTHREADS), LDS, a.stream,
-                       (const bf16_t*)a.qkv, (bf16_t*)a.o, a.lse, a.S, a.nl, BH, part, ch);
+                       (const bf16_t*)a.qkv, (bf16_t*)a.o, a.lse, a.S, a.nl, a.dh, BH, part, ch);
     int blk0 = 0, ncut = 0;
     cut_range(a, false, ch, &blk0, &ncut);
     if (ncut)
-        hipLaunchKernelGGL((attn_fwd_combine_kernel<DH, CAUSAL>), dim3(ncut * (BLK * DH / 1024), BH), dim3(256), 0,
-                           a.stream, part, (bf16_t*)a.o, a.lse, a.S, a.nl, BH, ch, blk0);
+        hipLaunchKernelGGL((attn_fwd_combine_kernel<DH, CAUSAL>), dim3(ncut * (BLK * combine_tpr<DH>() / 256), BH), dim3(256), 0,
+                           a.stream, part, (bf16_t*)a.o, a.lse, a.S, a.nl, a.dh, BH, ch, blk0);
     return hipGetLastError();
 }
 
@@ -1068,30 +1075,37 @@ static hipError_t bwd_t(const AttnArgs& a) {
     if (wgs_q + wgs_kv > 0x7fffffffLL) return hipErrorInvalidValue;
     float* part_q = static_cast<float*>(a.ws);
     float* part_kv = a.ws ? reinterpret_cast<float*>(static_cast<char*>(a.ws) + bytes_q) : nullptr;
-    const int64_t rows = (int64_t)a.B * a.S;
-    hipLaunchKernelGGL((attn_dsum_kernel<DH>), dim3((unsigned)((rows + 3) / 4)), dim3(256), 0, a.stream,
-                       (const bf16_t*)a.o, (const bf16_t*)a.d_o, a.dsum, a.B, a.S, a.nl);
+    const int64_t lanes = (int64_t)a.B * a.S * a.nl * (DH <= 32 ? 4 : DH == 64 ? 8 : 16);
+    hipLaunchKernelGGL((attn_dsum_kernel<DH>), dim3((unsigned)((lanes + 255) / 256)), dim3(256), 0, a.stream,
+                       (const bf16_t*)a.o, (const bf16_t*)a.d_o, a.dsum, a.B, a.S, a.nl, a.dh);
     hipLaunchKernelGGL((attn_bwd_kernel<DH, CAUSAL>), dim3((unsigned)(wgs_kv + wgs_q)), dim3(FTHREADS), LDS, a.stream,
-                       (const bf16_t*)a.qkv, (const bf16_t*)a.d_o, a.lse, a.dsum, (bf16_t*)a.dqkv, a.S, a.nl, BH,
+                       (const bf16_t*)a.qkv, (const bf16_t*)a.d_o, a.lse, a.dsum, (bf16_t*)a.dqkv, a.S, a.nl, a.dh, BH,
                        part_kv, part_q, ch_kv, ch_q, (int)wgs_kv);
     int blk0_q = 0, ncut_q = 0, blk0_kv = 0, ncut_kv = 0;
     cut_range(a, false, ch_q, &blk0_q, &ncut_q);
     cut_range(a, true, ch_kv, &blk0_kv, &ncut_kv);
     if (ncut_q || ncut_kv)
         hipLaunchKernelGGL((attn_bwd_combine_kernel<DH, CAUSAL>),
-                           dim3((ncut_q > ncut_kv ? ncut_q : ncut_kv) * (BLK * DH / 1024), BH, 3), dim3(256), 0, a.stream,
-                           part_q, part_kv, (bf16_t*)a.dqkv, a.S, a.nl, BH, ch_q, ch_kv, blk0_q, ncut_q, blk0_kv,
+                           dim3((ncut_q > ncut_kv ? ncut_q : ncut_kv) * (BLK * combine_tpr<DH>() / 256), BH, 3), dim3(256), 0, a.stream,
+                           part_q, part_kv, (bf16_t*)a.dqkv, a.S, a.nl, a.dh, BH, ch_q, ch_kv, blk0_q, ncut_q, blk0_kv,
                            ncut_kv);
     return hipGetLastError();
 }
 
-hipError_t attn_bf16_fwd(const AttnArgs& a) {
-    if (a.dh == 64) return a.causal ? fwd_t<64, true>(a) : fwd_t<64, false>(a);
-    return a.causal ? fwd_t<128, true>(a) : fwd_t<128, false>(a);
+template <int DH>
+static hipError_t run_dh(const AttnArgs& a, bool bwd) {
+    if (bwd) return a.causal ? bwd_t<DH, true>(a) : bwd_t<DH, false>(a);
+    return a.causal ? fwd_t<DH, true>(a) : fwd_t<DH, false>(a);
 }
-hipError_t attn_bf16_bwd(const AttnArgs& a) {
-    if (a.dh == 64) return a.causal ? bwd_t<64, true>(a) : bwd_t<64, false>(a);
-    return a.causal ? bwd_t<128, true>(a) : bwd_t<128, false>(a);
+static hipError_t run_attention(const AttnArgs& a, bool bwd) {
+    switch (padded_dh(a.dh)) {
+        case 32: return run_dh<32>(a, bwd);
+        case 64: return run_dh<64>(a, bwd);
+        case 96: return run_dh<96>(a, bwd);
+        default: return run_dh<128>(a, bwd);
+    }
 }
+hipError_t attn_bf16_fwd(const AttnArgs& a) { return run_attention(a, false); }
+hipError_t attn_bf16_bwd(const AttnArgs& a) { return run_attention(a, true); }
 
 }  // namespace tpl
