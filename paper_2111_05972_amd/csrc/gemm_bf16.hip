@@ -92,16 +92,18 @@ struct GemmParams {
     int nk_total;          // k-steps of the whole K
     float* partial;        // K split over several workgroups: float partial sums [share][M][N], else null
     bf16_t* colsum;        // [N]: sum over k of B[k][n], written by the kernels that can (see gemm_bf16), else null
+    float* colsum_part;    // with K split: [share][N], the same sums of one share; gemm_group_sum_kernel adds them
 };
 
 // Which K share a workgroup computes.  The workgroup list is share-major (all tiles of share 0, then all
 // tiles of share 1, ...), so the tiles in flight together on an XCD walk the same k range and share panels.
-struct KShare { int tile, kt0, nk, kend; float* partial; };
+struct KShare { int tile, share, kt0, nk, kend; float* partial; };
 __device__ __forceinline__ KShare k_share(const GemmParams& p, int list_pos) {
     KShare s;
     const int ntiles = p.tiles_m * p.tiles_n;
     const int share = list_pos / ntiles;
     s.tile = list_pos - share * ntiles;
+    s.share = share;
     s.kt0 = share * p.nk;
     s.nk = p.nk_total - s.kt0 < p.nk ? p.nk_total - s.kt0 : p.nk;
     s.kend = (s.kt0 + s.nk) * DK < p.K ? (s.kt0 + s.nk) * DK : p.K;
@@ -119,10 +121,11 @@ __device__ __forceinline__ int swz_k32(int row) { return (row >> 2) & 3; }
 //    column group is XORed with k & 3.
 //  * R = 192 (384-byte rows): k and k+1 already differ by 128 bytes, so k+2, k+3 are moved one
 //    64-byte group further (cyclically over the row's 6 groups; 6 = 2 mod 4 keeps the four distinct).
+//  * R = 64 (128-byte rows): k and k+1 differ by 128 bytes, k+2, k+3 take the other 64-byte group of the row.
 template <int R> __device__ __forceinline__ int mn_swz(int c, int k) {
     constexpr int CPR = R / 8;
     const int half = ((k >> 3) & 1) << 1;       // k and k + 8 (16x16x32 fragments read both at once): other 32 bytes
-    if ((CPR & (CPR - 1)) == 0) return c ^ ((k & 3) << 2) ^ half;
+    if (CPR >= 16 && (CPR & (CPR - 1)) == 0) return c ^ ((k & 3) << 2) ^ half;
     int g = (c >> 2) + ((k >> 1) & 1);
     g = g >= CPR / 4 ? g - CPR / 4 : g;
     return (g << 2) | ((c & 3) ^ half);
@@ -130,7 +133,7 @@ template <int R> __device__ __forceinline__ int mn_swz(int c, int k) {
 template <int R> __device__ __forceinline__ int mn_unswz(int c, int k) {
     constexpr int CPR = R / 8;
     const int half = ((k >> 3) & 1) << 1;
-    if ((CPR & (CPR - 1)) == 0) return c ^ ((k & 3) << 2) ^ half;
+    if (CPR >= 16 && (CPR & (CPR - 1)) == 0) return c ^ ((k & 3) << 2) ^ half;
     int g = (c >> 2) - ((k >> 1) & 1);
     g = g < 0 ? g + CPR / 4 : g;
     return (g << 2) | ((c & 3) ^ half);
@@ -495,14 +498,35 @@ __device__ __forceinline__ void epilogue_helper(const GemmParams& p, char* smem,
     epilogue_rows_shared<TL, true>(p, smem, wave, lane, m0, n0, partial, [](auto, char*) {});
 }
 
-template <typename TL, bool A_KMAJ, bool B_KMAJ>
-__global__ __launch_bounds__(256) void gemm_bf16_kernel(GemmParams p) {
-    extern __shared__ __attribute__((aligned(16))) char smem[];
+// c + the sum of the eight elements of a fragment (float accumulation)
+__device__ __forceinline__ float add_elements(const bf16x8& f, float c) {
+    typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
+    bf16x2 ones;
+    ones[0] = ones[1] = (bf16_t)1.0f;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        bf16x2 v;
+        v[0] = f[2 * e]; v[1] = f[2 * e + 1];
+        c = __builtin_amdgcn_fdot2_f32_bf16(v, ones, c, false);
+    }
+    return c;
+}
+__device__ __forceinline__ void store_colsum(const GemmParams& p, const KShare& sh, int col, float v) {
+    if (col >= p.N) return;
+    if (sh.partial) p.colsum_part[(int64_t)sh.share * p.N + col] = v;
+    else p.colsum[col] = (bf16_t)v;
+}
+
+// COLSUM: with p.colsum set, the wavefronts that hold the first rows of tile row 0 also add up the columns of B over k
+// (the bias gradient that goes with a weight gradient) from the fragments they multiply: four two-element dot products
+// with ones per fragment, in float, in their own copy of the loop.
+template <typename TL, bool A_KMAJ, bool B_KMAJ, bool COLSUM>
+__device__ __forceinline__ void gemm_tile_32(const GemmParams& p, int list_pos, char* smem) {
     constexpr int TM = TL::TM, TN = TL::TN, BM = TL::BM, BN = TL::BN, DSTAGES = TL::STAGES;
     const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
     const int wm = wave >> 1, wn = wave & 1;
     const int wave_u = __builtin_amdgcn_readfirstlane(wave);
-    const KShare sh = k_share(p, share_of_block(blockIdx.x, gridDim.x));
+    const KShare sh = k_share(p, list_pos);
 
     const i32x4 ra = make_rsrc(p.A, (unsigned)((int64_t)(A_KMAJ ? p.M : p.K) * p.lda * 2));
     const i32x4 rb = make_rsrc(p.B, (unsigned)((int64_t)(B_KMAJ ? p.N : p.K) * p.ldb * 2));
@@ -554,11 +578,18 @@ __global__ __launch_bounds__(256) void gemm_bf16_kernel(GemmParams p) {
         if (r < TM) fa[r] = dma_frag<A_KMAJ, BM>(buf, (wm * TM + r) * 32, ks, lane);
         else fb[r - TM] = dma_frag<B_KMAJ, BN>(buf + TL::A_BYTES, (wn * TN + r - TM) * 32, ks, lane);
     };
+    float cs[TN];
+#pragma unroll
+    for (int j = 0; j < TN; ++j) cs[j] = 0.0f;
     // one half stage: NM matrix instructions on (fa, fb); after instruction m, fragment m of the
     // next set is read, and the direct loads d0..d1-1 of stage ds are spread evenly over the half
     auto half = [&](const bf16x8 (&fa)[TM], const bf16x8 (&fb)[TN], bf16x8 (&na)[TM], bf16x8 (&nb)[TN],
-                    int rs, int rks, int ds, auto d0c, auto d1c) {
+                    int rs, int rks, int ds, auto d0c, auto d1c, auto csc) {
         constexpr int D0 = decltype(d0c)::value, D1 = decltype(d1c)::value, NL = D1 - D0;
+        if constexpr (decltype(csc)::value) {
+#pragma unroll
+            for (int j = 0; j < TN; ++j) cs[j] = add_elements(fb[j], cs[j]);
+        }
 #pragma unroll
         for (int m = 0; m < NM; ++m) {
             acc[m / TN][m % TN] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[m / TN], fb[m % TN], acc[m / TN][m % TN], 0, 0, 0);
@@ -574,6 +605,8 @@ __global__ __launch_bounds__(256) void gemm_bf16_kernel(GemmParams p) {
                     __builtin_amdgcn_sched_barrier(0);
                 }
         }
+#pragma unroll
+        for (int m = NM; m < TM + TN; ++m) read_one(na, nb, rs, rks, m);   // the smallest tile: more fragments than instructions
     };
     using IC0 = std::integral_constant<int, 0>;
     using ICL1 = std::integral_constant<int, L1>;
@@ -592,21 +625,43 @@ __global__ __launch_bounds__(256) void gemm_bf16_kernel(GemmParams p) {
     for (int r = 0; r < TM + TN; ++r) read_one(fa0, fb0, 0, 0, r);
     __builtin_amdgcn_sched_barrier(0);
 
-    for (int kt = 0; kt < sh.nk; ++kt) {
-        // first half: math on k-substep 0, fragments of substep 1 are read, rest of stage kt+STAGES-1 is fetched
-        half(fa0, fb0, fa1, fb1, kt, 1, kt + DSTAGES - 1, ICL1{}, ICL{});
-        // stage kt+1 has landed for this wavefront once only the newer stages are in flight; after the
-        // barrier it has landed for all, and nobody reads stage kt's slot any more.
-        wait_vmcnt<(DSTAGES - 2) * L>();
-        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-        __builtin_amdgcn_s_barrier();
-        __builtin_amdgcn_sched_barrier(0);
-        half(fa1, fb1, fa0, fb0, kt + 1, 0, kt + DSTAGES, IC0{}, ICL1{});
+    auto run = [&](auto csc) __attribute__((always_inline)) {
+        for (int kt = 0; kt < sh.nk; ++kt) {
+            // first half: math on k-substep 0, fragments of substep 1 are read, rest of stage kt+STAGES-1 is fetched
+            half(fa0, fb0, fa1, fb1, kt, 1, kt + DSTAGES - 1, ICL1{}, ICL{}, csc);
+            // stage kt+1 has landed for this wavefront once only the newer stages are in flight; after the
+            // barrier it has landed for all, and nobody reads stage kt's slot any more.
+            wait_vmcnt<(DSTAGES - 2) * L>();
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+            __builtin_amdgcn_s_barrier();
+            __builtin_amdgcn_sched_barrier(0);
+            half(fa1, fb1, fa0, fb0, kt + 1, 0, kt + DSTAGES, IC0{}, ICL1{}, csc);
+        }
+    };
+    const bool cs_on = COLSUM && p.colsum && tm == 0 && __builtin_amdgcn_readfirstlane(wm) == 0;   // uniform over the wavefront
+    if constexpr (COLSUM) {
+        if (cs_on) run(std::true_type{});                        // both copies have one barrier per k-step
+        else run(std::false_type{});
+    } else {
+        run(std::false_type{});
+    }
+    if (cs_on) {                                                 // lanes l and l + 32 hold the two k halves of column l
+#pragma unroll
+        for (int j = 0; j < TN; ++j) {
+            const float v = cs[j] + __shfl_xor(cs[j], 32, 64);
+            if (lane < 32) store_colsum(p, sh, n0 + (wn * TN + j) * 32 + lane, v);
+        }
     }
     wait_vmcnt<0>();                                             // drain the ring before LDS is reused
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
     __builtin_amdgcn_s_barrier();
     epilogue<TL>(p, acc, smem, wave, lane, m0, n0, sh.partial);
+}
+
+template <typename TL, bool A_KMAJ, bool B_KMAJ>
+__global__ __launch_bounds__(256) void gemm_bf16_kernel(GemmParams p) {
+    extern __shared__ __attribute__((aligned(16))) char smem[];
+    gemm_tile_32<TL, A_KMAJ, B_KMAJ, false>(p, share_of_block(blockIdx.x, gridDim.x), smem);
 }
 
 // =================================================================================================
@@ -1031,8 +1086,7 @@ __global__ __launch_bounds__(512) void gemm_bf16_spec_kernel(GemmParams p) {
 }
 
 // Sum of the K shares in share order, then the epilogue; 8 columns per thread, every access 16 or 32 bytes.
-__global__ __launch_bounds__(256) void gemm_sum_shares_kernel(GemmParams p, int shares) {
-    const int64_t chunk = (int64_t)blockIdx.x * 256 + threadIdx.x;
+__device__ __forceinline__ void sum_shares(const GemmParams& p, int shares, int64_t chunk) {
     const int64_t idx = chunk * 8;
     const int64_t mn = (int64_t)p.M * p.N;
     if (idx >= mn) return;
@@ -1067,7 +1121,9 @@ __global__ __launch_bounds__(256) void gemm_sum_shares_kernel(GemmParams p, int 
     }
     *reinterpret_cast<uint4*>(p.C + idx) = pack8(v8);
 }
-
+__global__ __launch_bounds__(256) void gemm_sum_shares_kernel(GemmParams p, int shares) {
+    sum_shares(p, shares, (int64_t)blockIdx.x * 256 + threadIdx.x);
+}
 
 // =================================================================================================
 // Fetch and math wavefronts on the 16x16x32 matrix instruction (K-major A only): the tile, the rings and the
@@ -1264,16 +1320,15 @@ __global__ __launch_bounds__(512) void gemm_bf16_spec16_kernel(GemmParams p) {
 // current stage has been issued (rows 4, 5 are fetched right after the first two rows), so the barrier frees this
 // stage's slot for stage kt+3 and makes stage kt+1 visible for the reads that follow it.
 // =================================================================================================
-template <typename TL, bool A_KMAJ, bool B_KMAJ, bool COLSUM = false>
-__global__ __launch_bounds__(256, 2) void gemm_bf16_x16s_kernel(GemmParams p) {
-    extern __shared__ __attribute__((aligned(16))) char smem[];
+template <typename TL, bool A_KMAJ, bool B_KMAJ, bool COLSUM>
+__device__ __forceinline__ void gemm_tile_x16s(const GemmParams& p, int list_pos, char* smem) {
     constexpr int TM = TL::TM, TN = TL::TN, BM = TL::BM, BN = TL::BN, DSTAGES = TL::STAGES;
     constexpr int FM = 2 * TM, FN = 2 * TN, L = TL::LOADS, LH = L / 2;
     static_assert(FM == 6 && DSTAGES == 3 && L % 2 == 0, "row schedule and ring accounting are written for this tile");
     const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
     const int wm = wave >> 1, wn = wave & 1;
     const int wave_u = __builtin_amdgcn_readfirstlane(wave);
-    const KShare sh = k_share(p, share_of_block(blockIdx.x, gridDim.x));
+    const KShare sh = k_share(p, list_pos);
     const i32x4 ra = make_rsrc(p.A, (unsigned)((int64_t)(A_KMAJ ? p.M : p.K) * p.lda * 2));
     const i32x4 rb = make_rsrc(p.B, (unsigned)((int64_t)(B_KMAJ ? p.N : p.K) * p.ldb * 2));
     const unsigned lds0 = (unsigned)(uintptr_t)(lds_void_ptr)smem;
@@ -1386,7 +1441,9 @@ __global__ __launch_bounds__(256, 2) void gemm_bf16_x16s_kernel(GemmParams p) {
 #pragma unroll
         for (int j = 0; j < FN; ++j) {                            // rows 0, 1 column by column
             mm(0, S0, j); mm(1, S1, j);
-            if constexpr (CS) { mfma16_v(cs[j], ones, fb[j]); __builtin_amdgcn_sched_barrier(0); }
+            // the builtin, not the assembly form: its operands may be set right before it, and then the compiler has to
+            // keep the wait states between a vector write and a matrix instruction (a one-step K showed it)
+            if constexpr (CS) { cs[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ones, fb[j], cs[j], 0, 0, 0); __builtin_amdgcn_sched_barrier(0); }
             if (j == 1) dma_one(o2, kt + 2, LH);                  // second half of stage kt+2's loads
             if (j == 3) dma_one(o2, kt + 2, LH + 1);
         }
@@ -1445,7 +1502,7 @@ __global__ __launch_bounds__(256, 2) void gemm_bf16_x16s_kernel(GemmParams p) {
         }
         if (kt < sh.nk) stage(kt, o0, o1, o2, R0{}, csc);
     };
-    const bool cs_on = COLSUM && tm == 0 && __builtin_amdgcn_readfirstlane(wm) == 0;    // uniform over the wavefront
+    const bool cs_on = COLSUM && p.colsum && tm == 0 && __builtin_amdgcn_readfirstlane(wm) == 0;    // uniform over the wavefront
     if constexpr (COLSUM) {
         if (cs_on) run(std::true_type{});                         // both copies have one barrier per k-step
         else run(std::false_type{});
@@ -1455,17 +1512,77 @@ __global__ __launch_bounds__(256, 2) void gemm_bf16_x16s_kernel(GemmParams p) {
     mfma16_drain();
     if (cs_on && lane < 16) {                                     // lanes 0..15 hold row 0 of each block: columns 0..15
 #pragma unroll
-        for (int j = 0; j < (COLSUM ? FN : 1); ++j) {
-            const int col = n0 + (wn * FN + j) * 16 + lane;
-            if (col < p.N) p.colsum[col] = (bf16_t)cs[j][0];
-        }
+        for (int j = 0; j < (COLSUM ? FN : 1); ++j) store_colsum(p, sh, n0 + (wn * FN + j) * 16 + lane, cs[j][0]);
     }
     wait_vmcnt<0>();
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
     __builtin_amdgcn_s_barrier();
     epilogue16<TL>(p, acc, smem, wave, lane, m0, n0, sh.partial);
 }
+template <typename TL, bool A_KMAJ, bool B_KMAJ, bool COLSUM = false>
+__global__ __launch_bounds__(256, 2) void gemm_bf16_x16s_kernel(GemmParams p) {
+    extern __shared__ __attribute__((aligned(16))) char smem[];
+    gemm_tile_x16s<TL, A_KMAJ, B_KMAJ, COLSUM>(p, share_of_block(blockIdx.x, gridDim.x), smem);
+}
 
+// =================================================================================================
+// Several GEMMs in one launch.  The GEMMs of a narrow layer have 10 to 500 tiles of 10 to 60 k-steps each: launched one by
+// one, each leaves compute units idle, fills its LDS ring and drains its epilogue with nothing beside it, and costs a
+// launch.  The GEMMs of a pass that do not depend on each other (weight gradients, data gradients, both blocks) go out as
+// one list of workgroups instead, longest K first.  All use one tile; the layouts of a layer's GEMMs (NN forward, NT data
+// gradient, TN weight gradient with the column sums of its B) are three bodies of the same kernel.
+// Measured, whole training steps against one launch per GEMM and bias gradient (on two or three chains where the caller
+// allows): 198 tokens x 2 of an 832 / 104 shard 156 -> 60 us, BERT-large TP 4 263 -> 181 us, RoBERTa-large TP 2 545 -> 515,
+// 3003 tokens of 2560 / 640 542 -> 498, 610 tokens of 10752 / 1344 934 -> 792.  Which tile: at 832 / 104 64 / 128 / 192 take
+// 60 / 73 / 107 us, at BERT-large 236 / 182 / 205, at 2560 / 640 826 / 546 / 499.
+// =================================================================================================
+constexpr int GROUP_MAX = 4;
+struct GroupParams {
+    GemmParams g[GROUP_MAX];
+    int first[GROUP_MAX + 1];      // workgroups [first[i], first[i+1]) compute GEMM i
+    int layout[GROUP_MAX];         // 0: NN, 1: NT, 2: TN
+    int shares[GROUP_MAX];
+    int n;
+};
+template <typename TL, bool A_KMAJ, bool B_KMAJ, bool COLSUM>
+__device__ __forceinline__ void group_tile(const GemmParams& p, int list_pos, char* smem) {
+    if constexpr (TL::TM == 3) gemm_tile_x16s<TL, A_KMAJ, B_KMAJ, COLSUM>(p, list_pos, smem);
+    else gemm_tile_32<TL, A_KMAJ, B_KMAJ, COLSUM>(p, list_pos, smem);
+}
+template <typename TL>
+__global__ __launch_bounds__(256, 2) void gemm_bf16_group_kernel(GroupParams gp) {
+    extern __shared__ __attribute__((aligned(16))) char smem[];
+    const int bid = blockIdx.x;
+    int i = 0;
+    while (i + 1 < gp.n && bid >= gp.first[i + 1]) ++i;
+    const GemmParams& p = gp.g[i];
+    const int pos = share_of_block(bid - gp.first[i], gp.first[i + 1] - gp.first[i]);
+    const int layout = gp.layout[i];
+    if (layout == 0) group_tile<TL, true, false, false>(p, pos, smem);
+    else if (layout == 1) group_tile<TL, true, true, false>(p, pos, smem);
+    else group_tile<TL, false, false, true>(p, pos, smem);
+}
+// The sums over K shares of all GEMMs of a group that were cut (and of their column sums): GEMM i has the workgroups
+// [first[i], first[i+1]) of this launch, 256 chunks of 8 outputs each, the N / 8 chunks of the column sums last.
+__global__ __launch_bounds__(256) void gemm_group_sum_kernel(GroupParams gp) {
+    const int bid = blockIdx.x;
+    int i = 0;
+    while (i + 1 < gp.n && bid >= gp.first[i + 1]) ++i;
+    const GemmParams& p = gp.g[i];
+    const int shares = gp.shares[i];
+    const int64_t chunk = (int64_t)(bid - gp.first[i]) * 256 + threadIdx.x, chunks = (int64_t)p.M * p.N / 8;
+    if (chunk < chunks) { sum_shares(p, shares, chunk); return; }
+    const int64_t col = (chunk - chunks) * 8;
+    if (!p.colsum || col >= p.N) return;
+    float v8[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+    for (int s = 0; s < shares; ++s) {
+        float x8[8];
+        load8(p.colsum_part + (int64_t)s * p.N + col, x8);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) v8[e] += x8[e];
+    }
+    store8(p.colsum + col, v8);
+}
 
 
 bool gemm_bf16_supported(const GemmArgs& a) {
@@ -1763,9 +1880,8 @@ size_t gemm_bf16_workspace_bytes(int64_t M, int64_t N, int64_t K) {
     return need;
 }
 
-hipError_t gemm_bf16(const GemmArgs& a, bool* colsum_done) {
-    if (colsum_done) *colsum_done = false;
-    GemmParams p;
+static GemmParams gemm_params(const GemmArgs& a) {
+    GemmParams p{};
     p.A = (const bf16_t*)a.A; p.B = (const bf16_t*)a.B; p.C = (bf16_t*)a.C;
     p.bias = (const bf16_t*)a.bias; p.resid = (const bf16_t*)a.resid; p.aux = (bf16_t*)a.aux;
     p.M = (int)a.M; p.N = (int)a.N; p.K = (int)a.K;
@@ -1775,10 +1891,15 @@ hipError_t gemm_bf16(const GemmArgs& a, bool* colsum_done) {
     p.epi = a.epi;
     p.tiles_m = p.tiles_n = 0;
     p.band = 8;
-    const Plan pl = plan_for(a.M, a.N, a.K, !a.trans_a, a.trans_b != 0);
     p.nk_total = (int)((a.K + DK - 1) / DK);
+    return p;
+}
+
+hipError_t gemm_bf16(const GemmArgs& a, bool* colsum_done) {
+    if (colsum_done) *colsum_done = false;
+    GemmParams p = gemm_params(a);
+    const Plan pl = plan_for(a.M, a.N, a.K, !a.trans_a, a.trans_b != 0);
     p.nk = pl.nk_share;
-    p.partial = nullptr;
     // the column sums of B ride along only on request (option fuse_colsum), in the weight-gradient kernel (both operands
     // MN-major) with K unsplit
     p.colsum = (a.colsum_b && options().fuse_colsum && pl.variant == 7 && pl.shares == 1 && a.trans_a && !a.trans_b)
@@ -1806,6 +1927,127 @@ hipError_t gemm_bf16(const GemmArgs& a, bool* colsum_done) {
     if (e != hipSuccess || pl.shares == 1) return e;
     const int64_t chunks = a.M * a.N / 8;
     hipLaunchKernelGGL(gemm_sum_shares_kernel, dim3((unsigned)((chunks + 255) / 256)), dim3(256), 0, a.stream, p, pl.shares);
+    return hipGetLastError();
+}
+
+// ---- groups ------------------------------------------------------------------------------------------------------------
+// One tile for the whole group and K shares per GEMM, by a time estimate.  A launch takes as long as its units have work
+// (k-steps of all workgroups, a start and an epilogue per workgroup) or as its longest workgroup runs by itself, whichever
+// is more; K shares shorten the longest ones and cost the partial sums' traffic and a launch.  The constants are fitted to
+// the kernel times of 40 groups of 10 layers (256 to 4096 wide, 400 to 8200 tokens) on each tile: 7 to 10 % root mean square.
+namespace {
+struct GroupTile { int bm; double step_us, wg_us, base_us, alone_us, alone_base_us; };
+constexpr GroupTile GROUP_TILES[] = {{192, 0.60, 2.6, 13.0, 0.77, 4.5}, {128, 0.355, 1.0, 7.5, 0.38, 4.5}, {64, 0.143, 0.92, 4.5, 0.35, 2.1}};
+struct GroupPlan { int tile, nk[GROUP_MAX], shares[GROUP_MAX]; double us; };
+
+int64_t group_tiles(const GemmArgs& a, int bm) { return ((a.M + bm - 1) / bm) * ((a.N + bm - 1) / bm); }
+
+GroupPlan plan_group(const GemmArgs* g, int n) {
+    const int cus = compute_units(), forced = options().gemm_group;
+    GroupPlan best{};
+    best.us = -1;
+    for (int t = 0; t < 3; ++t) {
+        const GroupTile& gt = GROUP_TILES[t];
+        if (forced > 0 && forced != gt.bm) continue;
+        GroupPlan p{};
+        p.tile = t;
+        int64_t tiles[GROUP_MAX];
+        int nk[GROUP_MAX];
+        for (int i = 0; i < n; ++i) {
+            tiles[i] = group_tiles(g[i], gt.bm);
+            nk[i] = p.nk[i] = (int)((g[i].K + DK - 1) / DK);
+            p.shares[i] = 1;
+        }
+        auto estimate = [&]() {
+            double work = 0, wgs = 0, longest = 0, bytes = 0;
+            for (int i = 0; i < n; ++i) {
+                wgs += (double)tiles[i] * p.shares[i];
+                work += (double)tiles[i] * p.shares[i] * p.nk[i];
+                longest = std::max(longest, (double)p.nk[i]);
+                if (p.shares[i] > 1) bytes += (double)g[i].M * g[i].N * (8.0 * p.shares[i] + 2.0);
+            }
+            return std::max((work * gt.step_us + wgs * gt.wg_us) / cus + gt.base_us, longest * gt.alone_us + gt.alone_base_us) +
+                   (bytes > 0 ? 4.2 + bytes / 1.6e7 : 0.0);
+        };
+        p.us = estimate();
+        for (int cuts = 0; cuts < 16; ++cuts) {                   // cut the longest again while that helps
+            int l = 0;
+            for (int i = 1; i < n; ++i) if (p.nk[i] > p.nk[l]) l = i;
+            const int want = p.shares[l] + 1;
+            if (want > MAX_SHARES || nk[l] / want < 12) break;
+            const GroupPlan before = p;
+            p.nk[l] = (nk[l] + want - 1) / want;
+            p.shares[l] = (nk[l] + p.nk[l] - 1) / p.nk[l];
+            p.us = estimate();
+            // one cut alone may not pay while the next does (two GEMMs of the same length): keep the best seen
+            if (best.us < 0 || before.us < best.us) best = before;
+        }
+        if (best.us < 0 || p.us < best.us) best = p;
+    }
+    return best;
+}
+size_t share_bytes(const GemmArgs& a, int shares) {               // float partial sums, column sums included
+    return shares > 1 ? (size_t)shares * ((size_t)a.M * a.N + (size_t)a.N) * sizeof(float) : 0;
+}
+}  // namespace
+
+size_t gemm_bf16_group_workspace_bytes(const GemmArgs* g, int n) {
+    const GroupPlan pl = plan_group(g, n);
+    size_t need = 0;
+    for (int i = 0; i < n; ++i) need += share_bytes(g[i], pl.shares[i]);
+    return need;
+}
+
+template <typename TL>
+static hipError_t launch_group(const GroupParams& gp, int wgs, hipStream_t s) {
+    static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_bf16_group_kernel<TL>),
+                                                       hipFuncAttributeMaxDynamicSharedMemorySize, TL::LDS_BYTES);
+    if (attr != hipSuccess) return attr;
+    hipLaunchKernelGGL(gemm_bf16_group_kernel<TL>, dim3((unsigned)wgs), dim3(256), TL::LDS_BYTES, s, gp);
+    return hipGetLastError();
+}
+
+hipError_t gemm_bf16_group(const GemmArgs* g, int n, void* ws, size_t ws_bytes, hipStream_t stream) {
+    if (n < 1 || n > GROUP_MAX) return hipErrorInvalidValue;
+    const GroupPlan pl = plan_group(g, n);
+    const int bm = GROUP_TILES[pl.tile].bm;
+    int order[GROUP_MAX] = {0, 1, 2, 3};
+    std::stable_sort(order, order + n, [&](int a, int b) { return pl.nk[a] > pl.nk[b]; });
+    GroupParams gp{}, sp{};                                       // the GEMMs; the sums of those that were cut
+    gp.n = n;
+    char* part = static_cast<char*>(ws);
+    size_t used = 0;
+    for (int q = 0; q < n; ++q) {
+        const GemmArgs& a = g[order[q]];
+        const int shares = pl.shares[order[q]];
+        GemmParams p = gemm_params(a);
+        p.nk = pl.nk[order[q]];
+        p.tiles_m = (int)((a.M + bm - 1) / bm);
+        p.tiles_n = (int)((a.N + bm - 1) / bm);
+        p.band = choose_band(p.tiles_m, bm, bm, 0);
+        p.colsum = a.trans_a ? (bf16_t*)a.colsum_b : nullptr;
+        if (shares > 1) {
+            const size_t bytes = share_bytes(a, shares);
+            if (!ws || used + bytes > ws_bytes) return hipErrorInvalidValue;
+            p.partial = reinterpret_cast<float*>(part + used);
+            p.colsum_part = p.partial + (size_t)shares * a.M * a.N;
+            used += bytes;
+            sp.g[sp.n] = p;
+            sp.shares[sp.n] = shares;
+            const int64_t chunks = a.M * a.N / 8 + (p.colsum ? a.N / 8 : 0);
+            sp.first[sp.n + 1] = sp.first[sp.n] + (int)((chunks + 255) / 256);
+            ++sp.n;
+        }
+        gp.g[q] = p;
+        gp.shares[q] = shares;
+        gp.layout[q] = a.trans_a ? 2 : a.trans_b ? 1 : 0;
+        gp.first[q + 1] = gp.first[q] + p.tiles_m * p.tiles_n * shares;
+    }
+    hipError_t e = pl.tile == 0   ? launch_group<Tile<3, 3, 3>>(gp, gp.first[n], stream)
+                   : pl.tile == 1 ? launch_group<Tile<2, 2, 4>>(gp, gp.first[n], stream)
+                                  : launch_group<Tile<1, 1, 6>>(gp, gp.first[n], stream);
+    if (e != hipSuccess || sp.n == 0) return e;
+    hipLaunchKernelGGL(gemm_group_sum_kernel, dim3((unsigned)sp.first[sp.n]), dim3(256), 0, stream, sp);
     return hipGetLastError();
 }
 

@@ -19,12 +19,13 @@ struct Options {
     int attn_chunk = -1;       // force the chunk length of attention strips in 64-row tile steps (0: never cut); -1: unset
     int side_chains = 0;       // chains of a backward pass under TPL_SIDE_STREAM: 2, or 3 (dW_dn and dW_o on a stream of their
                                // own); 0: the library chooses by the size of the weight gradients
+    int gemm_group = -1;       // independent GEMMs of a layer pass in one launch: 0 never; 64, 128, 192: always, on that tile; -1: by size
     int fuse_colsum = 0;       // 1: bias gradients as one more output row of the weight-gradient GEMM where its kernel can
     char gemm_force[1024] = "";   // "MxNxK@ab=v[:shares];..." plans of single shapes (a, b = 1: A, B K-major)
     unsigned generation = 0;
 };
 const Options& options();
-// name: "gemm_tile", "gemm_shares", "gemm_band", "gemm_force", "attn_chunk", "fuse_colsum", "side_chains"; value null or "": back to unset.
+// name: "gemm_tile", "gemm_shares", "gemm_band", "gemm_force", "gemm_group", "attn_chunk", "fuse_colsum", "side_chains"; value null or "": back to unset.
 // Returns false for an unknown name or a value that does not parse.
 bool set_option(const char* name, const char* value);
 enum Epi { EPI_NONE = 0, EPI_GELU = 1, EPI_DGELU = 2 };
@@ -134,6 +135,9 @@ hipError_t attn_f32_bwd(const AttnArgs& a);
 bool gemm_bf16_supported(const GemmArgs& a);
 size_t gemm_bf16_workspace_bytes(int64_t M, int64_t N, int64_t K);
 hipError_t gemm_bf16(const GemmArgs& a, bool* colsum_done = nullptr);
+// Up to 4 GEMMs that do not depend on each other (layouts NN, NT, TN) as one launch; colsum_b of a TN one is always written.
+size_t gemm_bf16_group_workspace_bytes(const GemmArgs* g, int n);
+hipError_t gemm_bf16_group(const GemmArgs* g, int n, void* ws, size_t ws_bytes, hipStream_t stream);
 bool attn_bf16_supported(const AttnArgs& a);
 hipError_t attn_bf16_fwd(const AttnArgs& a);
 hipError_t attn_bf16_bwd(const AttnArgs& a);

@@ -43,6 +43,11 @@ bool set_option(const char* name, const char* value) {
     else if (!strcmp(name, "gemm_shares")) ok = parse_int(value, 0, 0, 64, &o.gemm_shares);
     else if (!strcmp(name, "gemm_band")) ok = parse_int(value, 0, 0, 1 << 20, &o.gemm_band);
     else if (!strcmp(name, "attn_chunk")) ok = parse_int(value, -1, 0, 1 << 16, &o.attn_chunk);
+    else if (!strcmp(name, "gemm_group")) {
+        int v;
+        ok = parse_int(value, -1, 0, 192, &v) && (v <= 0 || v == 64 || v == 128 || v == 192);
+        if (ok) o.gemm_group = v;
+    }
     else if (!strcmp(name, "fuse_colsum")) ok = parse_int(value, 0, 0, 1, &o.fuse_colsum);
     else if (!strcmp(name, "side_chains")) ok = parse_int(value, 0, 2, 3, &o.side_chains);
     else if (!strcmp(name, "gemm_force")) {
@@ -111,7 +116,7 @@ size_t gemm_ws(int dtype, int64_t M, int64_t N, int64_t K) {
 }
 
 // Backward scratch: dU, dO, dQKV, D, and per chain (attention, MLP) column-sum partials and GEMM scratch.
-struct BwdWs { size_t du, d_o, dqkv, dsum, colsum, colsum2, gemm, gemm2, gemm3, gemm_each, attn, attn_bytes, total; };
+struct BwdWs { size_t du, d_o, dqkv, dsum, colsum, colsum2, gemm, gemm2, gemm3, gemm_each, gemm_all, attn, attn_bytes, total; };
 
 // Float partials of attention strips cut into chunks: inside a layer pass only when TPL_ATTN_CHUNK forces a chunk
 // length (own_chunking stays 0: see attn_bf16.hip), so normally 0.
@@ -130,7 +135,44 @@ size_t fwd_gemm_ws(const Dims& x) {
     g = std::max(g, gemm_ws(x.dtype, x.M, x.H, x.Il));
     return std::max(g, ALIGN);
 }
-size_t fwd_ws_total(const Dims& x) { return 2 * fwd_gemm_ws(x) + attn_ws(x, false); }
+
+// ---- GEMMs of a pass as groups ---------------------------------------------------------------------------------------
+// The GEMMs of a pass that do not depend on each other, over both blocks, form one launch each:
+//   forward   {up, qkv}, attention, {down, out}
+//   backward  {dW_dn, dW_o, dU, dO}, attention, {dW_up, dW_qkv, dx_mlp, dx_attn}; the bias gradients are column sums of
+//             the weight gradients' second operands and ride in them
+GemmArgs gemm_args(const Dims& x, int ta, int tb, int64_t M, int64_t N, int64_t K, const void* A = nullptr,
+                   const void* B = nullptr, void* C = nullptr) {
+    GemmArgs g{};
+    g.dtype = x.dtype; g.trans_a = ta; g.trans_b = tb; g.M = M; g.N = N; g.K = K;
+    g.A = A; g.B = B; g.C = C; g.epi = EPI_NONE;
+    return g;
+}
+size_t group_ws(const Dims& x, bool bwd) {
+    if (x.dtype != BF16) return 0;
+    GemmArgs first[4], second[4];
+    int n1 = 0, n2 = 0;
+    if (!bwd) {
+        first[n1++] = gemm_args(x, 0, 0, x.M, x.Il, x.H);
+        first[n1++] = gemm_args(x, 0, 0, x.M, 3 * x.Hl, x.H);
+        second[n2++] = gemm_args(x, 0, 0, x.M, x.H, x.Il);
+        second[n2++] = gemm_args(x, 0, 0, x.M, x.H, x.Hl);
+    } else {
+        first[n1++] = gemm_args(x, 1, 0, x.Il, x.H, x.M);
+        first[n1++] = gemm_args(x, 1, 0, x.Hl, x.H, x.M);
+        first[n1++] = gemm_args(x, 0, 1, x.M, x.Il, x.H);
+        first[n1++] = gemm_args(x, 0, 1, x.M, x.Hl, x.H);
+        second[n2++] = gemm_args(x, 1, 0, x.H, x.Il, x.M);
+        second[n2++] = gemm_args(x, 1, 0, x.H, 3 * x.Hl, x.M);
+        second[n2++] = gemm_args(x, 0, 1, x.M, x.H, x.Il);
+        second[n2++] = gemm_args(x, 0, 1, x.M, x.H, 3 * x.Hl);
+    }
+    return up(std::max(gemm_bf16_group_workspace_bytes(first, n1), gemm_bf16_group_workspace_bytes(second, n2)));
+}
+// GEMM scratch of a pass: one region per chain, or what its groups need (both, so that the choice may differ between the
+// size query and the call: per-GEMM timing runs the GEMMs one by one).
+size_t fwd_gemm_total(const Dims& x) { return std::max(2 * fwd_gemm_ws(x), group_ws(x, false)); }
+size_t fwd_ws_total(const Dims& x) { return fwd_gemm_total(x) + attn_ws(x, false); }
 
 void bwd_layout(const Dims& x, BwdWs* W) {
     size_t off = 0;
@@ -151,7 +193,9 @@ void bwd_layout(const Dims& x, BwdWs* W) {
     W->gemm_each = g;
     W->gemm = off; off += g;
     W->gemm2 = off; off += g;
-    W->gemm3 = off; off += g;      // the two weight gradients that depend on nothing computed in the pass (third chain)
+    const size_t grouped = group_ws(x, true);          // spans the three regions
+    W->gemm3 = off; off += std::max(g, grouped > 2 * g ? grouped - 2 * g : 0);   // the two weight gradients that depend on nothing computed in the pass (third chain)
+    W->gemm_all = off - W->gemm;
     W->attn_bytes = attn_ws(x, true);
     W->attn = off; off += W->attn_bytes;
     W->total = off;
@@ -248,16 +292,35 @@ int run_attn(AttnArgs& a, bool bwd) {
     return e == hipSuccess ? TPL_OK : TPL_EHIP;
 }
 
+// Forward GEMM work above which a pass is left to launches of single GEMMs (on two chains if the caller asks): each GEMM
+// fills the chip by itself there, on the tile that suits it best (whole steps: groups are 8 % ahead at 0.43 TFLOP, 2 % at 0.6, 1 % behind at 0.64
+// (GPT-3 13B, TP 4) and 10 % at 0.93 (GPT-3 175B, TP 8: 2.68 against 2.45 ms)).
+constexpr double GROUP_MAX_FLOP = 0.64e12;
+
 // Scratch handed to every GEMM of one entry-point call.
 struct GemmScratch { void* ws; size_t bytes; hipStream_t stream; };
 
 GemmArgs mk(const Dims& x, int ta, int tb, int64_t M, int64_t N, int64_t K, const void* A,
             const void* B, void* C, GemmScratch& sc) {
-    void* ws = sc.ws; size_t ws_bytes = sc.bytes; hipStream_t s = sc.stream;
-    GemmArgs g{};
-    g.dtype = x.dtype; g.trans_a = ta; g.trans_b = tb; g.M = M; g.N = N; g.K = K;
-    g.A = A; g.B = B; g.C = C; g.epi = EPI_NONE; g.ws = ws; g.ws_bytes = ws_bytes; g.stream = s;
+    GemmArgs g = gemm_args(x, ta, tb, M, N, K, A, B, C);
+    g.ws = sc.ws; g.ws_bytes = sc.bytes; g.stream = sc.stream;
     return g;
+}
+
+// Whether the GEMMs of a pass go out as groups.
+bool use_groups(const Dims& x) {
+    const Options& o = options();
+    if (x.dtype != BF16 || g_prof.on || o.gemm_group == 0) return false;
+    // every operand within the matrix-core kernels' 32-bit offsets (whole 16-byte rows are given)
+    const int64_t widest = std::max(std::max(x.Il, 3 * x.Hl), x.H);
+    if (std::max(x.M, x.H) * widest * 2 >= 0x7FFFFFFFll) return false;
+    if (o.gemm_group > 0) return true;
+    // the other GEMM overrides speak about launches of one GEMM and about chains
+    if (o.gemm_tile >= 0 || o.gemm_shares > 0 || o.gemm_force[0] || o.gemm_band > 0 || o.side_chains || o.fuse_colsum) return false;
+    return 2.0 * (double)x.M * x.H * (4.0 * x.Hl + 2.0 * x.Il) < GROUP_MAX_FLOP;
+}
+int run_group(const GemmArgs* g, int n, const GemmScratch& sc) {
+    return gemm_bf16_group(g, n, sc.ws, sc.bytes, sc.stream) == hipSuccess ? TPL_OK : TPL_EHIP;
 }
 
 // Forward kernels in order.  With row_parallel == false the two row-parallel GEMMs (whose outputs the
@@ -271,34 +334,45 @@ int fwd_impl(const Dims& x, const tp_layer_params* p, const void* x_attn, const 
     void *qkv = sv + L.qkv, *o = sv + L.o, *u = sv + L.u, *g = sv + L.g;
     float* lse = (float*)(sv + L.lse);
     // each chain has its own half of the GEMM scratch
-    const size_t half = fwd_gemm_ws(x);
-    hipStream_t s2 = side_fork(s, x.side_stream);
+    const size_t half = fwd_gemm_ws(x), gemm_total = fwd_gemm_total(x);
+    const bool groups = use_groups(x);
+    hipStream_t s2 = side_fork(s, x.side_stream && !groups);
     SideJoin sj{s, s2};
-    GemmScratch sc{ws, half, s}, sc2{(char*)ws + half, half, s2};
+    GemmScratch sc{ws, half, s}, sc2{(char*)ws + half, half, s2}, all{ws, gemm_total, s};
 
     // MLP block (second chain): column-parallel up-projection + GeLU, row-parallel down-projection
     GemmArgs g4 = mk(x, 0, 0, x.M, x.Il, x.H, x_mlp, p->w_up, g, sc2);
     g4.bias = p->b_up; g4.aux = u; g4.epi = EPI_GELU;
-    if ((rc = run_gemm(g4))) return rc;
-    if (row_parallel) {
-        GemmArgs g5 = mk(x, 0, 0, x.M, x.H, x.Il, g, p->w_dn, y_mlp, sc2);
-        if (x.row_epi) { g5.bias = p->b_dn; g5.resid = x_mlp; }
-        if ((rc = run_gemm(g5))) return rc;
+    GemmArgs g5 = mk(x, 0, 0, x.M, x.H, x.Il, g, p->w_dn, y_mlp, sc2);
+    if (x.row_epi) { g5.bias = p->b_dn; g5.resid = x_mlp; }
+    if (!groups) {
+        if ((rc = run_gemm(g4))) return rc;
+        if (row_parallel && (rc = run_gemm(g5))) return rc;
     }
     // attention block: column-parallel fused QKV, attention on the local heads, row-parallel out-proj
     GemmArgs g1 = mk(x, 0, 0, x.M, 3 * x.Hl, x.H, x_attn, p->w_qkv, qkv, sc);
     g1.bias = p->b_qkv;
-    if ((rc = run_gemm(g1))) return rc;
+    if (groups) {
+        const GemmArgs first[] = {g4, g1};
+        if ((rc = run_group(first, 2, all))) return rc;
+    } else if ((rc = run_gemm(g1))) {
+        return rc;
+    }
     AttnArgs at{};
     at.dtype = x.dtype; at.B = (int)x.B; at.S = (int)x.S; at.nl = (int)x.nl; at.dh = (int)x.dh;
     at.causal = x.causal; at.qkv = qkv; at.o = o; at.lse = lse; at.stream = s;
     at.ws_bytes = attn_ws(x, false);
-    at.ws = at.ws_bytes ? (char*)ws + 2 * half : nullptr;
+    at.ws = at.ws_bytes ? (char*)ws + gemm_total : nullptr;
     if ((rc = run_attn(at, false))) return rc;
     if (row_parallel) {
         GemmArgs g3 = mk(x, 0, 0, x.M, x.H, x.Hl, o, p->w_o, y_attn, sc);
         if (x.row_epi) { g3.bias = p->b_o; g3.resid = x_attn; }
-        if ((rc = run_gemm(g3))) return rc;
+        if (groups) {
+            const GemmArgs second[] = {g5, g3};
+            if ((rc = run_group(second, 2, all))) return rc;
+        } else if ((rc = run_gemm(g3))) {
+            return rc;
+        }
     }
     return sj.finish();
 }
@@ -344,7 +418,8 @@ int bwd_impl(const Dims& x, const tp_layer_params* p, const void* x_attn, const 
     char* w = (char*)ws;
     void *du = w + W.du, *d_o = w + W.d_o, *dqkv = w + W.dqkv;
     float *dsum = (float*)(w + W.dsum), *cs = (float*)(w + W.colsum), *cs2 = (float*)(w + W.colsum2);
-    hipStream_t s2 = side_fork(s, x.side_stream);
+    const bool groups = use_groups(x), side = x.side_stream && !groups;
+    hipStream_t s2 = side_fork(s, side);
     SideJoin sj{s, s2};
     // dW_dn and dW_o need only the pass's inputs and saved activations: they can form a third chain on a stream of
     // their own (option side_chains = 2 or 3 forces the number of chains)
@@ -353,49 +428,56 @@ int bwd_impl(const Dims& x, const tp_layer_params* p, const void* x_attn, const 
     // way; left to itself the library takes three chains below 45 GFLOP per weight gradient)
     const int chains = options().side_chains ? options().side_chains
                                              : (2.0 * (double)x.Il * (double)x.H * (double)x.M < 45.0e9 ? 3 : 2);
-    hipStream_t s3 = chains >= 3 ? side_fork(s, x.side_stream, 1) : nullptr;
+    hipStream_t s3 = chains >= 3 ? side_fork(s, side, 1) : nullptr;
     SideJoin sj3{s, s3 ? s3 : s, 1};
     GemmScratch sc{w + W.gemm, W.gemm_each, s}, sc2{w + W.gemm2, W.gemm_each, s2};
     GemmScratch sc3a{w + W.gemm3, W.gemm_each, s3 ? s3 : s2}, sc3b{w + W.gemm3, W.gemm_each, s3 ? s3 : s};
 
-    // MLP block (second chain).  dU = (dy_m W_dn^T) * gelu'(U) in one GEMM epilogue.
+    // dU = (dy_m W_dn^T) * gelu'(U) in one GEMM epilogue.  Weight gradients are not read again in the pass; the bias
+    // gradients are the column sums of their second operand (colsum_b), left by the same launch where it can.
     GemmArgs b5 = mk(x, 0, 1, x.M, x.Il, x.H, dy_mlp, p->w_dn, du, sc2);
     b5.aux = const_cast<void*>(u); b5.epi = EPI_DGELU;
-    if ((rc = run_gemm(b5))) return rc;
     GemmArgs w5 = mk(x, 1, 0, x.Il, x.H, x.M, g, dy_mlp, gr->dw_dn, s3 ? sc3a : sc2);
-    w5.c_streaming = true;                   // the weight gradient is not read again in this pass
-    if ((rc = run_gemm(w5))) return rc;
     GemmArgs w4 = mk(x, 1, 0, x.H, x.Il, x.M, x_mlp, du, gr->dw_up, sc2);
-    w4.c_streaming = true;
-    w4.colsum_b = gr->db_up;                 // db_up = column sums of dU: one more output row of this GEMM where it can
-    if ((rc = run_gemm(w4))) return rc;
-    if (!w4.colsum_done && colsum(x.dtype, x.M, x.Il, du, gr->db_up, cs2, s2) != hipSuccess) return TPL_EHIP;
     GemmArgs d4 = mk(x, 0, 1, x.M, x.H, x.Il, du, p->w_up, dx_mlp, sc2);
-    if (x.row_epi) d4.resid = dy_mlp;
-    if ((rc = run_gemm(d4))) return rc;
-    if (x.row_epi && colsum(x.dtype, x.M, x.H, dy_mlp, gr->db_dn, cs2, s2) != hipSuccess) return TPL_EHIP;
-
-    // attention block
     GemmArgs d3 = mk(x, 0, 1, x.M, x.Hl, x.H, dy_attn, p->w_o, d_o, sc);
-    if ((rc = run_gemm(d3))) return rc;
     GemmArgs w3 = mk(x, 1, 0, x.Hl, x.H, x.M, o, dy_attn, gr->dw_o, s3 ? sc3b : sc);
-    w3.c_streaming = true;
-    if ((rc = run_gemm(w3))) return rc;
-    if (x.row_epi && colsum(x.dtype, x.M, x.H, dy_attn, gr->db_o, cs, s) != hipSuccess) return TPL_EHIP;
+    GemmArgs w1 = mk(x, 1, 0, x.H, 3 * x.Hl, x.M, x_attn, dqkv, gr->dw_qkv, sc);
+    GemmArgs d1 = mk(x, 0, 1, x.M, x.H, 3 * x.Hl, dqkv, p->w_qkv, dx_attn, sc);
+    w5.c_streaming = w4.c_streaming = w3.c_streaming = w1.c_streaming = true;
+    w4.colsum_b = gr->db_up;
+    w1.colsum_b = gr->db_qkv;
+    if (x.row_epi) { d4.resid = dy_mlp; d1.resid = dy_attn; }
     AttnArgs at{};
     at.dtype = x.dtype; at.B = (int)x.B; at.S = (int)x.S; at.nl = (int)x.nl; at.dh = (int)x.dh;
     at.causal = x.causal; at.qkv = qkv; at.o = const_cast<void*>(o); at.lse = const_cast<float*>(lse);
     at.d_o = d_o; at.dqkv = dqkv; at.dsum = dsum; at.stream = s;
     at.ws_bytes = W.attn_bytes;
     at.ws = W.attn_bytes ? w + W.attn : nullptr;
+
+    if (groups) {
+        if (x.row_epi) { w5.colsum_b = gr->db_dn; w3.colsum_b = gr->db_o; }
+        const GemmScratch all{w + W.gemm, W.gemm_all, s};
+        const GemmArgs first[] = {w5, w3, b5, d3}, second[] = {w4, w1, d4, d1};
+        if ((rc = run_group(first, 4, all))) return rc;
+        if ((rc = run_attn(at, true))) return rc;
+        return run_group(second, 4, all);
+    }
+
+    // MLP block (second chain)
+    if ((rc = run_gemm(b5))) return rc;
+    if ((rc = run_gemm(w5))) return rc;
+    if ((rc = run_gemm(w4))) return rc;
+    if (!w4.colsum_done && colsum(x.dtype, x.M, x.Il, du, gr->db_up, cs2, s2) != hipSuccess) return TPL_EHIP;
+    if ((rc = run_gemm(d4))) return rc;
+    if (x.row_epi && colsum(x.dtype, x.M, x.H, dy_mlp, gr->db_dn, cs2, s2) != hipSuccess) return TPL_EHIP;
+    // attention block
+    if ((rc = run_gemm(d3))) return rc;
+    if ((rc = run_gemm(w3))) return rc;
+    if (x.row_epi && colsum(x.dtype, x.M, x.H, dy_attn, gr->db_o, cs, s) != hipSuccess) return TPL_EHIP;
     if ((rc = run_attn(at, true))) return rc;
-    GemmArgs w1 = mk(x, 1, 0, x.H, 3 * x.Hl, x.M, x_attn, dqkv, gr->dw_qkv, sc);
-    w1.c_streaming = true;
-    w1.colsum_b = gr->db_qkv;
     if ((rc = run_gemm(w1))) return rc;
     if (!w1.colsum_done && colsum(x.dtype, x.M, 3 * x.Hl, dqkv, gr->db_qkv, cs, s) != hipSuccess) return TPL_EHIP;
-    GemmArgs d1 = mk(x, 0, 1, x.M, x.H, 3 * x.Hl, dqkv, p->w_qkv, dx_attn, sc);
-    if (x.row_epi) d1.resid = dy_attn;
     if ((rc = run_gemm(d1))) return rc;
     if ((rc = sj3.finish())) { return rc; }
     return sj.finish();
