@@ -31,6 +31,7 @@
 #include "device_math.h"
 #include "kernels.h"
 #include "lds_dma.h"
+#include "tile_order.h"
 
 namespace tpl {
 
@@ -55,7 +56,10 @@ struct GemmF32Params {
     int M, N, K, lda, ldb, epi;
     int tiles_m, tiles_n, nk, nk_total;         // nk: k-steps of one share
     float* partial;                             // [share][M][N], or null
+    float* colsum;                              // [N]: sum over k of B[k][n] (weight gradients of a group), or null
+    float* colsum_part;                         // with K shares: [share][N]
 };
+constexpr int F_BAND = 8;                       // tile rows per band of the tile order
 
 // LDS position (in 16-byte chunks) of the stage tile of an operand of R rows.  K contiguous: chunk c of row r at
 // 8 r + (c ^ (r / 2 % 8)), so 16 rows read at one k lie on all banks.  M/N contiguous: row k holds R / 4 chunks; the two
@@ -78,16 +82,19 @@ template <bool KMAJ, int R> __device__ __forceinline__ int f32_mn_addr(int k, in
     return pr * (R * 4) + mn * 4;
 }
 
-template <typename T, bool A_KMAJ, bool B_KMAJ>
-__global__ __launch_bounds__(256) void gemm_f32_kernel(GemmF32Params p) {
-    extern __shared__ __attribute__((aligned(16))) char smem[];
+// One output tile (and K share): number list_pos of the share-major list of the GEMM's workgroups.
+template <typename T, bool A_KMAJ, bool B_KMAJ, bool COLSUM>
+__device__ __forceinline__ void gemm_f32_tile(const GemmF32Params& p, int list_pos, char* smem) {
+    static_assert(!COLSUM || !B_KMAJ, "column sums ride on the floats a lane reads of an N-contiguous B");
     constexpr int TM = T::TM, TN = T::TN, BM = T::BM, BN = T::BN, LA = T::LA, LB = T::LB, S = T::STAGES;
     const int t = threadIdx.x, lane = t & 63, half = lane >> 5;
     const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
     const int wk = T::KW > 1 ? wave : 0, wm = T::KW > 1 ? 0 : wave / T::WN, wn = T::KW > 1 ? 0 : wave % T::WN;
     const int ntiles = p.tiles_m * p.tiles_n;
-    const int share = blockIdx.x / ntiles, tile = blockIdx.x - share * ntiles;
-    const int m0 = (tile % p.tiles_m) * BM, n0 = (tile / p.tiles_m) * BN;
+    const int share = list_pos / ntiles;
+    int tm, tn;
+    tile_coords(list_pos - share * ntiles, p.tiles_m, p.tiles_n, F_BAND, tm, tn);
+    const int m0 = tm * BM, n0 = tn * BN;
     const int kt0 = share * p.nk;
     const int nk = p.nk_total - kt0 < p.nk ? p.nk_total - kt0 : p.nk;
 
@@ -152,6 +159,13 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(GemmF32Params p) {
             for (int j = 0; j < 4; ++j) f[j] = *reinterpret_cast<const float*>(st + f32_mn_addr<KM, R>(8 * g + 4 * half + j, row));
         }
     };
+    // Column sums of B: the wavefronts of the first row of blocks in the first tile row hold every k of their columns once
+    // (one half of each group of 8 per lane half).  A stage is summed by itself before it joins the running sum, so the
+    // chain of dependent roundings is K / 32 long.
+    const bool cs_on = COLSUM && p.colsum && tm == 0 && wm == 0;   // uniform over the wavefront
+    float cs[TN], cs_stage[TN];
+#pragma unroll
+    for (int j = 0; j < TN; ++j) cs[j] = cs_stage[j] = 0.0f;
     auto group = [&](const char* st, int g) {                     // 8 k: TM TN x 4 matrix instructions
         float fa[TM][4], fb[TN][4];
 #pragma unroll
@@ -160,6 +174,10 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(GemmF32Params p) {
 #pragma unroll
         for (int j = 0; j < TN; ++j)
             frag(fb[j], st + T::A_BYTES, (wn * TN + j) * 32, g, std::integral_constant<bool, B_KMAJ>{}, std::integral_constant<int, BN>{});
+        if (COLSUM && cs_on) {
+#pragma unroll
+            for (int j = 0; j < TN; ++j) cs_stage[j] += (fb[j][0] + fb[j][1]) + (fb[j][2] + fb[j][3]);
+        }
 #pragma unroll
         for (int e = 0; e < 4; ++e)
 #pragma unroll
@@ -184,54 +202,124 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(GemmF32Params p) {
 #pragma unroll
             for (int g = 0; g < 4; ++g) group(st, g);
         }
+        if (COLSUM && cs_on) {
+#pragma unroll
+            for (int j = 0; j < TN; ++j) { cs[j] += cs_stage[j]; cs_stage[j] = 0.0f; }
+        }
     }
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
 
     // Epilogue straight from the accumulators: register v of a block is row 8 (v / 4) + 4 half + v % 4, column lane % 32,
-    // so a store covers two rows of 128 bytes.
+    // so an access covers two rows of 128 bytes.  All reads of a block (residual, GeLU input) go out before the first is
+    // used; rows and columns past the end read element 0 and are not stored.
     const bool split = p.partial != nullptr;
-    auto emit = [&](int gm, int gn, float v, float bias) {
-        if (gm >= p.M || gn >= p.N) return;
-        const int64_t idx = (int64_t)gm * p.N + gn;
-        if (split) { p.partial[(int64_t)share * p.M * p.N + idx] = v; return; }
-        v += bias;
-        if (p.resid) v += p.resid[idx];
-        if (p.epi == EPI_GELU) { p.aux[idx] = v; v = gelu_f(v); }
-        else if (p.epi == EPI_DGELU) v *= gelu_grad_f(p.aux[idx]);
-        p.C[idx] = v;
+    auto emit = [&](int gn, auto count, auto row, auto value) {
+        constexpr int NV = decltype(count)::value;
+        const bool col = gn < p.N;
+        if (split) {
+            float* part = p.partial + (int64_t)share * p.M * p.N;
+#pragma unroll
+            for (int v = 0; v < NV; ++v)
+                if (col && row(v) < p.M) part[(int64_t)row(v) * p.N + gn] = value(v);
+            return;
+        }
+        auto at = [&](int v) { return col && row(v) < p.M ? (int64_t)row(v) * p.N + gn : (int64_t)0; };
+        const float bias = p.bias ? p.bias[col ? gn : 0] : 0.0f;
+        float r[NV], u[NV];
+        if (p.resid) {
+#pragma unroll
+            for (int v = 0; v < NV; ++v) r[v] = p.resid[at(v)];
+        }
+        if (p.epi == EPI_DGELU) {
+#pragma unroll
+            for (int v = 0; v < NV; ++v) u[v] = p.aux[at(v)];
+        }
+#pragma unroll
+        for (int v = 0; v < NV; ++v) {
+            float x = value(v) + bias;
+            if (p.resid) x += r[v];
+            const bool ok = col && row(v) < p.M;
+            if (p.epi == EPI_GELU) {
+                if (ok) p.aux[at(v)] = x;
+                x = gelu_f(x);
+            } else if (p.epi == EPI_DGELU) {
+                x *= gelu_grad_f(u[v]);
+            }
+            if (ok) p.C[at(v)] = x;
+        }
+    };
+    auto emit_colsum = [&](int gn, float s) {
+        if (half == 0 && gn < p.N) (split ? p.colsum_part + (int64_t)share * p.N : p.colsum)[gn] = s;
     };
     if (T::KW > 1) {
         // four partial sums of one block: each wavefront adds the four, in wavefront order, for a quarter of the rows
-        float* red = reinterpret_cast<float*>(smem);              // [wavefront][register][lane]
+        float* red = reinterpret_cast<float*>(smem);              // [wavefront][register][lane], then [wavefront][column]
         __syncthreads();
 #pragma unroll
         for (int v = 0; v < 16; ++v) red[(wave * 16 + v) * 64 + lane] = acc[0][0][v];
+        if (COLSUM && cs_on) red[4096 + wave * 64 + lane] = cs[0];
         __syncthreads();
         const int gn = n0 + (lane & 31);
-        const float bias = (p.bias && !split && gn < p.N) ? p.bias[gn] : 0.0f;
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
+        emit(gn, std::integral_constant<int, 4>{}, [&](int q) { return m0 + 8 * wave + 4 * half + q; }, [&](int q) {
             const int v = wave * 4 + q;
-            const float s = ((red[v * 64 + lane] + red[(16 + v) * 64 + lane]) + red[(32 + v) * 64 + lane]) + red[(48 + v) * 64 + lane];
-            emit(m0 + 8 * wave + 4 * half + q, gn, s, bias);
+            return ((red[v * 64 + lane] + red[(16 + v) * 64 + lane]) + red[(32 + v) * 64 + lane]) + red[(48 + v) * 64 + lane];
+        });
+        if (COLSUM && cs_on && wave == 0) {
+            float s = 0.0f;
+#pragma unroll
+            for (int w = 0; w < 4; ++w) s += red[4096 + w * 64 + (lane & 31)] + red[4096 + w * 64 + 32 + (lane & 31)];
+            emit_colsum(gn, s);
         }
         return;
     }
 #pragma unroll
     for (int j = 0; j < TN; ++j) {
         const int gn = n0 + (wn * TN + j) * 32 + (lane & 31);
-        const float bias = (p.bias && !split && gn < p.N) ? p.bias[gn] : 0.0f;
 #pragma unroll
         for (int i = 0; i < TM; ++i)
-#pragma unroll
-            for (int v = 0; v < 16; ++v) emit(m0 + (wm * TM + i) * 32 + 8 * (v >> 2) + 4 * half + (v & 3), gn, acc[i][j][v], bias);
+            emit(gn, std::integral_constant<int, 16>{},
+                 [&](int v) { return m0 + (wm * TM + i) * 32 + 8 * (v >> 2) + 4 * half + (v & 3); },
+                 [&](int v) { return acc[i][j][v]; });
+        if (COLSUM && cs_on) emit_colsum(gn, cs[j] + __shfl_xor(cs[j], 32, 64));
     }
+}
+template <typename T, bool A_KMAJ, bool B_KMAJ>
+__global__ __launch_bounds__(256) void gemm_f32_kernel(GemmF32Params p) {
+    extern __shared__ __attribute__((aligned(16))) char smem[];
+    gemm_f32_tile<T, A_KMAJ, B_KMAJ, false>(p, share_of_block(blockIdx.x, gridDim.x), smem);
+}
+
+// Independent GEMMs of a layer pass as one list of workgroups, as in gemm_bf16.hip: GEMM i is the workgroups
+// [first[i], first[i+1]); the three layouts of a layer are three bodies of the kernel, the bias gradients ride in the
+// weight gradients.  A launch of one of these GEMMs costs 4 to 6 us whatever it computes, and its last round leaves units
+// idle.  Whole training steps, one launch per GEMM and bias gradient -> groups: 256 tokens of 256 / 128 109 -> 61 us, 260 of
+// 768 / 384 203 -> 126, 2048 of 1024 / 256 499 -> 414 (floor 272 at 154 TFLOP/s), 4096 of 256 / 256 1219 -> 981, 700 of
+// 1920 / 960 1051 -> 1048, 2000 of 2048 / 1024 2934 -> 2863: never behind, so float layers always go this way.
+constexpr int F_GROUP_MAX = 4;
+struct GroupF32Params {
+    GemmF32Params g[F_GROUP_MAX];
+    int first[F_GROUP_MAX + 1];
+    int layout[F_GROUP_MAX];                    // 0: NN, 1: NT, 2: TN
+    int shares[F_GROUP_MAX];
+    int n;
+};
+template <typename T>
+__global__ __launch_bounds__(256) void gemm_f32_group_kernel(GroupF32Params gp) {
+    extern __shared__ __attribute__((aligned(16))) char smem[];
+    const int bid = blockIdx.x;
+    int i = 0;
+    while (i + 1 < gp.n && bid >= gp.first[i + 1]) ++i;
+    const GemmF32Params& p = gp.g[i];
+    const int pos = share_of_block(bid - gp.first[i], gp.first[i + 1] - gp.first[i]);
+    const int layout = gp.layout[i];
+    if (layout == 0) gemm_f32_tile<T, true, false, false>(p, pos, smem);
+    else if (layout == 1) gemm_f32_tile<T, true, true, false>(p, pos, smem);
+    else gemm_f32_tile<T, false, false, true>(p, pos, smem);
 }
 
 // Sum of the K shares in share order, then the epilogue; 4 columns per thread.
-__global__ __launch_bounds__(256) void gemm_f32_sum_kernel(GemmF32Params p, int shares) {
-    const int64_t idx = ((int64_t)blockIdx.x * 256 + threadIdx.x) * 4, mn = (int64_t)p.M * p.N;
-    if (idx >= mn) return;
+__device__ __forceinline__ void f32_sum_shares(const GemmF32Params& p, int shares, int64_t idx) {
+    const int64_t mn = (int64_t)p.M * p.N;
     float v[4] = {0, 0, 0, 0};
     auto add4 = [&](const float* q) {
         const float4 x = *reinterpret_cast<const float4*>(q);
@@ -249,6 +337,27 @@ __global__ __launch_bounds__(256) void gemm_f32_sum_kernel(GemmF32Params p, int 
         v[0] *= gelu_grad_f(u.x); v[1] *= gelu_grad_f(u.y); v[2] *= gelu_grad_f(u.z); v[3] *= gelu_grad_f(u.w);
     }
     *reinterpret_cast<float4*>(p.C + idx) = make_float4(v[0], v[1], v[2], v[3]);
+}
+__global__ __launch_bounds__(256) void gemm_f32_sum_kernel(GemmF32Params p, int shares) {
+    const int64_t idx = ((int64_t)blockIdx.x * 256 + threadIdx.x) * 4;
+    if (idx < (int64_t)p.M * p.N) f32_sum_shares(p, shares, idx);
+}
+// The same for the GEMMs of a group that were cut: GEMM i has the workgroups [first[i], first[i+1]), the column sums last.
+__global__ __launch_bounds__(256) void gemm_f32_group_sum_kernel(GroupF32Params gp) {
+    const int bid = blockIdx.x;
+    int i = 0;
+    while (i + 1 < gp.n && bid >= gp.first[i + 1]) ++i;
+    const GemmF32Params& p = gp.g[i];
+    const int64_t idx = ((int64_t)(bid - gp.first[i]) * 256 + threadIdx.x) * 4, mn = (int64_t)p.M * p.N;
+    if (idx < mn) { f32_sum_shares(p, gp.shares[i], idx); return; }
+    const int64_t col = idx - mn;
+    if (!p.colsum || col >= p.N) return;
+    float4 v = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+    for (int s = 0; s < gp.shares[i]; ++s) {
+        const float4 x = *reinterpret_cast<const float4*>(p.colsum_part + (int64_t)s * p.N + col);
+        v.x += x.x; v.y += x.y; v.z += x.z; v.w += x.w;
+    }
+    *reinterpret_cast<float4*>(p.colsum + col) = v;
 }
 
 bool gemm_f32_supported(const GemmArgs& a) {
@@ -307,16 +416,21 @@ static hipError_t launch_f32_layout(const GemmF32Params& p, const GemmArgs& a, i
     return a.trans_b ? launch_f32<T, false, true>(p, shares, a.stream) : launch_f32<T, false, false>(p, shares, a.stream);
 }
 
-hipError_t gemm_f32(const GemmArgs& a) {
+static GemmF32Params f32_params(const GemmArgs& a) {
     GemmF32Params p{};
     p.A = (const float*)a.A; p.B = (const float*)a.B; p.C = (float*)a.C;
     p.bias = (const float*)a.bias; p.resid = (const float*)a.resid; p.aux = (float*)a.aux;
     p.M = (int)a.M; p.N = (int)a.N; p.K = (int)a.K; p.epi = a.epi;
     p.lda = a.trans_a ? p.M : p.K;
     p.ldb = a.trans_b ? p.K : p.N;
+    p.nk_total = (p.K + FK - 1) / FK;
+    return p;
+}
+
+hipError_t gemm_f32(const GemmArgs& a) {
+    GemmF32Params p = f32_params(a);
     const F32Plan pl = f32_plan(a.M, a.N, a.K);
     p.nk = pl.nk;
-    p.nk_total = (p.K + FK - 1) / FK;
     if (pl.shares > 1) {
         if (!a.ws || a.ws_bytes < (size_t)pl.shares * (size_t)a.M * (size_t)a.N * sizeof(float)) return hipErrorInvalidValue;
         p.partial = (float*)a.ws;
@@ -329,6 +443,125 @@ hipError_t gemm_f32(const GemmArgs& a) {
     }
     if (e != hipSuccess || pl.shares == 1) return e;
     hipLaunchKernelGGL(gemm_f32_sum_kernel, dim3((unsigned)((a.M * a.N / 4 + 255) / 256)), dim3(256), 0, a.stream, p, pl.shares);
+    return hipGetLastError();
+}
+
+// ---- groups ----------------------------------------------------------------------------------------------------------
+// One tile for the whole group and K shares per GEMM by a time estimate: the units' work evenly spread, plus half of the
+// longest workgroup for the end of the launch, or the longest workgroup by itself, whichever is more.
+// On 10 layers (17 to 4096 tokens, 256 to 2048 wide) the tile it takes is the best of the three or within 5 % of it: 32 at
+// 256 tokens of 256 / 128 (61 us; 75 and 107 on 64 and 128), 64 at 2048 of 1024 / 256 (414; 446 on 32, 518 on 128).
+using F32Tile128 = F32Tile<2, 2, 2, 2, 1, 2>;
+using F32Tile64 = F32Tile<2, 2, 1, 1, 1, 3>;
+using F32Tile32 = F32Tile<1, 1, 1, 1, 4, 4>;
+namespace {
+struct F32GroupTile { int bm; double step_us, wg_us, alone_us; };
+constexpr F32GroupTile F32_GROUP_TILES[] = {{128, 1.95, 3.0, 2.2}, {64, 0.50, 1.0, 0.65}, {32, 0.15, 0.5, 0.45}};
+struct F32GroupPlan { int tile, nk[F_GROUP_MAX], shares[F_GROUP_MAX]; double us; };
+
+F32GroupPlan plan_f32_group(const GemmArgs* g, int n) {
+    const int cus = compute_units(), forced = options().gemm_group;
+    F32GroupPlan best{};
+    best.us = -1;
+    for (int t = 0; t < 3; ++t) {
+        const F32GroupTile& gt = F32_GROUP_TILES[t];
+        if (forced > 0 && gt.bm != (forced == 192 ? 32 : forced)) continue;
+        F32GroupPlan p{};
+        p.tile = t;
+        int64_t tiles[F_GROUP_MAX];
+        int nk[F_GROUP_MAX];
+        for (int i = 0; i < n; ++i) {
+            tiles[i] = ((g[i].M + gt.bm - 1) / gt.bm) * ((g[i].N + gt.bm - 1) / gt.bm);
+            nk[i] = p.nk[i] = (int)((g[i].K + FK - 1) / FK);
+            p.shares[i] = 1;
+        }
+        auto estimate = [&]() {
+            double work = 0, longest = 0, bytes = 0;
+            for (int i = 0; i < n; ++i) {
+                work += (double)tiles[i] * p.shares[i] * (p.nk[i] * gt.step_us + gt.wg_us);
+                longest = std::max(longest, (double)p.nk[i]);
+                if (p.shares[i] > 1) bytes += (double)g[i].M * g[i].N * (8.0 * p.shares[i] + 4.0);
+            }
+            return std::max(work / cus + 0.5 * longest * gt.step_us, longest * gt.alone_us) + 4.0 +
+                   (bytes > 0 ? 4.5 + bytes / 3.0e6 : 0.0);
+        };
+        p.us = estimate();
+        for (int cuts = 0; cuts < 32; ++cuts) {                   // cut the longest again while that helps
+            int l = 0;
+            for (int i = 1; i < n; ++i) if (p.nk[i] > p.nk[l]) l = i;
+            const int want = p.shares[l] + 1;
+            if (want > 16 || nk[l] / want < 4) break;
+            const F32GroupPlan before = p;
+            p.nk[l] = (nk[l] + want - 1) / want;
+            p.shares[l] = (nk[l] + p.nk[l] - 1) / p.nk[l];
+            p.us = estimate();
+            if (best.us < 0 || before.us < best.us) best = before;
+        }
+        if (best.us < 0 || p.us < best.us) best = p;
+    }
+    return best;
+}
+size_t f32_share_bytes(const GemmArgs& a, int shares) {           // partial sums, column sums included
+    return shares > 1 ? (size_t)shares * ((size_t)a.M * a.N + (size_t)a.N) * sizeof(float) : 0;
+}
+}  // namespace
+
+size_t gemm_f32_group_workspace_bytes(const GemmArgs* g, int n) {
+    const F32GroupPlan pl = plan_f32_group(g, n);
+    size_t need = 0;
+    for (int i = 0; i < n; ++i) need += f32_share_bytes(g[i], pl.shares[i]);
+    return need;
+}
+
+template <typename T>
+static hipError_t launch_f32_group(const GroupF32Params& gp, hipStream_t s) {
+    static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_f32_group_kernel<T>),
+                                                       hipFuncAttributeMaxDynamicSharedMemorySize, T::LDS_BYTES);
+    if (attr != hipSuccess) return attr;
+    hipLaunchKernelGGL(gemm_f32_group_kernel<T>, dim3((unsigned)gp.first[gp.n]), dim3(256), T::LDS_BYTES, s, gp);
+    return hipGetLastError();
+}
+
+hipError_t gemm_f32_group(const GemmArgs* g, int n, void* ws, size_t ws_bytes, hipStream_t stream) {
+    if (n < 1 || n > F_GROUP_MAX) return hipErrorInvalidValue;
+    const F32GroupPlan pl = plan_f32_group(g, n);
+    const int bm = F32_GROUP_TILES[pl.tile].bm;
+    int order[F_GROUP_MAX] = {0, 1, 2, 3};
+    std::stable_sort(order, order + n, [&](int a, int b) { return pl.nk[a] > pl.nk[b]; });
+    GroupF32Params gp{}, sp{};                                    // the GEMMs; the sums of those that were cut
+    gp.n = n;
+    char* part = static_cast<char*>(ws);
+    size_t used = 0;
+    for (int q = 0; q < n; ++q) {
+        const GemmArgs& a = g[order[q]];
+        const int shares = pl.shares[order[q]];
+        GemmF32Params p = f32_params(a);
+        p.nk = pl.nk[order[q]];
+        p.tiles_m = (int)((a.M + bm - 1) / bm);
+        p.tiles_n = (int)((a.N + bm - 1) / bm);
+        p.colsum = a.trans_a ? (float*)a.colsum_b : nullptr;
+        if (shares > 1) {
+            const size_t bytes = f32_share_bytes(a, shares);
+            if (!ws || used + bytes > ws_bytes) return hipErrorInvalidValue;
+            p.partial = reinterpret_cast<float*>(part + used);
+            p.colsum_part = p.partial + (size_t)shares * a.M * a.N;
+            used += bytes;
+            sp.g[sp.n] = p;
+            sp.shares[sp.n] = shares;
+            const int64_t outs = a.M * a.N + (p.colsum ? a.N : 0);
+            sp.first[sp.n + 1] = sp.first[sp.n] + (int)((outs + 1023) / 1024);
+            ++sp.n;
+        }
+        gp.g[q] = p;
+        gp.shares[q] = shares;
+        gp.layout[q] = a.trans_a ? 2 : a.trans_b ? 1 : 0;
+        gp.first[q + 1] = gp.first[q] + p.tiles_m * p.tiles_n * shares;
+    }
+    hipError_t e = pl.tile == 0   ? launch_f32_group<F32Tile128>(gp, stream)
+                   : pl.tile == 1 ? launch_f32_group<F32Tile64>(gp, stream)
+                                  : launch_f32_group<F32Tile32>(gp, stream);
+    if (e != hipSuccess || sp.n == 0) return e;
+    hipLaunchKernelGGL(gemm_f32_group_sum_kernel, dim3((unsigned)sp.first[sp.n]), dim3(256), 0, stream, sp);
     return hipGetLastError();
 }
 

@@ -19,7 +19,7 @@ struct Options {
     int attn_chunk = -1;       // force the chunk length of attention strips in 64-row tile steps (0: never cut); -1: unset
     int side_chains = 0;       // chains of a backward pass under TPL_SIDE_STREAM: 2, or 3 (dW_dn and dW_o on a stream of their
                                // own); 0: the library chooses by the size of the weight gradients
-    int gemm_group = -1;       // independent GEMMs of a layer pass in one launch: 0 never; 64, 128, 192: always, on that tile; -1: by size
+    int gemm_group = -1;       // independent GEMMs of a layer pass in one launch: 0 never; 64, 128, 192: always, on that tile (float: 64, 128, 32); -1: by size
     int fuse_colsum = 0;       // 1: bias gradients as one more output row of the weight-gradient GEMM where its kernel can
     char gemm_force[1024] = "";   // "MxNxK@ab=v[:shares];..." plans of single shapes (a, b = 1: A, B K-major)
     unsigned generation = 0;
@@ -127,6 +127,9 @@ hipError_t gelu_bwd(int dtype, int64_t M, int64_t N, const void* dg, const void*
 bool gemm_f32_supported(const GemmArgs& a);
 size_t gemm_f32_workspace_bytes(int64_t M, int64_t N, int64_t K);
 hipError_t gemm_f32(const GemmArgs& a);
+// As gemm_bf16_group below.
+size_t gemm_f32_group_workspace_bytes(const GemmArgs* g, int n);
+hipError_t gemm_f32_group(const GemmArgs* g, int n, void* ws, size_t ws_bytes, hipStream_t stream);
 bool attn_f32_supported(const AttnArgs& a);
 hipError_t attn_f32_fwd(const AttnArgs& a);
 hipError_t attn_f32_bwd(const AttnArgs& a);

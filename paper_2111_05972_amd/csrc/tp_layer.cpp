@@ -149,7 +149,6 @@ GemmArgs gemm_args(const Dims& x, int ta, int tb, int64_t M, int64_t N, int64_t 
     return g;
 }
 size_t group_ws(const Dims& x, bool bwd) {
-    if (x.dtype != BF16) return 0;
     GemmArgs first[4], second[4];
     int n1 = 0, n2 = 0;
     if (!bwd) {
@@ -167,7 +166,8 @@ size_t group_ws(const Dims& x, bool bwd) {
         second[n2++] = gemm_args(x, 0, 1, x.M, x.H, x.Il);
         second[n2++] = gemm_args(x, 0, 1, x.M, x.H, 3 * x.Hl);
     }
-    return up(std::max(gemm_bf16_group_workspace_bytes(first, n1), gemm_bf16_group_workspace_bytes(second, n2)));
+    const auto bytes = x.dtype == BF16 ? gemm_bf16_group_workspace_bytes : gemm_f32_group_workspace_bytes;
+    return up(std::max(bytes(first, n1), bytes(second, n2)));
 }
 // GEMM scratch of a pass: one region per chain, or what its groups need (both, so that the choice may differ between the
 // size query and the call: per-GEMM timing runs the GEMMs one by one).
@@ -295,7 +295,7 @@ int run_attn(AttnArgs& a, bool bwd) {
 // Forward GEMM work above which a pass is left to launches of single GEMMs (on two chains if the caller asks): each GEMM
 // fills the chip by itself there, on the tile that suits it best (whole steps: groups are 8 % ahead at 0.43 TFLOP, 2 % at 0.6, 1 % behind at 0.64
 // (GPT-3 13B, TP 4) and 10 % at 0.93 (GPT-3 175B, TP 8: 2.68 against 2.45 ms)).
-constexpr double GROUP_MAX_FLOP = 0.64e12;
+constexpr double GROUP_MAX_FLOP = 0.64e12;   // bf16; float GEMMs are matrix-bound on any tile and group at every size
 
 // Scratch handed to every GEMM of one entry-point call.
 struct GemmScratch { void* ws; size_t bytes; hipStream_t stream; };
@@ -310,17 +310,18 @@ GemmArgs mk(const Dims& x, int ta, int tb, int64_t M, int64_t N, int64_t K, cons
 // Whether the GEMMs of a pass go out as groups.
 bool use_groups(const Dims& x) {
     const Options& o = options();
-    if (x.dtype != BF16 || g_prof.on || o.gemm_group == 0) return false;
-    // every operand within the matrix-core kernels' 32-bit offsets (whole 16-byte rows are given)
+    if (g_prof.on || o.gemm_group == 0) return false;
+    // every operand within the matrix-core kernels' 32-bit offsets (whole 16-byte rows are given, in either type)
     const int64_t widest = std::max(std::max(x.Il, 3 * x.Hl), x.H);
-    if (std::max(x.M, x.H) * widest * 2 >= 0x7FFFFFFFll) return false;
+    if (std::max(x.M, x.H) * widest * x.esz >= 0x7FFFFFFFll) return false;
     if (o.gemm_group > 0) return true;
     // the other GEMM overrides speak about launches of one GEMM and about chains
     if (o.gemm_tile >= 0 || o.gemm_shares > 0 || o.gemm_force[0] || o.gemm_band > 0 || o.side_chains || o.fuse_colsum) return false;
-    return 2.0 * (double)x.M * x.H * (4.0 * x.Hl + 2.0 * x.Il) < GROUP_MAX_FLOP;
+    return x.dtype == F32 || 2.0 * (double)x.M * x.H * (4.0 * x.Hl + 2.0 * x.Il) < GROUP_MAX_FLOP;
 }
 int run_group(const GemmArgs* g, int n, const GemmScratch& sc) {
-    return gemm_bf16_group(g, n, sc.ws, sc.bytes, sc.stream) == hipSuccess ? TPL_OK : TPL_EHIP;
+    const auto group = g[0].dtype == BF16 ? gemm_bf16_group : gemm_f32_group;
+    return group(g, n, sc.ws, sc.bytes, sc.stream) == hipSuccess ? TPL_OK : TPL_EHIP;
 }
 
 // Forward kernels in order.  With row_parallel == false the two row-parallel GEMMs (whose outputs the
