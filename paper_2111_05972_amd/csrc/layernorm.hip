@@ -315,6 +315,183 @@ __global__ __launch_bounds__(THREADS) void ln_bwd_fused_kernel(int64_t M, int64_
     }
 }
 
+// Sums over a wavefront, same value in every lane; fixed combination order.
+__device__ __forceinline__ float wave_sum(float v) {
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
+    return v;
+}
+
+// Narrow rows (H <= 512 * MAXC, MAXC <= 2): one wavefront holds a row, so the row sums need no barrier and no lane is
+// idle where a 256-thread workgroup would give most of its threads no column.
+template <typename T, int MAXC>
+__global__ __launch_bounds__(LN_THREADS) void ln_fwd_wave_kernel(int64_t M, int64_t H, const T* __restrict__ a,
+                                                                 const T* __restrict__ b, const T* __restrict__ gamma,
+                                                                 const T* __restrict__ beta, float eps, T* __restrict__ z,
+                                                                 T* __restrict__ y, float* __restrict__ mean,
+                                                                 float* __restrict__ rstd) {
+    const int lane = threadIdx.x & 63;
+    const float inv_h = 1.0f / (float)H;
+    const int64_t step = (int64_t)gridDim.x * (LN_THREADS / 64);
+    for (int64_t row = (int64_t)blockIdx.x * (LN_THREADS / 64) + (threadIdx.x >> 6); row < M; row += step) {
+        float v[MAXC][8];
+        float s = 0.0f;
+#pragma unroll
+        for (int i = 0; i < MAXC; ++i) {
+            const int64_t col = (lane + 64 * i) * 8;
+            if (col < H) {
+                load8(a + row * H + col, v[i]);
+                if (b) {
+                    float w[8];
+                    load8(b + row * H + col, w);
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) v[i][e] += w[e];
+                }
+                if (z) store8(z + row * H + col, v[i]);
+#pragma unroll
+                for (int e = 0; e < 8; ++e) s += v[i][e];
+            }
+        }
+        const float mu = wave_sum(s) * inv_h;
+        float q = 0.0f;
+#pragma unroll
+        for (int i = 0; i < MAXC; ++i) {
+            if ((lane + 64 * i) * 8 < H) {
+#pragma unroll
+                for (int e = 0; e < 8; ++e) { v[i][e] -= mu; q = fmaf(v[i][e], v[i][e], q); }
+            }
+        }
+        const float rs = 1.0f / sqrtf(wave_sum(q) * inv_h + eps);
+#pragma unroll
+        for (int i = 0; i < MAXC; ++i) {
+            const int64_t col = (lane + 64 * i) * 8;
+            if (col < H) {
+                float g[8], bt[8];
+                load8(gamma + col, g);
+                load8(beta + col, bt);
+#pragma unroll
+                for (int e = 0; e < 8; ++e) v[i][e] = fmaf(v[i][e] * rs, g[e], bt[e]);
+                store8(y + row * H + col, v[i]);
+            }
+        }
+        if (lane == 0) { mean[row] = mu; rstd[row] = rs; }
+    }
+}
+
+// Backward of narrow rows, one wavefront per row: wavefront w of workgroup g walks rows 8 g + w, + 8 G, ... with the
+// next DEPTH of its rows in flight (addresses clamped to the last row, so that the loads are unconditional and can be
+// counted), and the eight wavefronts' column sums are added pairwise through LDS in a fixed order at the end.  A
+// 256-thread workgroup per row keeps one row and two barriers in the chain per CU: latency, not bytes.
+// Forward and backward together, before and now: bfloat16 16384 x 512 86 -> 34 us, 8192 x 1024 54 -> 34, 4096 x 768 29 -> 19;
+// float 8192 x 1024 66 -> 56.
+constexpr int LN_WAVE_ROWS = 8;        // wavefronts of a workgroup = its rows at a time
+template <typename T, int MAXC, int DEPTH>
+__global__ __launch_bounds__(64 * LN_WAVE_ROWS) void ln_bwd_wave_kernel(int64_t M, int64_t H, const T* __restrict__ dy,
+                                                                        const T* __restrict__ z,
+                                                                        const float* __restrict__ mean,
+                                                                        const float* __restrict__ rstd,
+                                                                        const T* __restrict__ gamma, T* __restrict__ dz,
+                                                                        float* __restrict__ partials) {
+    __shared__ float red[LN_WAVE_ROWS / 2][2][MAXC * 512];
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    const int64_t step = (int64_t)gridDim.x * LN_WAVE_ROWS;
+    const float inv_h = 1.0f / (float)H;
+    float gm[MAXC][8], dgam[MAXC][8], dbet[MAXC][8];
+#pragma unroll
+    for (int i = 0; i < MAXC; ++i) {
+        const int64_t col = (lane + 64 * i) * 8;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) { gm[i][e] = 0.0f; dgam[i][e] = 0.0f; dbet[i][e] = 0.0f; }
+        if (col < H) load8(gamma + col, gm[i]);
+    }
+    Raw8<T> rg[DEPTH][MAXC], rz[DEPTH][MAXC];
+    auto fetch = [&](int64_t row, Raw8<T> (&a)[MAXC], Raw8<T> (&b)[MAXC]) {
+        const int64_t r = row < M ? row : M - 1;
+#pragma unroll
+        for (int i = 0; i < MAXC; ++i) {
+            const int64_t col = (lane + 64 * i) * 8, c = col < H ? col : 0;     // lanes past the row read its start
+            a[i].load(dy + r * H + c);
+            b[i].load(z + r * H + c);
+        }
+    };
+    const int64_t first = (int64_t)blockIdx.x * LN_WAVE_ROWS + w;
+#pragma unroll
+    for (int d = 0; d < DEPTH; ++d) fetch(first + d * step, rg[d], rz[d]);
+    for (int64_t row0 = first; row0 < M; row0 += DEPTH * step) {
+#pragma unroll
+        for (int d = 0; d < DEPTH; ++d) {
+            const int64_t row = row0 + d * step;
+            if (row < M) {                                     // uniform over the wavefront
+                float g[MAXC][8], zz[MAXC][8];
+#pragma unroll
+                for (int i = 0; i < MAXC; ++i) { rg[d][i].get(g[i]); rz[d][i].get(zz[i]); }
+                fetch(row + DEPTH * step, rg[d], rz[d]);       // the ring slot is free again
+                const float mu = mean[row], rs = rstd[row];
+                float c1 = 0.0f, c2 = 0.0f;
+#pragma unroll
+                for (int i = 0; i < MAXC; ++i) {
+                    if ((lane + 64 * i) * 8 < H) {
+#pragma unroll
+                        for (int e = 0; e < 8; ++e) {
+                            zz[i][e] = (zz[i][e] - mu) * rs;   // zh
+                            const float gg = g[i][e] * gm[i][e];
+                            c1 += gg;
+                            c2 = fmaf(gg, zz[i][e], c2);
+                        }
+                    }
+                }
+                c1 = wave_sum(c1) * inv_h;
+                c2 = wave_sum(c2) * inv_h;
+#pragma unroll
+                for (int i = 0; i < MAXC; ++i) {
+                    const int64_t col = (lane + 64 * i) * 8;
+                    if (col < H) {
+                        float o[8];
+#pragma unroll
+                        for (int e = 0; e < 8; ++e) {
+                            dbet[i][e] += g[i][e];
+                            dgam[i][e] = fmaf(g[i][e], zz[i][e], dgam[i][e]);
+                            o[e] = (g[i][e] * gm[i][e] - c1 - zz[i][e] * c2) * rs;
+                        }
+                        store8(dz + row * H + col, o);
+                    }
+                }
+            }
+        }
+    }
+#pragma unroll
+    for (int half = LN_WAVE_ROWS / 2; half > 0; half >>= 1) {
+        if (w >= half && w < 2 * half) {
+#pragma unroll
+            for (int i = 0; i < MAXC; ++i)
+#pragma unroll
+                for (int e = 0; e < 8; ++e) {
+                    red[w - half][0][(i * 8 + e) * 64 + lane] = dgam[i][e];
+                    red[w - half][1][(i * 8 + e) * 64 + lane] = dbet[i][e];
+                }
+        }
+        __syncthreads();
+        if (w < half) {
+#pragma unroll
+            for (int i = 0; i < MAXC; ++i)
+#pragma unroll
+                for (int e = 0; e < 8; ++e) {
+                    dgam[i][e] += red[w][0][(i * 8 + e) * 64 + lane];
+                    dbet[i][e] += red[w][1][(i * 8 + e) * 64 + lane];
+                }
+        }
+        __syncthreads();
+    }
+    if (w == 0) {
+        float* pg = partials + (int64_t)blockIdx.x * 2 * H;
+#pragma unroll
+        for (int i = 0; i < MAXC; ++i) {
+            const int64_t col = (lane + 64 * i) * 8;
+            if (col < H) { store8(pg + col, dgam[i]); store8(pg + H + col, dbet[i]); }
+        }
+    }
+}
+
 // dgamma, dbeta = sums of the per-workgroup partials [groups][2][H]: group lane g of 16 adds groups g, g + 16, ... in
 // order, then the 16 lanes are combined in lane order (fixed order).  A thread owns four adjacent columns (16-byte
 // loads); 16 such threads x 16 group lanes per workgroup, so that [256][2][12288] is spread over 384 workgroups;
@@ -365,6 +542,12 @@ static hipError_t fwd_t(const LnArgs& a) {
                        (T*)a.y, a.mean, a.rstd);
     return hipGetLastError();
 }
+template <typename T>
+static hipError_t sum_groups(const LnArgs& a, int64_t groups) {
+    hipLaunchKernelGGL((ln_sum_partials_kernel<T>), dim3((unsigned)((a.H + LN_SUM_COLS - 1) / LN_SUM_COLS), 2), dim3(256), 0, a.stream,
+                       groups, a.H, a.partials, (T*)a.dgamma, (T*)a.dbeta);
+    return hipGetLastError();
+}
 // MAXC counts the 8-element chunks per thread of a 256-thread workgroup; rows of more than two such chunks go to
 // 512-thread workgroups with half the chunks, so that two wavefronts share each SIMD.
 template <typename T, int MAXC>
@@ -382,15 +565,41 @@ static hipError_t bwd_t(const LnArgs& a) {
                            a.stream, a.M, a.H, (const T*)a.dy, (const T*)a.z, a.mean, a.rstd, (const T*)a.gamma,
                            (T*)a.dz, part);
     hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((ln_sum_partials_kernel<T>), dim3((unsigned)((a.H + LN_SUM_COLS - 1) / LN_SUM_COLS), 2), dim3(256), 0, a.stream,
-                       groups, a.H, part, (T*)a.dgamma, (T*)a.dbeta);
+    return e != hipSuccess ? e : sum_groups<T>(a, groups);
+}
+
+// One wavefront per row up to H = 1024.  Beyond, a lane would hold four chunks, only one workgroup of the backward fits a
+// CU and its column sums cost more than the barriers saved (workgroup against wavefront per row, both directions together):
+// float 16384 x 2048 185 us against 203, 1024 x 2048 21.0 against 22.7; bfloat16 1001 x 1536 16.8 against 20.3.
+// Few rows are launch-bound either way (256 x 256 17.2 us on both sides); from 4096 rows on, two per wavefront of a full
+// chip, the gain is measured (29 -> 19 us at 4096 x 768).
+constexpr int64_t LN_WAVE_MIN_M = 4096;
+template <typename T, int MAXC>
+static hipError_t fwd_wave_t(const LnArgs& a) {
+    constexpr int64_t ROWS = LN_THREADS / 64;
+    const int64_t want = (a.M + ROWS - 1) / ROWS;
+    const unsigned grid = (unsigned)(want < 65535 * 16 ? want : 65535 * 16);
+    hipLaunchKernelGGL((ln_fwd_wave_kernel<T, MAXC>), dim3(grid), dim3(LN_THREADS), 0, a.stream, a.M, a.H,
+                       (const T*)a.a, (const T*)a.b, (const T*)a.gamma, (const T*)a.beta, a.eps, (T*)a.z, (T*)a.y, a.mean,
+                       a.rstd);
     return hipGetLastError();
+}
+template <typename T, int MAXC>
+static hipError_t bwd_wave_t(const LnArgs& a) {
+    const int64_t want = (a.M + LN_WAVE_ROWS - 1) / LN_WAVE_ROWS;
+    const int64_t groups = want < LN_BWD_GROUPS ? want : LN_BWD_GROUPS;      // at most the rows of the partial sums
+    constexpr int DEPTH = MAXC * sizeof(T) <= 4 ? 4 : 2;                     // 32 to 64 registers of rows in flight
+    hipLaunchKernelGGL((ln_bwd_wave_kernel<T, MAXC, DEPTH>), dim3((unsigned)groups), dim3(64 * LN_WAVE_ROWS), 0, a.stream, a.M,
+                       a.H, (const T*)a.dy, (const T*)a.z, a.mean, a.rstd, (const T*)a.gamma, (T*)a.dz, a.partials);
+    hipError_t e = hipGetLastError();
+    return e != hipSuccess ? e : sum_groups<T>(a, groups);
 }
 
 template <typename T>
 static hipError_t dispatch(const LnArgs& a, bool bwd) {
     const int64_t chunks = (a.H / 8 + LN_THREADS - 1) / LN_THREADS;
+    if (a.M >= LN_WAVE_MIN_M && a.H <= 512) return bwd ? bwd_wave_t<T, 1>(a) : fwd_wave_t<T, 1>(a);
+    if (a.M >= LN_WAVE_MIN_M && a.H <= 1024) return bwd ? bwd_wave_t<T, 2>(a) : fwd_wave_t<T, 2>(a);
     if (chunks <= 2) return bwd ? bwd_t<T, 2>(a) : fwd_t<T, 2>(a);
     if (chunks <= 4) return bwd ? bwd_t<T, 4>(a) : fwd_t<T, 4>(a);
     if (chunks <= 6) return bwd ? bwd_t<T, 6>(a) : fwd_t<T, 6>(a);
