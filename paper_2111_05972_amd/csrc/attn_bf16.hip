@@ -2,7 +2,11 @@
 //
 // DH is the head size rounded up to 32, 64, 96 or 128: tiles, fragments and accumulators are DH wide, columns past the
 // head size dh read as zero (they must not be the next head's) and are not stored.  (8 heads x 3 x 1001 tokens x 80: the
-// training step around it took 3.52 ms with one wavefront per row on vector arithmetic, 0.54 ms on the 96-wide kernels.)
+// training step around it took 3.52 ms with one wavefront per row on vector arithmetic, 0.51 ms on the 96-wide kernels.)
+//
+// Precision of the weights.  At head sizes 64 and 128 probabilities and dS are rounded to bf16 before the products with V,
+// dO, K and Q.  At every other head size (FLOATW) they keep their 24 bits: an operand is the sum of three bf16 terms
+// (split_terms), each multiplied by a matrix instruction of its own (that step: 0.48 ms with rounded weights, 0.51 so).
 //
 // qkv is [B*S, 3*nl*dh] with columns (q | k | v, local head, dh); o is [B*S, nl*dh].  The S x S
 // score matrix is never stored: scores are recomputed tile by tile on the matrix cores (MFMA
@@ -35,6 +39,7 @@
 // chunk order.  Strips of one chunk write their result directly, as without a workspace.
 #include <hip/hip_runtime.h>
 
+#include <cmath>
 #include <cstdlib>
 #include <type_traits>
 
@@ -172,11 +177,49 @@ __device__ __forceinline__ bf16x8 frag_k_global(const bf16_t* base, int64_t ld, 
     if (row >= nrows || 16 * ks + 8 * (lane >> 5) >= dh) return z;
     return *reinterpret_cast<const bf16x8*>(base + (int64_t)row * ld + 16 * ks + 8 * (lane >> 5));
 }
+#define MFMA(a, b, c) __builtin_amdgcn_mfma_f32_32x32x16_bf16((a), (b), (c), 0, 0, 0)
 __device__ __forceinline__ bf16x8 pack_regs(const f32x16& a, int first) {
     bf16x8 o;
 #pragma unroll
     for (int e = 0; e < 8; ++e) o[e] = (bf16_t)a[first + e];
     return o;
+}
+// The weights of a second product (probabilities or dS, accumulator order) as matrix operands: terms g[0] + g[1] + ...
+// of rows 0..15 (g[.][0]) and 16..31 (g[.][1]).  FLOATW: a float's 24 significant bits are cut into three runs of 8, which
+// are bf16 exactly, so the products and their float sums are those of float weights (results that differ from the
+// correctly rounded bf16 one at head size 80: 0.05 % of dV, as with float arithmetic; 42 % with rounded weights).  The
+// upper halves are taken by truncation: one lane permute per pair, and an infinity stays one.
+template <bool FLOATW> constexpr int weight_terms() { return FLOATW ? 3 : 1; }
+template <bool FLOATW>
+__device__ __forceinline__ void split_terms(f32x16 w, bf16x8 (&g)[weight_terms<FLOATW>()][2]) {
+    if constexpr (!FLOATW) {
+        g[0][0] = pack_regs(w, 0);
+        g[0][1] = pack_regs(w, 8);
+    } else {
+#pragma unroll
+        for (int n = 0; n < 3; ++n)
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                unsigned u[4];
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    u[e] = __builtin_amdgcn_perm(__float_as_uint(w[8 * h + 2 * e + 1]), __float_as_uint(w[8 * h + 2 * e]), 0x07060302u);
+                g[n][h] = __builtin_bit_cast(bf16x8, make_uint4(u[0], u[1], u[2], u[3]));
+                if (n == 2) continue;
+#pragma unroll
+                for (int e = 8 * h; e < 8 * h + 8; ++e) {
+                    const float top = __uint_as_float(__float_as_uint(w[e]) & 0xffff0000u);
+                    w[e] = top == w[e] ? 0.0f : w[e] - top;      // not inf - inf
+                }
+            }
+    }
+}
+// acc += F W for the weight rows 16 h ... of F's columns
+template <bool FLOATW>
+__device__ __forceinline__ f32x16 mfma_terms(const bf16x8& f, const bf16x8 (&g)[weight_terms<FLOATW>()][2], int h, f32x16 acc) {
+#pragma unroll
+    for (int n = 0; n < weight_terms<FLOATW>(); ++n) acc = MFMA(f, g[n][h], acc);
+    return acc;
 }
 __device__ __forceinline__ f32x16 zero16() {
     f32x16 z;
@@ -198,7 +241,11 @@ __device__ __forceinline__ float cross_half_max(float v) {
 }
 // 2^x on the hardware transcendental unit (arguments here are <= ~0; results below 2^-126 flush to 0).
 __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
-#define MFMA(a, b, c) __builtin_amdgcn_mfma_f32_32x32x16_bf16((a), (b), (c), 0, 0, 0)
+
+// Log-sum-exp of a row from its reference point (log2) and sum.
+template <bool FLOATW> __device__ __forceinline__ float strip_lse(float m, float l) {
+    return FLOATW ? fmaf(m, LN2, logf(l)) : (m + log2f(l)) * LN2;
+}
 
 // ---- strips and chunks (host and device agree through these) --------------------------------------
 // Blocks are ranked heaviest first: query blocks from the last one down (forward, dQ), key blocks from the
@@ -281,10 +328,10 @@ template <int DH> constexpr int fwd_lds_bytes() {
     return ring > merge ? ring : merge;
 }
 
-template <int DH, bool CAUSAL>
+template <int DH, bool CAUSAL, bool FLOATW>
 __global__ __launch_bounds__(FTHREADS, DH <= 64 ? 4 : 2) void attn_fwd_kernel(const bf16_t* __restrict__ qkv,
                                                             bf16_t* __restrict__ o,
-                                                            float* __restrict__ lse, int S, int nl, int dh, int BH,
+                                                            float* __restrict__ lse, int S, int nl, int dh, float c2f, int BH,
                                                             float* __restrict__ part, ChunkLen ch) {
     extern __shared__ __attribute__((aligned(16))) char smem[];
     constexpr int TB = tile_bytes<DH>();
@@ -301,7 +348,7 @@ __global__ __launch_bounds__(FTHREADS, DH <= 64 ? 4 : 2) void attn_fwd_kernel(co
     const bf16_t* vbase = kbase + (int64_t)nl * dh;
     const int q0 = qb * BLK + qs * 32;                    // first query of this wavefront
     const int q = q0 + (lane & 31);                       // this lane's query
-    const float c2 = LOG2E / sqrtf((float)dh);
+    const float c2 = FLOATW ? c2f : LOG2E / sqrtf((float)dh);
 
     bf16x8 qf[DH / 16];
 #pragma unroll
@@ -394,12 +441,13 @@ __global__ __launch_bounds__(FTHREADS, DH <= 64 ? 4 : 2) void attn_fwd_kernel(co
 #pragma unroll
                     for (int v = 0; v < 16; ++v) oacc[dt][v] *= alpha;
             }
-            bf16x8 pb0 = pack_regs(s, 0), pb1 = pack_regs(s, 8);
+            bf16x8 pb[weight_terms<FLOATW>()][2];
+            split_terms<FLOATW>(s, pb);
             __builtin_amdgcn_s_setprio(1);
 #pragma unroll
             for (int dt = 0; dt < DH / 32; ++dt) {
-                oacc[dt] = MFMA(fr[2 * dt], pb0, oacc[dt]);
-                oacc[dt] = MFMA(fr[2 * dt + 1], pb1, oacc[dt]);
+                oacc[dt] = mfma_terms<FLOATW>(fr[2 * dt], pb, 0, oacc[dt]);
+                oacc[dt] = mfma_terms<FLOATW>(fr[2 * dt + 1], pb, 1, oacc[dt]);
             }
             __builtin_amdgcn_s_setprio(0);
         }
@@ -460,7 +508,7 @@ __global__ __launch_bounds__(FTHREADS, DH <= 64 ? 4 : 2) void attn_fwd_kernel(co
                         r[j] = (oacc[dt][4 * i + j] * f0 + mg[(2 + dt * 16 + 4 * i + j) * 64] * f1) * inv;
                     if (dt * 32 + 8 * i + 4 * half < dh) store4(op + dt * 32 + 8 * i + 4 * half, r[0], r[1], r[2], r[3]);
                 }
-            if (half == 0) lse[((int64_t)b * nl + h) * S + q] = (mn + log2f(ltot)) * LN2;
+            if (half == 0) lse[((int64_t)b * nl + h) * S + q] = strip_lse<FLOATW>(mn, ltot);
         }
     }
 }
@@ -470,7 +518,7 @@ template <int DH> constexpr int combine_tpr() { return DH == 96 ? 32 : DH / 4; }
 
 // Forward, second kernel: merges the chunks of every strip that was cut (max, rescale, add, in chunk order),
 // normalises and writes O and LSE.  Workgroup = (256 / TPR query rows of a block, batch*head), TPR threads per row.
-template <int DH, bool CAUSAL>
+template <int DH, bool CAUSAL, bool FLOATW>
 __global__ __launch_bounds__(256) void attn_fwd_combine_kernel(const float* __restrict__ part, bf16_t* __restrict__ o,
                                                                float* __restrict__ lse, int S, int nl, int dh, int BH, ChunkLen ch,
                                                                int blk0) {
@@ -498,7 +546,7 @@ __global__ __launch_bounds__(256) void attn_fwd_combine_kernel(const float* __re
         const float inv = ltot > 0.0f ? 1.0f / ltot : 0.0f;
         store4(o + ((int64_t)b * S + q) * ((int64_t)nl * dh) + (int64_t)h * dh + 4 * tc, a0 * inv, a1 * inv, a2 * inv,
                a3 * inv);
-        if (tc == 0) lse[((int64_t)b * nl + h) * S + q] = (mtot + log2f(ltot)) * LN2;
+        if (tc == 0) lse[((int64_t)b * nl + h) * S + q] = strip_lse<FLOATW>(mtot, ltot);
     }
 }
 
@@ -571,11 +619,11 @@ __global__ __launch_bounds__(256) void attn_dsum_kernel(const bf16_t* __restrict
 // SIMD) and shortens its dependent chain per tile.  Q, dO (and LSE, D) are streamed in tiles of 64
 // queries.  Score tile is untransposed: lane = key (l%32), registers = queries 8i + 4*(l/32) + j.
 // =================================================================================================
-template <int DH, bool CAUSAL, bool DK_ROLE>
+template <int DH, bool CAUSAL, bool FLOATW, bool DK_ROLE>
 __device__ __forceinline__ void attn_dkv_body(char* smem, const bf16_t* __restrict__ qkv,
                                               const bf16_t* __restrict__ d_o, const float* __restrict__ lse,
                                               const float* __restrict__ dsum, bf16_t* __restrict__ dqkv,
-                                              int S, int nl, int dh, int bh, const Chunk& ck, float* __restrict__ pslot) {
+                                              int S, int nl, int dh, float c2f, int bh, const Chunk& ck, float* __restrict__ pslot) {
     constexpr int TB = tile_bytes<DH>();
     constexpr int NCH = NCHUNKS<DH, FTHREADS>;
     constexpr int STAGE = 2 * TB + 2 * TILE * 4;          // Q tile, dO tile, LSE*log2e, D
@@ -592,7 +640,7 @@ __device__ __forceinline__ void attn_dkv_body(char* smem, const bf16_t* __restri
     const int k0 = kb * BLK + (wave & 3) * 32;
     const int kv = k0 + (lane & 31);
     const float scale = 1.0f / sqrtf((float)dh);
-    const float c2 = LOG2E * scale;
+    const float c2 = FLOATW ? c2f : LOG2E * scale;
 
     bf16x8 kf[DH / 16], vf[DK_ROLE ? DH / 16 : 1];
 #pragma unroll
@@ -695,11 +743,12 @@ __device__ __forceinline__ void attn_dkv_body(char* smem, const bf16_t* __restri
                     s[v] = DK_ROLE ? p * (dp[v] - dvv[j]) : p;             // dS, or P
                 }
             }
-            bf16x8 g0 = pack_regs(s, 0), g1 = pack_regs(s, 8);
+            bf16x8 g[weight_terms<FLOATW>()][2];
+            split_terms<FLOATW>(s, g);
             __builtin_amdgcn_s_setprio(1);
 #pragma unroll
             for (int k = 0; k < NF; ++k) {
-                acc[k >> 1] = MFMA(fr[k % W], (k & 1) ? g1 : g0, acc[k >> 1]);
+                acc[k >> 1] = mfma_terms<FLOATW>(fr[k % W], g, k & 1, acc[k >> 1]);
                 if (k + W < NF) {
                     fr[k % W] = fetch(NP + k + W);
                     __builtin_amdgcn_sched_barrier(0);
@@ -734,17 +783,17 @@ __device__ __forceinline__ void attn_dkv_body(char* smem, const bf16_t* __restri
 }
 
 // dK/dV workgroup number wg (head fastest, then slot)
-template <int DH, bool CAUSAL>
+template <int DH, bool CAUSAL, bool FLOATW>
 __device__ __forceinline__ void attn_dkv_wg(char* smem, const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ d_o,
                                             const float* __restrict__ lse, const float* __restrict__ dsum,
-                                            bf16_t* __restrict__ dqkv, int S, int nl, int dh, int BH,
+                                            bf16_t* __restrict__ dqkv, int S, int nl, int dh, float c2f, int BH,
                                             float* __restrict__ part, ChunkLen ch, int wg) {
     const int bh = wg % BH, slot = wg / BH;
     const Chunk ck = find_chunk(CAUSAL, true, S, ch, slot, 0);
     float* pslot = part + ((int64_t)slot * BH + bh) * (2 * BLK * DH);
     // the role is uniform per wavefront; both bodies run the same loop and the same barriers
-    if ((threadIdx.x >> 6) < 4) attn_dkv_body<DH, CAUSAL, false>(smem, qkv, d_o, lse, dsum, dqkv, S, nl, dh, bh, ck, pslot);
-    else attn_dkv_body<DH, CAUSAL, true>(smem, qkv, d_o, lse, dsum, dqkv, S, nl, dh, bh, ck, pslot);
+    if ((threadIdx.x >> 6) < 4) attn_dkv_body<DH, CAUSAL, FLOATW, false>(smem, qkv, d_o, lse, dsum, dqkv, S, nl, dh, c2f, bh, ck, pslot);
+    else attn_dkv_body<DH, CAUSAL, FLOATW, true>(smem, qkv, d_o, lse, dsum, dqkv, S, nl, dh, c2f, bh, ck, pslot);
 }
 
 // =================================================================================================
@@ -759,10 +808,10 @@ template <int DH> constexpr int dq_lds_bytes() {
 }
 
 // dQ workgroup number wg (head fastest, then slot)
-template <int DH, bool CAUSAL>
+template <int DH, bool CAUSAL, bool FLOATW>
 __device__ __forceinline__ void attn_dq_wg(char* smem, const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ d_o,
                                            const float* __restrict__ lse, const float* __restrict__ dsum,
-                                           bf16_t* __restrict__ dqkv, int S, int nl, int dh, int BH,
+                                           bf16_t* __restrict__ dqkv, int S, int nl, int dh, float c2f, int BH,
                                            float* __restrict__ part, ChunkLen ch, int wg) {
     constexpr int TB = tile_bytes<DH>();
     constexpr int NCH = NCHUNKS<DH, FTHREADS>;
@@ -780,7 +829,7 @@ __device__ __forceinline__ void attn_dq_wg(char* smem, const bf16_t* __restrict_
     const int q0 = qb * BLK + qs * 32;
     const int q = q0 + (lane & 31);
     const float scale = 1.0f / sqrtf((float)dh);
-    const float c2 = LOG2E * scale;
+    const float c2 = FLOATW ? c2f : LOG2E * scale;
     const float l2 = q < S ? lse[((int64_t)b * nl + h) * S + q] * LOG2E : 0.0f;
     const float dq_d = q < S ? dsum[((int64_t)b * nl + h) * S + q] : 0.0f;
 
@@ -855,11 +904,12 @@ __device__ __forceinline__ void attn_dq_wg(char* smem, const bf16_t* __restrict_
             }
 #pragma unroll
             for (int v = 0; v < 16; ++v) dp[v] = fast_exp2(fmaf(s[v], c2, -l2)) * (dp[v] - dq_d);
-            bf16x8 g0 = pack_regs(dp, 0), g1 = pack_regs(dp, 8);
+            bf16x8 g[weight_terms<FLOATW>()][2];
+            split_terms<FLOATW>(dp, g);
             __builtin_amdgcn_s_setprio(1);
 #pragma unroll
             for (int k = 0; k < NF; ++k) {
-                dq[k >> 1] = MFMA(fr[k % W], (k & 1) ? g1 : g0, dq[k >> 1]);
+                dq[k >> 1] = mfma_terms<FLOATW>(fr[k % W], g, k & 1, dq[k >> 1]);
                 if (k + W < NF) {
                     fr[k % W] = fetch(2 * NF + k + W);
                     __builtin_amdgcn_sched_barrier(0);
@@ -910,18 +960,18 @@ __device__ __forceinline__ void attn_dq_wg(char* smem, const bf16_t* __restrict_
 // workgroup at a time: in one launch the units that finish the short chunks of one kind pick up chunks of the other
 // instead of idling until the launch ends.  dK/dV first: its steps are the longer ones.
 // =================================================================================================
-template <int DH, bool CAUSAL>
+template <int DH, bool CAUSAL, bool FLOATW>
 __global__ __launch_bounds__(FTHREADS, 2) void attn_bwd_kernel(const bf16_t* __restrict__ qkv,
                                                                const bf16_t* __restrict__ d_o,
                                                                const float* __restrict__ lse,
                                                                const float* __restrict__ dsum,
-                                                               bf16_t* __restrict__ dqkv, int S, int nl, int dh, int BH,
+                                                               bf16_t* __restrict__ dqkv, int S, int nl, int dh, float c2f, int BH,
                                                                float* __restrict__ part_kv, float* __restrict__ part_q,
                                                                ChunkLen ch_kv, ChunkLen ch_q, int wgs_kv) {
     extern __shared__ __attribute__((aligned(16))) char smem[];
     const int wg = blockIdx.x;                               // uniform: one kind per workgroup, its own barriers
-    if (wg < wgs_kv) attn_dkv_wg<DH, CAUSAL>(smem, qkv, d_o, lse, dsum, dqkv, S, nl, dh, BH, part_kv, ch_kv, wg);
-    else attn_dq_wg<DH, CAUSAL>(smem, qkv, d_o, lse, dsum, dqkv, S, nl, dh, BH, part_q, ch_q, wg - wgs_kv);
+    if (wg < wgs_kv) attn_dkv_wg<DH, CAUSAL, FLOATW>(smem, qkv, d_o, lse, dsum, dqkv, S, nl, dh, c2f, BH, part_kv, ch_kv, wg);
+    else attn_dq_wg<DH, CAUSAL, FLOATW>(smem, qkv, d_o, lse, dsum, dqkv, S, nl, dh, c2f, BH, part_q, ch_q, wg - wgs_kv);
 }
 
 // ---- host side ----------------------------------------------------------------------------------
@@ -994,6 +1044,9 @@ static int chunk_tiles_bwd(const AttnArgs& a, bool kv_side) {
     }
     return NEVER_CUT;
 }
+static bool float_weights(int dh) { return dh != 64 && dh != 128; }
+// log2(e) / sqrt(dh), the scale of the scores with FLOATW: rounded once, not once per operation
+static float scale_log2(int dh) { return (float)(1.44269504088896340736 / sqrt((double)dh)); }
 static int padded_dh(int dh) { return (dh + 31) / 32 * 32; }
 static size_t part_bytes_fwd(const AttnArgs& a, ChunkLen ch) {
     return (size_t)strip_slots(a.causal, false, a.S, ch) * a.B * a.nl * BLK * (padded_dh(a.dh) + 2) * sizeof(float);
@@ -1029,12 +1082,12 @@ size_t attn_bf16_workspace_bytes(const AttnArgs& a0, bool bwd) {
     return (cuts(a, false, ch_q) ? part_bytes_dq(a, ch_q) : 0) + (cuts(a, true, ch_kv) ? part_bytes_dkv(a, ch_kv) : 0);
 }
 
-template <int DH, bool CAUSAL>
+template <int DH, bool CAUSAL, bool FLOATW>
 static hipError_t fwd_t(const AttnArgs& a) {
     constexpr int LDS = fwd_lds_bytes<DH>();
     static bool once = false;
     if (!once) {
-        hipError_t e = set_lds(&attn_fwd_kernel<DH, CAUSAL>, LDS);
+        hipError_t e = set_lds(&attn_fwd_kernel<DH, CAUSAL, FLOATW>, LDS);
         if (e != hipSuccess) return e;
         once = true;
     }
@@ -1044,24 +1097,24 @@ static hipError_t fwd_t(const AttnArgs& a) {
     const int64_t wgs = (int64_t)strip_slots(CAUSAL, false, a.S, ch) * BH;
     if (wgs > 0x7fffffffLL) return hipErrorInvalidValue;
     float* part = static_cast<float*>(a.ws);
-    hipLaunchKernelGGL((attn_fwd_kernel<DH, CAUSAL>), dim3((unsigned)wgs), dim3(FTHREADS), LDS, a.stream,
-                       (const bf16_t*)a.qkv, (bf16_t*)a.o, a.lse, a.S, a.nl, a.dh, BH, part, ch);
+    hipLaunchKernelGGL((attn_fwd_kernel<DH, CAUSAL, FLOATW>), dim3((unsigned)wgs), dim3(FTHREADS), LDS, a.stream,
+                       (const bf16_t*)a.qkv, (bf16_t*)a.o, a.lse, a.S, a.nl, a.dh, scale_log2(a.dh), BH, part, ch);
     int blk0 = 0, ncut = 0;
     cut_range(a, false, ch, &blk0, &ncut);
     if (ncut)
-        hipLaunchKernelGGL((attn_fwd_combine_kernel<DH, CAUSAL>), dim3(ncut * (BLK * combine_tpr<DH>() / 256), BH), dim3(256), 0,
+        hipLaunchKernelGGL((attn_fwd_combine_kernel<DH, CAUSAL, FLOATW>), dim3(ncut * (BLK * combine_tpr<DH>() / 256), BH), dim3(256), 0,
                            a.stream, part, (bf16_t*)a.o, a.lse, a.S, a.nl, a.dh, BH, ch, blk0);
     return hipGetLastError();
 }
 
-template <int DH, bool CAUSAL>
+template <int DH, bool CAUSAL, bool FLOATW>
 static hipError_t bwd_t(const AttnArgs& a) {
     constexpr int LDS_KV = 2 * (2 * tile_bytes<DH>() + 2 * TILE * 4);
     constexpr int LDS_Q = dq_lds_bytes<DH>();
     constexpr int LDS = LDS_KV > LDS_Q ? LDS_KV : LDS_Q;
     static bool once = false;
     if (!once) {
-        hipError_t e = set_lds(&attn_bwd_kernel<DH, CAUSAL>, LDS);
+        hipError_t e = set_lds(&attn_bwd_kernel<DH, CAUSAL, FLOATW>, LDS);
         if (e != hipSuccess) return e;
         once = true;
     }
@@ -1078,8 +1131,8 @@ static hipError_t bwd_t(const AttnArgs& a) {
     const int64_t lanes = (int64_t)a.B * a.S * a.nl * (DH <= 32 ? 4 : DH == 64 ? 8 : 16);
     hipLaunchKernelGGL((attn_dsum_kernel<DH>), dim3((unsigned)((lanes + 255) / 256)), dim3(256), 0, a.stream,
                        (const bf16_t*)a.o, (const bf16_t*)a.d_o, a.dsum, a.B, a.S, a.nl, a.dh);
-    hipLaunchKernelGGL((attn_bwd_kernel<DH, CAUSAL>), dim3((unsigned)(wgs_kv + wgs_q)), dim3(FTHREADS), LDS, a.stream,
-                       (const bf16_t*)a.qkv, (const bf16_t*)a.d_o, a.lse, a.dsum, (bf16_t*)a.dqkv, a.S, a.nl, a.dh, BH,
+    hipLaunchKernelGGL((attn_bwd_kernel<DH, CAUSAL, FLOATW>), dim3((unsigned)(wgs_kv + wgs_q)), dim3(FTHREADS), LDS, a.stream,
+                       (const bf16_t*)a.qkv, (const bf16_t*)a.d_o, a.lse, a.dsum, (bf16_t*)a.dqkv, a.S, a.nl, a.dh, scale_log2(a.dh), BH,
                        part_kv, part_q, ch_kv, ch_q, (int)wgs_kv);
     int blk0_q = 0, ncut_q = 0, blk0_kv = 0, ncut_kv = 0;
     cut_range(a, false, ch_q, &blk0_q, &ncut_q);
@@ -1092,17 +1145,17 @@ static hipError_t bwd_t(const AttnArgs& a) {
     return hipGetLastError();
 }
 
-template <int DH>
+template <int DH, bool FLOATW>
 static hipError_t run_dh(const AttnArgs& a, bool bwd) {
-    if (bwd) return a.causal ? bwd_t<DH, true>(a) : bwd_t<DH, false>(a);
-    return a.causal ? fwd_t<DH, true>(a) : fwd_t<DH, false>(a);
+    if (bwd) return a.causal ? bwd_t<DH, true, FLOATW>(a) : bwd_t<DH, false, FLOATW>(a);
+    return a.causal ? fwd_t<DH, true, FLOATW>(a) : fwd_t<DH, false, FLOATW>(a);
 }
 static hipError_t run_attention(const AttnArgs& a, bool bwd) {
     switch (padded_dh(a.dh)) {
-        case 32: return run_dh<32>(a, bwd);
-        case 64: return run_dh<64>(a, bwd);
-        case 96: return run_dh<96>(a, bwd);
-        default: return run_dh<128>(a, bwd);
+        case 32: return run_dh<32, true>(a, bwd);
+        case 64: return float_weights(a.dh) ? run_dh<64, true>(a, bwd) : run_dh<64, false>(a, bwd);
+        case 96: return run_dh<96, true>(a, bwd);
+        default: return float_weights(a.dh) ? run_dh<128, true>(a, bwd) : run_dh<128, false>(a, bwd);
     }
 }
 hipError_t attn_bf16_fwd(const AttnArgs& a) { return run_attention(a, false); }
