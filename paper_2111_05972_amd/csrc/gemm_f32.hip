@@ -59,6 +59,7 @@ struct GemmF32Params {
     float* colsum;                              // [N]: sum over k of B[k][n] (weight gradients of a group), or null
     float* colsum_part;                         // with K shares: [share][N]
 };
+constexpr int F_CS_RUN = 16;                    // stages of a run of the column sums
 constexpr int F_BAND = 8;                       // tile rows per band of the tile order
 
 // LDS position (in 16-byte chunks) of the stage tile of an operand of R rows.  K contiguous: chunk c of row r at
@@ -160,12 +161,13 @@ __device__ __forceinline__ void gemm_f32_tile(const GemmF32Params& p, int list_p
         }
     };
     // Column sums of B: the wavefronts of the first row of blocks in the first tile row hold every k of their columns once
-    // (one half of each group of 8 per lane half).  A stage is summed by itself before it joins the running sum, so the
-    // chain of dependent roundings is K / 32 long.
+    // (one half of each group of 8 per lane half).  A stage is summed by itself, F_CS_RUN stages by themselves, then the
+    // runs.  Stage by stage into one sum lost 1.5 times what the column-sum kernels lose (relative error of a bias gradient
+    // over 2048 tokens 1.7e-7, now 1.1e-7 as with those kernels; time of the step unchanged).
     const bool cs_on = COLSUM && p.colsum && tm == 0 && wm == 0;   // uniform over the wavefront
-    float cs[TN], cs_stage[TN];
+    float cs[TN], cs_run[TN], cs_stage[TN];
 #pragma unroll
-    for (int j = 0; j < TN; ++j) cs[j] = cs_stage[j] = 0.0f;
+    for (int j = 0; j < TN; ++j) cs[j] = cs_run[j] = cs_stage[j] = 0.0f;
     auto group = [&](const char* st, int g) {                     // 8 k: TM TN x 4 matrix instructions
         float fa[TM][4], fb[TN][4];
 #pragma unroll
@@ -189,22 +191,30 @@ __device__ __forceinline__ void gemm_f32_tile(const GemmF32Params& p, int list_p
 
 #pragma unroll
     for (int s = 0; s < S - 1; ++s) fetch(s);
-    for (int kt = 0; kt < nk; ++kt) {
-        asm volatile("s_waitcnt vmcnt(%0)" :: "n"((S - 2) * (LA + LB)) : "memory");   // stage kt has landed (this wavefront's part)
-        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");                           // reads of stage kt - 1 are done
-        __builtin_amdgcn_s_barrier();
-        __builtin_amdgcn_sched_barrier(0);
-        fetch(kt + S - 1);                                        // into the slot of stage kt - 1
-        const char* st = smem + (kt % S) * T::STAGE_BYTES;
-        if (T::KW > 1) {
-            group(st, wk);
-        } else {
+    const int run = COLSUM ? F_CS_RUN : nk;
+    for (int run0 = 0; run0 < nk; run0 += run) {
+        const int run1 = run0 + run < nk ? run0 + run : nk;
+        for (int kt = run0; kt < run1; ++kt) {
+            asm volatile("s_waitcnt vmcnt(%0)" :: "n"((S - 2) * (LA + LB)) : "memory");   // stage kt has landed (this wavefront's part)
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");                           // reads of stage kt - 1 are done
+            __builtin_amdgcn_s_barrier();
+            __builtin_amdgcn_sched_barrier(0);
+            fetch(kt + S - 1);                                    // into the slot of stage kt - 1
+            const char* st = smem + (kt % S) * T::STAGE_BYTES;
+            if (T::KW > 1) {
+                group(st, wk);
+            } else {
 #pragma unroll
-            for (int g = 0; g < 4; ++g) group(st, g);
+                for (int g = 0; g < 4; ++g) group(st, g);
+            }
+            if (COLSUM && cs_on) {
+#pragma unroll
+                for (int j = 0; j < TN; ++j) { cs_run[j] += cs_stage[j]; cs_stage[j] = 0.0f; }
+            }
         }
         if (COLSUM && cs_on) {
 #pragma unroll
-            for (int j = 0; j < TN; ++j) { cs[j] += cs_stage[j]; cs_stage[j] = 0.0f; }
+            for (int j = 0; j < TN; ++j) { cs[j] += cs_run[j]; cs_run[j] = 0.0f; }
         }
     }
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
