@@ -8,6 +8,11 @@
 // dO, K and Q.  At every other head size (FLOATW) they keep their 24 bits: an operand is the sum of three bf16 terms
 // (split_terms), each multiplied by a matrix instruction of its own (that step: 0.48 ms with rounded weights, 0.51 so).
 //
+// Infinities and NaN under the causal mask.  A matrix instruction multiplies a masked weight, zero, with its row, and zero
+// times infinity is NaN: in the tile that the diagonal crosses, a token would reach tokens before it.  With FLOATW a
+// wavefront that ends with a value that is not finite therefore computes its 32 rows again, row by row, where a masked row
+// is not read (attn_rows.h).  Head sizes 64 and 128 have the matrix instruction's behaviour.
+//
 // qkv is [B*S, 3*nl*dh] with columns (q | k | v, local head, dh); o is [B*S, nl*dh].  The S x S
 // score matrix is never stored: scores are recomputed tile by tile on the matrix cores (MFMA
 // 32x32x16 bf16, float accumulation), softmax statistics stay in registers, and only
@@ -43,6 +48,7 @@
 #include <cstdlib>
 #include <type_traits>
 
+#include "attn_rows.h"
 #include "device_math.h"
 #include "kernels.h"
 #include "lds_dma.h"
@@ -239,6 +245,12 @@ __device__ __forceinline__ float cross_half_max(float v) {
     const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
     return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
 }
+// z stays 0 while the values are finite, and becomes NaN otherwise.
+__device__ __forceinline__ void note4(float& z, const float (&r)[4]) {
+#pragma unroll
+    for (int j = 0; j < 4; ++j) z = fmaf(r[j], 0.0f, z);
+}
+__device__ __forceinline__ bool any_nonfinite(float z) { return __any(z != 0.0f); }
 // 2^x on the hardware transcendental unit (arguments here are <= ~0; results below 2^-126 flush to 0).
 __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
 
@@ -480,7 +492,8 @@ __global__ __launch_bounds__(FTHREADS, DH <= 64 ? 4 : 2) void attn_fwd_kernel(co
         const float mu = mn == -INFINITY ? 0.0f : mn;
         const float f0 = fast_exp2(m - mu), f1 = fast_exp2(m1 - mu);
         const float ltot = lsum * f0 + l1 * f1;
-        const float inv = ltot > 0.0f ? 1.0f / ltot : 0.0f;
+        const float inv = FLOATW || ltot > 0.0f ? 1.0f / ltot : 0.0f;
+        float z = 0.0f;
         if (ck.nch > 1) {
             // one chunk of a longer strip: (max, sum, unnormalised O) of this chunk's keys, float, [query][dh]
             float* pp = part + ((int64_t)slot * BH + bh) * (BLK * (DH + 2));
@@ -493,6 +506,7 @@ __global__ __launch_bounds__(FTHREADS, DH <= 64 ? 4 : 2) void attn_fwd_kernel(co
 #pragma unroll
                     for (int j = 0; j < 4; ++j)
                         r[j] = oacc[dt][4 * i + j] * f0 + mg[(2 + dt * 16 + 4 * i + j) * 64] * f1;
+                    if (FLOATW && CAUSAL) note4(z, r);
                     store_f4(pp + ql * DH + dt * 32 + 8 * i + 4 * half, r[0], r[1], r[2], r[3]);
                 }
             if (half == 0) { pp[BLK * DH + ql] = mn; pp[BLK * DH + BLK + ql] = ltot; }
@@ -506,9 +520,29 @@ __global__ __launch_bounds__(FTHREADS, DH <= 64 ? 4 : 2) void attn_fwd_kernel(co
 #pragma unroll
                     for (int j = 0; j < 4; ++j)
                         r[j] = (oacc[dt][4 * i + j] * f0 + mg[(2 + dt * 16 + 4 * i + j) * 64] * f1) * inv;
+                    if (FLOATW && CAUSAL) note4(z, r);
                     if (dt * 32 + 8 * i + 4 * half < dh) store4(op + dt * 32 + 8 * i + 4 * half, r[0], r[1], r[2], r[3]);
                 }
             if (half == 0) lse[((int64_t)b * nl + h) * S + q] = strip_lse<FLOATW>(mn, ltot);
+        }
+        if (!FLOATW || !CAUSAL || !any_nonfinite(z)) return;
+        rows_stored();
+        float* q_s = reinterpret_cast<float*>(smem) + qs * NV * 64;      // this wavefront alone reads its merge area
+        float* pp = part + ((int64_t)slot * BH + bh) * (BLK * (DH + 2));
+        const bool whole = ck.nch == 1;
+        for (int i = q0; i < q0 + 32 && i < S; ++i) {
+            load_row(q_s, qbase + (int64_t)i * ld, dh, lane);
+            row_loaded();
+            bf16_t* op = o + ((int64_t)b * S + i) * ((int64_t)nl * dh) + (int64_t)h * dh;
+            const int ql = i - qb * BLK;
+            float mr, lr;
+            attn_row_fwd<(DH + 63) / 64>(q_s, kbase, vbase, ld, dh, tile0 * TILE, min(i + 1, ntiles * TILE), 1.0f / sqrtf((float)dh), whole,
+                                         lane, mr, lr, [&](int d, float v) { if (whole) op[d] = (bf16_t)v; else pp[ql * DH + d] = v; });
+            if (lane == 0) {
+                if (whole) lse[((int64_t)b * nl + h) * S + i] = mr + logf(lr);
+                else { pp[BLK * DH + ql] = mr * LOG2E; pp[BLK * DH + BLK + ql] = lr; }
+            }
+            row_loaded();
         }
     }
 }
@@ -543,7 +577,7 @@ __global__ __launch_bounds__(256) void attn_fwd_combine_kernel(const float* __re
             const float4 v = *reinterpret_cast<const float4*>(pc + ql * DH + 4 * tc);
             a0 = fmaf(v.x, f, a0); a1 = fmaf(v.y, f, a1); a2 = fmaf(v.z, f, a2); a3 = fmaf(v.w, f, a3);
         }
-        const float inv = ltot > 0.0f ? 1.0f / ltot : 0.0f;
+        const float inv = FLOATW || ltot > 0.0f ? 1.0f / ltot : 0.0f;
         store4(o + ((int64_t)b * S + q) * ((int64_t)nl * dh) + (int64_t)h * dh + 4 * tc, a0 * inv, a1 * inv, a2 * inv,
                a3 * inv);
         if (tc == 0) lse[((int64_t)b * nl + h) * S + q] = strip_lse<FLOATW>(mtot, ltot);
@@ -760,25 +794,46 @@ __device__ __forceinline__ void attn_dkv_body(char* smem, const bf16_t* __restri
         dma_wait();
         __syncthreads();
     }
+    float z = 0.0f;
     if (ck.nch > 1) {
         // one chunk of a longer strip: unscaled float partial, [dK | dV][key][dh]
         float* pp = pslot + (DK_ROLE ? 0 : BLK * DH) + ((wave & 3) * 32 + (lane & 31)) * DH;
 #pragma unroll
         for (int dt = 0; dt < DH / 32; ++dt)
 #pragma unroll
-            for (int i = 0; i < 4; ++i)
-                store_f4(pp + dt * 32 + 8 * i + 4 * half, acc[dt][4 * i], acc[dt][4 * i + 1], acc[dt][4 * i + 2],
-                         acc[dt][4 * i + 3]);
+            for (int i = 0; i < 4; ++i) {
+                const float r[4] = {acc[dt][4 * i], acc[dt][4 * i + 1], acc[dt][4 * i + 2], acc[dt][4 * i + 3]};
+                if (FLOATW && CAUSAL) note4(z, r);
+                store_f4(pp + dt * 32 + 8 * i + 4 * half, r[0], r[1], r[2], r[3]);
+            }
     } else if (kv < S) {
         bf16_t* outp = dqkv + ((int64_t)b * S + kv) * ld + (int64_t)(DK_ROLE ? 1 : 2) * nl * dh + (int64_t)h * dh;
         const float f = DK_ROLE ? scale : 1.0f;
 #pragma unroll
         for (int dt = 0; dt < DH / 32; ++dt)
 #pragma unroll
-            for (int i = 0; i < 4; ++i)
-                if (dt * 32 + 8 * i + 4 * half < dh)
-                    store4(outp + dt * 32 + 8 * i + 4 * half, acc[dt][4 * i] * f, acc[dt][4 * i + 1] * f,
-                           acc[dt][4 * i + 2] * f, acc[dt][4 * i + 3] * f);
+            for (int i = 0; i < 4; ++i) {
+                const float r[4] = {acc[dt][4 * i] * f, acc[dt][4 * i + 1] * f, acc[dt][4 * i + 2] * f, acc[dt][4 * i + 3] * f};
+                if (FLOATW && CAUSAL) note4(z, r);
+                if (dt * 32 + 8 * i + 4 * half < dh) store4(outp + dt * 32 + 8 * i + 4 * half, r[0], r[1], r[2], r[3]);
+            }
+    }
+    if (!FLOATW || !CAUSAL || !any_nonfinite(z)) return;
+    rows_stored();
+    float* k_s = reinterpret_cast<float*>(smem) + wave * 2 * DH;     // the ring has been read
+    for (int j = k0; j < k0 + 32 && j < S; ++j) {
+        load_row(k_s, kbase + (int64_t)j * ld, dh, lane);
+        load_row(k_s + DH, vbase + (int64_t)j * ld, dh, lane);
+        row_loaded();
+        bf16_t* outp = dqkv + ((int64_t)b * S + j) * ld + (int64_t)(DK_ROLE ? 1 : 2) * nl * dh + (int64_t)h * dh;
+        float* pp = pslot + (DK_ROLE ? 0 : BLK * DH) + (j - kb * BLK) * DH;
+        attn_row_dkv<(DH + 63) / 64>(k_s, k_s + DH, qbase, ld, dobase, ldo, lrow, drow, dh, max(j, qt0 * TILE), min(S, ntiles * TILE),
+                               scale, lane, [&](int d, float dk, float dv) {
+                                   const float v = DK_ROLE ? dk : dv;
+                                   if (ck.nch > 1) pp[d] = v;
+                                   else outp[d] = (bf16_t)(DK_ROLE ? v * scale : v);
+                               });
+        row_loaded();
     }
 }
 
@@ -928,6 +983,7 @@ __device__ __forceinline__ void attn_dq_wg(char* smem, const bf16_t* __restrict_
             for (int v = 0; v < 16; ++v) mg[(dt * 16 + v) * 64] = dq[dt][v];
     }
     __syncthreads();
+    float z = 0.0f;
     if (kvh == 0 && ck.nch > 1) {
         // one chunk of a longer strip: unscaled float partial, [query][dh]
         float* pp = part + ((int64_t)slot * BH + bh) * (BLK * DH) + (qs * 32 + (lane & 31)) * DH;
@@ -938,6 +994,7 @@ __device__ __forceinline__ void attn_dq_wg(char* smem, const bf16_t* __restrict_
                 float r[4];
 #pragma unroll
                 for (int j = 0; j < 4; ++j) r[j] = dq[dt][4 * i + j] + mg[(dt * 16 + 4 * i + j) * 64];
+                if (FLOATW && CAUSAL) note4(z, r);
                 store_f4(pp + dt * 32 + 8 * i + 4 * half, r[0], r[1], r[2], r[3]);
             }
     } else if (kvh == 0 && q < S) {
@@ -949,8 +1006,23 @@ __device__ __forceinline__ void attn_dq_wg(char* smem, const bf16_t* __restrict_
                 float r[4];
 #pragma unroll
                 for (int j = 0; j < 4; ++j) r[j] = (dq[dt][4 * i + j] + mg[(dt * 16 + 4 * i + j) * 64]) * scale;
+                if (FLOATW && CAUSAL) note4(z, r);
                 if (dt * 32 + 8 * i + 4 * half < dh) store4(dqp + dt * 32 + 8 * i + 4 * half, r[0], r[1], r[2], r[3]);
             }
+    }
+    if (!FLOATW || !CAUSAL || kvh != 0 || !any_nonfinite(z)) return;
+    rows_stored();
+    float* q_s = reinterpret_cast<float*>(smem) + qs * (DH / 2) * 64;      // this wavefront alone reads its merge area
+    for (int i = q0; i < q0 + 32 && i < S; ++i) {
+        load_row(q_s, qbase + (int64_t)i * ld, dh, lane);
+        load_row(q_s + DH, dobase + (int64_t)i * ldo, dh, lane);
+        row_loaded();
+        const int64_t row = ((int64_t)b * nl + h) * S + i;
+        bf16_t* dqp = dqkv + ((int64_t)b * S + i) * ld + (int64_t)h * dh;
+        float* pp = part + ((int64_t)slot * BH + bh) * (BLK * DH) + (i - qb * BLK) * DH;
+        attn_row_dq<(DH + 63) / 64>(q_s, q_s + DH, kbase, vbase, ld, dh, tile0 * TILE, min(i + 1, ntiles * TILE), scale, lse[row],
+                              dsum[row], lane, [&](int d, float v) { if (ck.nch > 1) pp[d] = v; else dqp[d] = (bf16_t)(v * scale); });
+        row_loaded();
     }
 }
 

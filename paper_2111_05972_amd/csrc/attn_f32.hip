@@ -21,6 +21,7 @@
 // to 32) read zero.  A tile is requested as soon as its slot has been read for the last time and is waited for by count.
 #include <hip/hip_runtime.h>
 
+#include "attn_rows.h"
 #include "device_math.h"
 #include "kernels.h"
 #include "lds_dma.h"
@@ -111,9 +112,16 @@ __device__ __forceinline__ i32x4 xrsrc(const float* base, int64_t ld, int S, int
 __device__ __forceinline__ float xother(float v) { return __shfl_xor(v, 32, 64); }
 
 // Adds the four wavefronts' blocks in wavefront order, each scaled by its f, and hands element (row 8 i + 4 half + j,
-// column) to put(d block, i, four rows' values): wavefront w writes accumulator quads w of every block.
+// column) to put(d block, i, four rows' values): wavefront w writes accumulator quads w of every block, rows for which
+// xmine(row, w).  Returns 0, or NaN if one of the lane's values is not finite.
+//
+// Infinities and NaN under the causal mask.  The matrix instruction multiplies a masked weight, zero, with its row, and zero
+// times infinity is NaN: in the tile that the diagonal crosses, a token would reach tokens before it.  A wavefront that ends
+// with a value that is not finite therefore computes what it has written again, row by row, where a masked row is not read
+// (attn_rows.h; LDS at xrows).
+__device__ __forceinline__ bool xmine(int row, int wave) { return ((row >> 3) & 3) == wave; }
 template <int DH, typename Put>
-__device__ __forceinline__ void xcombine(char* smem, const f32x16 (&acc)[DH / 32], const float (&f)[4], int wave, int lane, Put put) {
+__device__ __forceinline__ float xcombine(char* smem, const f32x16 (&acc)[DH / 32], const float (&f)[4], int wave, int lane, Put put) {
     float* red = reinterpret_cast<float*>(smem);                  // [wavefront][block][register][lane]
     __syncthreads();
 #pragma unroll
@@ -121,6 +129,7 @@ __device__ __forceinline__ void xcombine(char* smem, const f32x16 (&acc)[DH / 32
 #pragma unroll
         for (int v = 0; v < 16; ++v) red[((wave * (DH / 32) + d) * 16 + v) * 64 + lane] = acc[d][v];
     __syncthreads();
+    float z = 0.0f;
 #pragma unroll
     for (int d = 0; d < DH / 32; ++d) {
         float r[4];
@@ -131,13 +140,17 @@ __device__ __forceinline__ void xcombine(char* smem, const f32x16 (&acc)[DH / 32
 #pragma unroll
             for (int w = 1; w < 4; ++w) s = fmaf(red[((w * (DH / 32) + d) * 16 + v) * 64 + lane], f[w], s);
             r[j] = s;
+            z = fmaf(s, 0.0f, z);
         }
         put(d, wave, r);
     }
+    return z;
 }
 
-template <int DH> constexpr int xlds_bytes() {
-    return 4 * 2 * xtile_bytes<DH>() + 4 * 2 * XT * 4;            // two tiles per wavefront (also the combine area), row terms
+// two tiles per wavefront (also the combine area), row terms, two rows per wavefront for attn_rows.h
+template <int DH> constexpr int xlds_bytes() { return 4 * 2 * xtile_bytes<DH>() + 4 * 2 * XT * 4 + 4 * 2 * DH * 4; }
+template <int DH> __device__ __forceinline__ float* xrows(char* smem, int wave) {
+    return reinterpret_cast<float*>(smem + 4 * 2 * xtile_bytes<DH>() + 4 * 2 * XT * 4) + wave * 2 * DH;
 }
 
 // ---- forward: workgroup = (32 queries, batch*head) ---------------------------------------------------------------
@@ -213,17 +226,29 @@ __global__ __launch_bounds__(256) void attn_f32_fwd_kernel(int S, int nl, int dh
     for (int w = 0; w < 4; ++w) mt = fmaxf(mt, st[w * 64 + (lane & 31)]);
 #pragma unroll
     for (int w = 0; w < 4; ++w) {
-        f[w] = expf(st[w * 64 + (lane & 31)] - mt);
+        f[w] = expf(st[w * 64 + (lane & 31)] - (mt == -INFINITY ? 0.0f : mt));   // all scores -inf: sum 0, LSE -inf
         lt = fmaf(st[w * 64 + 32 + (lane & 31)], f[w], lt);
     }
 #pragma unroll
     for (int w = 0; w < 4; ++w) f[w] /= lt;
     float* op = o + ((int64_t)b * S + q) * ((int64_t)nl * dh) + (int64_t)h * dh;
-    xcombine<DH>(smem, acc, f, wave, lane, [&](int d, int i, const float (&r)[4]) {
+    const float z = xcombine<DH>(smem, acc, f, wave, lane, [&](int d, int i, const float (&r)[4]) {
         const int c = d * 32 + 8 * i + 4 * half;
         if (q < S && c < dh) *reinterpret_cast<float4*>(op + c) = make_float4(r[0], r[1], r[2], r[3]);
     });
     if (wave == 0 && half == 0 && q < S) lse[(int64_t)bh * S + q] = mt + logf(lt);
+    if (!causal || !__any(z != 0.0f)) return;
+    rows_stored();
+    float* q_s = xrows<DH>(smem, wave);
+    for (int i = q0; i < q0 + XT && i < S; ++i) {
+        load_row(q_s, qbase + (int64_t)i * ld, dh, lane);
+        row_loaded();
+        float* oi = o + ((int64_t)b * S + i) * ((int64_t)nl * dh) + (int64_t)h * dh;
+        float mr, lr;
+        attn_row_fwd<(DH + 63) / 64>(q_s, qbase + (int64_t)nl * dh, qbase + 2LL * nl * dh, ld, dh, 0, i + 1, scale, true, lane, mr, lr,
+                                     [&](int d, float v) { if (xmine(d, wave)) oi[d] = v; });
+        row_loaded();
+    }
 }
 
 // ---- dQ: workgroup = (32 queries, batch*head); also leaves D = rowsum(dO * O) for the dK/dV kernel -----------------
@@ -293,10 +318,24 @@ __global__ __launch_bounds__(256) void attn_f32_dq_kernel(int S, int nl, int dh,
     xwait<0>();
     const float f[4] = {scale, scale, scale, scale};
     float* dqp = dqkv + ((int64_t)b * S + q) * ld + (int64_t)h * dh;
-    xcombine<DH>(smem, acc, f, wave, lane, [&](int d, int i, const float (&r)[4]) {
+    const float z = xcombine<DH>(smem, acc, f, wave, lane, [&](int d, int i, const float (&r)[4]) {
         const int c = d * 32 + 8 * i + 4 * half;
         if (q < S && c < dh) *reinterpret_cast<float4*>(dqp + c) = make_float4(r[0], r[1], r[2], r[3]);
     });
+    if (!causal || !__any(z != 0.0f)) return;
+    rows_stored();
+    float* q_s = xrows<DH>(smem, wave);
+    for (int i = q0; i < q0 + XT && i < S; ++i) {
+        load_row(q_s, qbase + (int64_t)i * ld, dh, lane);
+        load_row(q_s + DH, d_o + orow + (int64_t)i * ldo, dh, lane);
+        row_loaded();
+        float* dqi = dqkv + ((int64_t)b * S + i) * ld + (int64_t)h * dh;
+        float Di = 0.0f;
+        for (int d = lane; d < dh; d += 64) Di = fmaf(q_s[DH + d], o[orow + (int64_t)i * ldo + d], Di);
+        attn_row_dq<(DH + 63) / 64>(q_s, q_s + DH, qbase + (int64_t)nl * dh, qbase + 2LL * nl * dh, ld, dh, 0, i + 1, scale,
+                                    lse[(int64_t)bh * S + i], row_sum(Di), lane, [&](int d, float v) { if (xmine(d, wave)) dqi[d] = v * scale; });
+        row_loaded();
+    }
 }
 
 // ---- dK, dV: workgroup = (32 keys, batch*head) -----------------------------------------------------------------------
@@ -377,14 +416,28 @@ __global__ __launch_bounds__(256) void attn_f32_dkv_kernel(int S, int nl, int dh
     float* kp = dqkv + ((int64_t)b * S + k) * ld + (int64_t)nl * dh + (int64_t)h * dh;
     float* vp = kp + (int64_t)nl * dh;
     const float fk[4] = {scale, scale, scale, scale}, fv[4] = {1.0f, 1.0f, 1.0f, 1.0f};
-    xcombine<DH>(smem, dk, fk, wave, lane, [&](int d, int i, const float (&r)[4]) {
+    float z = xcombine<DH>(smem, dk, fk, wave, lane, [&](int d, int i, const float (&r)[4]) {
         const int c = d * 32 + 8 * i + 4 * half;
         if (k < S && c < dh) *reinterpret_cast<float4*>(kp + c) = make_float4(r[0], r[1], r[2], r[3]);
     });
-    xcombine<DH>(smem, dv, fv, wave, lane, [&](int d, int i, const float (&r)[4]) {
+    z += xcombine<DH>(smem, dv, fv, wave, lane, [&](int d, int i, const float (&r)[4]) {
         const int c = d * 32 + 8 * i + 4 * half;
         if (k < S && c < dh) *reinterpret_cast<float4*>(vp + c) = make_float4(r[0], r[1], r[2], r[3]);
     });
+    if (!causal || !__any(z != 0.0f)) return;
+    rows_stored();
+    float* k_s = xrows<DH>(smem, wave);
+    for (int j = k0; j < k0 + XT && j < S; ++j) {
+        const float* kj = qbase + (int64_t)nl * dh + (int64_t)j * ld;
+        load_row(k_s, kj, dh, lane);
+        load_row(k_s + DH, kj + (int64_t)nl * dh, dh, lane);
+        row_loaded();
+        float* dkj = dqkv + ((int64_t)b * S + j) * ld + (int64_t)nl * dh + (int64_t)h * dh;
+        float* dvj = dkj + (int64_t)nl * dh;
+        attn_row_dkv<(DH + 63) / 64>(k_s, k_s + DH, qbase, ld, d_o + (int64_t)b * S * ldo + (int64_t)h * dh, ldo, lrow, drow, dh, j, S, scale,
+                                     lane, [&](int d, float a, float v) { if (xmine(d, wave)) { dkj[d] = a * scale; dvj[d] = v; } });
+        row_loaded();
+    }
 }
 
 // ---- host ----------------------------------------------------------------------------------------------------------------

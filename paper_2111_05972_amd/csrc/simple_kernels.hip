@@ -4,6 +4,7 @@
 
 #include <mutex>
 
+#include "attn_rows.h"
 #include "device_math.h"
 #include "kernels.h"
 
@@ -89,21 +90,10 @@ hipError_t gemm_simple(const GemmArgs& a) {
 
 // ------------------------------------------------------------------------------------------------
 // Attention, one wavefront per query row (forward, dQ) or per key row (dK, dV).
-// qkv is [B*S, 3*nl*dh] with columns (q|k|v, head, dh).  Keys are visited 64 at a time: lane j of
-// the wavefront owns key j0+j for the logits, then lane d owns output column d for the
-// value-weighted sums, with the weights passed across lanes by shuffles.
+// qkv is [B*S, 3*nl*dh] with columns (q|k|v, head, dh); the arithmetic of a row is in attn_rows.h.
 // ------------------------------------------------------------------------------------------------
 constexpr int AT_WAVES = 4;
 constexpr int AT_MAXDH = 256;
-
-__device__ __forceinline__ float wave_max(float v) {
-    for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o, 64));
-    return v;
-}
-__device__ __forceinline__ float wave_sum(float v) {
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-    return v;
-}
 
 template <typename T>
 __global__ __launch_bounds__(64 * AT_WAVES) void attn_simple_fwd_kernel(
@@ -119,56 +109,13 @@ __global__ __launch_bounds__(64 * AT_WAVES) void attn_simple_fwd_kernel(
     const T* qp = qkv + ((int64_t)b * S + i) * ld + (int64_t)h * dh;
     const T* kbase = qkv + (int64_t)b * S * ld + (int64_t)nl * dh + (int64_t)h * dh;
     const T* vbase = kbase + (int64_t)nl * dh;
-    for (int d = lane; d < dh; d += 64) q_s[w][d] = to_f32(qp[d]);
+    load_row(q_s[w], qp, dh, lane);
     __syncthreads();
-    const float scale = 1.0f / sqrtf((float)dh);
-    const int jend = causal ? i + 1 : S;
-    // pass 1: row maximum and sum of exponentials
-    float mx = -INFINITY, sum = 0.0f;
-    for (int j0 = 0; j0 < jend; j0 += 64) {
-        int j = j0 + lane;
-        if (j < jend) {
-            const T* kp = kbase + (int64_t)j * ld;
-            float s = 0.0f;
-            for (int d = 0; d < dh; ++d) s = fmaf(q_s[w][d], to_f32(kp[d]), s);
-            s *= scale;
-            float nm = fmaxf(mx, s);
-            sum = sum * expf(mx - nm) + expf(s - nm);
-            mx = nm;
-        }
-    }
-    float gmx = wave_max(mx);
-    sum = wave_sum(mx == -INFINITY ? 0.0f : sum * expf(mx - gmx));
-    const float inv = 1.0f / sum;
-    // pass 2: O = sum_j p_j V_j
-    float acc[AT_MAXDH / 64] = {};
-    for (int j0 = 0; j0 < jend; j0 += 64) {
-        int j = j0 + lane;
-        float p = 0.0f;
-        if (j < jend) {
-            const T* kp = kbase + (int64_t)j * ld;
-            float s = 0.0f;
-            for (int d = 0; d < dh; ++d) s = fmaf(q_s[w][d], to_f32(kp[d]), s);
-            p = expf(s * scale - gmx) * inv;
-        }
-        int cnt = min(64, jend - j0);
-        for (int jj = 0; jj < cnt; ++jj) {
-            float pj = __shfl(p, jj, 64);
-            const T* vp = vbase + (int64_t)(j0 + jj) * ld;
-#pragma unroll
-            for (int t = 0; t < AT_MAXDH / 64; ++t) {
-                int d = lane + 64 * t;
-                if (d < dh) acc[t] = fmaf(pj, to_f32(vp[d]), acc[t]);
-            }
-        }
-    }
+    float m, l;
     T* op = o + ((int64_t)b * S + i) * ((int64_t)nl * dh) + (int64_t)h * dh;
-#pragma unroll
-    for (int t = 0; t < AT_MAXDH / 64; ++t) {
-        int d = lane + 64 * t;
-        if (valid && d < dh) op[d] = from_f32<T>(acc[t]);
-    }
-    if (valid && lane == 0) lse[((int64_t)b * nl + h) * S + i] = gmx + logf(sum);
+    attn_row_fwd<AT_MAXDH / 64>(q_s[w], kbase, vbase, ld, dh, 0, causal ? i + 1 : S, 1.0f / sqrtf((float)dh), true, lane, m, l,
+                                [&](int d, float v) { if (valid) op[d] = from_f32<T>(v); });
+    if (valid && lane == 0) lse[((int64_t)b * nl + h) * S + i] = m + logf(l);
 }
 
 // dQ_i = sum_j dS_ij K_j / sqrt(dh), dS_ij = P_ij (dO_i.V_j - D_i), D_i = dO_i.O_i; also stores D.
@@ -197,42 +144,12 @@ __global__ __launch_bounds__(64 * AT_WAVES) void attn_simple_dq_kernel(
         do_s[w][d] = g;
         dpart = fmaf(g, to_f32(op[d]), dpart);
     }
-    const float Di = wave_sum(dpart);
+    const float Di = row_sum(dpart);
     __syncthreads();
     const float scale = 1.0f / sqrtf((float)dh);
-    const float L = lse[((int64_t)b * nl + h) * S + i];
-    const int jend = causal ? i + 1 : S;
-    float acc[AT_MAXDH / 64] = {};
-    for (int j0 = 0; j0 < jend; j0 += 64) {
-        int j = j0 + lane;
-        float ds = 0.0f;
-        if (j < jend) {
-            const T* kp = kbase + (int64_t)j * ld;
-            const T* vp = vbase + (int64_t)j * ld;
-            float s = 0.0f, dp = 0.0f;
-            for (int d = 0; d < dh; ++d) {
-                s = fmaf(q_s[w][d], to_f32(kp[d]), s);
-                dp = fmaf(do_s[w][d], to_f32(vp[d]), dp);
-            }
-            ds = expf(s * scale - L) * (dp - Di);
-        }
-        int cnt = min(64, jend - j0);
-        for (int jj = 0; jj < cnt; ++jj) {
-            float dsj = __shfl(ds, jj, 64);
-            const T* kp = kbase + (int64_t)(j0 + jj) * ld;
-#pragma unroll
-            for (int t = 0; t < AT_MAXDH / 64; ++t) {
-                int d = lane + 64 * t;
-                if (d < dh) acc[t] = fmaf(dsj, to_f32(kp[d]), acc[t]);
-            }
-        }
-    }
     T* dqp = dqkv + ((int64_t)b * S + i) * ld + (int64_t)h * dh;
-#pragma unroll
-    for (int t = 0; t < AT_MAXDH / 64; ++t) {
-        int d = lane + 64 * t;
-        if (valid && d < dh) dqp[d] = from_f32<T>(acc[t] * scale);
-    }
+    attn_row_dq<AT_MAXDH / 64>(q_s[w], do_s[w], kbase, vbase, ld, dh, 0, causal ? i + 1 : S, scale, lse[((int64_t)b * nl + h) * S + i], Di,
+                               lane, [&](int d, float v) { if (valid) dqp[d] = from_f32<T>(v * scale); });
     if (valid && lane == 0) dsum[((int64_t)b * nl + h) * S + i] = Di;
 }
 
@@ -254,49 +171,16 @@ __global__ __launch_bounds__(64 * AT_WAVES) void attn_simple_dkv_kernel(
     const T* kp = qbase + (int64_t)j * ld + (int64_t)nl * dh;
     const T* vp = kp + (int64_t)nl * dh;
     const T* dobase = d_o + (int64_t)b * S * ldo + (int64_t)h * dh;
-    for (int d = lane; d < dh; d += 64) { k_s[w][d] = to_f32(kp[d]); v_s[w][d] = to_f32(vp[d]); }
+    load_row(k_s[w], kp, dh, lane);
+    load_row(v_s[w], vp, dh, lane);
     __syncthreads();
     const float scale = 1.0f / sqrtf((float)dh);
-    const float* lrow = lse + ((int64_t)b * nl + h) * S;
-    const float* drow = dsum + ((int64_t)b * nl + h) * S;
-    const int ibeg = causal ? j : 0;
-    float dk[AT_MAXDH / 64] = {}, dv[AT_MAXDH / 64] = {};
-    for (int i0 = ibeg; i0 < S; i0 += 64) {
-        int i = i0 + lane;
-        float p = 0.0f, ds = 0.0f;
-        if (i < S) {
-            const T* qp = qbase + (int64_t)i * ld;
-            const T* dop = dobase + (int64_t)i * ldo;
-            float s = 0.0f, dp = 0.0f;
-            for (int d = 0; d < dh; ++d) {
-                s = fmaf(to_f32(qp[d]), k_s[w][d], s);
-                dp = fmaf(to_f32(dop[d]), v_s[w][d], dp);
-            }
-            p = expf(s * scale - lrow[i]);
-            ds = p * (dp - drow[i]);
-        }
-        int cnt = min(64, S - i0);
-        for (int ii = 0; ii < cnt; ++ii) {
-            float pi = __shfl(p, ii, 64), dsi = __shfl(ds, ii, 64);
-            const T* qp = qbase + (int64_t)(i0 + ii) * ld;
-            const T* dop = dobase + (int64_t)(i0 + ii) * ldo;
-#pragma unroll
-            for (int t = 0; t < AT_MAXDH / 64; ++t) {
-                int d = lane + 64 * t;
-                if (d < dh) {
-                    dk[t] = fmaf(dsi, to_f32(qp[d]), dk[t]);
-                    dv[t] = fmaf(pi, to_f32(dop[d]), dv[t]);
-                }
-            }
-        }
-    }
     T* dkp = dqkv + ((int64_t)b * S + j) * ld + (int64_t)nl * dh + (int64_t)h * dh;
     T* dvp = dkp + (int64_t)nl * dh;
-#pragma unroll
-    for (int t = 0; t < AT_MAXDH / 64; ++t) {
-        int d = lane + 64 * t;
-        if (valid && d < dh) { dkp[d] = from_f32<T>(dk[t] * scale); dvp[d] = from_f32<T>(dv[t]); }
-    }
+    attn_row_dkv<AT_MAXDH / 64>(k_s[w], v_s[w], qbase, ld, dobase, ldo, lse + ((int64_t)b * nl + h) * S, dsum + ((int64_t)b * nl + h) * S, dh,
+                                causal ? j : 0, S, scale, lane, [&](int d, float dk, float dv) {
+                                    if (valid) { dkp[d] = from_f32<T>(dk * scale); dvp[d] = from_f32<T>(dv); }
+                                });
 }
 
 template <typename T>
