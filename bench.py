@@ -17,7 +17,7 @@ if ROOT not in sys.path:
     sys.path.insert(0, ROOT)
 
 BF16_PEAK_TFLOPS = 2500.0     # MI355X dense bf16 MFMA (vendor figure, no sparsity)
-F32_PEAK_TFLOPS = 157.3       # fp32 vector
+F32_PEAK_TFLOPS = 157.3       # fp32, vector and matrix alike
 
 
 def gemm_list(cfg):
@@ -327,8 +327,8 @@ def bench_layer(args, cfg, dt, pkg, torch, synthetic, ckpt=False, extras=True, o
                                   "steps": n_split, "what": "same shard with the bias + residual epilogue of the row-parallel GEMMs on"}
         del layer_on, grads_on
 
-    # dominant kernel: the GEMM kernel.  Its 12 launches per step are timed inside real steps: the
-    # library brackets each GEMM launch with HIP events on the launch stream (tp_layer_profile).
+    # dominant kernel: the GEMM kernel.  Its launches (12 per step, or 4 of grouped GEMMs) are timed inside real steps:
+    # the library brackets each GEMM launch with HIP events on the launch stream (tp_layer_profile).
     roofline = None
     if not args.no_kernel_timing:
         names = [g_[0] for g_ in gemm_list(cfg)]
@@ -341,16 +341,23 @@ def bench_layer(args, cfg, dt, pkg, torch, synthetic, ckpt=False, extras=True, o
         torch.cuda.synchronize()
         ms = pkg.tp_layer_profile_read()
         pkg.tp_layer_profile(0)
-        per_step = len(ms) // reps          # 12, or 14 with the recomputed QKV and up-projection GEMMs
-        assert len(ms) == per_step * reps and per_step in (12, 14), len(ms)
-        if per_step == 14:                  # launch order: 4 fwd, then recomputed up_fwd and qkv_fwd, then 8 bwd
-            order = names[:4] + ["up_fwd", "qkv_fwd"] + names[4:]
+        per_step = len(ms) // reps
+        grouped = per_step in (4, 5)        # launches of independent GEMMs together
+        if grouped:
+            order = ["up_fwd qkv_fwd", "down_fwd out_fwd", "down_wgrad out_wgrad down_dgrad out_dgrad",
+                     "up_wgrad qkv_wgrad up_dgrad qkv_dgrad"]
+            flops = {n: sum(flops[k] for k in n.split()) for n in order}
+            shapes = {n: {k: shapes[k] for k in n.split()} for n in order}
+            names, redone = list(order), ["up_fwd qkv_fwd"]
         else:
-            order = names
-        per = {n: sum(ms[i] for i in range(len(ms)) if order[i % per_step] == n) / reps for n in names}
-        if per_step == 14:
-            for n in ("qkv_fwd", "up_fwd"):
+            order, redone = list(names), ["up_fwd", "qkv_fwd"]
+        if per_step == len(order) + len(redone):   # checkpointing: recomputed after the forward launches
+            n_fwd = 2 if grouped else 4
+            order = order[:n_fwd] + redone + order[n_fwd:]
+            for n in redone:
                 flops[n] *= 2
+        assert len(ms) == per_step * reps and per_step == len(order), len(ms)
+        per = {n: sum(ms[i] for i in range(len(ms)) if order[i % per_step] == n) / reps for n in names}
         tot_ms, tot_fl = sum(per.values()), sum(flops.values())
         achieved = tot_fl / (tot_ms * 1e-3) / 1e12
         traffic = None
@@ -360,11 +367,12 @@ def bench_layer(args, cfg, dt, pkg, torch, synthetic, ckpt=False, extras=True, o
                 traffic = json.load(open(tpath)).get(cfg.name, {}).get("bytes_per_launch")
             except Exception:
                 traffic = None
-        roofline = {"kernel": "bf16 MFMA GEMM kernels of gemm_bf16.hip (12 launches per step, one at a time)" if cfg.dtype == "bf16" else "gemm_simple_kernel",
-                    "bound": "mfma" if cfg.dtype == "bf16" else "alu",
+        kind = "bf16 MFMA GEMM kernels of gemm_bf16.hip" if cfg.dtype == "bf16" else "float MFMA GEMM kernels of gemm_f32.hip"
+        how = f"{len(names)} launches per step, each of independent GEMMs" if grouped else f"{len(names)} launches per step, one at a time"
+        roofline = {"kernel": f"{kind} ({how})", "bound": "mfma",
                     "achieved": round(achieved, 2), "peak": peak, "unit": "TFLOP/s",
                     "frac": round(achieved / peak, 4), "traffic": traffic,
-                    "flops_per_launch": tot_fl / 12, "avg_launch_ms": round(tot_ms / 12, 4),
+                    "flops_per_launch": tot_fl / len(names), "avg_launch_ms": round(tot_ms / len(names), 4),
                     "gemm_ms_per_step": round(tot_ms, 4)}
         if extras:
             roofline["launches"] = {n: {**shapes[n], "ms": round(per[n], 4), "tflops": round(flops[n] / per[n] / 1e9, 1)} for n in names}

@@ -280,8 +280,13 @@ int tp_layer_attn_bwd(int dtype, int B, int S, int nl, int dh, int causal,
                       void* dqkv, float* d_scratch, void* ws, size_t ws_bytes, void* hip_stream);
 
 /* Diagnostics for benchmarks (not thread-safe, off by default).  tp_layer_profile(1) makes every
- * GEMM launched by this library (inside tp_layer_fwd / tp_layer_bwd / tp_layer_gemm) be bracketed by
- * two HIP events on its launch stream and restarts the record; tp_layer_profile(0) stops.
+ * GEMM launch of this library (inside tp_layer_fwd / tp_layer_bwd / tp_layer_gemm) be bracketed by
+ * two HIP events on its launch stream and restarts the record; tp_layer_profile(0) stops.  A launch
+ * is one GEMM or a group of independent ones, whichever the call takes without timing, with the
+ * kernel that adds its partial sums: a grouped layer has 2 records in forward ({up, qkv}, {down,
+ * out}; recomputation the first alone) and 2 in backward ({dW_dn, dW_o, dU, dO}, {dW_up, dW_qkv,
+ * dx_mlp, dx_attn}), any other 4 (2) and 8.  While timing is on every kernel is enqueued on the
+ * caller's stream; results are the same.
  * tp_layer_profile_read waits for the recorded launches (at most 4096, in launch order), writes their
  * durations in milliseconds to ms_out[0..*count) and restarts the record.  ms_out is HOST memory. */
 int tp_layer_profile(int enable);

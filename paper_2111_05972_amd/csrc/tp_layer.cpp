@@ -169,8 +169,7 @@ size_t group_ws(const Dims& x, bool bwd) {
     const auto bytes = x.dtype == BF16 ? gemm_bf16_group_workspace_bytes : gemm_f32_group_workspace_bytes;
     return up(std::max(bytes(first, n1), bytes(second, n2)));
 }
-// GEMM scratch of a pass: one region per chain, or what its groups need (both, so that the choice may differ between the
-// size query and the call: per-GEMM timing runs the GEMMs one by one).
+// GEMM scratch of a pass: one region per chain, or what its groups need (the larger of both).
 size_t fwd_gemm_total(const Dims& x) { return std::max(2 * fwd_gemm_ws(x), group_ws(x, false)); }
 size_t fwd_ws_total(const Dims& x) { return fwd_gemm_total(x) + attn_ws(x, false); }
 
@@ -203,7 +202,7 @@ void bwd_layout(const Dims& x, BwdWs* W) {
 
 inline bool misaligned(const void* p) { return ((uintptr_t)p & 15u) != 0; }
 
-// Diagnostic timing of GEMM launches with HIP events on the launch stream (off by default).
+// Diagnostic timing of GEMM launches, single or grouped, with HIP events on the launch stream (off by default).
 struct GemmProfile {
     static constexpr int CAP = 4096;
     bool on = false;
@@ -264,8 +263,9 @@ struct SideJoin {
     ~SideJoin() { if (!done) side_join(s, s2, which); }
 };
 
-int run_gemm(GemmArgs& g) {
-    hipError_t e;
+// Runs launch() between the two events of a record where launches are timed.
+template <typename Launch>
+int profiled(hipStream_t stream, Launch launch) {
     int slot = -1;
     if (g_prof.on && g_prof.n < GemmProfile::CAP) {
         slot = g_prof.n++;
@@ -274,14 +274,19 @@ int run_gemm(GemmArgs& g) {
                 return TPL_EHIP;
             g_prof.created[slot] = true;
         }
-        if (hipEventRecord(g_prof.start[slot], g.stream) != hipSuccess) return TPL_EHIP;
+        if (hipEventRecord(g_prof.start[slot], stream) != hipSuccess) return TPL_EHIP;
     }
-    g.colsum_done = false;
-    if (g.dtype == BF16 && gemm_bf16_supported(g)) e = gemm_bf16(g, &g.colsum_done);
-    else if (gemm_f32_supported(g)) e = gemm_f32(g);
-    else e = gemm_simple(g);
-    if (slot >= 0 && hipEventRecord(g_prof.stop[slot], g.stream) != hipSuccess) return TPL_EHIP;
+    const hipError_t e = launch();
+    if (slot >= 0 && hipEventRecord(g_prof.stop[slot], stream) != hipSuccess) return TPL_EHIP;
     return e == hipSuccess ? TPL_OK : TPL_EHIP;
+}
+
+int run_gemm(GemmArgs& g) {
+    return profiled(g.stream, [&] {
+        g.colsum_done = false;
+        if (g.dtype == BF16 && gemm_bf16_supported(g)) return gemm_bf16(g, &g.colsum_done);
+        return gemm_f32_supported(g) ? gemm_f32(g) : gemm_simple(g);
+    });
 }
 
 int run_attn(AttnArgs& a, bool bwd) {
@@ -310,7 +315,7 @@ GemmArgs mk(const Dims& x, int ta, int tb, int64_t M, int64_t N, int64_t K, cons
 // Whether the GEMMs of a pass go out as groups.
 bool use_groups(const Dims& x) {
     const Options& o = options();
-    if (g_prof.on || o.gemm_group == 0) return false;
+    if (o.gemm_group == 0) return false;
     // every operand within the matrix-core kernels' 32-bit offsets (whole 16-byte rows are given, in either type)
     const int64_t widest = std::max(std::max(x.Il, 3 * x.Hl), x.H);
     if (std::max(x.M, x.H) * widest * x.esz >= 0x7FFFFFFFll) return false;
@@ -321,7 +326,7 @@ bool use_groups(const Dims& x) {
 }
 int run_group(const GemmArgs* g, int n, const GemmScratch& sc) {
     const auto group = g[0].dtype == BF16 ? gemm_bf16_group : gemm_f32_group;
-    return group(g, n, sc.ws, sc.bytes, sc.stream) == hipSuccess ? TPL_OK : TPL_EHIP;
+    return profiled(sc.stream, [&] { return group(g, n, sc.ws, sc.bytes, sc.stream); });
 }
 
 // Forward kernels in order.  With row_parallel == false the two row-parallel GEMMs (whose outputs the
