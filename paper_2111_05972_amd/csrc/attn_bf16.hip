@@ -1048,9 +1048,11 @@ __global__ __launch_bounds__(FTHREADS, 2) void attn_bwd_kernel(const bf16_t* __r
 
 // ---- host side ----------------------------------------------------------------------------------
 bool attn_bf16_supported(const AttnArgs& a) {
-    // tile loads address a (batch, head) slice with 32-bit byte offsets
+    // tile loads address a (batch, head) slice with 32-bit byte offsets; where columns may be padded, HEAD_OOB plus the
+    // offset of any row of the last tile must not wrap either
+    const int64_t rows = a.dh == 64 || a.dh == 128 ? a.S : (int64_t)a.S + TILE;
     return a.dtype == BF16 && a.dh % 8 == 0 && a.dh <= 128 && a.S >= 1 && (int64_t)a.B * a.nl <= 65535 &&
-           ((int64_t)a.S + TILE) * 3 * a.nl * a.dh * 2 < (1LL << 31);
+           rows * 3 * a.nl * a.dh * 2 < (1LL << 31);
 }
 
 template <typename K>
