@@ -1806,16 +1806,6 @@ static Plan make_plan(int64_t M, int64_t N, int64_t K, bool a_kmaj, bool b_kmaj)
         }
     }
     if (forced_shape_v >= 0) forced_v = forced_shape_v;
-    // Shapes whose plan was measured inside a whole layer step (two chains) against the estimate's choice and came out
-    // ahead by more than 1 % of the step: the short-K and square GEMMs of the 1024- and 4096-wide encoder shards,
-    // where the estimate below (calibrated on long-K GEMMs under the power cap) overrates the 256-wide tiles.
-    static const struct { int M, N, K; bool a_kmaj, b_kmaj; int variant; } measured[] = {
-        {8192, 2048, 1024, true, false, 7}, {8192, 2048, 1024, true, true, 7},      // roberta-large, TP 2: up / down-dgrad
-        {4096, 4096, 4096, true, false, 7}, {4096, 4096, 1024, true, false, 7},     // 10B encoder, TP 4: up / out
-    };
-    if (forced_v < 0 && forced_s <= 0)
-        for (const auto& e : measured)
-            if (e.M == M && e.N == N && e.K == K && e.a_kmaj == a_kmaj && e.b_kmaj == b_kmaj) { forced_v = e.variant; forced_s = 1; }
     const int cus = compute_units();
     const int nk = (int)((K + DK - 1) / DK);
     Plan best{0, 1, nk};
