@@ -427,14 +427,10 @@ int bwd_impl(const Dims& x, const tp_layer_params* p, const void* x_attn, const 
     const bool groups = use_groups(x), side = x.side_stream && !groups;
     hipStream_t s2 = side_fork(s, side);
     SideJoin sj{s, s2};
-    // dW_dn and dW_o need only the pass's inputs and saved activations: they can form a third chain on a stream of
-    // their own (option side_chains = 2 or 3 forces the number of chains)
-    // (measured inside whole steps: -4 % at the RoBERTa-large shard and -2 % at the BERT-large one, whose GEMMs leave
-    // compute units idle; +1 to +2 % at the 10B and GPT-3 shards, whose GEMMs fill the chip and only get in each other's
-    // way; left to itself the library takes three chains below 45 GFLOP per weight gradient)
-    const int chains = options().side_chains ? options().side_chains
-                                             : (2.0 * (double)x.Il * (double)x.H * (double)x.M < 45.0e9 ? 3 : 2);
-    hipStream_t s3 = chains >= 3 ? side_fork(s, side, 1) : nullptr;
+    // dW_dn and dW_o need only the pass's inputs and saved activations: with option side_chains = 3 they are a third chain on a
+    // stream of their own (-4 % of the step of a RoBERTa-large shard launched GEMM by GEMM, +1 to +2 % where GEMMs fill the
+    // chip; the layers it helps go out as groups, so it is not taken by size)
+    hipStream_t s3 = options().side_chains == 3 ? side_fork(s, side, 1) : nullptr;
     SideJoin sj3{s, s3 ? s3 : s, 1};
     GemmScratch sc{w + W.gemm, W.gemm_each, s}, sc2{w + W.gemm2, W.gemm_each, s2};
     GemmScratch sc3a{w + W.gemm3, W.gemm_each, s3 ? s3 : s2}, sc3b{w + W.gemm3, W.gemm_each, s3 ? s3 : s};
