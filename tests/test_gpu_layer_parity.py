@@ -61,17 +61,34 @@ def test_named_configs_full_size(cid):
     _run(C[cid])
 
 
-@pytest.mark.parametrize("cid", [2, 3, 4, 5])
-def test_two_chain_schedule_at_full_size(cid):
-    """The launch configuration bench.py times: the attention block and the MLP block of a pass on two streams
-    (TPL_SIDE_STREAM).  Element by element against the oracle, and bit-identical to the one-stream schedule (the
-    kernels and their order within a chain are the same; only what runs beside what changes)."""
+@pytest.mark.parametrize("cid,group", [(2, None), (2, "0"), (3, None), (3, "0"), (4, None), (5, None)])
+def test_two_chain_schedule_at_full_size(cid, group, tune):
+    """The launch configuration bench.py times (TPL_SIDE_STREAM): the attention block and the MLP block of a pass on two
+    streams where GEMMs are launched one by one (configs 4 and 5, and option gemm_group 0), groups on one stream otherwise.
+    Element by element against the oracle, and bit-identical to the call without the flag (the kernels and their order
+    within a chain are the same; only what runs beside what changes)."""
+    tune.set("gemm_group", group)
     cfg = C[cid]
-    print(f"\n[case] two chains, {cfg.name}", flush=True)
+    print(f"\n[case] two chains, {cfg.name}, gemm_group={group}", flush=True)
     d, sh = shard_inputs(cfg)
     two = gpu_outputs(cfg, d, sh, side_stream=True)
     compare(cfg, two, oracle_outputs(cfg, d, sh))
     one = gpu_outputs(cfg, d, sh)
+    for k in one:
+        assert np.array_equal(one[k], two[k]), k
+
+
+@pytest.mark.parametrize("epilogue", [True, False])
+def test_float_layer_launched_one_by_one(epilogue, tune):
+    """A float layer without groups (option gemm_group 0, and operands of 2 GiB): single GEMMs, column-sum kernels for the
+    bias gradients, on one stream and on two."""
+    tune.set("gemm_group", "0")
+    cfg = small_variant(C[1], name="f32-one-by-one", hidden=260, heads=5, head_dim=52, intermediate=516, tp_degree=1, tp_rank=0,
+                        seq=131, micro_batch=2, causal=True, row_epilogue=epilogue)
+    d, sh = shard_inputs(cfg)
+    one = gpu_outputs(cfg, d, sh)
+    compare(cfg, one, oracle_outputs(cfg, d, sh))
+    two = gpu_outputs(cfg, d, sh, side_stream=True)
     for k in one:
         assert np.array_equal(one[k], two[k]), k
 
