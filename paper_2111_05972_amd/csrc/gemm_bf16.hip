@@ -1540,9 +1540,10 @@ __global__ __launch_bounds__(256, 2) void gemm_bf16_x16s_kernel(GemmParams p) {
 // one list of workgroups instead, longest K first.  All use one tile; the layouts of a layer's GEMMs (NN forward, NT data
 // gradient, TN weight gradient with the column sums of its B) are three bodies of the same kernel.
 // Measured, whole training steps against one launch per GEMM and bias gradient (on two or three chains where the caller
-// allows): 198 tokens x 2 of an 832 / 104 shard 156 -> 60 us, BERT-large TP 4 263 -> 181 us, RoBERTa-large TP 2 545 -> 515,
-// 3003 tokens of 2560 / 640 542 -> 498, 610 tokens of 10752 / 1344 934 -> 792.  Which tile: at 832 / 104 64 / 128 / 192 take
-// 60 / 73 / 107 us, at BERT-large 236 / 182 / 205, at 2560 / 640 826 / 546 / 499.
+// allows): 198 tokens x 2 of an 832 / 104 shard 156 -> 60 us, BERT-large TP 4 256 -> 166 us, RoBERTa-large TP 2 516 -> 472,
+// 3003 tokens of 2560 / 640 548 -> 466, 610 tokens of 10752 / 1344 934 -> 792.  Which tile (the four launches of a step on
+// 64 / 128 / 192): 832 / 104 45 / 56 / 81 us, BERT-large 206 / 148 / 179, RoBERTa-large TP 2 669 / 411 / 412, 2560 / 640
+// 734 / 452 / 407, the 10B encoder TP 4 2365 / 1393 / 1155.
 // =================================================================================================
 constexpr int GROUP_MAX = 4;
 struct GroupParams {
@@ -1931,8 +1932,10 @@ hipError_t gemm_bf16(const GemmArgs& a, bool* colsum_done) {
 // ---- groups ------------------------------------------------------------------------------------------------------------
 // One tile for the whole group and K shares per GEMM, by a time estimate.  A launch takes as long as its units have work
 // (k-steps of all workgroups, a start and an epilogue per workgroup) or as its longest workgroup runs by itself, whichever
-// is more; K shares shorten the longest ones and cost the partial sums' traffic and a launch.  The constants are fitted to
-// the kernel times of 40 groups of 10 layers (256 to 4096 wide, 400 to 8200 tokens) on each tile: 7 to 10 % root mean square.
+// is more; K shares shorten the longest ones and cost the partial sums' traffic and a launch.  Against the measured times of
+// 24 groups of 6 layers on each tile the estimate is off by 15 % root mean square: up to 28 % too long for the widest layers
+// (10B encoder, GPT-3 13B), up to 28 % too short for the narrowest (832 / 104), the three tiles of a group mostly alike: the
+// tile with the least estimate is the fastest of the three on 23 of the 24 and 6 % behind on one.
 namespace {
 struct GroupTile { int bm; double step_us, wg_us, base_us, alone_us, alone_base_us; };
 constexpr GroupTile GROUP_TILES[] = {{192, 0.60, 2.6, 13.0, 0.77, 4.5}, {128, 0.355, 1.0, 7.5, 0.38, 4.5}, {64, 0.143, 0.92, 4.5, 0.35, 2.1}};

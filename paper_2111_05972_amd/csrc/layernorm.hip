@@ -384,10 +384,12 @@ __global__ __launch_bounds__(LN_THREADS) void ln_fwd_wave_kernel(int64_t M, int6
     }
 }
 
-// Backward of narrow rows, one wavefront per row: wavefront w of workgroup g walks rows 8 g + w, + 8 G, ... with the
-// next DEPTH of its rows in flight (addresses clamped to the last row, so that the loads are unconditional and can be
-// counted), and the eight wavefronts' column sums are added pairwise through LDS in a fixed order at the end.  A
-// 256-thread workgroup per row keeps one row and two barriers in the chain per CU: latency, not bytes.
+// Backward of narrow rows, one wavefront per row: wavefront w of workgroup g walks rows 8 g + w, + 8 G, ... with a ring of
+// DEPTH rows requested ahead (addresses clamped to the last row, so that the loads are unconditional), and the eight
+// wavefronts' column sums are added pairwise through LDS in a fixed order at the end.  The ring does not stay in flight: the
+// row number is a vector value to the compiler, so mean and rstd of a row are vector loads requested after the prefetch, and
+// the wait for them is a wait for everything.  A 256-thread workgroup per row keeps one row and two barriers in the chain
+// per CU: latency, not bytes.
 // Forward and backward together, before and now: bfloat16 16384 x 512 86 -> 34 us, 8192 x 1024 54 -> 34, 4096 x 768 29 -> 19;
 // float 8192 x 1024 66 -> 56.
 constexpr int LN_WAVE_ROWS = 8;        // wavefronts of a workgroup = its rows at a time
@@ -577,8 +579,10 @@ static hipError_t bwd_t(const LnArgs& a) {
 // One wavefront per row up to H = 1024.  Beyond, a lane would hold four chunks, only one workgroup of the backward fits a
 // CU and its column sums cost more than the barriers saved (workgroup against wavefront per row, both directions together):
 // float 16384 x 2048 185 us against 203, 1024 x 2048 21.0 against 22.7; bfloat16 1001 x 1536 16.8 against 20.3.
-// Few rows are launch-bound either way (256 x 256 17.2 us on both sides); from 4096 rows on, two per wavefront of a full
-// chip, the gain is measured (29 -> 19 us at 4096 x 768).
+// Up to 1024 rows both are launch-bound and level (bfloat16 1024 x 512 13.4 against 13.7 us, float 1024 x 1024 15.6 against
+// 15.7).  At 2048 and 3072 rows a wavefront per row is ahead too (bfloat16 512 columns 17.9 against 13.6 and 22.9 against 14.0,
+// 1024 columns 19.7 against 16.7 and 25.3 against 19.1; float 1024 columns 22.7 against 20.4 and 30.1 against 25.9), so the
+// line lies higher than it need; from 4096 rows on it always is (29 -> 19 us at 4096 x 768).
 constexpr int64_t LN_WAVE_MIN_M = 4096;
 template <typename T, int MAXC>
 static hipError_t fwd_wave_t(const LnArgs& a) {
