@@ -1051,8 +1051,10 @@ bool attn_bf16_supported(const AttnArgs& a) {
     // tile loads address a (batch, head) slice with 32-bit byte offsets; where columns may be padded, HEAD_OOB plus the
     // offset of any row of the last tile must not wrap either
     const int64_t rows = a.dh == 64 || a.dh == 128 ? a.S : (int64_t)a.S + TILE;
+    // a launch has fewer than 2^32 threads, in backward those of two workgroups per block
+    const int64_t threads = (a.S + BLK - 1) / BLK * (int64_t)a.B * a.nl * 2 * FTHREADS;
     return a.dtype == BF16 && a.dh % 8 == 0 && a.dh <= 128 && a.S >= 1 && (int64_t)a.B * a.nl <= 65535 &&
-           rows * 3 * a.nl * a.dh * 2 < (1LL << 31);
+           rows * 3 * a.nl * a.dh * 2 < (1LL << 31) && threads < (1LL << 32);
 }
 
 template <typename K>

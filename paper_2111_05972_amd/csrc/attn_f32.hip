@@ -442,9 +442,10 @@ __global__ __launch_bounds__(256) void attn_f32_dkv_kernel(int S, int nl, int dh
 
 // ---- host ----------------------------------------------------------------------------------------------------------------
 bool attn_f32_supported(const AttnArgs& a) {
-    // 16-byte chunks of a head's row; 32-bit byte offsets inside a (batch, head) slice, 32 rows past its end included
+    // 16-byte chunks of a head's row; 32-bit byte offsets inside a (batch, head) slice, 32 rows past its end included; fewer
+    // than 2^32 threads in a launch
     return a.dtype == F32 && a.dh % 4 == 0 && a.dh <= 128 && ((int64_t)a.S + XT) * 3 * a.nl * a.dh * 4 < (1LL << 31) &&
-           (int64_t)a.B * a.nl * ((a.S + XT - 1) / XT) < (1LL << 31);
+           (int64_t)a.B * a.nl * ((a.S + XT - 1) / XT) * 256 < (1LL << 32);
 }
 template <int DH>
 static hipError_t set_lds() {
