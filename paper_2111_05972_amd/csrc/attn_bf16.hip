@@ -8,9 +8,9 @@
 // dO, K and Q.  At every other head size (FLOATW) they keep their 24 bits: an operand is the sum of three bf16 terms
 // (split_terms), each multiplied by a matrix instruction of its own (that step: 0.48 ms with rounded weights, 0.51 so).
 //
-// Infinities and NaN under the causal mask.  A matrix instruction multiplies a masked weight, zero, with its row, and zero
-// times infinity is NaN: in the tile that the diagonal crosses, a token would reach tokens before it.  With FLOATW a
-// wavefront that ends with a value that is not finite therefore computes its 32 rows again, row by row, where a masked row
+// Infinities and NaN.  Zero times infinity is NaN, and a matrix instruction multiplies masked weights, which are zero, with
+// their rows: in the tile that the diagonal crosses, a token would reach tokens before it.  So does a term of a split weight
+// that happens to be zero: an infinite sum would become NaN.  With FLOATW a wavefront that ends with a value that is not finite therefore computes its 32 rows again, row by row, where a masked row
 // is not read (attn_rows.h).  Head sizes 64 and 128 have the matrix instruction's behaviour.
 //
 // qkv is [B*S, 3*nl*dh] with columns (q | k | v, local head, dh); o is [B*S, nl*dh].  The S x S
@@ -506,7 +506,7 @@ __global__ __launch_bounds__(FTHREADS, DH <= 64 ? 4 : 2) void attn_fwd_kernel(co
 #pragma unroll
                     for (int j = 0; j < 4; ++j)
                         r[j] = oacc[dt][4 * i + j] * f0 + mg[(2 + dt * 16 + 4 * i + j) * 64] * f1;
-                    if (FLOATW && CAUSAL) note4(z, r);
+                    if (FLOATW) note4(z, r);
                     store_f4(pp + ql * DH + dt * 32 + 8 * i + 4 * half, r[0], r[1], r[2], r[3]);
                 }
             if (half == 0) { pp[BLK * DH + ql] = mn; pp[BLK * DH + BLK + ql] = ltot; }
@@ -520,12 +520,12 @@ __global__ __launch_bounds__(FTHREADS, DH <= 64 ? 4 : 2) void attn_fwd_kernel(co
 #pragma unroll
                     for (int j = 0; j < 4; ++j)
                         r[j] = (oacc[dt][4 * i + j] * f0 + mg[(2 + dt * 16 + 4 * i + j) * 64] * f1) * inv;
-                    if (FLOATW && CAUSAL) note4(z, r);
+                    if (FLOATW) note4(z, r);
                     if (dt * 32 + 8 * i + 4 * half < dh) store4(op + dt * 32 + 8 * i + 4 * half, r[0], r[1], r[2], r[3]);
                 }
             if (half == 0) lse[((int64_t)b * nl + h) * S + q] = strip_lse<FLOATW>(mn, ltot);
         }
-        if (!FLOATW || !CAUSAL || !any_nonfinite(z)) return;
+        if (!FLOATW || !any_nonfinite(z)) return;
         rows_stored();
         float* q_s = reinterpret_cast<float*>(smem) + qs * NV * 64;      // this wavefront alone reads its merge area
         float* pp = part + ((int64_t)slot * BH + bh) * (BLK * (DH + 2));
@@ -536,7 +536,7 @@ __global__ __launch_bounds__(FTHREADS, DH <= 64 ? 4 : 2) void attn_fwd_kernel(co
             bf16_t* op = o + ((int64_t)b * S + i) * ((int64_t)nl * dh) + (int64_t)h * dh;
             const int ql = i - qb * BLK;
             float mr, lr;
-            attn_row_fwd<(DH + 63) / 64>(q_s, kbase, vbase, ld, dh, tile0 * TILE, min(i + 1, ntiles * TILE), 1.0f / sqrtf((float)dh), whole,
+            attn_row_fwd<(DH + 63) / 64>(q_s, kbase, vbase, ld, dh, tile0 * TILE, min(CAUSAL ? i + 1 : S, ntiles * TILE), 1.0f / sqrtf((float)dh), whole,
                                          lane, mr, lr, [&](int d, float v) { if (whole) op[d] = (bf16_t)v; else pp[ql * DH + d] = v; });
             if (lane == 0) {
                 if (whole) lse[((int64_t)b * nl + h) * S + i] = mr + logf(lr);
@@ -803,7 +803,7 @@ __device__ __forceinline__ void attn_dkv_body(char* smem, const bf16_t* __restri
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
                 const float r[4] = {acc[dt][4 * i], acc[dt][4 * i + 1], acc[dt][4 * i + 2], acc[dt][4 * i + 3]};
-                if (FLOATW && CAUSAL) note4(z, r);
+                if (FLOATW) note4(z, r);
                 store_f4(pp + dt * 32 + 8 * i + 4 * half, r[0], r[1], r[2], r[3]);
             }
     } else if (kv < S) {
@@ -814,11 +814,11 @@ __device__ __forceinline__ void attn_dkv_body(char* smem, const bf16_t* __restri
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
                 const float r[4] = {acc[dt][4 * i] * f, acc[dt][4 * i + 1] * f, acc[dt][4 * i + 2] * f, acc[dt][4 * i + 3] * f};
-                if (FLOATW && CAUSAL) note4(z, r);
+                if (FLOATW) note4(z, r);
                 if (dt * 32 + 8 * i + 4 * half < dh) store4(outp + dt * 32 + 8 * i + 4 * half, r[0], r[1], r[2], r[3]);
             }
     }
-    if (!FLOATW || !CAUSAL || !any_nonfinite(z)) return;
+    if (!FLOATW || !any_nonfinite(z)) return;
     rows_stored();
     float* k_s = reinterpret_cast<float*>(smem) + wave * 2 * DH;     // the ring has been read
     for (int j = k0; j < k0 + 32 && j < S; ++j) {
@@ -827,7 +827,7 @@ __device__ __forceinline__ void attn_dkv_body(char* smem, const bf16_t* __restri
         row_loaded();
         bf16_t* outp = dqkv + ((int64_t)b * S + j) * ld + (int64_t)(DK_ROLE ? 1 : 2) * nl * dh + (int64_t)h * dh;
         float* pp = pslot + (DK_ROLE ? 0 : BLK * DH) + (j - kb * BLK) * DH;
-        attn_row_dkv<(DH + 63) / 64>(k_s, k_s + DH, qbase, ld, dobase, ldo, lrow, drow, dh, max(j, qt0 * TILE), min(S, ntiles * TILE),
+        attn_row_dkv<(DH + 63) / 64>(k_s, k_s + DH, qbase, ld, dobase, ldo, lrow, drow, dh, max(CAUSAL ? j : 0, qt0 * TILE), min(S, ntiles * TILE),
                                scale, lane, [&](int d, float dk, float dv) {
                                    const float v = DK_ROLE ? dk : dv;
                                    if (ck.nch > 1) pp[d] = v;
@@ -994,7 +994,7 @@ __device__ __forceinline__ void attn_dq_wg(char* smem, const bf16_t* __restrict_
                 float r[4];
 #pragma unroll
                 for (int j = 0; j < 4; ++j) r[j] = dq[dt][4 * i + j] + mg[(dt * 16 + 4 * i + j) * 64];
-                if (FLOATW && CAUSAL) note4(z, r);
+                if (FLOATW) note4(z, r);
                 store_f4(pp + dt * 32 + 8 * i + 4 * half, r[0], r[1], r[2], r[3]);
             }
     } else if (kvh == 0 && q < S) {
@@ -1006,11 +1006,11 @@ __device__ __forceinline__ void attn_dq_wg(char* smem, const bf16_t* __restrict_
                 float r[4];
 #pragma unroll
                 for (int j = 0; j < 4; ++j) r[j] = (dq[dt][4 * i + j] + mg[(dt * 16 + 4 * i + j) * 64]) * scale;
-                if (FLOATW && CAUSAL) note4(z, r);
+                if (FLOATW) note4(z, r);
                 if (dt * 32 + 8 * i + 4 * half < dh) store4(dqp + dt * 32 + 8 * i + 4 * half, r[0], r[1], r[2], r[3]);
             }
     }
-    if (!FLOATW || !CAUSAL || kvh != 0 || !any_nonfinite(z)) return;
+    if (!FLOATW || kvh != 0 || !any_nonfinite(z)) return;
     rows_stored();
     float* q_s = reinterpret_cast<float*>(smem) + qs * (DH / 2) * 64;      // this wavefront alone reads its merge area
     for (int i = q0; i < q0 + 32 && i < S; ++i) {
@@ -1020,7 +1020,7 @@ __device__ __forceinline__ void attn_dq_wg(char* smem, const bf16_t* __restrict_
         const int64_t row = ((int64_t)b * nl + h) * S + i;
         bf16_t* dqp = dqkv + ((int64_t)b * S + i) * ld + (int64_t)h * dh;
         float* pp = part + ((int64_t)slot * BH + bh) * (BLK * DH) + (i - qb * BLK) * DH;
-        attn_row_dq<(DH + 63) / 64>(q_s, q_s + DH, kbase, vbase, ld, dh, tile0 * TILE, min(i + 1, ntiles * TILE), scale, lse[row],
+        attn_row_dq<(DH + 63) / 64>(q_s, q_s + DH, kbase, vbase, ld, dh, tile0 * TILE, min(CAUSAL ? i + 1 : S, ntiles * TILE), scale, lse[row],
                               dsum[row], lane, [&](int d, float v) { if (ck.nch > 1) pp[d] = v; else dqp[d] = (bf16_t)(v * scale); });
         row_loaded();
     }
