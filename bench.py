@@ -349,6 +349,7 @@ def bench_layer(args, cfg, dt, pkg, torch, synthetic, ckpt=False, extras=True, o
             flops = {n: sum(flops[k] for k in n.split()) for n in order}
             shapes = {n: {k: shapes[k] for k in n.split()} for n in order}
             names, redone = list(order), ["up_fwd qkv_fwd"]
+            out["config"]["schedule"] = "independent GEMMs in groups, one stream"
         else:
             order, redone = list(names), ["up_fwd", "qkv_fwd"]
         if per_step == len(order) + len(redone):   # checkpointing: recomputed after the forward launches
