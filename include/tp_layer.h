@@ -35,9 +35,9 @@
  * tp_layer_fwd / tp_layer_bwd / tp_layer_bwd_recompute enqueue the attention block and the MLP
  * block, which share no tensor, as two chains, the second on a stream the library creates once per
  * device (default priority) and forks from / joins to `hip_stream` with events (also when the call
- * fails half-way).  Float layers, and bf16 layers of less than 0.64 TFLOP of forward GEMMs, launch the
- * independent GEMMs of both blocks together instead, on `hip_stream` alone whatever the flag says; a
- * layer with an operand of 2 GiB or more does not.  The library's streams and their events are shared
+ * fails half-way).  The independent GEMMs of both blocks are launched together instead, on `hip_stream`
+ * alone whatever the flag says, unless an operand has 2 GiB or more or an option about single GEMMs or
+ * chains is set (tp_layer_set_option).  The library's streams and their events are shared
  * by all calls on a device: host threads that make such calls on the same device at the same time must
  * serialise them.
  * Pointers must be 16-byte aligned.  Outputs must not alias inputs.  Gradients are overwritten,
@@ -302,9 +302,9 @@ int tp_layer_profile_read(float* ms_out, int capacity, int* count);
  *   "side_chains" 2 or 3: chains of a backward pass under TPL_SIDE_STREAM (3: the two weight gradients that depend on
  *                 nothing computed in the pass, dW_dn and dW_o, on a second library stream), its GEMMs one by one; unset: 2
  *                 where they are
- *   "gemm_group"  0, 64, 128, 192: the GEMMs of a pass that do not depend on each other in one launch: never, or always on
- *                 tiles of that size (float layers: 192 stands for tiles of 32); unset: every float layer and the bf16 layers
- *                 named above, unless an option about single GEMMs or chains is set.  Operands of 2 GiB or more: never
+ *   "gemm_group"  0, 64, 128, 192, 256: the GEMMs of a pass that do not depend on each other in one launch: never, or always on
+ *                 tiles of that size (float layers: 192 stands for tiles of 32, 256 is as unset); unset: every layer,
+ *                 on the tile that is estimated fastest, unless an option about single GEMMs or chains is set.  Operands of 2 GiB or more: never
  *   "fuse_colsum" 1: the bias gradients db_qkv, db_up are one more output row of the weight-gradient GEMM whenever
  *                 its kernel supports that; 0 (default): they come from the column-sum kernels (measured inside the
  *                 whole step the two are equal on one stream and the fused form is 0.4 % slower on two chains)

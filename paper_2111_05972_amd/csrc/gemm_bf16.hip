@@ -49,22 +49,11 @@
 #include <cstdlib>
 #include <mutex>
 
-#include "device_math.h"
+#include "gemm_bf16_common.h"
+#include "gemm_bf16_pp.h"
 #include "kernels.h"
-#include "lds_dma.h"
-#include "tile_order.h"
 
 namespace tpl {
-
-typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
-typedef __attribute__((ext_vector_type(4))) __bf16 bf16x4;
-typedef __attribute__((ext_vector_type(4))) short s16x4;
-typedef __attribute__((ext_vector_type(16))) float f32x16;
-typedef __attribute__((ext_vector_type(4))) float f32x4;
-typedef __attribute__((address_space(3))) s16x4* lds_s16x4_ptr;
-
-constexpr int DK = 32;                      // k per stage
-constexpr unsigned OOB_OFFSET = 0xFFFFFFF0u;   // beyond any buffer this kernel accepts
 
 // Tile variant: 2 x 2 wavefronts, each owning TM x TN MFMA 32x32 blocks -> a (64 TM) x (64 TN) tile.
 template <int TM_, int TN_, int STAGES_>
@@ -80,182 +69,6 @@ struct Tile {
     static_assert((STAGES - 1) * LOADS <= 63, "vmcnt is a 6-bit counter");
 };
 
-struct GemmParams {
-    const bf16_t* A; const bf16_t* B; bf16_t* C;
-    const bf16_t* bias; const bf16_t* resid; bf16_t* aux;
-    int M, N, K;
-    int lda, ldb;          // row strides (elements) of A and B as stored
-    int epi;
-    int tiles_m, tiles_n;
-    int band;              // tile rows per band of the tile order (see tile_coords)
-    int nt_store;          // C stored with the non-temporal hint
-    int nk;                // k-steps of one workgroup (one K share when K is split)
-    int nk_total;          // k-steps of the whole K
-    float* partial;        // K split over several workgroups: float partial sums [share][M][N], else null
-    bf16_t* colsum;        // [N]: sum over k of B[k][n], written by the kernels that can (see gemm_bf16), else null
-    float* colsum_part;    // with K split: [share][N], the same sums of one share; gemm_group_sum_kernel adds them
-};
-
-// Which K share a workgroup computes.  The workgroup list is share-major (all tiles of share 0, then all
-// tiles of share 1, ...), so the tiles in flight together on an XCD walk the same k range and share panels.
-struct KShare { int tile, share, kt0, nk, kend; float* partial; };
-__device__ __forceinline__ KShare k_share(const GemmParams& p, int list_pos) {
-    KShare s;
-    const int ntiles = p.tiles_m * p.tiles_n;
-    const int share = list_pos / ntiles;
-    s.tile = list_pos - share * ntiles;
-    s.share = share;
-    s.kt0 = share * p.nk;
-    s.nk = p.nk_total - s.kt0 < p.nk ? p.nk_total - s.kt0 : p.nk;
-    s.kend = (s.kt0 + s.nk) * DK < p.K ? (s.kt0 + s.nk) * DK : p.K;
-    s.partial = p.partial ? p.partial + (int64_t)share * p.M * p.N : nullptr;
-    return s;
-}
-
-// ---- LDS layouts -------------------------------------------------------------------------------
-// K-major stage tile: 64-byte rows (32 k), four 16-byte chunks, swizzled by row.
-__device__ __forceinline__ int swz_k32(int row) { return (row >> 2) & 3; }
-// MN-major stage tile: one row of R (m or n) bf16 per k = R/8 16-byte chunks, R*2 bytes per k.
-// A transposing read touches four consecutive k at the same 64 bytes of columns (two 16-lane groups,
-// 32 bytes each); the four k must land in four different 64-byte quarters of the 256-byte bank line.
-//  * R*2 a multiple of 256 (R = 128, 256): every k starts at the same bank offset, so the 64-byte
-//    column group is XORed with k & 3.
-//  * R = 192 (384-byte rows): k and k+1 already differ by 128 bytes, so k+2, k+3 are moved one
-//    64-byte group further (cyclically over the row's 6 groups; 6 = 2 mod 4 keeps the four distinct).
-//  * R = 64 (128-byte rows): k and k+1 differ by 128 bytes, k+2, k+3 take the other 64-byte group of the row.
-template <int R> __device__ __forceinline__ int mn_swz(int c, int k) {
-    constexpr int CPR = R / 8;
-    const int half = ((k >> 3) & 1) << 1;       // k and k + 8 (16x16x32 fragments read both at once): other 32 bytes
-    if (CPR >= 16 && (CPR & (CPR - 1)) == 0) return c ^ ((k & 3) << 2) ^ half;
-    int g = (c >> 2) + ((k >> 1) & 1);
-    g = g >= CPR / 4 ? g - CPR / 4 : g;
-    return (g << 2) | ((c & 3) ^ half);
-}
-template <int R> __device__ __forceinline__ int mn_unswz(int c, int k) {
-    constexpr int CPR = R / 8;
-    const int half = ((k >> 3) & 1) << 1;
-    if (CPR >= 16 && (CPR & (CPR - 1)) == 0) return c ^ ((k & 3) << 2) ^ half;
-    int g = (c >> 2) - ((k >> 1) & 1);
-    g = g < 0 ? g + CPR / 4 : g;
-    return (g << 2) | ((c & 3) ^ half);
-}
-
-constexpr unsigned OOB_HALF = 0x80000000u;     // out of bounds for operands below 2 GiB, and no wrap when a
-                                               // scalar offset below 2 GiB is added
-
-// Byte offsets (relative to the operand base, for tile origin mn0 and k = 0) of the T 16-byte chunks
-// this lane fetches per stage (operand tile of R = 64 T rows); chunk j of wavefront w lands in LDS
-// block w*T + j (1 KiB blocks) at 16*lane.
-// XOR16: MN-major chunk positions for the kernel that reads 16x16x32 fragments with per-lane base registers
-// (chunk c of row k at position c ^ xor16(k)); otherwise mn_swz.
-__device__ __forceinline__ int xor16(int k) { return (((k >> 1) & 1) << 1) | (((k >> 3) & 1) << 2); }
-// K16: K-major chunk positions for tiles read as 16-row fragments (swz_k32_16 below).
-__device__ __forceinline__ int swz_k32_16(int row) { return (row >> 1) & 3; }
-// k row (0..31) of the MN-major stage tile of R = 64 T columns that load j of wavefront `wave` fetches for this lane.
-template <int T> __device__ __forceinline__ int mn_krow(int wave, int j, int lane) {
-    return ((wave * T + j) * 64 + lane) / (64 * T / 8);
-}
-template <bool KMAJ, int T, bool XOR16 = false, bool K16 = false>
-__device__ __forceinline__ void dma_offsets(unsigned (&off)[T], bool (&mn_ok)[T], int& kcol, int ld,
-                                            int mn0, int MN, int wave, int lane) {
-    constexpr int R = 64 * T;
-#pragma unroll
-    for (int j = 0; j < T; ++j) {
-        int block = wave * T + j;
-        if (KMAJ) {
-            int row = block * 16 + (lane >> 2);
-            int c = (lane & 3) ^ (K16 ? swz_k32_16(row) : swz_k32(row));
-            kcol = c * 8;                                   // same for every j
-            mn_ok[j] = true;                                // rows beyond MN point past the buffer
-            off[j] = mn0 + row < MN ? (unsigned)(((int64_t)(mn0 + row) * ld + c * 8) * 2) : OOB_HALF;
-        } else {
-            int idx = block * 64 + lane;                    // physical chunk index inside the stage tile
-            int k = idx / (R / 8);
-            int c = XOR16 ? (idx % (R / 8)) ^ xor16(k) : mn_unswz<R>(idx % (R / 8), k);   // logical chunk stored there
-            kcol = 0;
-            mn_ok[j] = mn0 + c * 8 < MN;
-            off[j] = (unsigned)(((int64_t)k * ld + mn0 + c * 8) * 2);
-        }
-    }
-}
-
-// LDS -> MFMA fragment: rows mn_base + (lane % 32), k = ks*16 + 8*(lane/32) + 0..7.
-template <bool KMAJ, int R>
-__device__ __forceinline__ bf16x8 dma_frag(const char* tile, int mn_base, int ks, int lane) {
-    if (KMAJ) {
-        int row = mn_base + (lane & 31);
-        int c = 2 * ks + (lane >> 5);
-        return *reinterpret_cast<const bf16x8*>(tile + row * 64 + ((c ^ swz_k32(row)) << 4));
-    } else {
-        // Two transposing reads; in each 16-lane group lane l points at (k = kb + l/4, 4 columns at
-        // 4*(l%4)) and receives k = kb..kb+3 of column l.
-        int l16 = lane & 15;
-        int mn = mn_base + (lane & 16) + 4 * (l16 & 3);
-        int kq = l16 >> 2;
-        int kb = ks * 16 + 8 * (lane >> 5);
-        bf16x8 out;
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            int k = kb + 4 * h + kq;
-            int off = k * (R * 2) + (mn_swz<R>(mn >> 3, k) << 4) + (mn & 7) * 2;
-            s16x4 v = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_ptr)(tile + off));
-            bf16x4 b = __builtin_bit_cast(bf16x4, v);
-            out[4 * h + 0] = b[0]; out[4 * h + 1] = b[1]; out[4 * h + 2] = b[2]; out[4 * h + 3] = b[3];
-        }
-        return out;
-    }
-}
-
-// LDS -> fragment of the 16x16x32 matrix instruction: rows mn_base + (lane % 16), k = 8*(lane/16) + 0..7 of
-// the 32-k stage.  For this lane pattern a K-major tile of 64-byte rows is free of bank conflicts with the chunk
-// XOR (row >> 1) & 3 (measured: 223 B/clk/CU, against 125 with the (row >> 2) & 3 of the 32-row fragments).
-template <bool KMAJ, int R>
-__device__ __forceinline__ bf16x8 dma_frag16(const char* tile, int mn_base, int lane) {
-    if (KMAJ) {
-        int row = mn_base + (lane & 15);
-        int c = lane >> 4;
-        return *reinterpret_cast<const bf16x8*>(tile + row * 64 + ((c ^ swz_k32_16(row)) << 4));
-    } else {
-        int l16 = lane & 15;
-        int mn = mn_base + 4 * (l16 & 3);
-        int kq = l16 >> 2;
-        int kb = 8 * (lane >> 4);
-        bf16x8 out;
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            int k = kb + 4 * h + kq;
-            int off = k * (R * 2) + (mn_swz<R>(mn >> 3, k) << 4) + (mn & 7) * 2;
-            s16x4 v = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_ptr)(tile + off));
-            bf16x4 b = __builtin_bit_cast(bf16x4, v);
-            out[4 * h + 0] = b[0]; out[4 * h + 1] = b[1]; out[4 * h + 2] = b[2]; out[4 * h + 3] = b[3];
-        }
-        return out;
-    }
-}
-
-template <int N> __device__ __forceinline__ void wait_vmcnt() {
-    asm volatile("s_waitcnt vmcnt(%0)" :: "n"(N) : "memory");
-}
-
-__device__ __forceinline__ void unpack8(const uint4& v, float (&f)[8]) {
-    const unsigned u[4] = {v.x, v.y, v.z, v.w};
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        f[2 * i] = __uint_as_float(u[i] << 16);
-        f[2 * i + 1] = __uint_as_float(u[i] & 0xffff0000u);
-    }
-}
-__device__ __forceinline__ uint4 pack8(const float (&f)[8]) {
-    unsigned u[4];
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        bf16_t lo = (bf16_t)f[2 * i], hi = (bf16_t)f[2 * i + 1];
-        u[i] = (unsigned)__builtin_bit_cast(unsigned short, lo) |
-               ((unsigned)__builtin_bit_cast(unsigned short, hi) << 16);
-    }
-    return make_uint4(u[0], u[1], u[2], u[3]);
-}
-
 // Epilogue of one wavefront: accumulators -> its LDS staging area -> 16-byte row accesses.  The wavefront's
 // part of the tile goes through the staging area in slabs of 32 rows; store_slab(I, stage) writes slab I
 // (row r, column c of the wavefront's part at stage + r * EROW + 4 c); a pass then takes 64 / LPR staged rows, 8 columns
@@ -268,7 +81,6 @@ __device__ __forceinline__ uint4 pack8(const float (&f)[8]) {
 // per kernel, of the 64 KB that the instruction cache of two compute units holds).  Measured against that form, whole
 // training steps: RoBERTa-large TP 2 0.552 -> 0.516 ms, GPT-3 13B TP 4 1.964 -> 1.886, 175B TP 8 2.368 -> 2.324.  With the
 // passes rolled too (a third of the code again) the first two gained 2 % and lost 0.5 %, the last lost 2 %.
-enum EpiKind { KIND_PARTIAL, KIND_PLAIN, KIND_RESID, KIND_GELU, KIND_DGELU, KIND_ANY };
 template <typename TL>
 struct EpilogueLane {
     static constexpr int TM = TL::TM, TN = TL::TN;
@@ -478,35 +290,6 @@ __device__ __forceinline__ void epilogue_helper(const GemmParams& p, char* smem,
     epilogue_rows_shared<TL, true>(p, smem, wave, lane, m0, n0, partial, [](auto, char*) {});
 }
 
-// Column sums are added in runs of CS_RUN k-steps (512 rows), then the runs: as one running sum over all rows they lose more
-// to rounding than the column-sum kernels (rms error over 32768 rows of unit variance that cancel: 1.8e-5 to 2.0e-5, those
-// kernels 1.3e-5, so 0.35e-5; BERT-large TP 4 step 165.2 -> 166.1 us).
-constexpr int CS_RUN = 16;
-// s += x; what the rounding loses goes into the next call.
-__device__ __forceinline__ void add_carrying(float& s, float& lost, float x) {
-    const float y = x - lost, t = s + y, l = (t - s) - y;
-    lost = l == l ? l : 0.0f;                  // infinite sums: inf - inf
-    s = t;
-}
-// c + the sum of the eight elements of a fragment (float accumulation)
-__device__ __forceinline__ float add_elements(const bf16x8& f, float c) {
-    typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
-    bf16x2 ones;
-    ones[0] = ones[1] = (bf16_t)1.0f;
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-        bf16x2 v;
-        v[0] = f[2 * e]; v[1] = f[2 * e + 1];
-        c = __builtin_amdgcn_fdot2_f32_bf16(v, ones, c, false);
-    }
-    return c;
-}
-__device__ __forceinline__ void store_colsum(const GemmParams& p, const KShare& sh, int col, float v) {
-    if (col >= p.N) return;
-    if (sh.partial) p.colsum_part[(int64_t)sh.share * p.N + col] = v;
-    else p.colsum[col] = (bf16_t)v;
-}
-
 // COLSUM: with p.colsum set, the wavefronts that hold the first rows of tile row 0 also add up the columns of B over k
 // (the bias gradient that goes with a weight gradient) from the fragments they multiply: four two-element dot products
 // with ones per fragment, in float, in their own copy of the loop.
@@ -686,7 +469,6 @@ __global__ __launch_bounds__(256) void gemm_bf16_kernel(GemmParams p) {
 __device__ __forceinline__ void mfma16_inplace(f32x4& acc, const bf16x8& a, const bf16x8& b) {
     asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(acc) : "v"(a), "v"(b));
 }
-__device__ __forceinline__ void mfma16_drain() { asm volatile("s_nop 7\n\ts_nop 7\n\ts_nop 7" ::: "memory"); }
 
 template <int TM_, int TN_, int STAGES_>
 struct Tile8 {
@@ -900,9 +682,6 @@ __device__ __forceinline__ void fetch_range(const i32x4& rsrc, unsigned lds_firs
     }
 }
 
-// K-major tile with rows of 128 bytes (64 k): 16-byte chunk c of row r sits at position c ^ ((r >> 1) & 7),
-// so the 16 rows a quarter-wavefront reads at one k are spread over all banks.
-__device__ __forceinline__ int swz_k64(int row) { return (row >> 1) & 7; }
 __device__ __forceinline__ bf16x8 wide_frag(const char* tile, int mn_base, int k16, int lane) {
     int row = mn_base + (lane & 31);
     int c = 2 * k16 + (lane >> 5);
@@ -1571,6 +1350,39 @@ __global__ __launch_bounds__(256, 2) void gemm_bf16_group_kernel(GroupParams gp)
     else if (layout == 1) group_tile<TL, true, true, false>(p, pos, smem);
     else group_tile<TL, false, false, true>(p, pos, smem);
 }
+// The same on 256 x 256 tiles (gemm_bf16_pp.h), one epilogue behind the three layouts.  Jobs are runs of a GEMM's tiles:
+// [first[j], first[j+1]) are the workgroups of job j.
+constexpr int JOB_MAX = 2 * GROUP_MAX;
+struct PPGroupParams {
+    GemmParams g[JOB_MAX];
+    PPRun run[JOB_MAX];
+    int layout[JOB_MAX], shares[JOB_MAX], first[JOB_MAX + 1];
+    int n;
+};
+template <typename TL>
+__global__ __launch_bounds__(512, 2) void gemm_bf16_group_pp_kernel(PPGroupParams gp) {
+    extern __shared__ __attribute__((aligned(16))) char smem[];
+    const int bid = blockIdx.x;
+    int i = 0;
+    while (i + 1 < gp.n && bid >= gp.first[i + 1]) ++i;
+    const GemmParams& p = gp.g[i];
+    const PPWork<TL> w = pp_work<TL>(p, gp.run[i], share_of_block(bid - gp.first[i], gp.first[i + 1] - gp.first[i]));
+    const int layout = gp.layout[i];
+    f32x4 acc[2][4][TL::NB];
+    if (layout == 0) pp_products<TL, true, false, false>(p, w, smem, acc);
+    else if (layout == 1) pp_products<TL, true, true, false>(p, w, smem, acc);
+    else pp_products<TL, false, false, true>(p, w, smem, acc);
+    pp_epilogue<TL>(p, acc, w.m0, w.n0, w.partial);
+}
+// The tiles whose K was cut: 8 workgroups each; [first[j], first[j+1]) are those of job j.
+template <typename TL>
+__global__ __launch_bounds__(512) void gemm_group_pp_sum_kernel(PPGroupParams gp) {
+    const int bid = blockIdx.x;
+    int i = 0;
+    while (i + 1 < gp.n && bid >= gp.first[i + 1]) ++i;
+    const int pos = bid - gp.first[i];
+    pp_sum_rows<TL>(gp.g[i], gp.run[i], gp.shares[i], pos >> 3, pos & 7);
+}
 // The sums over K shares of all GEMMs of a group that were cut (and of their column sums): GEMM i has the workgroups
 // [first[i], first[i+1]) of this launch, 256 chunks of 8 outputs each, the N / 8 chunks of the column sums last.
 __global__ __launch_bounds__(256) void gemm_group_sum_kernel(GroupParams gp) {
@@ -1936,22 +1748,139 @@ hipError_t gemm_bf16(const GemmArgs& a, bool* colsum_done) {
 // 24 groups of 6 layers on each tile the estimate is off by 15 % root mean square: up to 28 % too long for the widest layers
 // (10B encoder, GPT-3 13B), up to 28 % too short for the narrowest (832 / 104), the three tiles of a group mostly alike: the
 // tile with the least estimate is the fastest of the three on 23 of the 24 and 6 % behind on one.
+// 256 x 256 tiles take a compute unit each, so a launch is its list dealt out to the units (list_time).  Whole steps on 256
+// against the best of the smaller tiles: BERT-large TP 4 186 and 156 us, 2560 / 640 at 3003 tokens 445 and 476, RoBERTa-large
+// TP 2 433 and 468, the 10B encoder TP 4 1290 and 1471, GPT-3 13B TP 4 1700 and 1913, 175B TP 8 2205 and 2594.
 namespace {
 struct GroupTile { int bm; double step_us, wg_us, base_us, alone_us, alone_base_us; };
-constexpr GroupTile GROUP_TILES[] = {{192, 0.60, 2.6, 13.0, 0.77, 4.5}, {128, 0.355, 1.0, 7.5, 0.38, 4.5}, {64, 0.143, 0.92, 4.5, 0.35, 2.1}};
-struct GroupPlan { int tile, nk[GROUP_MAX], shares[GROUP_MAX]; double us; };
+constexpr GroupTile GROUP_TILES[] = {{256, 0.75, 8.5, 2.0, 0, 0}, {192, 0.60, 2.6, 13.0, 0.77, 4.5}, {128, 0.355, 1.0, 7.5, 0.38, 4.5}, {64, 0.143, 0.92, 4.5, 0.35, 2.1}};
+constexpr double MEM_BYTES_PER_US = 4.5e6;     // operands and results of a launch, streamed
+constexpr int PP_MIN_STEPS = 12;               // k-steps of a K share
+struct PPJob { int gemm, tile0, count, nk, shares; };
+struct GroupPlan { int tile, nk[GROUP_MAX], shares[GROUP_MAX]; double us; int njobs; PPJob job[JOB_MAX]; };   // jobs: tile 256 only
 
 int64_t group_tiles(const GemmArgs& a, int bm) { return ((a.M + bm - 1) / bm) * ((a.N + bm - 1) / bm); }
 
-GroupPlan plan_group(const GemmArgs* g, int n) {
+// How long `units` machines take for a list of jobs dealt out in order, count[i] of length len[i] each (longest first).
+double list_time(int units, int n, const int64_t* count, const double* len) {
+    struct { double t; int64_t c; } free_at[64];                  // units by the time at which they are free, earliest first
+    int m = 1;
+    free_at[0] = {0.0, units};
+    double end = 0.0;
+    for (int i = 0; i < n; ++i) {
+        int64_t left = count[i];
+        const int64_t rounds = left / units;                      // whole rounds move every unit alike
+        if (rounds > 2) {
+            for (int q = 0; q < m; ++q) free_at[q].t += (double)(rounds - 2) * len[i];
+            left -= (rounds - 2) * units;
+        }
+        while (left > 0) {
+            const int64_t c = std::min(left, free_at[0].c);
+            const double t = free_at[0].t + len[i];
+            end = std::max(end, t);
+            left -= c;
+            if (c < free_at[0].c && m < 64) free_at[0].c -= c;
+            else { for (int q = 1; q < m; ++q) free_at[q - 1] = free_at[q]; --m; }
+            int q = m++;
+            for (; q > 0 && free_at[q - 1].t > t; --q) free_at[q] = free_at[q - 1];
+            free_at[q] = {t, c};
+        }
+    }
+    return end;
+}
+
+// 256 x 256 tiles, one workgroup per compute unit: the last round of a list that does not fill it is cut.  Of each GEMM `cut`
+// tiles, its last ones, go out in `shares` K shares each; the plan is the best found by changing one GEMM at a time.
+GroupPlan make_pp_plan(const GemmArgs* g, int n, const GroupTile& gt) {
+    const int cus = compute_units();
+    struct Cut { int64_t cut; int shares, nk; };
+    int64_t tiles[GROUP_MAX];
+    int nk[GROUP_MAX];
+    double tile_bytes[GROUP_MAX], floor_us = 0;
+    for (int i = 0; i < n; ++i) {
+        tiles[i] = group_tiles(g[i], gt.bm);
+        nk[i] = (int)((g[i].K + DK - 1) / DK);
+        tile_bytes[i] = (double)g[i].M * g[i].N / (double)tiles[i];
+        floor_us += 2.0 * ((double)g[i].M * g[i].K + (double)g[i].N * g[i].K + (double)g[i].M * g[i].N) / MEM_BYTES_PER_US;
+    }
+    auto with_shares = [&](int i, int64_t cut, int want) {
+        Cut c{cut, 1, nk[i]};
+        if (want > 1) {
+            c.nk = ((nk[i] + want - 1) / want + 1) & ~1;              // two k-steps at a time
+            c.shares = (nk[i] + c.nk - 1) / c.nk;
+        }
+        if (c.shares == 1) c.cut = 0;
+        return c;
+    };
+    auto jobs = [&](const Cut* c, PPJob* job) {                       // longest first
+        int m = 0;
+        for (int i = 0; i < n; ++i) {
+            if (tiles[i] > c[i].cut) job[m++] = PPJob{i, 0, (int)(tiles[i] - c[i].cut), nk[i], 1};
+            if (c[i].cut) job[m++] = PPJob{i, (int)(tiles[i] - c[i].cut), (int)c[i].cut, c[i].nk, c[i].shares};
+        }
+        std::stable_sort(job, job + m, [](const PPJob& a, const PPJob& b) { return a.nk > b.nk; });
+        return m;
+    };
+    auto estimate = [&](const Cut* c) {
+        PPJob job[JOB_MAX];
+        int64_t count[JOB_MAX];
+        double len[JOB_MAX], bytes = 0;
+        const int m = jobs(c, job);
+        for (int q = 0; q < m; ++q) {
+            count[q] = (int64_t)job[q].count * job[q].shares;
+            len[q] = job[q].nk * gt.step_us + gt.wg_us;
+            if (job[q].shares > 1) bytes += job[q].count * tile_bytes[job[q].gemm] * (8.0 * job[q].shares + 2.0);
+        }
+        return std::max(list_time(cus, m, count, len) + gt.base_us, floor_us) + (bytes > 0 ? 4.2 + bytes / 8.0e6 : 0.0);
+    };
+    Cut best[GROUP_MAX], now[GROUP_MAX];
+    for (int i = 0; i < n; ++i) best[i] = now[i] = with_shares(i, 0, 1);
+    double best_us = estimate(best);
+    const int longest = *std::max_element(nk, nk + n);
+    for (int parts = 2; parts <= MAX_SHARES && longest / parts >= PP_MIN_STEPS; ++parts) {   // everything long cut to one length
+        for (int i = 0; i < n; ++i) now[i] = with_shares(i, tiles[i], std::max(1, (nk[i] * parts + longest - 1) / longest));
+        const double us = estimate(now);
+        if (us < best_us) { best_us = us; std::copy(now, now + n, best); }
+    }
+    for (int round = 0; round < 2 * n; ++round) {
+        const double before = best_us;
+        Cut base[GROUP_MAX];
+        std::copy(best, best + n, base);
+        for (int i = 0; i < n; ++i)
+            for (int want = 1; want <= MAX_SHARES && (want == 1 || nk[i] / want >= PP_MIN_STEPS); ++want) {
+                int64_t others = 0;
+                for (int q = 0; q < n; ++q) others += q == i ? tiles[q] : tiles[q] - base[q].cut;
+                for (int eighth = 0; eighth <= 8; ++eighth) {         // the tiles past whole rounds, or so many eighths
+                    const int64_t cut = eighth ? (tiles[i] * eighth + 7) / 8 : std::min(tiles[i], others % cus);
+                    std::copy(base, base + n, now);
+                    now[i] = with_shares(i, cut, want);
+                    const double us = estimate(now);
+                    if (us < best_us) { best_us = us; std::copy(now, now + n, best); }
+                    if (want == 1) break;
+                }
+            }
+        if (best_us >= before) break;
+    }
+    GroupPlan p{};
+    p.us = best_us;
+    p.njobs = jobs(best, p.job);
+    return p;
+}
+
+GroupPlan make_group_plan(const GemmArgs* g, int n) {
     const int cus = compute_units(), forced = options().gemm_group;
     GroupPlan best{};
     best.us = -1;
-    for (int t = 0; t < 3; ++t) {
+    for (int t = 0; t < 4; ++t) {
         const GroupTile& gt = GROUP_TILES[t];
         if (forced > 0 && forced != gt.bm) continue;
         GroupPlan p{};
         p.tile = t;
+        if (gt.bm == 256) {
+            best = make_pp_plan(g, n, gt);
+            best.tile = t;
+            continue;
+        }
         int64_t tiles[GROUP_MAX];
         int nk[GROUP_MAX];
         for (int i = 0; i < n; ++i) {
@@ -1960,15 +1889,17 @@ GroupPlan plan_group(const GemmArgs* g, int n) {
             p.shares[i] = 1;
         }
         auto estimate = [&]() {
-            double work = 0, wgs = 0, longest = 0, bytes = 0;
+            double work = 0, wgs = 0, longest = 0, bytes = 0, floor_us = 0;
             for (int i = 0; i < n; ++i) {
                 wgs += (double)tiles[i] * p.shares[i];
                 work += (double)tiles[i] * p.shares[i] * p.nk[i];
                 longest = std::max(longest, (double)p.nk[i]);
                 if (p.shares[i] > 1) bytes += (double)g[i].M * g[i].N * (8.0 * p.shares[i] + 2.0);
+                floor_us += 2.0 * ((double)g[i].M * g[i].K + (double)g[i].N * g[i].K + (double)g[i].M * g[i].N) / MEM_BYTES_PER_US;
             }
-            return std::max((work * gt.step_us + wgs * gt.wg_us) / cus + gt.base_us, longest * gt.alone_us + gt.alone_base_us) +
-                   (bytes > 0 ? 4.2 + bytes / 1.6e7 : 0.0);
+            const double us = std::max(floor_us, std::max((work * gt.step_us + wgs * gt.wg_us) / cus + gt.base_us,
+                                                          longest * gt.alone_us + gt.alone_base_us));
+            return us + (bytes > 0 ? 4.2 + bytes / 1.6e7 : 0.0);
         };
         p.us = estimate();
         for (int cuts = 0; cuts < 16; ++cuts) {                   // cut the longest again while that helps
@@ -1987,24 +1918,90 @@ GroupPlan plan_group(const GemmArgs* g, int n) {
     }
     return best;
 }
+// As plan_for: plans of groups are kept.
+GroupPlan plan_group(const GemmArgs* g, int n) {
+    struct Entry { int64_t key[GROUP_MAX][4]; int n; unsigned gen; GroupPlan plan; };
+    constexpr int CAP = 64;
+    static Entry cache[CAP];
+    static int used = 0, next = 0;
+    static std::mutex mu;
+    Entry e{};
+    e.n = n;
+    e.gen = options().generation;
+    for (int i = 0; i < n; ++i) {
+        const int64_t k[4] = {g[i].M, g[i].N, g[i].K, (g[i].trans_a ? 1 : 0) | (g[i].trans_b ? 2 : 0)};
+        std::copy(k, k + 4, e.key[i]);
+    }
+    std::lock_guard<std::mutex> lock(mu);
+    for (int i = 0; i < used; ++i)
+        if (cache[i].n == n && cache[i].gen == e.gen && std::equal(&e.key[0][0], &e.key[0][0] + 4 * GROUP_MAX, &cache[i].key[0][0])) return cache[i].plan;
+    e.plan = make_group_plan(g, n);
+    cache[used < CAP ? used++ : next++ % CAP] = e;
+    return e.plan;
+}
 size_t share_bytes(const GemmArgs& a, int shares) {               // float partial sums, column sums included
     return shares > 1 ? (size_t)shares * ((size_t)a.M * a.N + (size_t)a.N) * sizeof(float) : 0;
 }
 }  // namespace
 
+// Scratch of the K shares of a plan on 256 x 256 tiles: the tiles' sums, and column sums (of every GEMM that was cut).
+static size_t pp_bytes(const GroupPlan& pl, const GemmArgs* g) {
+    size_t need = 0;
+    for (int j = 0; j < pl.njobs; ++j)
+        if (pl.job[j].shares > 1)
+            need += (size_t)pl.job[j].shares * ((size_t)pl.job[j].count * pp_tile_floats<PPTile<2, 2>>() + (size_t)(g[pl.job[j].gemm].N + 3) / 4 * 4) * sizeof(float);
+    return need;
+}
 size_t gemm_bf16_group_workspace_bytes(const GemmArgs* g, int n) {
     const GroupPlan pl = plan_group(g, n);
+    if (GROUP_TILES[pl.tile].bm == 256) return pp_bytes(pl, g);
     size_t need = 0;
     for (int i = 0; i < n; ++i) need += share_bytes(g[i], pl.shares[i]);
     return need;
 }
 
-template <typename TL>
-static hipError_t launch_group(const GroupParams& gp, int wgs, hipStream_t s) {
-    static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_bf16_group_kernel<TL>),
+template <typename TL, typename Params>
+static hipError_t launch_group(void (*kernel)(Params), int threads, const Params& gp, hipStream_t s) {
+    static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel),
                                                        hipFuncAttributeMaxDynamicSharedMemorySize, TL::LDS_BYTES);
     if (attr != hipSuccess) return attr;
-    hipLaunchKernelGGL(gemm_bf16_group_kernel<TL>, dim3((unsigned)wgs), dim3(256), TL::LDS_BYTES, s, gp);
+    hipLaunchKernelGGL(kernel, dim3((unsigned)gp.first[gp.n]), dim3(threads), TL::LDS_BYTES, s, gp);
+    return hipGetLastError();
+}
+
+static hipError_t launch_pp_jobs(const GroupPlan& pl, const GemmArgs* g, void* ws, size_t ws_bytes, hipStream_t stream) {
+    using TL = PPTile<2, 2>;
+    if (pp_bytes(pl, g) > (ws ? ws_bytes : 0)) return hipErrorInvalidValue;
+    PPGroupParams gp{}, sp{};                                     // all jobs; the sums of those that were cut
+    float* part = static_cast<float*>(ws);
+    gp.n = pl.njobs;
+    for (int j = 0; j < pl.njobs; ++j) {
+        const PPJob& job = pl.job[j];
+        const GemmArgs& a = g[job.gemm];
+        GemmParams& p = gp.g[j];
+        p = gemm_params(a);
+        p.tiles_m = (int)((a.M + TL::BM - 1) / TL::BM);
+        p.tiles_n = (int)((a.N + TL::BN - 1) / TL::BN);
+        p.band = choose_band(p.tiles_m, TL::BM, TL::BN, TL::LDS_BYTES);
+        p.colsum = a.trans_a ? (bf16_t*)a.colsum_b : nullptr;
+        gp.layout[j] = a.trans_a ? 2 : a.trans_b ? 1 : 0;
+        gp.run[j] = PPRun{job.tile0, job.count, job.nk, nullptr};
+        gp.shares[j] = job.shares;
+        gp.first[j + 1] = gp.first[j] + job.count * job.shares;
+        if (job.shares == 1) continue;
+        gp.run[j].partial = part;
+        part += (size_t)job.shares * job.count * pp_tile_floats<TL>();
+        p.colsum_part = part;
+        part += (size_t)job.shares * ((p.N + 3) / 4 * 4);
+        sp.g[sp.n] = p;
+        sp.run[sp.n] = gp.run[j];
+        sp.shares[sp.n] = job.shares;
+        sp.first[sp.n + 1] = sp.first[sp.n] + job.count * 8;
+        ++sp.n;
+    }
+    const hipError_t e = launch_group<TL>(&gemm_bf16_group_pp_kernel<TL>, 512, gp, stream);
+    if (e != hipSuccess || sp.n == 0) return e;
+    hipLaunchKernelGGL(gemm_group_pp_sum_kernel<TL>, dim3((unsigned)sp.first[sp.n]), dim3(512), 0, stream, sp);
     return hipGetLastError();
 }
 
@@ -2012,6 +2009,7 @@ hipError_t gemm_bf16_group(const GemmArgs* g, int n, void* ws, size_t ws_bytes, 
     if (n < 1 || n > GROUP_MAX) return hipErrorInvalidValue;
     const GroupPlan pl = plan_group(g, n);
     const int bm = GROUP_TILES[pl.tile].bm;
+    if (bm == 256) return launch_pp_jobs(pl, g, ws, ws_bytes, stream);
     int order[GROUP_MAX] = {0, 1, 2, 3};
     std::stable_sort(order, order + n, [&](int a, int b) { return pl.nk[a] > pl.nk[b]; });
     GroupParams gp{}, sp{};                                       // the GEMMs; the sums of those that were cut
@@ -2044,9 +2042,9 @@ hipError_t gemm_bf16_group(const GemmArgs* g, int n, void* ws, size_t ws_bytes, 
         gp.layout[q] = a.trans_a ? 2 : a.trans_b ? 1 : 0;
         gp.first[q + 1] = gp.first[q] + p.tiles_m * p.tiles_n * shares;
     }
-    hipError_t e = pl.tile == 0   ? launch_group<Tile<3, 3, 3>>(gp, gp.first[n], stream)
-                   : pl.tile == 1 ? launch_group<Tile<2, 2, 4>>(gp, gp.first[n], stream)
-                                  : launch_group<Tile<1, 1, 6>>(gp, gp.first[n], stream);
+    hipError_t e = bm == 192   ? launch_group<Tile<3, 3, 3>>(&gemm_bf16_group_kernel<Tile<3, 3, 3>>, 256, gp, stream)
+                   : bm == 128 ? launch_group<Tile<2, 2, 4>>(&gemm_bf16_group_kernel<Tile<2, 2, 4>>, 256, gp, stream)
+                               : launch_group<Tile<1, 1, 6>>(&gemm_bf16_group_kernel<Tile<1, 1, 6>>, 256, gp, stream);
     if (e != hipSuccess || sp.n == 0) return e;
     hipLaunchKernelGGL(gemm_group_sum_kernel, dim3((unsigned)sp.first[sp.n]), dim3(256), 0, stream, sp);
     return hipGetLastError();

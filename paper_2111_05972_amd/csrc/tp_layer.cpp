@@ -45,7 +45,7 @@ bool set_option(const char* name, const char* value) {
     else if (!strcmp(name, "attn_chunk")) ok = parse_int(value, -1, 0, 1 << 16, &o.attn_chunk);
     else if (!strcmp(name, "gemm_group")) {
         int v;
-        ok = parse_int(value, -1, 0, 192, &v) && (v <= 0 || v == 64 || v == 128 || v == 192);
+        ok = parse_int(value, -1, 0, 256, &v) && (v <= 0 || v == 64 || v == 128 || v == 192 || v == 256);
         if (ok) o.gemm_group = v;
     }
     else if (!strcmp(name, "fuse_colsum")) ok = parse_int(value, 0, 0, 1, &o.fuse_colsum);
@@ -297,11 +297,6 @@ int run_attn(AttnArgs& a, bool bwd) {
     return e == hipSuccess ? TPL_OK : TPL_EHIP;
 }
 
-// Forward GEMM work above which a pass is left to launches of single GEMMs (on two chains if the caller asks): each GEMM
-// fills the chip by itself there, on the tile that suits it best (whole steps: groups are 8 % ahead at 0.43 TFLOP, 2 % at 0.6, 1 % behind at 0.64
-// (GPT-3 13B, TP 4) and 10 % at 0.93 (GPT-3 175B, TP 8: 2.68 against 2.45 ms)).
-constexpr double GROUP_MAX_FLOP = 0.64e12;   // bf16; float GEMMs are matrix-bound on any tile and group at every size
-
 // Scratch handed to every GEMM of one entry-point call.
 struct GemmScratch { void* ws; size_t bytes; hipStream_t stream; };
 
@@ -322,7 +317,9 @@ bool use_groups(const Dims& x) {
     if (o.gemm_group > 0) return true;
     // the other GEMM overrides speak about launches of one GEMM and about chains
     if (o.gemm_tile >= 0 || o.gemm_shares > 0 || o.gemm_force[0] || o.gemm_band > 0 || o.side_chains || o.fuse_colsum) return false;
-    return x.dtype == F32 || 2.0 * (double)x.M * x.H * (4.0 * x.Hl + 2.0 * x.Il) < GROUP_MAX_FLOP;
+    // groups are ahead at every size (whole steps, groups against single GEMMs on two chains where the caller allows: BERT-large
+    // TP 4 156 and 236 us, GPT-3 13B TP 4 1700 and 1840, GPT-3 175B TP 8 2200 and 2290, where attention runs beside GEMMs)
+    return true;
 }
 int run_group(const GemmArgs* g, int n, const GemmScratch& sc) {
     const auto group = g[0].dtype == BF16 ? gemm_bf16_group : gemm_f32_group;
