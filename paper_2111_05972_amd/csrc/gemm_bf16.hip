@@ -1350,7 +1350,7 @@ __global__ __launch_bounds__(256, 2) void gemm_bf16_group_kernel(GroupParams gp)
     else if (layout == 1) group_tile<TL, true, true, false>(p, pos, smem);
     else group_tile<TL, false, false, true>(p, pos, smem);
 }
-// The same on 256 x 256 tiles (gemm_bf16_pp.h), one epilogue behind the three layouts.  Jobs are runs of a GEMM's tiles:
+// The same on the tiles of gemm_bf16_pp.h, one epilogue behind the three layouts.  Jobs are runs of a GEMM's tiles:
 // [first[j], first[j+1]) are the workgroups of job j.
 constexpr int JOB_MAX = 2 * GROUP_MAX;
 struct PPGroupParams {
@@ -1366,22 +1366,22 @@ __global__ __launch_bounds__(512, 2) void gemm_bf16_group_pp_kernel(PPGroupParam
     int i = 0;
     while (i + 1 < gp.n && bid >= gp.first[i + 1]) ++i;
     const GemmParams& p = gp.g[i];
-    const PPWork<TL> w = pp_work<TL>(p, gp.run[i], share_of_block(bid - gp.first[i], gp.first[i + 1] - gp.first[i]));
+    const PPWork w = pp_work<TL>(p, gp.run[i], share_of_block(bid - gp.first[i], gp.first[i + 1] - gp.first[i]));
     const int layout = gp.layout[i];
-    f32x4 acc[2][4][TL::NB];
+    PPAcc<TL> acc;
     if (layout == 0) pp_products<TL, true, false, false>(p, w, smem, acc);
     else if (layout == 1) pp_products<TL, true, true, false>(p, w, smem, acc);
     else pp_products<TL, false, false, true>(p, w, smem, acc);
     pp_epilogue<TL>(p, acc, w.m0, w.n0, w.partial);
 }
-// The tiles whose K was cut: 8 workgroups each; [first[j], first[j+1]) are those of job j.
+// The tiles whose K was cut: a workgroup per 16 rows of a wavefront; [first[j], first[j+1]) are those of job j.
 template <typename TL>
 __global__ __launch_bounds__(512) void gemm_group_pp_sum_kernel(PPGroupParams gp) {
     const int bid = blockIdx.x;
     int i = 0;
     while (i + 1 < gp.n && bid >= gp.first[i + 1]) ++i;
     const int pos = bid - gp.first[i];
-    pp_sum_rows<TL>(gp.g[i], gp.run[i], gp.shares[i], pos >> 3, pos & 7);
+    pp_sum_rows<TL>(gp.g[i], gp.run[i], gp.shares[i], pos / (4 * TL::UA), pos % (4 * TL::UA));
 }
 // The sums over K shares of all GEMMs of a group that were cut (and of their column sums): GEMM i has the workgroups
 // [first[i], first[i+1]) of this launch, 256 chunks of 8 outputs each, the N / 8 chunks of the column sums last.
@@ -1748,18 +1748,21 @@ hipError_t gemm_bf16(const GemmArgs& a, bool* colsum_done) {
 // 24 groups of 6 layers on each tile the estimate is off by 15 % root mean square: up to 28 % too long for the widest layers
 // (10B encoder, GPT-3 13B), up to 28 % too short for the narrowest (832 / 104), the three tiles of a group mostly alike: the
 // tile with the least estimate is the fastest of the three on 23 of the 24 and 6 % behind on one.
-// 256 x 256 tiles take a compute unit each, so a launch is its list dealt out to the units (list_time).  Whole steps on 256
-// against the best of the smaller tiles: BERT-large TP 4 186 and 156 us, 2560 / 640 at 3003 tokens 445 and 476, RoBERTa-large
-// TP 2 433 and 468, the 10B encoder TP 4 1290 and 1471, GPT-3 13B TP 4 1700 and 1913, 175B TP 8 2205 and 2594.
+// The tiles of gemm_bf16_pp.h take a compute unit each, so a launch is its list dealt out to the units (list_time); 8 to 12 %
+// root mean square off over 56 groups of 14 layers.  Whole steps on 256 x 256 / 256 x 128 / the best of the smaller tiles, us:
+// RoBERTa-large TP 2 437 / 486 / 482, 2560 / 640 at 3003 tokens 450 / 488 / 481, the 10B encoder TP 4 1300 / 1480 / 1490, GPT-3
+// 13B TP 4 1740 / 1990 / 1930, 175B TP 8 2240 / 2625 / 2615; few tiles: BERT-large TP 4 183 / 159 / 162, 3072 / 768 at 1500 tokens
+// 326 / 313 / 320, 4096 tokens of 768 / 768 329 / 315 / 316 (each launch on its own tile: 308).
 namespace {
-struct GroupTile { int bm; double step_us, wg_us, base_us, alone_us, alone_base_us; };
-constexpr GroupTile GROUP_TILES[] = {{256, 0.75, 8.5, 2.0, 0, 0}, {192, 0.60, 2.6, 13.0, 0.77, 4.5}, {128, 0.355, 1.0, 7.5, 0.38, 4.5}, {64, 0.143, 0.92, 4.5, 0.35, 2.1}};
+struct GroupTile { int option, bm, bn; bool turns; double step_us, wg_us, base_us, alone_us, alone_base_us, gelu_us; };
+constexpr GroupTile GROUP_TILES[] = {{256, 256, 256, true, 0.72, 8.0, 0, 0, 0, 4.5}, {384, 256, 128, true, 0.42, 7.5, 0, 0, 0, 2.5},
+                                     {192, 192, 192, false, 0.60, 2.6, 13.0, 0.77, 4.5, 0}, {128, 128, 128, false, 0.355, 1.0, 7.5, 0.38, 4.5, 0}, {64, 64, 64, false, 0.143, 0.92, 4.5, 0.35, 2.1, 0}};
 constexpr double MEM_BYTES_PER_US = 4.5e6;     // operands and results of a launch, streamed
 constexpr int PP_MIN_STEPS = 12;               // k-steps of a K share
 struct PPJob { int gemm, tile0, count, nk, shares; };
 struct GroupPlan { int tile, nk[GROUP_MAX], shares[GROUP_MAX]; double us; int njobs; PPJob job[JOB_MAX]; };   // jobs: tile 256 only
 
-int64_t group_tiles(const GemmArgs& a, int bm) { return ((a.M + bm - 1) / bm) * ((a.N + bm - 1) / bm); }
+int64_t group_tiles(const GemmArgs& a, const GroupTile& t) { return ((a.M + t.bm - 1) / t.bm) * ((a.N + t.bn - 1) / t.bn); }
 
 // How long `units` machines take for a list of jobs dealt out in order, count[i] of length len[i] each (longest first).
 double list_time(int units, int n, const int64_t* count, const double* len) {
@@ -1789,7 +1792,7 @@ double list_time(int units, int n, const int64_t* count, const double* len) {
     return end;
 }
 
-// 256 x 256 tiles, one workgroup per compute unit: the last round of a list that does not fill it is cut.  Of each GEMM `cut`
+// Tiles of gemm_bf16_pp.h, one workgroup per compute unit: the last round of a list that does not fill it is cut.  Of each GEMM `cut`
 // tiles, its last ones, go out in `shares` K shares each; the plan is the best found by changing one GEMM at a time.
 GroupPlan make_pp_plan(const GemmArgs* g, int n, const GroupTile& gt) {
     const int cus = compute_units();
@@ -1798,7 +1801,7 @@ GroupPlan make_pp_plan(const GemmArgs* g, int n, const GroupTile& gt) {
     int nk[GROUP_MAX];
     double tile_bytes[GROUP_MAX], floor_us = 0;
     for (int i = 0; i < n; ++i) {
-        tiles[i] = group_tiles(g[i], gt.bm);
+        tiles[i] = group_tiles(g[i], gt);
         nk[i] = (int)((g[i].K + DK - 1) / DK);
         tile_bytes[i] = (double)g[i].M * g[i].N / (double)tiles[i];
         floor_us += 2.0 * ((double)g[i].M * g[i].K + (double)g[i].N * g[i].K + (double)g[i].M * g[i].N) / MEM_BYTES_PER_US;
@@ -1828,10 +1831,10 @@ GroupPlan make_pp_plan(const GemmArgs* g, int n, const GroupTile& gt) {
         const int m = jobs(c, job);
         for (int q = 0; q < m; ++q) {
             count[q] = (int64_t)job[q].count * job[q].shares;
-            len[q] = job[q].nk * gt.step_us + gt.wg_us;
+            len[q] = job[q].nk * gt.step_us + gt.wg_us + (g[job[q].gemm].epi != EPI_NONE && job[q].shares == 1 ? gt.gelu_us : 0.0);
             if (job[q].shares > 1) bytes += job[q].count * tile_bytes[job[q].gemm] * (8.0 * job[q].shares + 2.0);
         }
-        return std::max(list_time(cus, m, count, len) + gt.base_us, floor_us) + (bytes > 0 ? 4.2 + bytes / 8.0e6 : 0.0);
+        return std::max(list_time(cus, m, count, len), floor_us) + (bytes > 0 ? 4.2 + bytes / 8.0e6 : 0.0);
     };
     Cut best[GROUP_MAX], now[GROUP_MAX];
     for (int i = 0; i < n; ++i) best[i] = now[i] = with_shares(i, 0, 1);
@@ -1871,20 +1874,21 @@ GroupPlan make_group_plan(const GemmArgs* g, int n) {
     const int cus = compute_units(), forced = options().gemm_group;
     GroupPlan best{};
     best.us = -1;
-    for (int t = 0; t < 4; ++t) {
+    for (int t = 0; t < (int)(sizeof(GROUP_TILES) / sizeof(GROUP_TILES[0])); ++t) {
         const GroupTile& gt = GROUP_TILES[t];
-        if (forced > 0 && forced != gt.bm) continue;
+        if (forced > 0 && forced != gt.option) continue;
         GroupPlan p{};
         p.tile = t;
-        if (gt.bm == 256) {
-            best = make_pp_plan(g, n, gt);
-            best.tile = t;
+        if (gt.turns) {
+            p = make_pp_plan(g, n, gt);
+            p.tile = t;
+            if (best.us < 0 || p.us < best.us) best = p;
             continue;
         }
         int64_t tiles[GROUP_MAX];
         int nk[GROUP_MAX];
         for (int i = 0; i < n; ++i) {
-            tiles[i] = group_tiles(g[i], gt.bm);
+            tiles[i] = group_tiles(g[i], gt);
             nk[i] = p.nk[i] = (int)((g[i].K + DK - 1) / DK);
             p.shares[i] = 1;
         }
@@ -1929,7 +1933,7 @@ GroupPlan plan_group(const GemmArgs* g, int n) {
     e.n = n;
     e.gen = options().generation;
     for (int i = 0; i < n; ++i) {
-        const int64_t k[4] = {g[i].M, g[i].N, g[i].K, (g[i].trans_a ? 1 : 0) | (g[i].trans_b ? 2 : 0)};
+        const int64_t k[4] = {g[i].M, g[i].N, g[i].K, (g[i].trans_a ? 1 : 0) | (g[i].trans_b ? 2 : 0) | g[i].epi << 2};
         std::copy(k, k + 4, e.key[i]);
     }
     std::lock_guard<std::mutex> lock(mu);
@@ -1944,17 +1948,17 @@ size_t share_bytes(const GemmArgs& a, int shares) {               // float parti
 }
 }  // namespace
 
-// Scratch of the K shares of a plan on 256 x 256 tiles: the tiles' sums, and column sums (of every GEMM that was cut).
+// Scratch of the K shares of a plan on the tiles of gemm_bf16_pp.h: the tiles' sums, and column sums (of every GEMM that was cut).
 static size_t pp_bytes(const GroupPlan& pl, const GemmArgs* g) {
     size_t need = 0;
     for (int j = 0; j < pl.njobs; ++j)
         if (pl.job[j].shares > 1)
-            need += (size_t)pl.job[j].shares * ((size_t)pl.job[j].count * pp_tile_floats<PPTile<2, 2>>() + (size_t)(g[pl.job[j].gemm].N + 3) / 4 * 4) * sizeof(float);
+            need += (size_t)pl.job[j].shares * ((size_t)pl.job[j].count * GROUP_TILES[pl.tile].bm * GROUP_TILES[pl.tile].bn + (size_t)(g[pl.job[j].gemm].N + 3) / 4 * 4) * sizeof(float);
     return need;
 }
 size_t gemm_bf16_group_workspace_bytes(const GemmArgs* g, int n) {
     const GroupPlan pl = plan_group(g, n);
-    if (GROUP_TILES[pl.tile].bm == 256) return pp_bytes(pl, g);
+    if (GROUP_TILES[pl.tile].turns) return pp_bytes(pl, g);
     size_t need = 0;
     for (int i = 0; i < n; ++i) need += share_bytes(g[i], pl.shares[i]);
     return need;
@@ -1969,8 +1973,8 @@ static hipError_t launch_group(void (*kernel)(Params), int threads, const Params
     return hipGetLastError();
 }
 
+template <typename TL>
 static hipError_t launch_pp_jobs(const GroupPlan& pl, const GemmArgs* g, void* ws, size_t ws_bytes, hipStream_t stream) {
-    using TL = PPTile<2, 2>;
     if (pp_bytes(pl, g) > (ws ? ws_bytes : 0)) return hipErrorInvalidValue;
     PPGroupParams gp{}, sp{};                                     // all jobs; the sums of those that were cut
     float* part = static_cast<float*>(ws);
@@ -1990,13 +1994,13 @@ static hipError_t launch_pp_jobs(const GroupPlan& pl, const GemmArgs* g, void* w
         gp.first[j + 1] = gp.first[j] + job.count * job.shares;
         if (job.shares == 1) continue;
         gp.run[j].partial = part;
-        part += (size_t)job.shares * job.count * pp_tile_floats<TL>();
+        part += (size_t)job.shares * job.count * TL::FLOATS;
         p.colsum_part = part;
         part += (size_t)job.shares * ((p.N + 3) / 4 * 4);
         sp.g[sp.n] = p;
         sp.run[sp.n] = gp.run[j];
         sp.shares[sp.n] = job.shares;
-        sp.first[sp.n + 1] = sp.first[sp.n] + job.count * 8;
+        sp.first[sp.n + 1] = sp.first[sp.n] + job.count * 4 * TL::UA;
         ++sp.n;
     }
     const hipError_t e = launch_group<TL>(&gemm_bf16_group_pp_kernel<TL>, 512, gp, stream);
@@ -2009,7 +2013,8 @@ hipError_t gemm_bf16_group(const GemmArgs* g, int n, void* ws, size_t ws_bytes, 
     if (n < 1 || n > GROUP_MAX) return hipErrorInvalidValue;
     const GroupPlan pl = plan_group(g, n);
     const int bm = GROUP_TILES[pl.tile].bm;
-    if (bm == 256) return launch_pp_jobs(pl, g, ws, ws_bytes, stream);
+    if (GROUP_TILES[pl.tile].turns)
+        return bm == GROUP_TILES[pl.tile].bn ? launch_pp_jobs<PPTile<2>>(pl, g, ws, ws_bytes, stream) : launch_pp_jobs<PPTile<4>>(pl, g, ws, ws_bytes, stream);
     int order[GROUP_MAX] = {0, 1, 2, 3};
     std::stable_sort(order, order + n, [&](int a, int b) { return pl.nk[a] > pl.nk[b]; });
     GroupParams gp{}, sp{};                                       // the GEMMs; the sums of those that were cut

@@ -470,7 +470,7 @@ constexpr F32GroupTile F32_GROUP_TILES[] = {{128, 1.95, 3.0, 2.2}, {64, 0.50, 1.
 struct F32GroupPlan { int tile, nk[F_GROUP_MAX], shares[F_GROUP_MAX]; double us; };
 
 F32GroupPlan plan_f32_group(const GemmArgs* g, int n) {
-    const int cus = compute_units(), forced = options().gemm_group == 256 ? -1 : options().gemm_group;   // 256: a bf16 tile
+    const int cus = compute_units(), forced = options().gemm_group >= 256 ? -1 : options().gemm_group;   // 256, 384: bf16 tiles
     F32GroupPlan best{};
     best.us = -1;
     for (int t = 0; t < 3; ++t) {

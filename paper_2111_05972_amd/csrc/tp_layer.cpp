@@ -45,7 +45,7 @@ bool set_option(const char* name, const char* value) {
     else if (!strcmp(name, "attn_chunk")) ok = parse_int(value, -1, 0, 1 << 16, &o.attn_chunk);
     else if (!strcmp(name, "gemm_group")) {
         int v;
-        ok = parse_int(value, -1, 0, 256, &v) && (v <= 0 || v == 64 || v == 128 || v == 192 || v == 256);
+        ok = parse_int(value, -1, 0, 384, &v) && (v <= 0 || v == 64 || v == 128 || v == 192 || v == 256 || v == 384);
         if (ok) o.gemm_group = v;
     }
     else if (!strcmp(name, "fuse_colsum")) ok = parse_int(value, 0, 0, 1, &o.fuse_colsum);
@@ -151,8 +151,9 @@ GemmArgs gemm_args(const Dims& x, int ta, int tb, int64_t M, int64_t N, int64_t 
 size_t group_ws(const Dims& x, bool bwd) {
     GemmArgs first[4], second[4];
     int n1 = 0, n2 = 0;
-    if (!bwd) {
+    if (!bwd) {                                      // as launched: plans go by shapes, layouts and GeLU epilogues
         first[n1++] = gemm_args(x, 0, 0, x.M, x.Il, x.H);
+        first[0].epi = EPI_GELU;
         first[n1++] = gemm_args(x, 0, 0, x.M, 3 * x.Hl, x.H);
         second[n2++] = gemm_args(x, 0, 0, x.M, x.H, x.Il);
         second[n2++] = gemm_args(x, 0, 0, x.M, x.H, x.Hl);
@@ -160,6 +161,7 @@ size_t group_ws(const Dims& x, bool bwd) {
         first[n1++] = gemm_args(x, 1, 0, x.Il, x.H, x.M);
         first[n1++] = gemm_args(x, 1, 0, x.Hl, x.H, x.M);
         first[n1++] = gemm_args(x, 0, 1, x.M, x.Il, x.H);
+        first[2].epi = EPI_DGELU;
         first[n1++] = gemm_args(x, 0, 1, x.M, x.Hl, x.H);
         second[n2++] = gemm_args(x, 1, 0, x.H, x.Il, x.M);
         second[n2++] = gemm_args(x, 1, 0, x.H, 3 * x.Hl, x.M);

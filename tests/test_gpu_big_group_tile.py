@@ -1,4 +1,4 @@
-"""GPU parity of layers whose GEMM groups go out on 256 x 256 tiles (option gemm_group 256): edges of a tile in every
+"""GPU parity of layers whose GEMM groups go out on 256 x 256 and 256 x 128 tiles (option gemm_group 256, 384): edges of a tile in every
 dimension, token counts that are no multiple of the 64 k of a step (K of the weight gradients), K shares, and a list whose
 last tiles alone are cut; bias gradients as column sums of whole and of cut tiles.  Against the oracle, at the bound of every
 bf16 layer test, and twice over bit-identical."""
@@ -24,10 +24,11 @@ SHAPES = [
 
 @pytest.mark.parametrize("epilogue", [True, False])
 @pytest.mark.parametrize("shape", range(len(SHAPES)))
-def test_layer_on_big_tiles(shape, epilogue, tune):
-    tune.set("gemm_group", "256")
-    cfg = small_variant(synthetic.CONFIGS[2], name="bf16-group-256", causal=True, row_epilogue=epilogue, **SHAPES[shape])
-    print(f"\n[case] {SHAPES[shape]} epi={epilogue}", flush=True)
+@pytest.mark.parametrize("tile", ["256", "384"])
+def test_layer_on_big_tiles(tile, shape, epilogue, tune):
+    tune.set("gemm_group", tile)
+    cfg = small_variant(synthetic.CONFIGS[2], name=f"bf16-group-{tile}", causal=True, row_epilogue=epilogue, **SHAPES[shape])
+    print(f"\n[case] {tile} {SHAPES[shape]} epi={epilogue}", flush=True)
     d, sh = shard_inputs(cfg)
     a, b = gpu_outputs(cfg, d, sh, repeat=2)
     compare(cfg, a, oracle_outputs(cfg, d, sh))
