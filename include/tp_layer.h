@@ -261,6 +261,19 @@ int tp_layer_gemm(int dtype, int trans_a, int trans_b, int64_t M, int64_t N, int
                   const void* bias, const void* resid, void* aux, int epi,
                   void* ws, size_t ws_bytes, void* hip_stream);
 
+/* Up to four such GEMMs that do not depend on each other (no output is read or written by another) on one stream: in one launch
+ * where the kernels can, one after another otherwise.  ws: tp_layer_gemm_group_workspace_bytes of the same items (which
+ * looks at shapes, layouts and epilogues only). */
+typedef struct {
+    int32_t trans_a, trans_b;
+    int64_t M, N, K;
+    const void* A; const void* B; void* C;
+    const void* bias; const void* resid; void* aux;
+    int32_t epi;
+} tp_layer_gemm_item;
+size_t tp_layer_gemm_group_workspace_bytes(int dtype, int n, const tp_layer_gemm_item* items);
+int tp_layer_gemm_group(int dtype, int n, const tp_layer_gemm_item* items, void* ws, size_t ws_bytes, void* hip_stream);
+
 /* Softmax attention over local heads, exposed for per-kernel tests and timing.
  * qkv [B*S, 3*nl*dh] (columns q|k|v, head, dh) -> o [B*S, nl*dh], lse [B, nl, S] float.
  * ws (device, 16-byte aligned, caller-owned, contents undefined afterwards) may be NULL.  With a

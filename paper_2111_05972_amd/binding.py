@@ -36,6 +36,12 @@ class TpLayerSavedLayout(ctypes.Structure):
     _fields_ = [(n, ctypes.c_size_t) for n in ("qkv", "o", "lse", "u", "g", "total")]
 
 
+class TpLayerGemmItem(ctypes.Structure):
+    _fields_ = ([("trans_a", ctypes.c_int32), ("trans_b", ctypes.c_int32), ("M", ctypes.c_int64), ("N", ctypes.c_int64),
+                 ("K", ctypes.c_int64)] + [(n, _vp) for n in ("A", "B", "C", "bias", "resid", "aux")] +
+                [("epi", ctypes.c_int32)])
+
+
 class TpLayerError(RuntimeError):
     def __init__(self, status, what):
         self.status = status
@@ -71,6 +77,8 @@ def load_library():
         "tp_layer_bwd": (ci, [D, P, _vp, _vp, _vp, _vp, _vp, G, _vp, _vp, _vp, sz, _vp]),
         "tp_layer_gemm_workspace_bytes": (sz, [ci, i64, i64, i64]),
         "tp_layer_gemm": (ci, [ci, ci, ci, i64, i64, i64, _vp, _vp, _vp, _vp, _vp, _vp, ci, _vp, sz, _vp]),
+        "tp_layer_gemm_group_workspace_bytes": (sz, [ci, ci, ctypes.POINTER(TpLayerGemmItem)]),
+        "tp_layer_gemm_group": (ci, [ci, ci, ctypes.POINTER(TpLayerGemmItem), _vp, sz, _vp]),
         "tp_layer_attn_workspace_bytes": (sz, [ci, ci, ci, ci, ci, ci, ci]),
         "tp_layer_attn_fwd": (ci, [ci, ci, ci, ci, ci, ci, _vp, _vp, _vp, _vp, sz, _vp]),
         "tp_layer_attn_bwd": (ci, [ci, ci, ci, ci, ci, ci, _vp, _vp, _vp, _vp, _vp, _vp, _vp, sz, _vp]),
@@ -327,6 +335,28 @@ def tp_layer_gemm(dtype, trans_a, trans_b, M, N, K, A, B, C, bias=None, resid=No
         _stream(stream))
     if check and rc != TPL_OK:
         raise TpLayerError(rc, "tp_layer_gemm")
+    return rc
+
+
+def _gemm_items(items):
+    """items: (trans_a, trans_b, M, N, K, A, B, C[, aux, epi]) each."""
+    arr = (TpLayerGemmItem * len(items))()
+    for t, (ta, tb, M, N, K, A, Bm, C, *rest) in zip(arr, items):
+        aux, epi = rest if rest else (None, TPL_EPI_NONE)
+        t.trans_a, t.trans_b, t.M, t.N, t.K, t.epi = int(bool(ta)), int(bool(tb)), M, N, K, epi
+        t.A, t.B, t.C, t.aux = _ptr(A), _ptr(Bm), _ptr(C), _ptr(aux)
+    return arr
+
+
+def tp_layer_gemm_group_workspace_bytes(dtype, items):
+    return load_library().tp_layer_gemm_group_workspace_bytes(dtype, len(items), _gemm_items(items))
+
+
+def tp_layer_gemm_group(dtype, items, ws=None, ws_bytes=None, stream=None, check=True):
+    rc = load_library().tp_layer_gemm_group(dtype, len(items), _gemm_items(items), _ptr(ws),
+                                            (_nbytes(ws) or 0) if ws_bytes is None else ws_bytes, _stream(stream))
+    if check and rc != TPL_OK:
+        raise TpLayerError(rc, "tp_layer_gemm_group")
     return rc
 
 

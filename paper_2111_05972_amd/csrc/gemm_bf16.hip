@@ -1581,7 +1581,7 @@ int compute_units() {
 
 constexpr int NVARIANTS = 8;
 constexpr int MAX_SHARES = 16;
-struct Plan { int variant, shares, nk_share; };
+struct Plan { int variant, shares, nk_share; double us; };
 
 // Splitting K.  A GEMM with few output tiles and a long K (the data gradient of a narrow projection: N = 1536,
 // K = 12288 ... 49152) leaves compute units idle or gives each a very long serial K walk.  Its K range is then
@@ -1621,7 +1621,7 @@ static Plan make_plan(int64_t M, int64_t N, int64_t K, bool a_kmaj, bool b_kmaj)
     if (forced_shape_v >= 0) forced_v = forced_shape_v;
     const int cus = compute_units();
     const int nk = (int)((K + DK - 1) / DK);
-    Plan best{0, 1, nk};
+    Plan best{0, 1, nk, 0.0};
     double best_c = -1;
     for (int v = 0; v < NVARIANTS; ++v) {
         if (forced_v >= 0 && v != forced_v) continue;
@@ -1655,7 +1655,7 @@ static Plan make_plan(int64_t M, int64_t N, int64_t K, bool a_kmaj, bool b_kmaj)
             // measured inside the whole step, the out-projection data gradient is fastest with 3 shares (192
             // workgroups), 0.8 % of the step ahead of 4 (256 workgroups)
             if (shares > 1 && tiles * shares * 4 > (int64_t)cus * 3) c *= 1.10;
-            if (best_c < 0 || c < best_c) { best = Plan{v, shares, per}; best_c = c; }
+            if (best_c < 0 || c < best_c) { best = Plan{v, shares, per, c}; best_c = c; }
         }
     }
     return best;
@@ -1682,15 +1682,6 @@ static Plan plan_for(int64_t M, int64_t N, int64_t K, bool a_kmaj, bool b_kmaj) 
     return pl;
 }
 
-size_t gemm_bf16_workspace_bytes(int64_t M, int64_t N, int64_t K) {
-    size_t need = 0;
-    for (int layout = 0; layout < 4; ++layout) {
-        const Plan pl = plan_for(M, N, K, (layout & 1) != 0, (layout & 2) != 0);
-        if (pl.shares > 1) need = std::max(need, (size_t)pl.shares * (size_t)M * (size_t)N * sizeof(float));
-    }
-    return need;
-}
-
 static GemmParams gemm_params(const GemmArgs& a) {
     GemmParams p{};
     p.A = (const bf16_t*)a.A; p.B = (const bf16_t*)a.B; p.C = (bf16_t*)a.C;
@@ -1704,41 +1695,6 @@ static GemmParams gemm_params(const GemmArgs& a) {
     p.band = 8;
     p.nk_total = (int)((a.K + DK - 1) / DK);
     return p;
-}
-
-hipError_t gemm_bf16(const GemmArgs& a, bool* colsum_done) {
-    if (colsum_done) *colsum_done = false;
-    GemmParams p = gemm_params(a);
-    const Plan pl = plan_for(a.M, a.N, a.K, !a.trans_a, a.trans_b != 0);
-    p.nk = pl.nk_share;
-    // the column sums of B ride along only on request (option fuse_colsum), in the weight-gradient kernel (both operands
-    // MN-major) with K unsplit
-    p.colsum = (a.colsum_b && options().fuse_colsum && pl.variant == 7 && pl.shares == 1 && a.trans_a && !a.trans_b)
-                   ? (bf16_t*)a.colsum_b : nullptr;
-    if (colsum_done) *colsum_done = p.colsum != nullptr;
-    if (pl.shares > 1) {
-        if (a.ws == nullptr || a.ws_bytes < (size_t)pl.shares * (size_t)a.M * (size_t)a.N * sizeof(float))
-            return hipErrorInvalidValue;
-        p.partial = (float*)a.ws;
-    }
-    hipError_t e;
-    switch (pl.variant) {
-        case 4: e = launch_spec_layout<SpecTile<4, 3>>(p, a, pl.shares); break;   // 256 x 192, fetch and math wavefronts
-        case 1: e = launch_layout<Tile<4, 3, 4>>(p, a, pl.shares); break;    // 256 x 192
-        case 2: e = launch_layout<Tile<2, 2, 4>>(p, a, pl.shares); break;    // 128 x 128, two workgroups per CU
-        case 3: e = launch_layout<Tile<3, 3, 3>>(p, a, pl.shares); break;    // 192 x 192, two workgroups per CU
-        case 5: e = launch_w8_layout<Tile8<2, 3, 5>>(p, a, pl.shares); break;      // 256 x 192, 8 wavefronts, 16x16x32
-        case 7: e = launch_x16s_layout<Tile<3, 3, 3>>(p, a, pl.shares); break;     // 192 x 192, 2 workgroups/CU, 16x16x32
-        case 6:                                                                    // 256 x 192, fetch + math, 16x16x32
-            e = a.trans_b ? launch_spec16<SpecTile<4, 3>, true>(p, a, pl.shares)
-                          : launch_spec16<SpecTile<4, 3>, false>(p, a, pl.shares);
-            break;
-        default: e = launch_layout<Tile<4, 4, 4>>(p, a, pl.shares); break;   // 256 x 256
-    }
-    if (e != hipSuccess || pl.shares == 1) return e;
-    const int64_t chunks = a.M * a.N / 8;
-    hipLaunchKernelGGL(gemm_sum_shares_kernel, dim3((unsigned)((chunks + 255) / 256)), dim3(256), 0, a.stream, p, pl.shares);
-    return hipGetLastError();
 }
 
 // ---- groups ------------------------------------------------------------------------------------------------------------
@@ -1853,7 +1809,7 @@ GroupPlan make_pp_plan(const GemmArgs* g, int n, const GroupTile& gt) {
             for (int want = 1; want <= MAX_SHARES && (want == 1 || nk[i] / want >= PP_MIN_STEPS); ++want) {
                 int64_t others = 0;
                 for (int q = 0; q < n; ++q) others += q == i ? tiles[q] : tiles[q] - base[q].cut;
-                for (int eighth = 0; eighth <= 8; ++eighth) {         // the tiles past whole rounds, or so many eighths
+                for (int eighth = n == 1 ? 8 : 0; eighth <= 8; ++eighth) {   // the tiles past whole rounds, or so many eighths; one GEMM: all
                     const int64_t cut = eighth ? (tiles[i] * eighth + 7) / 8 : std::min(tiles[i], others % cus);
                     std::copy(base, base + n, now);
                     now[i] = with_shares(i, cut, want);
@@ -1876,7 +1832,7 @@ GroupPlan make_group_plan(const GemmArgs* g, int n) {
     best.us = -1;
     for (int t = 0; t < (int)(sizeof(GROUP_TILES) / sizeof(GROUP_TILES[0])); ++t) {
         const GroupTile& gt = GROUP_TILES[t];
-        if (forced > 0 && forced != gt.option) continue;
+        if (n == 1 ? gt.option != 256 : forced > 0 && forced != gt.option) continue;   // one GEMM: see by_turns
         GroupPlan p{};
         p.tile = t;
         if (gt.turns) {
@@ -1948,17 +1904,18 @@ size_t share_bytes(const GemmArgs& a, int shares) {               // float parti
 }
 }  // namespace
 
-// Scratch of the K shares of a plan on the tiles of gemm_bf16_pp.h: the tiles' sums, and column sums (of every GEMM that was cut).
-static size_t pp_bytes(const GroupPlan& pl, const GemmArgs* g) {
+// Scratch of the K shares of a plan on the tiles of gemm_bf16_pp.h: the tiles' sums, and column sums of a group's weight gradients.
+static size_t pp_colsum_floats(const GemmArgs& a, int n) { return n > 1 && a.trans_a ? (size_t)(a.N + 3) / 4 * 4 : 0; }
+static size_t pp_bytes(const GroupPlan& pl, const GemmArgs* g, int n) {
     size_t need = 0;
     for (int j = 0; j < pl.njobs; ++j)
         if (pl.job[j].shares > 1)
-            need += (size_t)pl.job[j].shares * ((size_t)pl.job[j].count * GROUP_TILES[pl.tile].bm * GROUP_TILES[pl.tile].bn + (size_t)(g[pl.job[j].gemm].N + 3) / 4 * 4) * sizeof(float);
+            need += (size_t)pl.job[j].shares * ((size_t)pl.job[j].count * GROUP_TILES[pl.tile].bm * GROUP_TILES[pl.tile].bn + pp_colsum_floats(g[pl.job[j].gemm], n)) * sizeof(float);
     return need;
 }
 size_t gemm_bf16_group_workspace_bytes(const GemmArgs* g, int n) {
     const GroupPlan pl = plan_group(g, n);
-    if (GROUP_TILES[pl.tile].turns) return pp_bytes(pl, g);
+    if (GROUP_TILES[pl.tile].turns) return pp_bytes(pl, g, n);
     size_t need = 0;
     for (int i = 0; i < n; ++i) need += share_bytes(g[i], pl.shares[i]);
     return need;
@@ -1974,8 +1931,8 @@ static hipError_t launch_group(void (*kernel)(Params), int threads, const Params
 }
 
 template <typename TL>
-static hipError_t launch_pp_jobs(const GroupPlan& pl, const GemmArgs* g, void* ws, size_t ws_bytes, hipStream_t stream) {
-    if (pp_bytes(pl, g) > (ws ? ws_bytes : 0)) return hipErrorInvalidValue;
+static hipError_t launch_pp_jobs(const GroupPlan& pl, const GemmArgs* g, int n, void* ws, size_t ws_bytes, hipStream_t stream) {
+    if (pp_bytes(pl, g, n) > (ws ? ws_bytes : 0)) return hipErrorInvalidValue;
     PPGroupParams gp{}, sp{};                                     // all jobs; the sums of those that were cut
     float* part = static_cast<float*>(ws);
     gp.n = pl.njobs;
@@ -1996,7 +1953,7 @@ static hipError_t launch_pp_jobs(const GroupPlan& pl, const GemmArgs* g, void* w
         gp.run[j].partial = part;
         part += (size_t)job.shares * job.count * TL::FLOATS;
         p.colsum_part = part;
-        part += (size_t)job.shares * ((p.N + 3) / 4 * 4);
+        part += (size_t)job.shares * pp_colsum_floats(a, n);
         sp.g[sp.n] = p;
         sp.run[sp.n] = gp.run[j];
         sp.shares[sp.n] = job.shares;
@@ -2009,12 +1966,15 @@ static hipError_t launch_pp_jobs(const GroupPlan& pl, const GemmArgs* g, void* w
     return hipGetLastError();
 }
 
+static hipError_t launch_pp(const GroupPlan& pl, const GemmArgs* g, int n, void* ws, size_t ws_bytes, hipStream_t stream) {
+    return GROUP_TILES[pl.tile].bn == 256 ? launch_pp_jobs<PPTile<2>>(pl, g, n, ws, ws_bytes, stream) : launch_pp_jobs<PPTile<4>>(pl, g, n, ws, ws_bytes, stream);
+}
+
 hipError_t gemm_bf16_group(const GemmArgs* g, int n, void* ws, size_t ws_bytes, hipStream_t stream) {
     if (n < 1 || n > GROUP_MAX) return hipErrorInvalidValue;
     const GroupPlan pl = plan_group(g, n);
     const int bm = GROUP_TILES[pl.tile].bm;
-    if (GROUP_TILES[pl.tile].turns)
-        return bm == GROUP_TILES[pl.tile].bn ? launch_pp_jobs<PPTile<2>>(pl, g, ws, ws_bytes, stream) : launch_pp_jobs<PPTile<4>>(pl, g, ws, ws_bytes, stream);
+    if (GROUP_TILES[pl.tile].turns) return launch_pp(pl, g, n, ws, ws_bytes, stream);
     int order[GROUP_MAX] = {0, 1, 2, 3};
     std::stable_sort(order, order + n, [&](int a, int b) { return pl.nk[a] > pl.nk[b]; });
     GroupParams gp{}, sp{};                                       // the GEMMs; the sums of those that were cut
@@ -2052,6 +2012,73 @@ hipError_t gemm_bf16_group(const GemmArgs* g, int n, void* ws, size_t ws_bytes, 
                                : launch_group<Tile<1, 1, 6>>(&gemm_bf16_group_kernel<Tile<1, 1, 6>>, 256, gp, stream);
     if (e != hipSuccess || sp.n == 0) return e;
     hipLaunchKernelGGL(gemm_group_sum_kernel, dim3((unsigned)sp.first[sp.n]), dim3(256), 0, stream, sp);
+    return hipGetLastError();
+}
+
+// ---- one GEMM ----------------------------------------------------------------------------------------------------------
+// On the 256 x 256 tile of gemm_bf16_pp.h where there is enough of it that its estimate and that of make_plan, which is long for
+// short GEMMs, can be compared, and the tile's is less.  Measured over 55 GEMMs, us, kernel of make_plan and tile by turns: NN
+// 2048 x 15360 x 1280 87 and 82, 2048 x 49152 x 1536 286 and 261, 2048 x 12288 x 6144 240 and 230, NT 2048 x 1536 x 49152 344 and
+// 250, 2048 x 1536 x 12288 80 and 76, TN 1280 x 15360 x 2048 88 and 82; estimates of less than 60 us: 0.98 to 1.8 times as long, the
+// 256 x 128 tile 0.8 to 1.8.  Its kernels are built for the layouts of a layer (NN, NT, TN), and the overrides are about the others.
+static bool by_turns(int64_t M, int64_t N, int64_t K, bool trans_a, bool trans_b, GroupPlan* plan) {
+    const Options& o = options();
+    if ((trans_a && trans_b) || o.gemm_tile >= 0 || o.gemm_shares > 0 || o.gemm_force[0] || o.gemm_band > 0 || o.fuse_colsum) return false;
+    GemmArgs a{};
+    a.dtype = BF16; a.trans_a = trans_a; a.trans_b = trans_b; a.M = M; a.N = N; a.K = K; a.epi = EPI_NONE;
+    *plan = plan_group(&a, 1);
+    return plan->us >= 60.0 && plan->us < 0.95 * plan_for(M, N, K, !trans_a, trans_b).us;
+}
+size_t gemm_bf16_workspace_bytes(int64_t M, int64_t N, int64_t K) {
+    size_t need = 0;
+    for (int layout = 0; layout < 4; ++layout) {
+        const Plan pl = plan_for(M, N, K, (layout & 1) != 0, (layout & 2) != 0);
+        if (pl.shares > 1) need = std::max(need, (size_t)pl.shares * (size_t)M * (size_t)N * sizeof(float));
+        GroupPlan gp;
+        const GemmArgs a{};
+        if (by_turns(M, N, K, (layout & 1) == 0, (layout & 2) != 0, &gp)) need = std::max(need, pp_bytes(gp, &a, 1));
+    }
+    return need;
+}
+
+hipError_t gemm_bf16(const GemmArgs& a, bool* colsum_done) {
+    if (colsum_done) *colsum_done = false;
+    GroupPlan gp;
+    if (by_turns(a.M, a.N, a.K, a.trans_a != 0, a.trans_b != 0, &gp) && pp_bytes(gp, &a, 1) <= (a.ws ? a.ws_bytes : 0)) {
+        GemmArgs one = a;
+        one.colsum_b = nullptr;
+        return launch_pp(gp, &one, 1, a.ws, a.ws_bytes, a.stream);
+    }
+    GemmParams p = gemm_params(a);
+    const Plan pl = plan_for(a.M, a.N, a.K, !a.trans_a, a.trans_b != 0);
+    p.nk = pl.nk_share;
+    // the column sums of B ride along only on request (option fuse_colsum), in the weight-gradient kernel (both operands
+    // MN-major) with K unsplit
+    p.colsum = (a.colsum_b && options().fuse_colsum && pl.variant == 7 && pl.shares == 1 && a.trans_a && !a.trans_b)
+                   ? (bf16_t*)a.colsum_b : nullptr;
+    if (colsum_done) *colsum_done = p.colsum != nullptr;
+    if (pl.shares > 1) {
+        if (a.ws == nullptr || a.ws_bytes < (size_t)pl.shares * (size_t)a.M * (size_t)a.N * sizeof(float))
+            return hipErrorInvalidValue;
+        p.partial = (float*)a.ws;
+    }
+    hipError_t e;
+    switch (pl.variant) {
+        case 4: e = launch_spec_layout<SpecTile<4, 3>>(p, a, pl.shares); break;   // 256 x 192, fetch and math wavefronts
+        case 1: e = launch_layout<Tile<4, 3, 4>>(p, a, pl.shares); break;    // 256 x 192
+        case 2: e = launch_layout<Tile<2, 2, 4>>(p, a, pl.shares); break;    // 128 x 128, two workgroups per CU
+        case 3: e = launch_layout<Tile<3, 3, 3>>(p, a, pl.shares); break;    // 192 x 192, two workgroups per CU
+        case 5: e = launch_w8_layout<Tile8<2, 3, 5>>(p, a, pl.shares); break;      // 256 x 192, 8 wavefronts, 16x16x32
+        case 7: e = launch_x16s_layout<Tile<3, 3, 3>>(p, a, pl.shares); break;     // 192 x 192, 2 workgroups/CU, 16x16x32
+        case 6:                                                                    // 256 x 192, fetch + math, 16x16x32
+            e = a.trans_b ? launch_spec16<SpecTile<4, 3>, true>(p, a, pl.shares)
+                          : launch_spec16<SpecTile<4, 3>, false>(p, a, pl.shares);
+            break;
+        default: e = launch_layout<Tile<4, 4, 4>>(p, a, pl.shares); break;   // 256 x 256
+    }
+    if (e != hipSuccess || pl.shares == 1) return e;
+    const int64_t chunks = a.M * a.N / 8;
+    hipLaunchKernelGGL(gemm_sum_shares_kernel, dim3((unsigned)((chunks + 255) / 256)), dim3(256), 0, a.stream, p, pl.shares);
     return hipGetLastError();
 }
 

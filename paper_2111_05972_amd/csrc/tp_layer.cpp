@@ -772,6 +772,57 @@ int tp_layer_gemm(int dtype, int trans_a, int trans_b, int64_t M, int64_t N, int
     return run_gemm(g);
 }
 
+// GEMMs that do not depend on each other.  One launch where the group kernels take them all.
+static int group_items(int dtype, int n, const tp_layer_gemm_item* items, GemmArgs* g) {
+    if (dtype != TPL_F32 && dtype != TPL_BF16) return TPL_EINVAL;
+    if (n < 1 || n > 4 || !items) return TPL_EINVAL;
+    const int64_t q = dtype == TPL_BF16 ? 8 : 4;
+    for (int i = 0; i < n; ++i) {
+        const tp_layer_gemm_item& t = items[i];
+        if (t.M <= 0 || t.N <= 0 || t.K <= 0) return TPL_EINVAL;
+        if (t.epi != TPL_EPI_NONE && t.epi != TPL_EPI_GELU && t.epi != TPL_EPI_DGELU) return TPL_EINVAL;
+        if (t.M % q || t.N % q || t.K % q) return TPL_EUNSUPPORTED;
+        g[i] = GemmArgs{};
+        g[i].dtype = dtype; g[i].trans_a = t.trans_a != 0; g[i].trans_b = t.trans_b != 0; g[i].M = t.M; g[i].N = t.N; g[i].K = t.K;
+        g[i].A = t.A; g[i].B = t.B; g[i].C = t.C; g[i].bias = t.bias; g[i].resid = t.resid; g[i].aux = t.aux; g[i].epi = t.epi;
+    }
+    return TPL_OK;
+}
+static bool items_in_one_launch(int n, const GemmArgs* g) {
+    const Options& o = options();
+    if (n < 2 || o.gemm_group == 0 || o.gemm_tile >= 0 || o.gemm_shares > 0 || o.gemm_force[0] || o.gemm_band > 0) return false;
+    for (int i = 0; i < n; ++i)
+        if ((g[i].trans_a && g[i].trans_b) || !(g[i].dtype == BF16 ? gemm_bf16_supported(g[i]) : gemm_f32_supported(g[i]))) return false;
+    return true;
+}
+size_t tp_layer_gemm_group_workspace_bytes(int dtype, int n, const tp_layer_gemm_item* items) {
+    GemmArgs g[4];
+    if (group_items(dtype, n, items, g) != TPL_OK) return 0;
+    size_t need = ALIGN;
+    for (int i = 0; i < n; ++i) need = std::max(need, gemm_ws(dtype, g[i].M, g[i].N, g[i].K));
+    if (items_in_one_launch(n, g)) need = std::max(need, up(dtype == TPL_BF16 ? gemm_bf16_group_workspace_bytes(g, n) : gemm_f32_group_workspace_bytes(g, n)));
+    return need;
+}
+int tp_layer_gemm_group(int dtype, int n, const tp_layer_gemm_item* items, void* ws, size_t ws_bytes, void* hip_stream) {
+    GemmArgs g[4];
+    int rc = group_items(dtype, n, items, g);
+    if (rc) return rc;
+    if (!ws) return TPL_EINVAL;
+    for (int i = 0; i < n; ++i) {
+        if (!g[i].A || !g[i].B || !g[i].C || (g[i].epi != EPI_NONE && !g[i].aux)) return TPL_EINVAL;
+        const void* ptrs[] = {g[i].A, g[i].B, g[i].C, g[i].bias, g[i].resid, g[i].aux, ws};
+        for (const void* pp : ptrs) if (misaligned(pp)) return TPL_EALIGN;
+    }
+    if (ws_bytes < tp_layer_gemm_group_workspace_bytes(dtype, n, items)) return TPL_EWORKSPACE;
+    const GemmScratch sc{ws, ws_bytes, (hipStream_t)hip_stream};
+    if (items_in_one_launch(n, g)) return run_group(g, n, sc);
+    for (int i = 0; i < n; ++i) {
+        g[i].ws = ws; g[i].ws_bytes = ws_bytes; g[i].stream = sc.stream;
+        if ((rc = run_gemm(g[i]))) return rc;
+    }
+    return TPL_OK;
+}
+
 static int attn_check(int dtype, int B, int S, int nl, int dh) {
     if (dtype != TPL_F32 && dtype != TPL_BF16) return TPL_EINVAL;
     if (B <= 0 || S <= 0 || nl <= 0 || dh <= 0) return TPL_EINVAL;

@@ -55,16 +55,17 @@ class MemOptRank:
         self.lse = f(self.B, self.nl, self.S)
         self.u, self.g = e(M, self.Il), e(M, self.Il)
         # backward
-        self.dg, self.du, self.dhid = e(M, self.Il), e(M, self.Il), e(M, self.Hs)
+        self.du, self.dhid = e(M, self.Il), e(M, self.Hs)
         self.dy1, self.dx = e(M, self.Hs), e(M, self.Hs)
         self.d_o, self.dqkv, self.dsum = e(M, self.Hl), e(M, 3 * self.Hl), f(self.B, self.nl, self.S)
         Hs, Hl, Il = self.Hs, self.Hl, self.Il
-        gemm_shapes = [(M, 3 * H, Hs), (M, H, Hl), (M, I, Hs), (M, H, Il),          # forward partial products
-                       (M, Il, H), (Il, H, M), (M, Hs, I), (Hs, I, M),              # data and weight gradients
-                       (M, Hl, H), (Hl, H, M), (M, Hs, 3 * H), (Hs, 3 * H, M)]
+        gemm_shapes = [(M, 3 * H, Hs), (M, H, Hl), (M, I, Hs), (M, H, Il)]          # forward partial products
+        pairs = [(Il, H), (Hs, I), (Hl, H), (Hs, 3 * H)]                             # data and weight gradients
         nws = max(B.tp_layer_ln_apply_workspace_bytes(M, Hs),
                   B.tp_layer_slice_epilogue_workspace_bytes(M, max(3 * Hl, Il, Hs)),
                   max(B.tp_layer_gemm_workspace_bytes(dtype, *g) for g in gemm_shapes),
+                  max(B.tp_layer_gemm_group_workspace_bytes(dtype, self._pair(k, n, None, None, None, None, None, epi=epi))
+                      for k, n in pairs for epi in (B.TPL_EPI_NONE, B.TPL_EPI_DGELU)),
                   max(B.tp_layer_attn_workspace_bytes(dtype, self.B, self.S, self.nl, self.dh, self.causal, bwd)
                       for bwd in (False, True)), 256)
         self.ws = torch.empty(nws, dtype=torch.uint8, device=device)
@@ -79,6 +80,13 @@ class MemOptRank:
 
     def _gemm(self, ta, tb, M, N, K, A, Bm, C):
         B.tp_layer_gemm(self.dtype, ta, tb, M, N, K, A, Bm, C, ws=self.ws, stream=self._st())
+
+    def _pair(self, k, n, dy, w, dx, x, dw, aux=None, epi=B.TPL_EPI_NONE):
+        """dx [M, k] = dy [M, n] w^T, and dw [k, n] = x^T dy: neither needs the other."""
+        return [(0, 1, self.M, k, n, dy, w, dx, aux, epi), (1, 0, k, n, self.M, x, dy, dw)]
+
+    def _linear_bwd(self, *args, **kw):
+        B.tp_layer_gemm_group(self.dtype, self._pair(*args, **kw), ws=self.ws, stream=self._st())
 
     # -- forward --------------------------------------------------------------------------------------
     def f0_moments(self, p, x):
@@ -141,15 +149,14 @@ class MemOptRank:
         return dy2
 
     def b1_down(self, dy2_full):
-        self._gemm(0, 1, self.M, self.Il, self.H, dy2_full, self.p["w_dn"], self.dg)
-        self._gemm(1, 0, self.Il, self.H, self.M, self.g, dy2_full, self.grads["w_dn"])
-        B.tp_layer_slice_epilogue_bwd(self.dtype, B.TPL_ACT_GELU, self.M, self.Il, self.dg, self.u, self.du,
+        self._linear_bwd(self.Il, self.H, dy2_full, self.p["w_dn"], self.du, self.g, self.grads["w_dn"], aux=self.u,
+                    epi=B.TPL_EPI_DGELU)
+        B.tp_layer_slice_epilogue_bwd(self.dtype, B.TPL_ACT_NONE, self.M, self.Il, self.du, None, None,
                                       self.grads["b_up"], self.ws, stream=self._st())
         return self.du
 
     def b2_up(self, du_full):
-        self._gemm(0, 1, self.M, self.Hs, self.I, du_full, self.p["w_up"], self.dhid)
-        self._gemm(1, 0, self.Hs, self.I, self.M, self.h2, du_full, self.grads["w_up"])
+        self._linear_bwd(self.Hs, self.I, du_full, self.p["w_up"], self.dhid, self.h2, self.grads["w_up"])
         B.tp_layer_ln_apply_bwd_sums(self.dtype, self.M, self.Hs, self.dhid, self.y1, self.mean2, self.rstd2,
                                      self.p["g2"], self.sums, stream=self._st())
         return self.sums
@@ -165,8 +172,7 @@ class MemOptRank:
 
     def b4_attn(self, dy1_full):
         st = self._st()
-        self._gemm(0, 1, self.M, self.Hl, self.H, dy1_full, self.p["w_o"], self.d_o)
-        self._gemm(1, 0, self.Hl, self.H, self.M, self.o, dy1_full, self.grads["w_o"])
+        self._linear_bwd(self.Hl, self.H, dy1_full, self.p["w_o"], self.d_o, self.o, self.grads["w_o"])
         B.tp_layer_attn_bwd(self.dtype, self.B, self.S, self.nl, self.dh, self.causal, self.qkv, self.o, self.lse,
                             self.d_o, self.dqkv, self.dsum, ws=self.ws, stream=st)
         B.tp_layer_slice_epilogue_bwd(self.dtype, B.TPL_ACT_NONE, self.M, 3 * self.Hl, self.dqkv, None, None,
@@ -174,8 +180,7 @@ class MemOptRank:
         return self.dqkv
 
     def b5_qkv(self, dqkv_full):
-        self._gemm(0, 1, self.M, self.Hs, 3 * self.H, dqkv_full, self.p["w_qkv"], self.dhid)
-        self._gemm(1, 0, self.Hs, 3 * self.H, self.M, self.h1, dqkv_full, self.grads["w_qkv"])
+        self._linear_bwd(self.Hs, 3 * self.H, dqkv_full, self.p["w_qkv"], self.dhid, self.h1, self.grads["w_qkv"])
         B.tp_layer_ln_apply_bwd_sums(self.dtype, self.M, self.Hs, self.dhid, self.x, self.mean1, self.rstd1,
                                      self.p["g1"], self.sums, stream=self._st())
         return self.sums
