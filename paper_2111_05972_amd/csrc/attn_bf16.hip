@@ -173,6 +173,11 @@ template <int IMM> __device__ __forceinline__ bf16x8 lds_frag_t(unsigned addr0, 
     out[4] = b1[0]; out[5] = b1[1]; out[6] = b1[2]; out[7] = b1[3];
     return out;
 }
+typedef __attribute__((ext_vector_type(4))) float f32x4;
+__device__ __forceinline__ f32x4 lds_f4(unsigned addr) {
+    typedef __attribute__((address_space(3))) const f32x4* p_t;
+    return *reinterpret_cast<p_t>((uintptr_t)addr);
+}
 template <typename T> __device__ __forceinline__ void keep_in_register(T& v) { asm volatile("" : "+v"(v)); }
 // The same operand straight from global memory (loop-invariant fragments kept in registers).
 __device__ __forceinline__ bf16x8 frag_k_global(const bf16_t* base, int64_t ld, int row, int nrows, int dh,
@@ -1046,6 +1051,544 @@ __global__ __launch_bounds__(FTHREADS, 2) void attn_bwd_kernel(const bf16_t* __r
     else attn_dq_wg<DH, CAUSAL, FLOATW>(smem, qkv, d_o, lse, dsum, dqkv, S, nl, dh, c2f, BH, part_q, ch_q, wg - wgs_kv);
 }
 
+// =================================================================================================
+// Head sizes 64 and 128, launches of many workgroups (own_rows): four wavefronts per workgroup, each owning 32 rows (queries, or
+// keys in dK/dV) of the block outright, two or more workgroups per compute unit.  The workgroups of a unit share no barrier, so
+// one's vector arithmetic and LDS latency run beside another's products, and the scores of dK and dV are worked out once; what
+// bounds them still is the sum of a wavefront's LDS reads, vector arithmetic and products (a third of the matrix rate).
+//   forward   64 keys at a time: one maximum and one rescale for both halves of a tile, two chains of products
+//   backward  (head size 64) the weights of a subtile of 32 rows are worked out between the score products of the next one (7 % at
+//             4096 tokens, 16 heads), hence three stages in LDS
+// =================================================================================================
+constexpr int WTHREADS = 256;
+
+template <int DH, bool CAUSAL>
+__global__ __launch_bounds__(WTHREADS, 2) void attn_fwd_rows_kernel(const bf16_t* __restrict__ qkv, bf16_t* __restrict__ o, float* __restrict__ lse,
+                                                                   int S, int nl, int BH, float* __restrict__ part, ChunkLen ch) {
+    extern __shared__ __attribute__((aligned(16))) char smem[];
+    constexpr int TB = tile_bytes<DH>(), NF = DH / 16, NT = DH / 32, HALF = 32 * DH * 2;
+    constexpr int NCH = NCHUNKS<DH, WTHREADS>;
+    const int t = threadIdx.x, lane = t & 63, half = lane >> 5;
+    const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
+    const int bh = blockIdx.x % BH, slot = blockIdx.x / BH;      // head fastest: heaviest chunks of all heads first
+    const Chunk ck = find_chunk(CAUSAL, false, S, ch, slot, 0);
+    const int b = bh / nl, h = bh % nl;
+    const int64_t ld = 3LL * nl * DH;
+    const bf16_t* qbase = qkv + (int64_t)b * S * ld + (int64_t)h * DH;
+    const bf16_t* kbase = qbase + (int64_t)nl * DH;
+    const bf16_t* vbase = kbase + (int64_t)nl * DH;
+    const int q0 = ck.blk * BLK + wave * 32, q = q0 + (lane & 31);
+    const float c2 = LOG2E / sqrtf((float)DH);
+
+    bf16x8 qf[NF];
+#pragma unroll
+    for (int ks = 0; ks < NF; ++ks) qf[ks] = frag_k_global(qbase, ld, q, S, DH, ks, lane);
+    f32x16 oacc[NT];
+#pragma unroll
+    for (int dt = 0; dt < NT; ++dt) oacc[dt] = zero16();
+    float m = -INFINITY, lsum = 0.0f;
+
+    const int kv_end = CAUSAL ? min(S, q0 + 32) : S;              // keys that any query of this wavefront sees
+    const unsigned lds0 = (unsigned)(uintptr_t)(lds_void_ptr)smem;
+    const i32x4 desc_k = head_rsrc(kbase, ld, S, DH), desc_v = head_rsrc(vbase, ld, S, DH);
+    unsigned off[NCH];
+    dma_offsets<DH, WTHREADS>(off, ld, DH, t);
+    auto fetch_tile = [&](int kt, unsigned stage) {
+        const unsigned r0 = (unsigned)kt * TILE * (unsigned)(ld * 2);
+        tile_dma<DH, WTHREADS>(desc_k, stage, off, r0, wave);
+        tile_dma<DH, WTHREADS>(desc_v, stage + TB, off, r0, wave);
+    };
+    unsigned ka[NF], va[NT][2];
+#pragma unroll
+    for (int ks = 0; ks < NF; ++ks) { ka[ks] = lds0 + frag_k_off<DH>(0, ks, lane); keep_in_register(ka[ks]); }
+#pragma unroll
+    for (int dt = 0; dt < NT; ++dt)
+#pragma unroll
+        for (int g = 0; g < 2; ++g) { va[dt][g] = lds0 + TB + frag_t_off<DH>(dt * 32, 0, g, lane); keep_in_register(va[dt][g]); }
+    fetch_tile(ck.t0, lds0);
+#pragma unroll
+    for (int ks = 0; ks < NF; ++ks) settle(qf[ks]);
+    dma_wait();
+    __syncthreads();
+    auto step = [&](int kt, auto stg) __attribute__((always_inline)) {
+        constexpr int SOFF = decltype(stg)::value * 2 * TB;
+        if (kt + 1 < ck.t1) fetch_tile(kt + 1, lds0 + (1 - decltype(stg)::value) * 2 * TB);
+        const int kv0 = kt * TILE;
+        if (kv0 < kv_end) {                                       // wavefront-uniform
+            f32x16 s[2] = {zero16(), zero16()};
+            bf16x8 fr[2 * NF];                                    // keys 0..31 and 32..63 in turn, two chains of products
+#pragma unroll
+            for (int ks = 0; ks < NF; ++ks) {
+                fr[2 * ks] = lds_frag_k<SOFF>(ka[ks]);
+                fr[2 * ks + 1] = lds_frag_k<SOFF + HALF>(ka[ks]);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+            __builtin_amdgcn_s_setprio(1);
+#pragma unroll
+            for (int ks = 0; ks < NF; ++ks) {
+                s[0] = MFMA(fr[2 * ks], qf[ks], s[0]);
+                s[1] = MFMA(fr[2 * ks + 1], qf[ks], s[1]);
+            }
+            __builtin_amdgcn_s_setprio(0);
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int dt = 0; dt < NT; ++dt) {                     // [16 rows][dt]
+                fr[dt] = lds_frag_t<SOFF>(va[dt][0], va[dt][1]);
+                fr[NT + dt] = lds_frag_t<SOFF + HALF / 2>(va[dt][0], va[dt][1]);
+                fr[2 * NT + dt] = lds_frag_t<SOFF + HALF>(va[dt][0], va[dt][1]);
+                fr[3 * NT + dt] = lds_frag_t<SOFF + HALF + HALF / 2>(va[dt][0], va[dt][1]);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+            if (kv0 + 63 >= S || (CAUSAL && kv0 + 63 > q0)) {
+#pragma unroll
+                for (int g = 0; g < 2; ++g)
+#pragma unroll
+                    for (int v = 0; v < 16; ++v) {
+                        const int kv = kv0 + 32 * g + (v >> 2) * 8 + half * 4 + (v & 3);
+                        s[g][v] = kv < S && (!CAUSAL || kv <= q) ? s[g][v] : -INFINITY;
+                    }
+            }
+            float mb = fmaxf(s[0][0], s[1][0]);
+#pragma unroll
+            for (int v = 1; v < 16; ++v) mb = fmaxf(fmaxf(mb, s[0][v]), s[1][v]);
+            mb = cross_half_max(mb) * c2;                         // c2 > 0: scaling commutes with max
+            const float mn = (mb - m > RESCALE_LAG) ? mb : m;     // see attn_fwd_kernel
+            const float mu = mn == -INFINITY ? 0.0f : mn;
+            const float alpha = fast_exp2(m - mu);
+            m = mn;
+            float ps[2] = {0.0f, 0.0f};
+#pragma unroll
+            for (int v = 0; v < 16; ++v)
+#pragma unroll
+                for (int g = 0; g < 2; ++g) { s[g][v] = fast_exp2(fmaf(s[g][v], c2, -mu)); ps[g] += s[g][v]; }
+            lsum = lsum * alpha + (ps[0] + ps[1]);
+            if (__any(alpha != 1.0f)) {
+#pragma unroll
+                for (int dt = 0; dt < NT; ++dt)
+#pragma unroll
+                    for (int v = 0; v < 16; ++v) oacc[dt][v] *= alpha;
+            }
+            const bf16x8 pb[4] = {pack_regs(s[0], 0), pack_regs(s[0], 8), pack_regs(s[1], 0), pack_regs(s[1], 8)};
+            __builtin_amdgcn_s_setprio(1);
+            auto add = [&](int r0) __attribute__((always_inline)) {
+#pragma unroll
+                for (int r = r0; r < r0 + 2; ++r)
+#pragma unroll
+                    for (int dt = 0; dt < NT; ++dt) oacc[dt] = MFMA(fr[r * NT + dt], pb[r], oacc[dt]);
+            };
+            add(0);
+            if (!CAUSAL || kv0 + 32 <= q0 + 31) add(2);           // uniform; zero times a later token's infinity is NaN
+            __builtin_amdgcn_s_setprio(0);
+        }
+        dma_wait();
+        __syncthreads();
+    };
+    {
+        int kt = ck.t0;
+        for (; kt + 1 < ck.t1; kt += 2) {
+            step(kt, std::integral_constant<int, 0>{});
+            step(kt + 1, std::integral_constant<int, 1>{});
+        }
+        if (kt < ck.t1) step(kt, std::integral_constant<int, 0>{});
+    }
+    lsum += __shfl_xor(lsum, 32, 64);
+    if (ck.nch > 1) {
+        // one chunk of a longer strip: (max, sum, unnormalised O) of this chunk's keys, float, [query][dh]
+        float* pp = part + ((int64_t)slot * BH + bh) * (BLK * (DH + 2));
+        const int ql = wave * 32 + (lane & 31);
+#pragma unroll
+        for (int dt = 0; dt < NT; ++dt)
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+                store_f4(pp + ql * DH + dt * 32 + 8 * i + 4 * half, oacc[dt][4 * i], oacc[dt][4 * i + 1], oacc[dt][4 * i + 2], oacc[dt][4 * i + 3]);
+        if (half == 0) { pp[BLK * DH + ql] = m; pp[BLK * DH + BLK + ql] = lsum; }
+    } else if (q < S) {
+        const float inv = lsum > 0.0f ? 1.0f / lsum : 0.0f;
+        bf16_t* op = o + ((int64_t)b * S + q) * ((int64_t)nl * DH) + (int64_t)h * DH;
+#pragma unroll
+        for (int dt = 0; dt < NT; ++dt)
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+                store4(op + dt * 32 + 8 * i + 4 * half, oacc[dt][4 * i] * inv, oacc[dt][4 * i + 1] * inv, oacc[dt][4 * i + 2] * inv, oacc[dt][4 * i + 3] * inv);
+        if (half == 0) lse[((int64_t)b * nl + h) * S + q] = strip_lse<false>(m, lsum);
+    }
+}
+
+// dK and dV of 32 keys per wavefront.  Score tile: lane = key, registers = queries.
+template <int DH, bool CAUSAL>
+__device__ __forceinline__ void attn_dkv_rows(char* smem, const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ d_o, const float* __restrict__ lse,
+                                              const float* __restrict__ dsum, bf16_t* __restrict__ dqkv, int S, int nl, int BH,
+                                              float* __restrict__ part, ChunkLen ch, int wg) {
+    constexpr int TB = tile_bytes<DH>(), NF = DH / 16, NT = DH / 32, STAGE = 2 * TB + 2 * TILE * 4;   // Q tile, dO tile, LSE*log2e, D
+    constexpr int NCH = NCHUNKS<DH, WTHREADS>;
+    const int t = threadIdx.x, lane = t & 63, half = lane >> 5;
+    const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
+    const int bh = wg % BH, slot = wg / BH;
+    const Chunk ck = find_chunk(CAUSAL, true, S, ch, slot, 0);
+    const int b = bh / nl, h = bh % nl;
+    const int64_t ld = 3LL * nl * DH, ldo = (int64_t)nl * DH;
+    const bf16_t* qbase = qkv + (int64_t)b * S * ld + (int64_t)h * DH;
+    const bf16_t* kbase = qbase + (int64_t)nl * DH;
+    const bf16_t* vbase = kbase + (int64_t)nl * DH;
+    const bf16_t* dobase = d_o + (int64_t)b * S * ldo + (int64_t)h * DH;
+    const float* lrow = lse + ((int64_t)b * nl + h) * S;
+    const float* drow = dsum + ((int64_t)b * nl + h) * S;
+    const int k0 = ck.blk * BLK + wave * 32, kv = k0 + (lane & 31);
+    const float scale = 1.0f / sqrtf((float)DH), c2 = LOG2E * scale;
+
+    bf16x8 kf[NF], vf[NF];
+#pragma unroll
+    for (int ks = 0; ks < NF; ++ks) {
+        kf[ks] = frag_k_global(kbase, ld, kv, S, DH, ks, lane);
+        vf[ks] = frag_k_global(vbase, ld, kv, S, DH, ks, lane);
+    }
+    f32x16 dk[NT], dv[NT];
+#pragma unroll
+    for (int dt = 0; dt < NT; ++dt) dk[dt] = dv[dt] = zero16();
+    const int qt0 = ck.t0, ntiles = ck.t1;
+    const unsigned lds0 = (unsigned)(uintptr_t)(lds_void_ptr)smem;
+    const i32x4 desc_q = head_rsrc(qbase, ld, S, DH), desc_do = head_rsrc(dobase, ldo, S, DH);
+    unsigned off_q[NCH], off_do[NCH];
+    dma_offsets<DH, WTHREADS>(off_q, ld, DH, t);
+    dma_offsets<DH, WTHREADS>(off_do, ldo, DH, t);
+    float rl = 0.0f, rd = 0.0f;
+    auto g2r = [&](int qt, unsigned stage) {
+        tile_dma<DH, WTHREADS>(desc_q, stage, off_q, (unsigned)qt * TILE * (unsigned)(ld * 2), wave);
+        tile_dma<DH, WTHREADS>(desc_do, stage + TB, off_do, (unsigned)qt * TILE * (unsigned)(ldo * 2), wave);
+        if (t < TILE) {
+            const int qi = qt * TILE + t;
+            rl = qi < S ? lrow[qi] * LOG2E : 0.0f;
+            rd = qi < S ? drow[qi] : 0.0f;
+        }
+    };
+    auto r2s = [&](char* st) {
+        if (t < TILE) {
+            reinterpret_cast<float*>(st + 2 * TB)[t] = rl;
+            reinterpret_cast<float*>(st + 2 * TB)[TILE + t] = rd;
+        }
+    };
+    if (qt0 < ntiles) { g2r(qt0, lds0); r2s(smem); }
+#pragma unroll
+    for (int ks = 0; ks < NF; ++ks) { settle(kf[ks]); settle(vf[ks]); }
+    dma_wait();
+    __syncthreads();
+    constexpr int W = 8;
+    f32x16 sc[2], dp[2];                                                   // scores and dP of the subtiles, by parity
+    unsigned ko[NF], to[NT][2];                                            // this lane's fragment reads in a tile
+#pragma unroll
+    for (int ks = 0; ks < NF; ++ks) { ko[ks] = frag_k_off<DH>(0, ks, lane); keep_in_register(ko[ks]); }
+#pragma unroll
+    for (int dt = 0; dt < NT; ++dt)
+#pragma unroll
+        for (int g = 0; g < 2; ++g) { to[dt][g] = frag_t_off<DH>(dt * 32, 0, g, lane); keep_in_register(to[dt][g]); }
+    bool pending = false;
+    unsigned prev = 0, prev_ls = 0;                                        // LDS addresses of the pending subtile's Q rows and LSE
+    int prev0 = 0;                                                         // its first query
+    // P and dS of the pending subtile, element by element, in the shadow of other products
+    bf16x8 gp[2], gs[2];
+    float lv[16], dd[16];
+    auto read_rows = [&]() __attribute__((always_inline)) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const f32x4 l4 = lds_f4(prev_ls + (8 * i + 4 * half) * 4), d4 = lds_f4(prev_ls + TILE * 4 + (8 * i + 4 * half) * 4);
+            lv[4 * i] = l4[0]; lv[4 * i + 1] = l4[1]; lv[4 * i + 2] = l4[2]; lv[4 * i + 3] = l4[3];
+            dd[4 * i] = d4[0]; dd[4 * i + 1] = d4[1]; dd[4 * i + 2] = d4[2]; dd[4 * i + 3] = d4[3];
+        }
+    };
+    auto mask = [&](f32x16& x) __attribute__((always_inline)) {            // wave-uniform: diagonal, or the end of S
+        if (prev0 + 31 >= S || k0 + 31 >= S || (CAUSAL && k0 + 31 > prev0)) {
+#pragma unroll
+            for (int v = 0; v < 16; ++v) {
+                const int qi = prev0 + 8 * (v >> 2) + 4 * half + (v & 3);
+                x[v] = qi < S && kv < S && (!CAUSAL || kv <= qi) ? x[v] : -INFINITY;   // exp2(-inf) = 0
+            }
+        }
+    };
+    auto weigh = [&](f32x16& x, f32x16& y, int v) __attribute__((always_inline)) {
+        x[v] = fast_exp2(fmaf(x[v], c2, -lv[v]));
+        y[v] = x[v] * (y[v] - dd[v]);
+        if ((v & 7) == 7) { gp[v >> 3] = pack_regs(x, v - 7); gs[v >> 3] = pack_regs(y, v - 7); }
+    };
+    // S and dP of a subtile (two chains of products), and beside them the weights of the pending one
+    auto scores = [&](unsigned qsb, f32x16& cs_, f32x16& cd, f32x16& ps_, f32x16& pd, auto pendc) __attribute__((always_inline)) {
+        bf16x8 fr[W];
+        auto fetch = [&](int i) { return i & 1 ? lds_frag_k<TB>(qsb + ko[i >> 1]) : lds_frag_k<0>(qsb + ko[i >> 1]); };
+        if constexpr (decltype(pendc)::value) read_rows();
+#pragma unroll
+        for (int i = 0; i < W; ++i) fr[i] = fetch(i);
+        __builtin_amdgcn_sched_barrier(0);
+        cs_ = zero16();
+        cd = zero16();
+#pragma unroll
+        for (int i = 0; i < 2 * NF; ++i) {
+            if (i & 1) cd = MFMA(fr[i % W], vf[i >> 1], cd);
+            else cs_ = MFMA(fr[i % W], kf[i >> 1], cs_);
+            if (i + W < 2 * NF) fr[i % W] = fetch(i + W);
+            if constexpr (decltype(pendc)::value) {
+#pragma unroll
+                for (int v = 0; v < 16; ++v)
+                    if (v * 2 * NF / 16 == i) weigh(ps_, pd, v);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    };
+    // dV and dK of the pending subtile
+    auto collect = [&]() __attribute__((always_inline)) {
+        bf16x8 fr[W];
+        auto fetch = [&](int k) {                                          // [dO, Q][16 rows][dt]
+            const unsigned a0 = prev + to[k % NT][0], a1 = prev + to[k % NT][1];
+            constexpr int R16 = 16 * DH * 2;
+            return k < NF ? (k < NT ? lds_frag_t<TB>(a0, a1) : lds_frag_t<TB + R16>(a0, a1))
+                          : (k < NF + NT ? lds_frag_t<0>(a0, a1) : lds_frag_t<R16>(a0, a1));
+        };
+#pragma unroll
+        for (int i = 0; i < W; ++i) fr[i] = fetch(i);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int k = 0; k < 2 * NF; ++k) {
+            if (k < NF) dv[k % NT] = MFMA(fr[k % W], gp[k / NT], dv[k % NT]);
+            else dk[k % NT] = MFMA(fr[k % W], gs[(k - NF) / NT], dk[k % NT]);
+            if (k + W < 2 * NF) fr[k % W] = fetch(k + W);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    };
+    auto subtile = [&](unsigned st, int qt, auto sbc) __attribute__((always_inline)) {
+        constexpr int SB = decltype(sbc)::value;
+        const int qs0 = qt * TILE + SB * 32;
+        if (qs0 >= S || (CAUSAL && qs0 + 31 < k0)) return;                 // wavefront-uniform; only before the first and after the last
+        const unsigned qsb = st + SB * 32 * DH * 2;
+        if (pending) {
+            mask(sc[SB ^ 1]);
+            scores(qsb, sc[SB], dp[SB], sc[SB ^ 1], dp[SB ^ 1], std::true_type{});
+            collect();
+        } else {
+            scores(qsb, sc[SB], dp[SB], sc[SB ^ 1], dp[SB ^ 1], std::false_type{});
+        }
+        pending = true;
+        prev = qsb;
+        prev0 = qs0;
+        prev_ls = st + 2 * TB + SB * 32 * 4;
+    };
+    int stage = 0;
+    for (int qt = qt0; qt < ntiles; ++qt) {
+        const unsigned st = lds0 + stage * STAGE;
+        const int nstage = stage == 2 ? 0 : stage + 1;                     // last read before the barrier before last
+        const bool more = qt + 1 < ntiles;
+        if (more) g2r(qt + 1, lds0 + nstage * STAGE);
+        subtile(st, qt, std::integral_constant<int, 0>{});
+        subtile(st, qt, std::integral_constant<int, 1>{});
+        if (more) r2s(smem + nstage * STAGE);
+        dma_wait();
+        __syncthreads();
+        stage = nstage;
+    }
+    if (pending) {
+        // the last one, by the parity of its place in a tile
+        if ((prev0 / 32) & 1) {
+            mask(sc[1]);
+            read_rows();
+#pragma unroll
+            for (int v = 0; v < 16; ++v) weigh(sc[1], dp[1], v);
+        } else {
+            mask(sc[0]);
+            read_rows();
+#pragma unroll
+            for (int v = 0; v < 16; ++v) weigh(sc[0], dp[0], v);
+        }
+        collect();
+    }
+#pragma unroll
+    for (int which = 0; which < 2; ++which) {                             // dK, dV
+        const f32x16 (&acc)[NT] = which ? dv : dk;
+        const float f = which ? 1.0f : scale;
+        if (ck.nch > 1) {
+            // one chunk of a longer strip: unscaled float partial, [dK | dV][key][dh]
+            float* pp = part + ((int64_t)slot * BH + bh) * (2 * BLK * DH) + which * BLK * DH + (wave * 32 + (lane & 31)) * DH;
+#pragma unroll
+            for (int dt = 0; dt < NT; ++dt)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) store_f4(pp + dt * 32 + 8 * i + 4 * half, acc[dt][4 * i], acc[dt][4 * i + 1], acc[dt][4 * i + 2], acc[dt][4 * i + 3]);
+        } else if (kv < S) {
+            bf16_t* outp = dqkv + ((int64_t)b * S + kv) * ld + (int64_t)(1 + which) * nl * DH + (int64_t)h * DH;
+#pragma unroll
+            for (int dt = 0; dt < NT; ++dt)
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+                    store4(outp + dt * 32 + 8 * i + 4 * half, acc[dt][4 * i] * f, acc[dt][4 * i + 1] * f, acc[dt][4 * i + 2] * f, acc[dt][4 * i + 3] * f);
+        }
+    }
+}
+
+// dQ of 32 queries per wavefront.  Transposed score tile: lane = query.
+template <int DH, bool CAUSAL>
+__device__ __forceinline__ void attn_dq_rows(char* smem, const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ d_o, const float* __restrict__ lse,
+                                             const float* __restrict__ dsum, bf16_t* __restrict__ dqkv, int S, int nl, int BH,
+                                             float* __restrict__ part, ChunkLen ch, int wg) {
+    constexpr int TB = tile_bytes<DH>(), NF = DH / 16, NT = DH / 32;
+    constexpr int NCH = NCHUNKS<DH, WTHREADS>;
+    const int t = threadIdx.x, lane = t & 63, half = lane >> 5;
+    const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
+    const int bh = wg % BH, slot = wg / BH;
+    const Chunk ck = find_chunk(CAUSAL, false, S, ch, slot, 0);
+    const int b = bh / nl, h = bh % nl;
+    const int64_t ld = 3LL * nl * DH, ldo = (int64_t)nl * DH;
+    const bf16_t* qbase = qkv + (int64_t)b * S * ld + (int64_t)h * DH;
+    const bf16_t* kbase = qbase + (int64_t)nl * DH;
+    const bf16_t* vbase = kbase + (int64_t)nl * DH;
+    const bf16_t* dobase = d_o + (int64_t)b * S * ldo + (int64_t)h * DH;
+    const int q0 = ck.blk * BLK + wave * 32, q = q0 + (lane & 31);
+    const float scale = 1.0f / sqrtf((float)DH), c2 = LOG2E * scale;
+    const float l2 = q < S ? lse[((int64_t)b * nl + h) * S + q] * LOG2E : 0.0f;
+    const float dq_d = q < S ? dsum[((int64_t)b * nl + h) * S + q] : 0.0f;
+
+    bf16x8 qf[NF], dof[NF];
+#pragma unroll
+    for (int ks = 0; ks < NF; ++ks) {
+        qf[ks] = frag_k_global(qbase, ld, q, S, DH, ks, lane);
+        dof[ks] = frag_k_global(dobase, ldo, q, S, DH, ks, lane);
+    }
+    f32x16 dq[NT];
+#pragma unroll
+    for (int dt = 0; dt < NT; ++dt) dq[dt] = zero16();
+    const int kv_end = CAUSAL ? min(S, q0 + 32) : S;
+    const int tile0 = ck.t0, ntiles = ck.t1;
+    const unsigned lds0 = (unsigned)(uintptr_t)(lds_void_ptr)smem;
+    const i32x4 desc_k = head_rsrc(kbase, ld, S, DH), desc_v = head_rsrc(vbase, ld, S, DH);
+    unsigned off[NCH];
+    dma_offsets<DH, WTHREADS>(off, ld, DH, t);
+    auto fetch_tile = [&](int kt, unsigned stage) {
+        const unsigned r0 = (unsigned)kt * TILE * (unsigned)(ld * 2);
+        tile_dma<DH, WTHREADS>(desc_k, stage, off, r0, wave);
+        tile_dma<DH, WTHREADS>(desc_v, stage + TB, off, r0, wave);
+    };
+    fetch_tile(tile0, lds0);
+#pragma unroll
+    for (int ks = 0; ks < NF; ++ks) { settle(qf[ks]); settle(dof[ks]); }
+    settle(l2);
+    settle(dq_d);
+    dma_wait();
+    __syncthreads();
+    constexpr int W = 8;
+    f32x16 sc[2], dp[2];                                                   // as in attn_dkv_rows
+    unsigned ko[NF], to[NT][2];
+#pragma unroll
+    for (int ks = 0; ks < NF; ++ks) { ko[ks] = frag_k_off<DH>(0, ks, lane); keep_in_register(ko[ks]); }
+#pragma unroll
+    for (int dt = 0; dt < NT; ++dt)
+#pragma unroll
+        for (int g = 0; g < 2; ++g) { to[dt][g] = frag_t_off<DH>(dt * 32, 0, g, lane); keep_in_register(to[dt][g]); }
+    bool pending = false;
+    unsigned prev = 0;
+    int prev0 = 0;
+    bf16x8 gs[2];
+    auto mask = [&](f32x16& x) __attribute__((always_inline)) {
+        if (q0 + 31 >= S || prev0 + 31 >= S || (CAUSAL && prev0 + 31 > q0)) {
+#pragma unroll
+            for (int v = 0; v < 16; ++v) {
+                const int kv = prev0 + (v >> 2) * 8 + half * 4 + (v & 3);
+                x[v] = q < S && kv < S && (!CAUSAL || kv <= q) ? x[v] : -INFINITY;
+            }
+        }
+    };
+    auto weigh = [&](f32x16& x, f32x16& y, int v) __attribute__((always_inline)) {
+        y[v] = fast_exp2(fmaf(x[v], c2, -l2)) * (y[v] - dq_d);
+        if ((v & 7) == 7) gs[v >> 3] = pack_regs(y, v - 7);
+    };
+    auto scores = [&](unsigned kb, f32x16& cs_, f32x16& cd, f32x16& ps_, f32x16& pd, auto pendc) __attribute__((always_inline)) {
+        bf16x8 fr[W];
+        auto fetch = [&](int i) { return i & 1 ? lds_frag_k<TB>(kb + ko[i >> 1]) : lds_frag_k<0>(kb + ko[i >> 1]); };
+#pragma unroll
+        for (int i = 0; i < W; ++i) fr[i] = fetch(i);
+        __builtin_amdgcn_sched_barrier(0);
+        cs_ = zero16();
+        cd = zero16();
+#pragma unroll
+        for (int i = 0; i < 2 * NF; ++i) {
+            if (i & 1) cd = MFMA(fr[i % W], dof[i >> 1], cd);
+            else cs_ = MFMA(fr[i % W], qf[i >> 1], cs_);
+            if (i + W < 2 * NF) fr[i % W] = fetch(i + W);
+            if constexpr (decltype(pendc)::value) {
+#pragma unroll
+                for (int v = 0; v < 16; ++v)
+                    if (v * 2 * NF / 16 == i) weigh(ps_, pd, v);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    };
+    auto collect = [&]() __attribute__((always_inline)) {
+        bf16x8 fr[NF];
+#pragma unroll
+        for (int k = 0; k < NF; ++k)
+            fr[k] = k < NT ? lds_frag_t<0>(prev + to[k % NT][0], prev + to[k % NT][1]) : lds_frag_t<16 * DH * 2>(prev + to[k % NT][0], prev + to[k % NT][1]);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int k = 0; k < NF; ++k) dq[k % NT] = MFMA(fr[k], gs[k / NT], dq[k % NT]);
+    };
+    auto subtile = [&](unsigned st, int kt, auto sbc) __attribute__((always_inline)) {
+        constexpr int SB = decltype(sbc)::value;
+        const int kv0 = kt * TILE + SB * 32;
+        if (kv0 >= kv_end) return;                                         // wavefront-uniform; only after the last
+        const unsigned kb = st + SB * 32 * DH * 2;
+        if (pending) {
+            mask(sc[SB ^ 1]);
+            scores(kb, sc[SB], dp[SB], sc[SB ^ 1], dp[SB ^ 1], std::true_type{});
+            collect();
+        } else {
+            scores(kb, sc[SB], dp[SB], sc[SB ^ 1], dp[SB ^ 1], std::false_type{});
+        }
+        pending = true;
+        prev = kb;
+        prev0 = kv0;
+    };
+    int stage = 0;
+    for (int kt = tile0; kt < ntiles; ++kt) {
+        const int nstage = stage == 2 ? 0 : stage + 1;
+        if (kt + 1 < ntiles) fetch_tile(kt + 1, lds0 + nstage * 2 * TB);
+        subtile(lds0 + stage * 2 * TB, kt, std::integral_constant<int, 0>{});
+        subtile(lds0 + stage * 2 * TB, kt, std::integral_constant<int, 1>{});
+        dma_wait();
+        __syncthreads();
+        stage = nstage;
+    }
+    if (pending) {
+        if ((prev0 / 32) & 1) {
+            mask(sc[1]);
+#pragma unroll
+            for (int v = 0; v < 16; ++v) weigh(sc[1], dp[1], v);
+        } else {
+            mask(sc[0]);
+#pragma unroll
+            for (int v = 0; v < 16; ++v) weigh(sc[0], dp[0], v);
+        }
+        collect();
+    }
+    if (ck.nch > 1) {
+        float* pp = part + ((int64_t)slot * BH + bh) * (BLK * DH) + (wave * 32 + (lane & 31)) * DH;
+#pragma unroll
+        for (int dt = 0; dt < NT; ++dt)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) store_f4(pp + dt * 32 + 8 * i + 4 * half, dq[dt][4 * i], dq[dt][4 * i + 1], dq[dt][4 * i + 2], dq[dt][4 * i + 3]);
+    } else if (q < S) {
+        bf16_t* dqp = dqkv + ((int64_t)b * S + q) * ld + (int64_t)h * DH;
+#pragma unroll
+        for (int dt = 0; dt < NT; ++dt)
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+                store4(dqp + dt * 32 + 8 * i + 4 * half, dq[dt][4 * i] * scale, dq[dt][4 * i + 1] * scale, dq[dt][4 * i + 2] * scale, dq[dt][4 * i + 3] * scale);
+    }
+}
+
+template <int DH, bool CAUSAL>
+__global__ __launch_bounds__(WTHREADS, 2) void attn_bwd_rows_kernel(const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ d_o, const float* __restrict__ lse,
+                                                                   const float* __restrict__ dsum, bf16_t* __restrict__ dqkv, int S, int nl, int BH,
+                                                                   float* __restrict__ part_kv, float* __restrict__ part_q, ChunkLen ch_kv, ChunkLen ch_q,
+                                                                   int wgs_kv) {
+    extern __shared__ __attribute__((aligned(16))) char smem[];
+    const int wg = blockIdx.x;                               // uniform: one kind per workgroup, its own barriers
+    if (wg < wgs_kv) attn_dkv_rows<DH, CAUSAL>(smem, qkv, d_o, lse, dsum, dqkv, S, nl, BH, part_kv, ch_kv, wg);
+    else attn_dq_rows<DH, CAUSAL>(smem, qkv, d_o, lse, dsum, dqkv, S, nl, BH, part_q, ch_q, wg - wgs_kv);
+}
+
 // ---- host side ----------------------------------------------------------------------------------
 bool attn_bf16_supported(const AttnArgs& a) {
     // tile loads address a (batch, head) slice with 32-bit byte offsets; where columns may be padded, HEAD_OOB plus the
@@ -1158,12 +1701,24 @@ size_t attn_bf16_workspace_bytes(const AttnArgs& a0, bool bwd) {
     return (cuts(a, false, ch_q) ? part_bytes_dq(a, ch_q) : 0) + (cuts(a, true, ch_kv) ? part_bytes_dkv(a, ch_kv) : 0);
 }
 
+// Whether a launch of n workgroups goes to the kernels whose wavefronts own their rows outright, measured on both sides, us with
+// keys (roles) shared by two wavefronts and with own rows.  Forward, head size 128: 768 causal workgroups 297 and 257, 320 39.5 and
+// 48.9, 192 35 and 42, 256 without a mask 17.5 and 17.2; head size 64: 256 causal 16.3 and 18.4, 512 59 and 59, 512 without a mask
+// 17.2 and 16.7.  A wavefront alone walks a strip in almost twice the time, so the longest of a few causal strips would set the
+// duration.  Backward, head size 64: 1024 workgroups 189 and 146 causal, 63 and 50 without a mask, 512 38 and 38.5, 256 20.5 and
+// 21.1; head size 128 (a wavefront per SIMD, 420 registers): 845 and 988, so not built.
+static bool own_rows(bool causal, bool bwd, int64_t n) {
+    const int64_t cus = compute_units();
+    return bwd ? n >= 3 * cus : !causal || n >= 5 * cus / 2;
+}
+
 template <int DH, bool CAUSAL, bool FLOATW>
 static hipError_t fwd_t(const AttnArgs& a) {
-    constexpr int LDS = fwd_lds_bytes<DH>();
+    constexpr int LDS = fwd_lds_bytes<DH>(), LDS_ROWS = 4 * tile_bytes<DH>();
     static bool once = false;
     if (!once) {
         hipError_t e = set_lds(&attn_fwd_kernel<DH, CAUSAL, FLOATW>, LDS);
+        if constexpr (!FLOATW) if (e == hipSuccess) e = set_lds(&attn_fwd_rows_kernel<DH, CAUSAL>, LDS_ROWS);
         if (e != hipSuccess) return e;
         once = true;
     }
@@ -1173,8 +1728,17 @@ static hipError_t fwd_t(const AttnArgs& a) {
     const int64_t wgs = (int64_t)strip_slots(CAUSAL, false, a.S, ch) * BH;
     if (wgs > 0x7fffffffLL) return hipErrorInvalidValue;
     float* part = static_cast<float*>(a.ws);
-    hipLaunchKernelGGL((attn_fwd_kernel<DH, CAUSAL, FLOATW>), dim3((unsigned)wgs), dim3(FTHREADS), LDS, a.stream,
-                       (const bf16_t*)a.qkv, (bf16_t*)a.o, a.lse, a.S, a.nl, a.dh, scale_log2(a.dh), BH, part, ch);
+    bool launched = false;
+    if constexpr (!FLOATW) {
+        if (own_rows(CAUSAL, false, wgs)) {
+            hipLaunchKernelGGL((attn_fwd_rows_kernel<DH, CAUSAL>), dim3((unsigned)wgs), dim3(WTHREADS), LDS_ROWS, a.stream,
+                               (const bf16_t*)a.qkv, (bf16_t*)a.o, a.lse, a.S, a.nl, BH, part, ch);
+            launched = true;
+        }
+    }
+    if (!launched)
+        hipLaunchKernelGGL((attn_fwd_kernel<DH, CAUSAL, FLOATW>), dim3((unsigned)wgs), dim3(FTHREADS), LDS, a.stream,
+                           (const bf16_t*)a.qkv, (bf16_t*)a.o, a.lse, a.S, a.nl, a.dh, scale_log2(a.dh), BH, part, ch);
     int blk0 = 0, ncut = 0;
     cut_range(a, false, ch, &blk0, &ncut);
     if (ncut)
@@ -1188,9 +1752,12 @@ static hipError_t bwd_t(const AttnArgs& a) {
     constexpr int LDS_KV = 2 * (2 * tile_bytes<DH>() + 2 * TILE * 4);
     constexpr int LDS_Q = dq_lds_bytes<DH>();
     constexpr int LDS = LDS_KV > LDS_Q ? LDS_KV : LDS_Q;
+    constexpr bool OWN_ROWS = DH == 64 && !FLOATW;
+    constexpr int LDS_ROWS = 3 * (2 * tile_bytes<DH>() + 2 * TILE * 4);
     static bool once = false;
     if (!once) {
         hipError_t e = set_lds(&attn_bwd_kernel<DH, CAUSAL, FLOATW>, LDS);
+        if constexpr (OWN_ROWS) if (e == hipSuccess) e = set_lds(&attn_bwd_rows_kernel<DH, CAUSAL>, LDS_ROWS);
         if (e != hipSuccess) return e;
         once = true;
     }
@@ -1207,9 +1774,19 @@ static hipError_t bwd_t(const AttnArgs& a) {
     const int64_t lanes = (int64_t)a.B * a.S * a.nl * (DH <= 32 ? 4 : DH == 64 ? 8 : 16);
     hipLaunchKernelGGL((attn_dsum_kernel<DH>), dim3((unsigned)((lanes + 255) / 256)), dim3(256), 0, a.stream,
                        (const bf16_t*)a.o, (const bf16_t*)a.d_o, a.dsum, a.B, a.S, a.nl, a.dh);
-    hipLaunchKernelGGL((attn_bwd_kernel<DH, CAUSAL, FLOATW>), dim3((unsigned)(wgs_kv + wgs_q)), dim3(FTHREADS), LDS, a.stream,
-                       (const bf16_t*)a.qkv, (const bf16_t*)a.d_o, a.lse, a.dsum, (bf16_t*)a.dqkv, a.S, a.nl, a.dh, scale_log2(a.dh), BH,
-                       part_kv, part_q, ch_kv, ch_q, (int)wgs_kv);
+    bool launched = false;
+    if constexpr (OWN_ROWS) {
+        if (own_rows(CAUSAL, true, wgs_kv + wgs_q)) {
+            hipLaunchKernelGGL((attn_bwd_rows_kernel<DH, CAUSAL>), dim3((unsigned)(wgs_kv + wgs_q)), dim3(WTHREADS), LDS_ROWS, a.stream,
+                               (const bf16_t*)a.qkv, (const bf16_t*)a.d_o, a.lse, a.dsum, (bf16_t*)a.dqkv, a.S, a.nl, BH, part_kv, part_q,
+                               ch_kv, ch_q, (int)wgs_kv);
+            launched = true;
+        }
+    }
+    if (!launched)
+        hipLaunchKernelGGL((attn_bwd_kernel<DH, CAUSAL, FLOATW>), dim3((unsigned)(wgs_kv + wgs_q)), dim3(FTHREADS), LDS, a.stream,
+                           (const bf16_t*)a.qkv, (const bf16_t*)a.d_o, a.lse, a.dsum, (bf16_t*)a.dqkv, a.S, a.nl, a.dh, scale_log2(a.dh), BH,
+                           part_kv, part_q, ch_kv, ch_q, (int)wgs_kv);
     int blk0_q = 0, ncut_q = 0, blk0_kv = 0, ncut_kv = 0;
     cut_range(a, false, ch_q, &blk0_q, &ncut_q);
     cut_range(a, true, ch_kv, &blk0_kv, &ncut_kv);
