@@ -35,28 +35,65 @@ __device__ __forceinline__ float block_sum(float v, float* red) {
     return s;
 }
 
-template <typename T, int MAXC>
-__global__ __launch_bounds__(LN_THREADS) void ln_fwd_kernel(int64_t M, int64_t H, const T* __restrict__ a,
-                                                            const T* __restrict__ b,
-                                                            const T* __restrict__ gamma,
-                                                            const T* __restrict__ beta, float eps,
-                                                            T* __restrict__ z, T* __restrict__ y,
-                                                            float* __restrict__ mean,
-                                                            float* __restrict__ rstd) {
-    __shared__ float red[4];
+// Eight consecutive elements as they sit in memory (16 or 32 bytes), converted only when used: rows that are
+// still in flight cost half the registers in bfloat16.
+template <typename T> struct Raw8;
+template <> struct Raw8<float> {
+    float4 a, b;
+    __device__ __forceinline__ void load(const float* p) { a = reinterpret_cast<const float4*>(p)[0]; b = reinterpret_cast<const float4*>(p)[1]; }
+    __device__ __forceinline__ void get(float (&v)[8]) const {
+        v[0] = a.x; v[1] = a.y; v[2] = a.z; v[3] = a.w; v[4] = b.x; v[5] = b.y; v[6] = b.z; v[7] = b.w;
+    }
+};
+template <> struct Raw8<bf16_t> {
+    uint4 u;
+    __device__ __forceinline__ void load(const bf16_t* p) { u = *reinterpret_cast<const uint4*>(p); }
+    __device__ __forceinline__ void get(float (&v)[8]) const {
+        const unsigned w[4] = {u.x, u.y, u.z, u.w};
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            v[2 * i] = __uint_as_float(w[i] << 16);
+            v[2 * i + 1] = __uint_as_float(w[i] & 0xffff0000u);
+        }
+    }
+};
+
+// EARLY: every load of a row is requested before the first sum.  That takes the latency of a launch of few rows down, and costs
+// registers, i.e. rows in flight, where there are many (see fwd_t).
+template <typename T, int MAXC, int THREADS, bool EARLY>
+__global__ __launch_bounds__(THREADS) void ln_fwd_kernel(int64_t M, int64_t H, const T* __restrict__ a, const T* __restrict__ b,
+                                                         const T* __restrict__ gamma, const T* __restrict__ beta, float eps,
+                                                         T* __restrict__ z, T* __restrict__ y, float* __restrict__ mean,
+                                                         float* __restrict__ rstd) {
+    __shared__ float red[THREADS / 64];
     const int t = threadIdx.x;
     const float inv_h = 1.0f / (float)H;
     for (int64_t row = blockIdx.x; row < M; row += gridDim.x) {
+        Raw8<T> ra[MAXC], rb[MAXC];
+#pragma unroll
+        for (int i = 0; i < MAXC; ++i) {
+            const int64_t col = ((int64_t)t + THREADS * i) * 8;
+            if (EARLY && col < H) ra[i].load(a + row * H + col);
+        }
+        if (EARLY && b) {
+#pragma unroll
+            for (int i = 0; i < MAXC; ++i) {
+                const int64_t col = ((int64_t)t + THREADS * i) * 8;
+                if (col < H) rb[i].load(b + row * H + col);
+            }
+        }
         float v[MAXC][8];
         float s = 0.0f;
 #pragma unroll
         for (int i = 0; i < MAXC; ++i) {
-            const int64_t col = ((int64_t)t + LN_THREADS * i) * 8;
+            const int64_t col = ((int64_t)t + THREADS * i) * 8;
             if (col < H) {
-                load8(a + row * H + col, v[i]);
+                if (!EARLY) ra[i].load(a + row * H + col);
+                ra[i].get(v[i]);
                 if (b) {
                     float w[8];
-                    load8(b + row * H + col, w);
+                    if (!EARLY) rb[i].load(b + row * H + col);
+                    rb[i].get(w);
 #pragma unroll
                     for (int e = 0; e < 8; ++e) v[i][e] += w[e];
                 }
@@ -65,20 +102,20 @@ __global__ __launch_bounds__(LN_THREADS) void ln_fwd_kernel(int64_t M, int64_t H
                 for (int e = 0; e < 8; ++e) s += v[i][e];
             }
         }
-        const float mu = block_sum(s, red) * inv_h;
+        const float mu = block_sum<THREADS / 64>(s, red) * inv_h;
         float q = 0.0f;
 #pragma unroll
         for (int i = 0; i < MAXC; ++i) {
-            const int64_t col = ((int64_t)t + LN_THREADS * i) * 8;
+            const int64_t col = ((int64_t)t + THREADS * i) * 8;
             if (col < H) {
 #pragma unroll
                 for (int e = 0; e < 8; ++e) { v[i][e] -= mu; q = fmaf(v[i][e], v[i][e], q); }
             }
         }
-        const float rs = 1.0f / sqrtf(block_sum(q, red) * inv_h + eps);
+        const float rs = 1.0f / sqrtf(block_sum<THREADS / 64>(q, red) * inv_h + eps);
 #pragma unroll
         for (int i = 0; i < MAXC; ++i) {
-            const int64_t col = ((int64_t)t + LN_THREADS * i) * 8;
+            const int64_t col = ((int64_t)t + THREADS * i) * 8;
             if (col < H) {
                 float g[8], bt[8];
                 load8(gamma + col, g);
@@ -189,29 +226,6 @@ __global__ __launch_bounds__(LN_THREADS) void ln_bwd_tile_kernel(int64_t M, int6
         store8(pg + H, b);
     }
 }
-
-// Eight consecutive elements as they sit in memory (16 or 32 bytes), converted only when used: rows that are
-// still in flight cost half the registers in bfloat16.
-template <typename T> struct Raw8;
-template <> struct Raw8<float> {
-    float4 a, b;
-    __device__ __forceinline__ void load(const float* p) { a = reinterpret_cast<const float4*>(p)[0]; b = reinterpret_cast<const float4*>(p)[1]; }
-    __device__ __forceinline__ void get(float (&v)[8]) const {
-        v[0] = a.x; v[1] = a.y; v[2] = a.z; v[3] = a.w; v[4] = b.x; v[5] = b.y; v[6] = b.z; v[7] = b.w;
-    }
-};
-template <> struct Raw8<bf16_t> {
-    uint4 u;
-    __device__ __forceinline__ void load(const bf16_t* p) { u = *reinterpret_cast<const uint4*>(p); }
-    __device__ __forceinline__ void get(float (&v)[8]) const {
-        const unsigned w[4] = {u.x, u.y, u.z, u.w};
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            v[2 * i] = __uint_as_float(w[i] << 16);
-            v[2 * i + 1] = __uint_as_float(w[i] & 0xffff0000u);
-        }
-    }
-};
 
 // Two sums over the workgroup at once (same values returned to every thread; fixed combination order).
 template <int NW>
@@ -542,13 +556,20 @@ int64_t ln_partial_rows(int64_t M) { return (M + LN_SLAB - 1) / LN_SLAB; }
 static int64_t ln_bwd_groups(int64_t M) { return M < LN_BWD_GROUPS ? M : LN_BWD_GROUPS; }
 size_t ln_scratch_bytes(int64_t M, int64_t H) { return (size_t)ln_bwd_groups(M) * 2 * H * sizeof(float); }
 
+template <typename T, int C, int THREADS, bool EARLY>
+static hipError_t launch_fwd(const LnArgs& a) {
+    const unsigned grid = (unsigned)(a.M < 65535 * 16 ? a.M : 65535 * 16);
+    hipLaunchKernelGGL((ln_fwd_kernel<T, C, THREADS, EARLY>), dim3(grid), dim3(THREADS), 0, a.stream, a.M, a.H, (const T*)a.a, (const T*)a.b,
+                       (const T*)a.gamma, (const T*)a.beta, a.eps, (T*)a.z, (T*)a.y, a.mean, a.rstd);
+    return hipGetLastError();
+}
+// Few wide rows: all loads first, on 512 threads.  us, bfloat16, a row on 256 threads chunk by chunk and so: 500 x 16384 15.8 and 13.2;
+// many rows the other way round: 2000 x 5120 17.0 and 18.7, 2048 x 12288 33.6 and 38.1.  Narrower rows are level (launch-bound).
 template <typename T, int MAXC>
 static hipError_t fwd_t(const LnArgs& a) {
-    const unsigned grid = (unsigned)(a.M < 65535 * 16 ? a.M : 65535 * 16);
-    hipLaunchKernelGGL((ln_fwd_kernel<T, MAXC>), dim3(grid), dim3(LN_THREADS), 0, a.stream, a.M, a.H,
-                       (const T*)a.a, (const T*)a.b, (const T*)a.gamma, (const T*)a.beta, a.eps, (T*)a.z,
-                       (T*)a.y, a.mean, a.rstd);
-    return hipGetLastError();
+    if constexpr (MAXC > 2)
+        if (a.M <= 2 * compute_units()) return launch_fwd<T, MAXC / 2, 512, true>(a);
+    return launch_fwd<T, MAXC, LN_THREADS, false>(a);
 }
 template <typename T>
 static hipError_t sum_groups(const LnArgs& a, int64_t groups) {
@@ -580,10 +601,9 @@ static hipError_t bwd_t(const LnArgs& a) {
 // CU and its column sums cost more than the barriers saved (workgroup against wavefront per row, both directions together):
 // float 16384 x 2048 185 us against 203, 1024 x 2048 21.0 against 22.7; bfloat16 1001 x 1536 16.8 against 20.3.
 // Up to 1024 rows both are launch-bound and level (bfloat16 1024 x 512 13.4 against 13.7 us, float 1024 x 1024 15.6 against
-// 15.7).  At 2048 and 3072 rows a wavefront per row is ahead too (bfloat16 512 columns 17.9 against 13.6 and 22.9 against 14.0,
-// 1024 columns 19.7 against 16.7 and 25.3 against 19.1; float 1024 columns 22.7 against 20.4 and 30.1 against 25.9), so the
-// line lies higher than it need; from 4096 rows on it always is (29 -> 19 us at 4096 x 768).
-constexpr int64_t LN_WAVE_MIN_M = 4096;
+// 15.7); from 2048 on a wavefront per row is ahead (bfloat16 512 columns 17.9 against 13.6, at 3072 rows 22.9 against 14.0;
+// 1024 columns 19.7 against 16.7 and 25.3 against 19.1; float 1024 columns 22.7 against 20.4 and 30.1 against 25.9).
+constexpr int64_t LN_WAVE_MIN_M = 1536;
 template <typename T, int MAXC>
 static hipError_t fwd_wave_t(const LnArgs& a) {
     constexpr int64_t ROWS = LN_THREADS / 64;
