@@ -1713,7 +1713,9 @@ namespace {
 struct GroupTile { int option, bm, bn; bool turns; double step_us, wg_us, base_us, alone_us, alone_base_us, gelu_us; };
 constexpr GroupTile GROUP_TILES[] = {{256, 256, 256, true, 0.72, 8.0, 0, 0, 0, 4.5}, {384, 256, 128, true, 0.42, 7.5, 0, 0, 0, 2.5},
                                      {192, 192, 192, false, 0.60, 2.6, 13.0, 0.77, 4.5, 0}, {128, 128, 128, false, 0.355, 1.0, 7.5, 0.38, 4.5, 0}, {64, 64, 64, false, 0.143, 0.92, 4.5, 0.35, 2.1, 0}};
-constexpr double MEM_BYTES_PER_US = 4.5e6;     // operands and results of a launch, streamed
+// Operands and results of a launch of few rows, streamed: 100 tokens through the forward of a 12288 / 1536 shard (453 MB) take
+// 150 us on 128 x 128 tiles, 137 on 256 x 256, which have twice the loads in flight.
+constexpr double MEM_BYTES_PER_US = 4.2e6, MEM_BYTES_PER_US_SMALL = 3.5e6;
 constexpr int PP_MIN_STEPS = 12;               // k-steps of a K share
 struct PPJob { int gemm, tile0, count, nk, shares; };
 struct GroupPlan { int tile, nk[GROUP_MAX], shares[GROUP_MAX]; double us; int njobs; PPJob job[JOB_MAX]; };   // jobs: tile 256 only
@@ -1855,7 +1857,7 @@ GroupPlan make_group_plan(const GemmArgs* g, int n) {
                 work += (double)tiles[i] * p.shares[i] * p.nk[i];
                 longest = std::max(longest, (double)p.nk[i]);
                 if (p.shares[i] > 1) bytes += (double)g[i].M * g[i].N * (8.0 * p.shares[i] + 2.0);
-                floor_us += 2.0 * ((double)g[i].M * g[i].K + (double)g[i].N * g[i].K + (double)g[i].M * g[i].N) / MEM_BYTES_PER_US;
+                floor_us += 2.0 * ((double)g[i].M * g[i].K + (double)g[i].N * g[i].K + (double)g[i].M * g[i].N) / MEM_BYTES_PER_US_SMALL;
             }
             const double us = std::max(floor_us, std::max((work * gt.step_us + wgs * gt.wg_us) / cus + gt.base_us,
                                                           longest * gt.alone_us + gt.alone_base_us));
@@ -1881,10 +1883,11 @@ GroupPlan make_group_plan(const GemmArgs* g, int n) {
 // As plan_for: plans of groups are kept.
 GroupPlan plan_group(const GemmArgs* g, int n) {
     struct Entry { int64_t key[GROUP_MAX][4]; int n; unsigned gen; GroupPlan plan; };
-    constexpr int CAP = 64;
-    static Entry cache[CAP];
-    static int used = 0, next = 0;
+    constexpr int CAP = 128;                                      // a layer has 4 groups, and up to 30 single GEMMs to size its workspace
+    struct Cache { Entry entry[CAP]; int used, next; };
+    static Cache caches[2];
     static std::mutex mu;
+    Cache& c = caches[n > 1];
     Entry e{};
     e.n = n;
     e.gen = options().generation;
@@ -1893,10 +1896,11 @@ GroupPlan plan_group(const GemmArgs* g, int n) {
         std::copy(k, k + 4, e.key[i]);
     }
     std::lock_guard<std::mutex> lock(mu);
-    for (int i = 0; i < used; ++i)
-        if (cache[i].n == n && cache[i].gen == e.gen && std::equal(&e.key[0][0], &e.key[0][0] + 4 * GROUP_MAX, &cache[i].key[0][0])) return cache[i].plan;
+    for (int i = 0; i < c.used; ++i)
+        if (c.entry[i].n == n && c.entry[i].gen == e.gen && std::equal(&e.key[0][0], &e.key[0][0] + 4 * GROUP_MAX, &c.entry[i].key[0][0]))
+            return c.entry[i].plan;
     e.plan = make_group_plan(g, n);
-    cache[used < CAP ? used++ : next++ % CAP] = e;
+    c.entry[c.used < CAP ? c.used++ : c.next++ % CAP] = e;
     return e.plan;
 }
 size_t share_bytes(const GemmArgs& a, int shares) {               // float partial sums, column sums included
