@@ -253,14 +253,12 @@ __global__ __launch_bounds__(256) void attn_f32_fwd_kernel(int S, int nl, int dh
 
 // ---- dQ: workgroup = (32 queries, batch*head); also leaves D = rowsum(dO * O) for the dK/dV kernel -----------------
 template <int DH>
-__global__ __launch_bounds__(256) void attn_f32_dq_kernel(int S, int nl, int dh, int causal, int nblk, const float* __restrict__ qkv,
-                                                          const float* __restrict__ o, const float* __restrict__ lse,
-                                                          const float* __restrict__ d_o, float* __restrict__ dqkv,
-                                                          float* __restrict__ dsum) {
-    extern __shared__ __attribute__((aligned(16))) char smem[];
+__device__ __forceinline__ void attn_f32_dq(char* smem, int wg, int S, int nl, int dh, int causal, int nblk, const float* __restrict__ qkv,
+                                            const float* __restrict__ o, const float* __restrict__ lse, const float* __restrict__ d_o,
+                                            float* __restrict__ dqkv, float* dsum) {
     constexpr int TB = xtile_bytes<DH>(), NL = xloads<DH>();
     const int lane = threadIdx.x & 63, half = lane >> 5, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int qb = nblk - 1 - (int)blockIdx.x % nblk, bh = blockIdx.x / nblk, b = bh / nl, h = bh % nl;
+    const int qb = nblk - 1 - wg % nblk, bh = wg / nblk, b = bh / nl, h = bh % nl;
     const int64_t ld = 3LL * nl * dh, ldo = (int64_t)nl * dh;
     const float* qbase = qkv + (int64_t)b * S * ld + (int64_t)h * dh;
     const i32x4 rk = xrsrc(qbase + (int64_t)nl * dh, ld, S, dh), rv = xrsrc(qbase + 2LL * nl * dh, ld, S, dh);
@@ -339,14 +337,14 @@ __global__ __launch_bounds__(256) void attn_f32_dq_kernel(int S, int nl, int dh,
 }
 
 // ---- dK, dV: workgroup = (32 keys, batch*head) -----------------------------------------------------------------------
-template <int DH>
-__global__ __launch_bounds__(256) void attn_f32_dkv_kernel(int S, int nl, int dh, int causal, int nblk, const float* __restrict__ qkv,
-                                                           const float* __restrict__ lse, const float* __restrict__ d_o,
-                                                           float* __restrict__ dqkv, const float* __restrict__ dsum) {
-    extern __shared__ __attribute__((aligned(16))) char smem[];
+// OWN_D: D of the query tiles is worked out here (and stored, the same value that dQ's workgroups store), not read.
+template <int DH, bool OWN_D>
+__device__ __forceinline__ void attn_f32_dkv(char* smem, int wg, int S, int nl, int dh, int causal, int nblk, const float* __restrict__ qkv,
+                                             const float* __restrict__ o, const float* __restrict__ lse, const float* __restrict__ d_o,
+                                             float* __restrict__ dqkv, float* dsum) {
     constexpr int TB = xtile_bytes<DH>(), NL = xloads<DH>();
     const int lane = threadIdx.x & 63, half = lane >> 5, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int kb = (int)blockIdx.x % nblk, bh = blockIdx.x / nblk, b = bh / nl, h = bh % nl;   // long strips first
+    const int kb = wg % nblk, bh = wg / nblk, b = bh / nl, h = bh % nl;   // long strips first
     const int64_t ld = 3LL * nl * dh, ldo = (int64_t)nl * dh;
     const float* qbase = qkv + (int64_t)b * S * ld + (int64_t)h * dh;
     const i32x4 rq = xrsrc(qbase, ld, S, dh), rg = xrsrc(d_o + (int64_t)b * S * ldo + (int64_t)h * dh, ldo, S, dh);
@@ -361,7 +359,7 @@ __global__ __launch_bounds__(256) void attn_f32_dkv_kernel(int S, int nl, int dh
 #pragma unroll
         for (int v = 0; v < 16; ++v) { dk[d][v] = 0.0f; dv[d][v] = 0.0f; }
     const float* lrow = lse + (int64_t)bh * S;
-    const float* drow = dsum + (int64_t)bh * S;
+    float* drow = dsum + (int64_t)bh * S;
     char* qt_ = smem + wave * 2 * TB;
     const unsigned lq = (unsigned)(uintptr_t)(lds_void_ptr)qt_, lg = lq + TB;
     float* terms = reinterpret_cast<float*>(smem + 8 * TB) + wave * 2 * XT;   // LSE, D of the tile's queries
@@ -371,6 +369,17 @@ __global__ __launch_bounds__(256) void attn_f32_dkv_kernel(int S, int nl, int dh
     xoffsets<DH>(offg, ldo, dh, lane);
     auto term = [&](int t) {                                      // lanes 0..31: LSE, lanes 32..63: D
         const int i = t * XT + (lane & 31);
+        if constexpr (OWN_D) {
+            float gr[DH / 2], orr[DH / 2], D = 0.0f;
+            const int64_t orow = (int64_t)b * S * ldo + (int64_t)h * dh;
+            xrow<DH>(gr, d_o + orow, ldo, i, S, dh, lane);
+            xrow<DH>(orr, o + orow, ldo, i, S, dh, lane);
+#pragma unroll
+            for (int e = 0; e < DH / 2; ++e) D = fmaf(gr[e], orr[e], D);
+            D += xother(D);
+            if (half == 0 && i < S) drow[i] = D;
+            return i < S ? (half ? D : lrow[i]) : 0.0f;
+        }
         return i < S ? (half ? drow[i] : lrow[i]) : 0.0f;
     };
     float tn = 0.0f;
@@ -440,6 +449,31 @@ __global__ __launch_bounds__(256) void attn_f32_dkv_kernel(int S, int nl, int dh
     }
 }
 
+template <int DH>
+__global__ __launch_bounds__(256) void attn_f32_dq_kernel(int S, int nl, int dh, int causal, int nblk, const float* __restrict__ qkv,
+                                                          const float* __restrict__ o, const float* __restrict__ lse,
+                                                          const float* __restrict__ d_o, float* __restrict__ dqkv, float* dsum) {
+    extern __shared__ __attribute__((aligned(16))) char smem[];
+    attn_f32_dq<DH>(smem, blockIdx.x, S, nl, dh, causal, nblk, qkv, o, lse, d_o, dqkv, dsum);
+}
+template <int DH>
+__global__ __launch_bounds__(256) void attn_f32_dkv_kernel(int S, int nl, int dh, int causal, int nblk, const float* __restrict__ qkv,
+                                                           const float* __restrict__ lse, const float* __restrict__ d_o,
+                                                           float* __restrict__ dqkv, float* dsum) {
+    extern __shared__ __attribute__((aligned(16))) char smem[];
+    attn_f32_dkv<DH, false>(smem, blockIdx.x, S, nl, dh, causal, nblk, qkv, nullptr, lse, d_o, dqkv, dsum);
+}
+// Both in one launch of n + n workgroups: dK/dV does not wait for D, it works it out for its query tiles as well.
+template <int DH>
+__global__ __launch_bounds__(256) void attn_f32_bwd_kernel(int n, int S, int nl, int dh, int causal, int nblk, const float* __restrict__ qkv,
+                                                           const float* __restrict__ o, const float* __restrict__ lse,
+                                                           const float* __restrict__ d_o, float* __restrict__ dqkv, float* dsum) {
+    extern __shared__ __attribute__((aligned(16))) char smem[];
+    const int wg = blockIdx.x;                                    // uniform: one kind per workgroup
+    if (wg < n) attn_f32_dkv<DH, true>(smem, wg, S, nl, dh, causal, nblk, qkv, o, lse, d_o, dqkv, dsum);
+    else attn_f32_dq<DH>(smem, wg - n, S, nl, dh, causal, nblk, qkv, o, lse, d_o, dqkv, dsum);
+}
+
 // ---- host ----------------------------------------------------------------------------------------------------------------
 bool attn_f32_supported(const AttnArgs& a) {
     // 16-byte chunks of a head's row; 32-bit byte offsets inside a (batch, head) slice, 32 rows past its end included; fewer
@@ -451,10 +485,15 @@ template <int DH>
 static hipError_t set_lds() {
     hipError_t e = hipSuccess;
     for (const void* k : {reinterpret_cast<const void*>(&attn_f32_fwd_kernel<DH>), reinterpret_cast<const void*>(&attn_f32_dq_kernel<DH>),
-                          reinterpret_cast<const void*>(&attn_f32_dkv_kernel<DH>)})
+                          reinterpret_cast<const void*>(&attn_f32_dkv_kernel<DH>), reinterpret_cast<const void*>(&attn_f32_bwd_kernel<DH>)})
         if (e == hipSuccess) e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, xlds_bytes<DH>());
     return e;
 }
+// dQ and dK/dV in one launch where all their workgroups find a compute unit at once: neither waits for the other, and a launch is
+// saved.  us, two launches and one, n workgroups of each kind: n = 16 (2 x 128 tokens, 2 heads of 64, causal) 21.0 and 13.2, n = 64
+// 31.4 and 21.7, n = 128 52 and 37 (heads of 128: 171 and 129); with more of them D, worked out again, costs more than that: n = 256
+// 58 and 63, n = 512 96 and 115.
+static bool one_launch(int64_t n) { return 2 * n <= compute_units(); }
 template <int DH>
 static hipError_t launch(const AttnArgs& a, bool bwd) {
     static const hipError_t attr = set_lds<DH>();
@@ -464,6 +503,12 @@ static hipError_t launch(const AttnArgs& a, bool bwd) {
     if (!bwd) {
         hipLaunchKernelGGL(attn_f32_fwd_kernel<DH>, grid, wg, xlds_bytes<DH>(), a.stream, a.S, a.nl, a.dh, a.causal, nblk,
                            (const float*)a.qkv, (float*)a.o, a.lse);
+        return hipGetLastError();
+    }
+    if (one_launch((int64_t)nblk * a.B * a.nl)) {
+        const dim3 both(2 * grid.x);
+        hipLaunchKernelGGL(attn_f32_bwd_kernel<DH>, both, wg, xlds_bytes<DH>(), a.stream, (int)grid.x, a.S, a.nl, a.dh, a.causal, nblk,
+                           (const float*)a.qkv, (const float*)a.o, a.lse, (const float*)a.d_o, (float*)a.dqkv, a.dsum);
         return hipGetLastError();
     }
     hipLaunchKernelGGL(attn_f32_dq_kernel<DH>, grid, wg, xlds_bytes<DH>(), a.stream, a.S, a.nl, a.dh, a.causal, nblk,
