@@ -651,21 +651,26 @@ __global__ __launch_bounds__(256) void attn_dsum_kernel(const bf16_t* __restrict
 }
 
 // =================================================================================================
-// dK, dV.  Workgroup = (key block of 128, batch*head), 8 wavefronts: wavefront w owns the 32 keys of
-// sub-block w % 4; wavefronts 0..3 accumulate dV = P^T dO (they need the scores only), wavefronts 4..7
-// accumulate dK = dS^T Q (scores and dP).  The scores are computed by both, which costs a quarter more
-// matrix-core work but halves the accumulators and fragments a wavefront holds (two wavefronts per
-// SIMD) and shortens its dependent chain per tile.  Q, dO (and LSE, D) are streamed in tiles of 64
-// queries.  Score tile is untransposed: lane = key (l%32), registers = queries 8i + 4*(l/32) + j.
+// dK, dV.  Workgroup = (key block of 128, batch*head), 8 wavefronts: wavefronts w and w + 4 share the 32 keys of sub-block w.
+// Wavefront w works out the scores and probabilities P and accumulates dV = P^T dO; wavefront w + 4 works out dP and
+// accumulates dK = dS^T Q from the same P, which it gets through LDS in float, one sub-tile of 32 queries later.  That is
+// two products of a sub-tile on either, half of the accumulators and fragments each (two wavefronts per SIMD), and one's
+// exponentials beside the other's products.  A SIMD's matrix work and vector work still add up for the most part.  Backward
+// with the scores worked out by both and so, us: 8192 tokens, 12 heads of 128, causal 831 and 771; 2 x 2048, 10 heads 115 and
+// 110; 8 x 512, 8 heads without a mask 52.4 and 50.0, heads of 64 level (4 heads 19.1 and 18.0; 2 x 1024, 16 heads 35.7 and 36.8).
+// Q, dO (and LSE, D) are streamed in tiles of 64 queries through three stages: dK still reads the tile before.
+// Score tile is untransposed: lane = key (l%32), registers = queries 8i + 4*(l/32) + j.
 // =================================================================================================
+constexpr int DKV_P_BYTES = 32 * 32 * 4;                  // P of a sub-tile and sub-block of keys
+template <int DH> constexpr int dkv_lds_bytes() { return 3 * (2 * tile_bytes<DH>() + 2 * TILE * 4) + 2 * 4 * DKV_P_BYTES; }
 template <int DH, bool CAUSAL, bool FLOATW, bool DK_ROLE>
 __device__ __forceinline__ void attn_dkv_body(char* smem, const bf16_t* __restrict__ qkv,
                                               const bf16_t* __restrict__ d_o, const float* __restrict__ lse,
                                               const float* __restrict__ dsum, bf16_t* __restrict__ dqkv,
                                               int S, int nl, int dh, float c2f, int bh, const Chunk& ck, float* __restrict__ pslot) {
-    constexpr int TB = tile_bytes<DH>();
+    constexpr int TB = tile_bytes<DH>(), NF = DH / 16, NT = DH / 32, HALF = 32 * DH * 2;
     constexpr int NCH = NCHUNKS<DH, FTHREADS>;
-    constexpr int STAGE = 2 * TB + 2 * TILE * 4;          // Q tile, dO tile, LSE*log2e, D
+    constexpr int TERMS = 6 * TB, PS = TERMS + 3 * 2 * TILE * 4;      // three Q tiles, three dO tiles, three times LSE*log2e and D, P
     const int t = threadIdx.x, lane = t & 63, wave = t >> 6, half = lane >> 5;
     const int kb = ck.blk;
     const int b = bh / nl, h = bh % nl;
@@ -681,15 +686,12 @@ __device__ __forceinline__ void attn_dkv_body(char* smem, const bf16_t* __restri
     const float scale = 1.0f / sqrtf((float)dh);
     const float c2 = FLOATW ? c2f : LOG2E * scale;
 
-    bf16x8 kf[DH / 16], vf[DK_ROLE ? DH / 16 : 1];
+    bf16x8 own[NF];                                        // K for the scores, V for dP
 #pragma unroll
-    for (int ks = 0; ks < DH / 16; ++ks) {
-        kf[ks] = frag_k_global(kbase, ld, kv, S, dh, ks, lane);
-        if (DK_ROLE) vf[ks] = frag_k_global(vbase, ld, kv, S, dh, ks, lane);
-    }
-    f32x16 acc[DH / 32];                                   // dK (DK_ROLE) or dV
+    for (int ks = 0; ks < NF; ++ks) own[ks] = frag_k_global(DK_ROLE ? vbase : kbase, ld, kv, S, dh, ks, lane);
+    f32x16 acc[NT];                                        // dK (DK_ROLE) or dV
 #pragma unroll
-    for (int dt = 0; dt < DH / 32; ++dt) acc[dt] = zero16();
+    for (int dt = 0; dt < NT; ++dt) acc[dt] = zero16();
 
     const int qt0 = ck.t0, ntiles = ck.t1;                // query tiles of this chunk (the strip starts at the diagonal)
     const unsigned lds0 = (unsigned)(uintptr_t)(lds_void_ptr)smem;
@@ -700,105 +702,147 @@ __device__ __forceinline__ void attn_dkv_body(char* smem, const bf16_t* __restri
     dma_offsets<DH, FTHREADS>(off_do, ldo, dh, t);
     float rl = 0.0f, rd = 0.0f;
     // Q and dO rows of tile qt straight into LDS; LSE and D of its rows through registers (r2s stores them)
-    auto g2r = [&](int qt, unsigned stage) {
-        tile_dma<DH, FTHREADS>(desc_q, stage, off_q, (unsigned)qt * TILE * (unsigned)(ld * 2), wave_u);
-        tile_dma<DH, FTHREADS>(desc_do, stage + TB, off_do, (unsigned)qt * TILE * (unsigned)(ldo * 2), wave_u);
+    auto g2r = [&](int qt, int stage) {
+        tile_dma<DH, FTHREADS>(desc_q, lds0 + stage * TB, off_q, (unsigned)qt * TILE * (unsigned)(ld * 2), wave_u);
+        tile_dma<DH, FTHREADS>(desc_do, lds0 + (3 + stage) * TB, off_do, (unsigned)qt * TILE * (unsigned)(ldo * 2), wave_u);
         if (t < TILE) {
             int qi = qt * TILE + t;
             rl = qi < S ? lrow[qi] * LOG2E : 0.0f;
             rd = qi < S ? drow[qi] : 0.0f;
         }
     };
-    auto r2s = [&](char* st) {
+    auto r2s = [&](int stage) {
         if (t < TILE) {
-            reinterpret_cast<float*>(st + 2 * TB)[t] = rl;
-            reinterpret_cast<float*>(st + 2 * TB)[TILE + t] = rd;
+            float* st = reinterpret_cast<float*>(smem + TERMS) + stage * 2 * TILE;
+            st[t] = rl;
+            st[TILE + t] = rd;
         }
     };
-    if (qt0 < ntiles) { g2r(qt0, lds0); r2s(smem); }
+    // LDS addresses in stage 0: rows as they are (scores: Q, dP: dO), transposed (dV: dO, dK: Q), LSE or D, P
+    unsigned ka[NF], ta[NT][2];
 #pragma unroll
-    for (int ks = 0; ks < DH / 16; ++ks) {
-        settle(kf[ks]);
-        if (DK_ROLE) settle(vf[ks]);
-    }
+    for (int ks = 0; ks < NF; ++ks) { ka[ks] = lds0 + (DK_ROLE ? 3 * TB : 0) + frag_k_off<DH>(0, ks, lane); keep_in_register(ka[ks]); }
+#pragma unroll
+    for (int dt = 0; dt < NT; ++dt)
+#pragma unroll
+        for (int g = 0; g < 2; ++g) {
+            ta[dt][g] = lds0 + (DK_ROLE ? 0 : 3 * TB) + frag_t_off<DH>(dt * 32, 0, g, lane);
+            keep_in_register(ta[dt][g]);
+        }
+    unsigned terms = lds0 + TERMS + (DK_ROLE ? TILE * 4 : 0) + half * 16;
+    char* pbuf = smem + PS + (wave_u & 3) * DKV_P_BYTES + lane * 16;
+    if (qt0 < ntiles) { g2r(qt0, 0); r2s(0); }
+#pragma unroll
+    for (int ks = 0; ks < NF; ++ks) settle(own[ks]);
     dma_wait();
     __syncthreads();
-    for (int qt = qt0; qt < ntiles; ++qt) {
-        const char* st = smem + ((qt - qt0) & 1) * STAGE;
-        char* nxt = smem + ((qt - qt0 + 1) & 1) * STAGE;
-        const char* qs = st;
-        const char* dos = st + TB;
-        const float* ls = reinterpret_cast<const float*>(st + 2 * TB);
-        const float* ds_ = ls + TILE;
-        const bool more = qt + 1 < ntiles;
-        if (more) g2r(qt + 1, lds0 + ((qt - qt0 + 1) & 1) * STAGE);
+
+    f32x16 x;                                              // scores, then P; or dP, then dS
+    bool pending = false;                                  // dP of the sub-tile before waits for its P
+    auto product = [&](auto stg, auto sbc) __attribute__((always_inline)) {
+        constexpr int OFF = decltype(stg)::value * TB + decltype(sbc)::value * HALF;
+        bf16x8 fr[NF];
 #pragma unroll
-        for (int sb = 0; sb < 2; ++sb) {
-            const int qs0 = qt * TILE + sb * 32;
-            if (qs0 >= S || (CAUSAL && qs0 + 31 < k0)) continue;          // wavefront-uniform
-            // Fragments of all MFMA phases (Q for S, dO for dP in the dK role, then Q or dO transposed) through a
-            // rolling window of W registers, as in the dQ kernel.
-            f32x16 s = zero16(), dp = zero16();
-            constexpr int NF = DH / 16, W = DH <= 64 ? NF : NF / 2, NP = DK_ROLE ? 2 * NF : NF;
-            bf16x8 fr[W];
-            const char* src = DK_ROLE ? qs : dos;                          // dK += dS^T Q ; dV += P^T dO
-            auto fetch = [&](int i) {
-                if (i < NF) return frag_k<DH>(qs, sb * 32, i, lane);
-                if (i < NP) return frag_k<DH>(dos, sb * 32, i - NF, lane);
-                const int k = i - NP;
-                return frag_t<DH>(src, (k >> 1) * 32, sb * 32 + (k & 1) * 16, lane);
-            };
+        for (int i = 0; i < NF; ++i) fr[i] = lds_frag_k<OFF>(ka[i]);
+        __builtin_amdgcn_sched_barrier(0);
+        __builtin_amdgcn_s_setprio(1);
+        x = zero16();
 #pragma unroll
-            for (int i = 0; i < W; ++i) fr[i] = fetch(i);
-            __builtin_amdgcn_sched_barrier(0);
-            __builtin_amdgcn_s_setprio(1);
+        for (int i = 0; i < NF; ++i) x = MFMA(fr[i], own[i], x);
+        __builtin_amdgcn_s_setprio(0);
+    };
+    // x, P or dS, times the rows of its sub-tile, transposed
+    auto fetch_t = [&](auto stg, auto sbc, bf16x8 (&fr)[NF]) __attribute__((always_inline)) {
+        constexpr int OFF = decltype(stg)::value * TB + decltype(sbc)::value * HALF;
 #pragma unroll
-            for (int i = 0; i < NP; ++i) {
-                if (i < NF) s = MFMA(fr[i % W], kf[i], s);
-                else dp = MFMA(fr[i % W], vf[DK_ROLE ? i - NF : 0], dp);
-                fr[i % W] = fetch(i + W);
-                __builtin_amdgcn_sched_barrier(0);
-            }
-            __builtin_amdgcn_s_setprio(0);
-            const bool need_mask = qs0 + 31 >= S || k0 + 31 >= S || (CAUSAL && k0 + 31 > qs0);
-            if (need_mask) {                          // wave-uniform: only tiles on the diagonal or at the end of S
+        for (int k = 0; k < NF; ++k)
+            fr[k] = k & 1 ? lds_frag_t<OFF + 16 * DH * 2>(ta[k >> 1][0], ta[k >> 1][1]) : lds_frag_t<OFF>(ta[k >> 1][0], ta[k >> 1][1]);
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    auto collect = [&](const bf16x8 (&fr)[NF]) __attribute__((always_inline)) {
+        bf16x8 g[weight_terms<FLOATW>()][2];
+        split_terms<FLOATW>(x, g);
+        __builtin_amdgcn_s_setprio(1);
+#pragma unroll
+        for (int k = 0; k < NF; ++k) acc[k >> 1] = mfma_terms<FLOATW>(fr[k], g, k & 1, acc[k >> 1]);
+        __builtin_amdgcn_s_setprio(0);
+    };
+    auto finish_dk = [&](auto stg, auto sbc) __attribute__((always_inline)) {
+        constexpr int STG = decltype(stg)::value, SB = decltype(sbc)::value;
+        f32x4 p[4], d[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            p[i] = *reinterpret_cast<const f32x4*>(pbuf + SB * 4 * DKV_P_BYTES + i * 1024);
+            d[i] = lds_f4(terms + STG * 2 * TILE * 4 + SB * 128 + i * 32);
+        }
+        bf16x8 fr[NF];
+        fetch_t(stg, sbc, fr);
+#pragma unroll
+        for (int v = 0; v < 16; ++v) x[v] = p[v >> 2][v & 3] * (x[v] - d[v >> 2][v & 3]);
+        collect(fr);
+    };
+    // A sub-tile of 32 queries: all of it in the dV role; dP, after the rest of the sub-tile before, in the dK role.
+    auto slot = [&](int qt, auto stg, auto sbc, auto before) __attribute__((always_inline)) {
+        constexpr int STG = decltype(stg)::value, SB = decltype(sbc)::value;
+        const int qs0 = qt * TILE + SB * 32;
+        const bool skip = qs0 >= S || (CAUSAL && qs0 + 31 < k0);         // wavefront-uniform, alike in both roles
+        if constexpr (DK_ROLE) {
+            if (pending) finish_dk(before, std::integral_constant<int, SB ^ 1>{});
+            pending = !skip;
+            if (!skip) product(stg, sbc);
+        } else if (!skip) {
+            product(stg, sbc);
+            bf16x8 fr[NF];
+            fetch_t(stg, sbc, fr);
+            if (qs0 + 31 >= S || k0 + 31 >= S || (CAUSAL && k0 + 31 > qs0)) {   // wave-uniform: on the diagonal, at the end of S
 #pragma unroll
                 for (int v = 0; v < 16; ++v) {
                     int qi = qs0 + 8 * (v >> 2) + 4 * half + (v & 3);
                     bool ok = qi < S && kv < S && (!CAUSAL || kv <= qi);
-                    s[v] = ok ? s[v] : -INFINITY;         // exp2(-inf) = 0
+                    x[v] = ok ? x[v] : -INFINITY;         // exp2(-inf) = 0
                 }
             }
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
-                const float4 l4 = *reinterpret_cast<const float4*>(ls + sb * 32 + 8 * i + 4 * half);
-                float4 d4 = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-                if (DK_ROLE) d4 = *reinterpret_cast<const float4*>(ds_ + sb * 32 + 8 * i + 4 * half);
-                const float lv[4] = {l4.x, l4.y, l4.z, l4.w}, dvv[4] = {d4.x, d4.y, d4.z, d4.w};
+                const f32x4 l = lds_f4(terms + STG * 2 * TILE * 4 + SB * 128 + i * 32);
+                f32x4 p;
 #pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    int v = 4 * i + j;
-                    const float p = fast_exp2(fmaf(s[v], c2, -lv[j]));
-                    s[v] = DK_ROLE ? p * (dp[v] - dvv[j]) : p;             // dS, or P
-                }
+                for (int j = 0; j < 4; ++j) p[j] = x[4 * i + j] = fast_exp2(fmaf(x[4 * i + j], c2, -l[j]));
+                *reinterpret_cast<f32x4*>(pbuf + SB * 4 * DKV_P_BYTES + i * 1024) = p;
             }
-            bf16x8 g[weight_terms<FLOATW>()][2];
-            split_terms<FLOATW>(s, g);
-            __builtin_amdgcn_s_setprio(1);
-#pragma unroll
-            for (int k = 0; k < NF; ++k) {
-                acc[k >> 1] = mfma_terms<FLOATW>(fr[k % W], g, k & 1, acc[k >> 1]);
-                if (k + W < NF) {
-                    fr[k % W] = fetch(NP + k + W);
-                    __builtin_amdgcn_sched_barrier(0);
-                }
-            }
-            __builtin_amdgcn_s_setprio(0);
+            collect(fr);
         }
-        if (more) r2s(nxt);
+    };
+    using C0 = std::integral_constant<int, 0>; using C1 = std::integral_constant<int, 1>; using C2 = std::integral_constant<int, 2>;
+    auto step = [&](int qt, auto stg, auto next, auto before) __attribute__((always_inline)) {
+        const bool more = qt + 1 < ntiles;
+        if (more) g2r(qt + 1, decltype(next)::value);     // read for the last time before the barrier before last
+        slot(qt, stg, C0{}, before);
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // P; the next tile stays in flight
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+        __builtin_amdgcn_sched_barrier(0);
+        slot(qt, stg, C1{}, stg);
+        if (more) r2s(decltype(next)::value);
         dma_wait();
         __syncthreads();
+    };
+    for (int qt = qt0; qt < ntiles;) {
+        step(qt, C0{}, C1{}, C2{});
+        if (++qt >= ntiles) break;
+        step(qt, C1{}, C2{}, C0{});
+        if (++qt >= ntiles) break;
+        step(qt, C2{}, C0{}, C1{});
+        ++qt;
     }
+    if (DK_ROLE && pending) {
+        const int last = (ntiles - 1 - qt0) % 3;          // the stage of the last tile
+        terms += last * 2 * TILE * 4;
+#pragma unroll
+        for (int dt = 0; dt < NT; ++dt) { ta[dt][0] += last * TB; ta[dt][1] += last * TB; }
+        finish_dk(C0{}, C1{});
+    }
+    if (FLOATW) __syncthreads();                          // the ring is overwritten below
     float z = 0.0f;
     if (ck.nch > 1) {
         // one chunk of a longer strip: unscaled float partial, [dK | dV][key][dh]
@@ -1749,7 +1793,7 @@ static hipError_t fwd_t(const AttnArgs& a) {
 
 template <int DH, bool CAUSAL, bool FLOATW>
 static hipError_t bwd_t(const AttnArgs& a) {
-    constexpr int LDS_KV = 2 * (2 * tile_bytes<DH>() + 2 * TILE * 4);
+    constexpr int LDS_KV = dkv_lds_bytes<DH>();
     constexpr int LDS_Q = dq_lds_bytes<DH>();
     constexpr int LDS = LDS_KV > LDS_Q ? LDS_KV : LDS_Q;
     constexpr bool OWN_ROWS = DH == 64 && !FLOATW;
