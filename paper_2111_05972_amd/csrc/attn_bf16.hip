@@ -23,7 +23,7 @@
 // tile (rows = keys, columns = queries), so one lane owns one query: row max / row sum are in-lane
 // reductions plus one exchange with lane l^32, and the probabilities are already laid out as the
 // K-operand of the next MFMA (P never passes through LDS).  The dK/dV kernel computes the
-// untransposed tile (lane = key) for the same reason.  Operands that are needed with the other
+// untransposed tile (lane = key) for the same reason, and hands P to the wavefront of dK in float.  Operands that are needed with the other
 // dimension contiguous (V in forward, Q and dO in dK/dV, K in dQ) are read from LDS with the
 // transposing ds_read_b64_tr_b16.
 //
@@ -31,7 +31,7 @@
 // block) or dQ workgroups (per query block), each accumulating in registers in a fixed order: no atomics, results
 // are run-to-run identical.
 //
-// Streaming.  K/V (or Q/dO) tiles of 64 rows go from global memory straight into a two-stage LDS ring (buffer
+// Streaming.  K/V (or Q/dO) tiles of 64 rows go from global memory straight into a ring of two or three LDS stages (buffer
 // loads with the LDS flag), the tile of step t+1 requested at the start of step t; fragments are read from LDS a
 // phase ahead of the MFMAs that use them.  A tile step is bound by vector arithmetic (exp2, scaling, conversions),
 // not by the matrix cores.
@@ -119,35 +119,14 @@ template <typename T> __device__ __forceinline__ void settle(const T& v) { asm v
 // that hands the tile to the readers.
 __device__ __forceinline__ void dma_wait() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
 
-// MFMA operand with the head dimension as K: row (row_base + lane%32), dh = 16*ks + 8*(lane/32) + 0..7
-template <int DH>
-__device__ __forceinline__ bf16x8 frag_k(const char* tile, int row_base, int ks, int lane) {
-    int row = row_base + (lane & 31);
-    int c = 2 * ks + (lane >> 5);
-    return *reinterpret_cast<const bf16x8*>(tile + row * (DH * 2) + ((c ^ swz<DH>(row)) << 4));
-}
-// MFMA operand with the tile's ROW index as K: column (d_base + lane%32); element e = 4h + j holds
-// row r_base + 8h + 4*(lane/32) + j, which is the order accumulator registers 0..7 hold their rows.
-template <int DH>
-__device__ __forceinline__ bf16x8 frag_t(const char* tile, int d_base, int r_base, int lane) {
-    int l16 = lane & 15;
-    int d = d_base + (lane & 16) + 4 * (l16 & 3);
-    bf16x8 out;
-#pragma unroll
-    for (int h = 0; h < 2; ++h) {
-        int row = r_base + 8 * h + 4 * (lane >> 5) + (l16 >> 2);
-        int off = row * (DH * 2) + ((((d >> 3) ^ swz<DH>(row))) << 4) + (d & 7) * 2;
-        s16x4 v = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_ptr)(tile + off));
-        bf16x4 b = __builtin_bit_cast(bf16x4, v);
-        out[4 * h + 0] = b[0]; out[4 * h + 1] = b[1]; out[4 * h + 2] = b[2]; out[4 * h + 3] = b[3];
-    }
-    return out;
-}
-// Byte offsets of those two kinds of read inside a tile, for kernels that keep them in registers across the streaming
-// loop (computed per read they are ~100 vector instructions per tile step, more than the softmax arithmetic itself;
-// matrix and vector instructions do not overlap on a SIMD, so every one of them is matrix time lost).  Both are
-// unchanged by adding a multiple of 16 to the row (the swizzle uses row bits 0..3 only): a second block of 16 rows is
-// the same offset plus 16 rows.
+// Two kinds of read, as byte offsets inside a tile that stay in registers across the streaming loop (computed per read they are
+// ~100 vector instructions per tile step, more than the softmax arithmetic itself; matrix and vector instructions do not overlap
+// on a SIMD, so every one of them is matrix time lost; backward over 8192 tokens, 12 heads of 128, causal: 771 and 761 us with
+// dQ's computed per read and kept).  Both are unchanged by adding a multiple of 16 to the row (the swizzle uses row bits 0..3
+// only): a second block of 16 rows is the same offset plus 16 rows.
+//   frag_k_off   MFMA operand with the head dimension as K: row (row_base + lane%32), dh = 16*ks + 8*(lane/32) + 0..7
+//   frag_t_off   MFMA operand with the tile's ROW index as K: column (d_base + lane%32); element e = 4h + j holds row
+//                r_base + 8h + 4*(lane/32) + j, which is the order accumulator registers 0..7 hold their rows
 template <int DH> __device__ __forceinline__ unsigned frag_k_off(int row_base, int ks, int lane) {
     int row = row_base + (lane & 31);
     int c = 2 * ks + (lane >> 5);
@@ -966,24 +945,32 @@ __device__ __forceinline__ void attn_dq_wg(char* smem, const bf16_t* __restrict_
     settle(dq_d);
     dma_wait();
     __syncthreads();
-    for (int kt = tile0; kt < ntiles; ++kt) {
-        const char* ks_ = smem + ((kt - tile0) & 1) * 2 * TB;
-        const char* vs_ = ks_ + TB;
+    // LDS addresses of the fragments in stage 0, this wavefront's 32 keys; V lies TB behind K.  Kept in registers as in forward.
+    constexpr int NF = DH / 16;
+    unsigned ka[NF], ta[DH / 32][2];
+#pragma unroll
+    for (int ks = 0; ks < NF; ++ks) { ka[ks] = lds0 + frag_k_off<DH>(kvh * 32, ks, lane); keep_in_register(ka[ks]); }
+#pragma unroll
+    for (int dt = 0; dt < DH / 32; ++dt)
+#pragma unroll
+        for (int g = 0; g < 2; ++g) { ta[dt][g] = lds0 + frag_t_off<DH>(dt * 32, kvh * 32, g, lane); keep_in_register(ta[dt][g]); }
+    auto step = [&](int kt, auto stg) __attribute__((always_inline)) {
+        constexpr int OFF = decltype(stg)::value * 2 * TB;
         // the other stage was last read before the barrier that ended the previous step
-        if (kt + 1 < ntiles) fetch_tile(kt + 1, lds0 + ((kt - tile0 + 1) & 1) * 2 * TB);
+        if (kt + 1 < ntiles) fetch_tile(kt + 1, lds0 + (1 - decltype(stg)::value) * 2 * TB);
         const int kv0 = kt * TILE + kvh * 32;
         if (kv0 < kv_end && !(CAUSAL && kv0 > q0 + 31)) {                 // wavefront-uniform
             // The fragments of the three MFMA phases (K for S, V for dP, K transposed for dQ) form one sequence that
             // is read through a rolling window of W registers: fragment i + W is requested right after the MFMA
             // that used fragment i, so LDS latency hides under W MFMAs instead of being paid before every one.
             f32x16 s = zero16(), dp = zero16();
-            constexpr int NF = DH / 16, W = DH <= 64 ? NF : NF / 2;
+            constexpr int W = DH <= 64 ? NF : NF / 2;
             bf16x8 fr[W];
-            auto fetch = [&](int i) {                       // i is a compile-time constant after unrolling
-                if (i < NF) return frag_k<DH>(ks_, kvh * 32, i, lane);
-                if (i < 2 * NF) return frag_k<DH>(vs_, kvh * 32, i - NF, lane);
+            auto fetch = [&](int i) __attribute__((always_inline)) {      // i is a compile-time constant after unrolling
+                if (i < NF) return lds_frag_k<OFF>(ka[i]);
+                if (i < 2 * NF) return lds_frag_k<OFF + TB>(ka[i - NF]);
                 const int k = i - 2 * NF;
-                return frag_t<DH>(ks_, (k >> 1) * 32, kvh * 32 + (k & 1) * 16, lane);
+                return k & 1 ? lds_frag_t<OFF + 16 * DH * 2>(ta[k >> 1][0], ta[k >> 1][1]) : lds_frag_t<OFF>(ta[k >> 1][0], ta[k >> 1][1]);
             };
 #pragma unroll
             for (int i = 0; i < W; ++i) fr[i] = fetch(i);
@@ -1023,6 +1010,12 @@ __device__ __forceinline__ void attn_dq_wg(char* smem, const bf16_t* __restrict_
         }
         dma_wait();
         __syncthreads();
+    };
+    for (int kt = tile0; kt < ntiles;) {
+        step(kt, std::integral_constant<int, 0>{});
+        if (++kt >= ntiles) break;
+        step(kt, std::integral_constant<int, 1>{});
+        ++kt;
     }
     float* mg = reinterpret_cast<float*>(smem) + (qs * (DH / 2)) * 64 + lane;   // element i at mg[i * 64]
     if (kvh == 1) {
