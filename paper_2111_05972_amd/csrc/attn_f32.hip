@@ -7,7 +7,7 @@
 // fourth 32-row tile of the other side with LDS tiles of their own (no barrier in the loop), and the four results are
 // combined through LDS at the end in wavefront order.
 //
-// Measured (16 heads x 512 x 64, no mask): forward 19.6 us (1.07 GFLOP), backward 57 us, where one wavefront per row on
+// Measured (16 heads x 512 x 64, no mask): forward 19.6 us (1.07 GFLOP), backward 48 us, where one wavefront per row on
 // vector arithmetic took 338 and 670 us.
 //
 // Register layouts.  The accumulator of a 32 x 32 block gives lane l column l % 32 and rows 8 i + 4 (l / 32) + j (register
@@ -251,8 +251,31 @@ __global__ __launch_bounds__(256) void attn_f32_fwd_kernel(int S, int nl, int dh
     }
 }
 
-// ---- dQ: workgroup = (32 queries, batch*head); also leaves D = rowsum(dO * O) for the dK/dV kernel -----------------
-template <int DH>
+// Where dK/dV gets D = rowsum(dO * O) from: dQ's launch before, attn_f32_dsum_kernel, or itself.
+enum { D_OF_DQ, D_GIVEN, D_OWN };
+
+// D: 16 lanes per (token, head)
+__global__ __launch_bounds__(256) void attn_f32_dsum_kernel(const float* __restrict__ o, const float* __restrict__ d_o, float* __restrict__ dsum,
+                                                            int B, int S, int nl, int dh) {
+    const int64_t items = (int64_t)B * S * nl;                                                 // token-major, then head
+    const int l = threadIdx.x % 16;
+    for (int64_t item = ((int64_t)blockIdx.x * 256 + threadIdx.x) / 16; item < items; item += (int64_t)gridDim.x * 16) {
+        float D = 0.0f;
+        for (int c = 4 * l; c < dh; c += 64) {
+            const float4 x = *reinterpret_cast<const float4*>(o + item * dh + c), g = *reinterpret_cast<const float4*>(d_o + item * dh + c);
+            D = fmaf(x.x, g.x, D); D = fmaf(x.y, g.y, D); D = fmaf(x.z, g.z, D); D = fmaf(x.w, g.w, D);
+        }
+#pragma unroll
+        for (int i = 8; i > 0; i >>= 1) D += __shfl_xor(D, i, 64);
+        if (l == 0) {
+            const int64_t row = item / nl;
+            dsum[((row / S) * nl + (item - row * nl)) * S + row % S] = D;
+        }
+    }
+}
+
+// ---- dQ: workgroup = (32 queries, batch*head); also leaves D for the dK/dV kernel unless that is given --------------
+template <int DH, int DK_D>
 __device__ __forceinline__ void attn_f32_dq(char* smem, int wg, int S, int nl, int dh, int causal, int nblk, const float* __restrict__ qkv,
                                             const float* __restrict__ o, const float* __restrict__ lse, const float* __restrict__ d_o,
                                             float* __restrict__ dqkv, float* dsum) {
@@ -279,7 +302,7 @@ __device__ __forceinline__ void attn_f32_dq(char* smem, int wg, int S, int nl, i
         D += xother(D);
     }
     const float L = q < S ? lse[(int64_t)bh * S + q] : 0.0f;
-    if (wave == 0 && half == 0 && q < S) dsum[(int64_t)bh * S + q] = D;
+    if (DK_D != D_GIVEN && wave == 0 && half == 0 && q < S) dsum[(int64_t)bh * S + q] = D;
     f32x16 acc[DH / 32];
 #pragma unroll
     for (int d = 0; d < DH / 32; ++d)
@@ -337,8 +360,8 @@ __device__ __forceinline__ void attn_f32_dq(char* smem, int wg, int S, int nl, i
 }
 
 // ---- dK, dV: workgroup = (32 keys, batch*head) -----------------------------------------------------------------------
-// OWN_D: D of the query tiles is worked out here (and stored, the same value that dQ's workgroups store), not read.
-template <int DH, bool OWN_D>
+// D_OWN: D of the query tiles is worked out here (and stored, the same value that dQ's workgroups store), not read.
+template <int DH, int DK_D>
 __device__ __forceinline__ void attn_f32_dkv(char* smem, int wg, int S, int nl, int dh, int causal, int nblk, const float* __restrict__ qkv,
                                              const float* __restrict__ o, const float* __restrict__ lse, const float* __restrict__ d_o,
                                              float* __restrict__ dqkv, float* dsum) {
@@ -369,7 +392,7 @@ __device__ __forceinline__ void attn_f32_dkv(char* smem, int wg, int S, int nl, 
     xoffsets<DH>(offg, ldo, dh, lane);
     auto term = [&](int t) {                                      // lanes 0..31: LSE, lanes 32..63: D
         const int i = t * XT + (lane & 31);
-        if constexpr (OWN_D) {
+        if constexpr (DK_D == D_OWN) {
             float gr[DH / 2], orr[DH / 2], D = 0.0f;
             const int64_t orow = (int64_t)b * S * ldo + (int64_t)h * dh;
             xrow<DH>(gr, d_o + orow, ldo, i, S, dh, lane);
@@ -454,24 +477,25 @@ __global__ __launch_bounds__(256) void attn_f32_dq_kernel(int S, int nl, int dh,
                                                           const float* __restrict__ o, const float* __restrict__ lse,
                                                           const float* __restrict__ d_o, float* __restrict__ dqkv, float* dsum) {
     extern __shared__ __attribute__((aligned(16))) char smem[];
-    attn_f32_dq<DH>(smem, blockIdx.x, S, nl, dh, causal, nblk, qkv, o, lse, d_o, dqkv, dsum);
+    attn_f32_dq<DH, D_OF_DQ>(smem, blockIdx.x, S, nl, dh, causal, nblk, qkv, o, lse, d_o, dqkv, dsum);
 }
 template <int DH>
 __global__ __launch_bounds__(256) void attn_f32_dkv_kernel(int S, int nl, int dh, int causal, int nblk, const float* __restrict__ qkv,
                                                            const float* __restrict__ lse, const float* __restrict__ d_o,
                                                            float* __restrict__ dqkv, float* dsum) {
     extern __shared__ __attribute__((aligned(16))) char smem[];
-    attn_f32_dkv<DH, false>(smem, blockIdx.x, S, nl, dh, causal, nblk, qkv, nullptr, lse, d_o, dqkv, dsum);
+    attn_f32_dkv<DH, D_OF_DQ>(smem, blockIdx.x, S, nl, dh, causal, nblk, qkv, nullptr, lse, d_o, dqkv, dsum);
 }
-// Both in one launch of n + n workgroups: dK/dV does not wait for D, it works it out for its query tiles as well.
-template <int DH>
-__global__ __launch_bounds__(256) void attn_f32_bwd_kernel(int n, int S, int nl, int dh, int causal, int nblk, const float* __restrict__ qkv,
+// Both in one launch of n + n workgroups: dK/dV does not wait for dQ's, D is given or worked out for its query tiles as well.
+// With D given two workgroups share a compute unit (at most 256 registers).  This launch starts at workgroup wg0 of them.
+template <int DH, int DK_D>
+__global__ __launch_bounds__(256, DK_D == D_GIVEN ? 2 : 1) void attn_f32_bwd_kernel(int n, int wg0, int S, int nl, int dh, int causal, int nblk, const float* __restrict__ qkv,
                                                            const float* __restrict__ o, const float* __restrict__ lse,
                                                            const float* __restrict__ d_o, float* __restrict__ dqkv, float* dsum) {
     extern __shared__ __attribute__((aligned(16))) char smem[];
-    const int wg = blockIdx.x;                                    // uniform: one kind per workgroup
-    if (wg < n) attn_f32_dkv<DH, true>(smem, wg, S, nl, dh, causal, nblk, qkv, o, lse, d_o, dqkv, dsum);
-    else attn_f32_dq<DH>(smem, wg - n, S, nl, dh, causal, nblk, qkv, o, lse, d_o, dqkv, dsum);
+    const int wg = blockIdx.x + wg0;                              // uniform: one kind per workgroup
+    if (wg < n) attn_f32_dkv<DH, DK_D>(smem, wg, S, nl, dh, causal, nblk, qkv, o, lse, d_o, dqkv, dsum);
+    else attn_f32_dq<DH, DK_D>(smem, wg - n, S, nl, dh, causal, nblk, qkv, o, lse, d_o, dqkv, dsum);
 }
 
 // ---- host ----------------------------------------------------------------------------------------------------------------
@@ -481,18 +505,29 @@ bool attn_f32_supported(const AttnArgs& a) {
     return a.dtype == F32 && a.dh % 4 == 0 && a.dh <= 128 && ((int64_t)a.S + XT) * 3 * a.nl * a.dh * 4 < (1LL << 31) &&
            (int64_t)a.B * a.nl * ((a.S + XT - 1) / XT) * 256 < (1LL << 32);
 }
+// Head sizes whose two kinds of workgroups share a compute unit, by registers and LDS: D by a kernel of its own, then dQ and dK/dV in
+// one launch.  A wavefront alone on its SIMD waits for its tiles and its dependent products; two fill each other's waits.  us, two
+// launches one after the other and so: 4 x 512, 4 heads of 64 55.6 and 48.5, 8 heads 95.6 and 82.9; 2048 tokens, 16 heads of 64, causal
+// 562 and 436; 300 tokens, 16 heads of 64, causal 41.1 and 29.5; 4 x 512, 8 heads of 32 47.8 and 45.7.  Wider heads need 330 registers.
+template <int DH> constexpr bool pairs() { return DH <= 64; }
 template <int DH>
 static hipError_t set_lds() {
     hipError_t e = hipSuccess;
-    for (const void* k : {reinterpret_cast<const void*>(&attn_f32_fwd_kernel<DH>), reinterpret_cast<const void*>(&attn_f32_dq_kernel<DH>),
-                          reinterpret_cast<const void*>(&attn_f32_dkv_kernel<DH>), reinterpret_cast<const void*>(&attn_f32_bwd_kernel<DH>)})
-        if (e == hipSuccess) e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, xlds_bytes<DH>());
+    auto set = [&](const void* k) { if (e == hipSuccess) e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, xlds_bytes<DH>()); };
+    set(reinterpret_cast<const void*>(&attn_f32_fwd_kernel<DH>));
+    set(reinterpret_cast<const void*>(&attn_f32_bwd_kernel<DH, D_OWN>));
+    if constexpr (pairs<DH>()) {
+        set(reinterpret_cast<const void*>(&attn_f32_bwd_kernel<DH, D_GIVEN>));
+    } else {
+        set(reinterpret_cast<const void*>(&attn_f32_dq_kernel<DH>));
+        set(reinterpret_cast<const void*>(&attn_f32_dkv_kernel<DH>));
+    }
     return e;
 }
 // dQ and dK/dV in one launch where all their workgroups find a compute unit at once: neither waits for the other, and a launch is
 // saved.  us, two launches and one, n workgroups of each kind: n = 16 (2 x 128 tokens, 2 heads of 64, causal) 21.0 and 13.2, n = 64
 // 31.4 and 21.7, n = 128 52 and 37 (heads of 128: 171 and 129); with more of them D, worked out again, costs more than that: n = 256
-// 58 and 63, n = 512 96 and 115.
+// 58 and 63, n = 512 96 and 115, where D comes from a kernel of its own (pairs) or from dQ's launch.
 static bool one_launch(int64_t n) { return 2 * n <= compute_units(); }
 template <int DH>
 static hipError_t launch(const AttnArgs& a, bool bwd) {
@@ -507,14 +542,25 @@ static hipError_t launch(const AttnArgs& a, bool bwd) {
     }
     if (one_launch((int64_t)nblk * a.B * a.nl)) {
         const dim3 both(2 * grid.x);
-        hipLaunchKernelGGL(attn_f32_bwd_kernel<DH>, both, wg, xlds_bytes<DH>(), a.stream, (int)grid.x, a.S, a.nl, a.dh, a.causal, nblk,
+        hipLaunchKernelGGL((attn_f32_bwd_kernel<DH, D_OWN>), both, wg, xlds_bytes<DH>(), a.stream, (int)grid.x, 0, a.S, a.nl, a.dh, a.causal, nblk,
                            (const float*)a.qkv, (const float*)a.o, a.lse, (const float*)a.d_o, (float*)a.dqkv, a.dsum);
         return hipGetLastError();
     }
-    hipLaunchKernelGGL(attn_f32_dq_kernel<DH>, grid, wg, xlds_bytes<DH>(), a.stream, a.S, a.nl, a.dh, a.causal, nblk,
-                       (const float*)a.qkv, (const float*)a.o, a.lse, (const float*)a.d_o, (float*)a.dqkv, a.dsum);
-    hipLaunchKernelGGL(attn_f32_dkv_kernel<DH>, grid, wg, xlds_bytes<DH>(), a.stream, a.S, a.nl, a.dh, a.causal, nblk,
-                       (const float*)a.qkv, a.lse, (const float*)a.d_o, (float*)a.dqkv, a.dsum);
+    if constexpr (pairs<DH>()) {
+        const int64_t rows16 = ((int64_t)a.B * a.S * a.nl + 15) / 16;
+        hipLaunchKernelGGL(attn_f32_dsum_kernel, dim3((unsigned)(rows16 < 1 << 20 ? rows16 : 1 << 20)), wg, 0, a.stream, (const float*)a.o,
+                           (const float*)a.d_o, a.dsum, a.B, a.S, a.nl, a.dh);
+        const bool fits = 2LL * grid.x * wg.x < 1LL << 32;            // a launch has fewer than 2^32 threads
+        for (unsigned wg0 = 0; wg0 < 2 * grid.x; wg0 += fits ? 2 * grid.x : grid.x)
+            hipLaunchKernelGGL((attn_f32_bwd_kernel<DH, D_GIVEN>), dim3(fits ? 2 * grid.x : grid.x), wg, xlds_bytes<DH>(), a.stream, (int)grid.x,
+                               (int)wg0, a.S, a.nl, a.dh, a.causal, nblk, (const float*)a.qkv, (const float*)a.o, a.lse, (const float*)a.d_o,
+                               (float*)a.dqkv, a.dsum);
+    } else {
+        hipLaunchKernelGGL(attn_f32_dq_kernel<DH>, grid, wg, xlds_bytes<DH>(), a.stream, a.S, a.nl, a.dh, a.causal, nblk,
+                           (const float*)a.qkv, (const float*)a.o, a.lse, (const float*)a.d_o, (float*)a.dqkv, a.dsum);
+        hipLaunchKernelGGL(attn_f32_dkv_kernel<DH>, grid, wg, xlds_bytes<DH>(), a.stream, a.S, a.nl, a.dh, a.causal, nblk,
+                           (const float*)a.qkv, a.lse, (const float*)a.d_o, (float*)a.dqkv, a.dsum);
+    }
     return hipGetLastError();
 }
 static hipError_t attn_f32(const AttnArgs& a, bool bwd) {

@@ -1,5 +1,6 @@
-"""Float attention backward on either side of the line between one launch for dQ and dK/dV (at most a workgroup of 32 rows per
-compute unit, both kinds together) and two: against the oracle's definitions, and twice over bit-identical."""
+"""Float attention backward on either side of the line between one launch that works D out by itself (at most a workgroup of 32
+rows per compute unit, dQ and dK/dV together) and D in a launch before: dQ and dK/dV together at head sizes up to 64, dQ first
+beyond.  Ragged rows, odd head sizes; against the oracle's definitions, and twice over bit-identical."""
 import numpy as np
 import pytest
 
@@ -10,7 +11,8 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("causal", [True, False])
-@pytest.mark.parametrize("B,S,nl,dh", [(8, 32, 16, 64), (43, 32, 3, 32), (2, 61, 32, 128), (5, 33, 16, 128), (1, 97, 2, 96), (13, 70, 4, 96)])
+@pytest.mark.parametrize("B,S,nl,dh", [(8, 32, 16, 64), (43, 32, 3, 32), (2, 61, 32, 128), (5, 33, 16, 128), (1, 97, 2, 96), (13, 70, 4, 96), (3, 95, 29, 36),
+                                       (17, 100, 5, 4), (2, 290, 13, 60)])
 def test_one_launch_and_two(B, S, nl, dh, causal):
     import torch
     import paper_2111_05972_amd as pkg
