@@ -80,9 +80,6 @@ size_t colsum_scratch_bytes(int64_t M, int64_t N);
 // *ptr = its address on the current device.  Calls that use it on one GPU share it.
 constexpr size_t STATIC_SCRATCH_BYTES = (size_t)4 << 20;
 hipError_t static_scratch(void** ptr);
-// out[n] = sum over slabs of part[slab * stride + n], in slab order.
-hipError_t sum_partials_strided(int dtype, int64_t slabs, int64_t N, const float* part, int64_t stride,
-                                void* out, hipStream_t s);
 
 // LayerNorm over the hidden dimension of z = a (+ b): HBM-bound, one pass over each tensor.
 struct LnArgs {

@@ -572,9 +572,9 @@ static hipError_t fwd_t(const LnArgs& a) {
     return launch_fwd<T, MAXC, LN_THREADS, false>(a);
 }
 template <typename T>
-static hipError_t sum_groups(const LnArgs& a, int64_t groups) {
-    hipLaunchKernelGGL((ln_sum_partials_kernel<T>), dim3((unsigned)((a.H + LN_SUM_COLS - 1) / LN_SUM_COLS), 2), dim3(256), 0, a.stream,
-                       groups, a.H, a.partials, (T*)a.dgamma, (T*)a.dbeta);
+static hipError_t sum_groups(int64_t groups, int64_t H, const float* partials, void* dgamma, void* dbeta, hipStream_t s) {
+    hipLaunchKernelGGL((ln_sum_partials_kernel<T>), dim3((unsigned)((H + LN_SUM_COLS - 1) / LN_SUM_COLS), 2), dim3(256), 0, s,
+                       groups, H, partials, (T*)dgamma, (T*)dbeta);
     return hipGetLastError();
 }
 // MAXC counts the 8-element chunks per thread of a 256-thread workgroup; rows of more than two such chunks go to
@@ -594,7 +594,7 @@ static hipError_t bwd_t(const LnArgs& a) {
                            a.stream, a.M, a.H, (const T*)a.dy, (const T*)a.z, a.mean, a.rstd, (const T*)a.gamma,
                            (T*)a.dz, part);
     hipError_t e = hipGetLastError();
-    return e != hipSuccess ? e : sum_groups<T>(a, groups);
+    return e != hipSuccess ? e : sum_groups<T>(groups, a.H, a.partials, a.dgamma, a.dbeta, a.stream);
 }
 
 // One wavefront per row up to H = 1024.  Beyond, a lane would hold four chunks, only one workgroup of the backward fits a
@@ -622,7 +622,7 @@ static hipError_t bwd_wave_t(const LnArgs& a) {
     hipLaunchKernelGGL((ln_bwd_wave_kernel<T, MAXC, DEPTH>), dim3((unsigned)groups), dim3(64 * LN_WAVE_ROWS), 0, a.stream, a.M,
                        a.H, (const T*)a.dy, (const T*)a.z, a.mean, a.rstd, (const T*)a.gamma, (T*)a.dz, a.partials);
     hipError_t e = hipGetLastError();
-    return e != hipSuccess ? e : sum_groups<T>(a, groups);
+    return e != hipSuccess ? e : sum_groups<T>(groups, a.H, a.partials, a.dgamma, a.dbeta, a.stream);
 }
 
 template <typename T>
@@ -779,9 +779,9 @@ hipError_t ln_dist_bwd_apply(int dtype, int64_t M, int64_t Hs, int64_t H, const 
                            (bf16_t*)dx, partials);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    e = sum_partials_strided(dtype, slabs, Hs, partials, 2 * Hs, dgamma, s);
-    if (e != hipSuccess) return e;
-    return sum_partials_strided(dtype, slabs, Hs, partials + Hs, 2 * Hs, dbeta, s);
+    // both in one launch, 16 lanes over the slabs; a launch of four lanes for either: [2048, 1280] bfloat16 13.7 us, now 10.4, [8192, 1024] 26.8
+    // and 16.9
+    return dtype == F32 ? sum_groups<float>(slabs, Hs, partials, dgamma, dbeta, s) : sum_groups<bf16_t>(slabs, Hs, partials, dgamma, dbeta, s);
 }
 size_t ln_dist_scratch_bytes(int64_t M, int64_t Hs) { return (size_t)ln_partial_rows(M) * 2 * Hs * sizeof(float); }
 

@@ -260,8 +260,7 @@ __global__ __launch_bounds__(256) void colsum_stage1(int64_t M, int64_t N, const
 // 64 columns x 4 slab lanes per workgroup: lane g adds slabs g, g+4, ... in order (four loads in flight), the four
 // lanes are combined through LDS in lane order.
 template <typename T>
-__global__ __launch_bounds__(256) void colsum_stage2(int64_t slabs, int64_t N, int64_t stride,
-                                                     const float* __restrict__ part,
+__global__ __launch_bounds__(256) void colsum_stage2(int64_t slabs, int64_t N, const float* __restrict__ part,
                                                      T* __restrict__ out) {
     __shared__ float red[4][64];
     const int cl = threadIdx.x & 63, gl = threadIdx.x >> 6;
@@ -271,11 +270,11 @@ __global__ __launch_bounds__(256) void colsum_stage2(int64_t slabs, int64_t N, i
         const float* src = part + n;
         int64_t i = gl;
         for (; i + 12 < slabs; i += 16) {
-            const float a = src[i * stride], b = src[(i + 4) * stride], c = src[(i + 8) * stride],
-                        d = src[(i + 12) * stride];
+            const float a = src[i * N], b = src[(i + 4) * N], c = src[(i + 8) * N],
+                        d = src[(i + 12) * N];
             s += a; s += b; s += c; s += d;
         }
-        for (; i < slabs; i += 4) s += src[i * stride];
+        for (; i < slabs; i += 4) s += src[i * N];
     }
     red[gl][cl] = s;
     __syncthreads();
@@ -284,14 +283,6 @@ __global__ __launch_bounds__(256) void colsum_stage2(int64_t slabs, int64_t N, i
 
 size_t colsum_scratch_bytes(int64_t M, int64_t N) {
     return (size_t)((M + CS_ROWS - 1) / CS_ROWS) * (size_t)N * sizeof(float);
-}
-
-hipError_t sum_partials_strided(int dtype, int64_t slabs, int64_t N, const float* part, int64_t stride,
-                                void* out, hipStream_t s) {
-    dim3 g2((unsigned)((N + 63) / 64));
-    if (dtype == F32) hipLaunchKernelGGL(colsum_stage2<float>, g2, dim3(256), 0, s, slabs, N, stride, part, (float*)out);
-    else hipLaunchKernelGGL(colsum_stage2<bf16_t>, g2, dim3(256), 0, s, slabs, N, stride, part, (bf16_t*)out);
-    return hipGetLastError();
 }
 
 // Scratch for the entry points that may not allocate: one array per GPU, held until the process ends.  In host
@@ -325,10 +316,10 @@ hipError_t colsum(int dtype, int64_t M, int64_t N, const void* X, void* out, flo
     dim3 g1((unsigned)((N + 511) / 512), (unsigned)slabs), g2((unsigned)((N + 63) / 64));
     if (dtype == F32) {
         hipLaunchKernelGGL(colsum_stage1<float>, g1, dim3(256), 0, s, M, N, (const float*)X, scratch);
-        hipLaunchKernelGGL(colsum_stage2<float>, g2, dim3(256), 0, s, slabs, N, N, scratch, (float*)out);
+        hipLaunchKernelGGL(colsum_stage2<float>, g2, dim3(256), 0, s, slabs, N, scratch, (float*)out);
     } else {
         hipLaunchKernelGGL(colsum_stage1<bf16_t>, g1, dim3(256), 0, s, M, N, (const bf16_t*)X, scratch);
-        hipLaunchKernelGGL(colsum_stage2<bf16_t>, g2, dim3(256), 0, s, slabs, N, N, scratch, (bf16_t*)out);
+        hipLaunchKernelGGL(colsum_stage2<bf16_t>, g2, dim3(256), 0, s, slabs, N, scratch, (bf16_t*)out);
     }
     return hipGetLastError();
 }
