@@ -1742,8 +1742,8 @@ size_t attn_bf16_workspace_bytes(const AttnArgs& a0, bool bwd) {
 // keys (roles) shared by two wavefronts and with own rows.  Forward, head size 128: 768 causal workgroups 297 and 257, 320 39.5 and
 // 48.9, 192 35 and 42, 256 without a mask 17.5 and 17.2; head size 64: 256 causal 16.3 and 18.4, 512 59 and 59, 512 without a mask
 // 17.2 and 16.7.  A wavefront alone walks a strip in almost twice the time, so the longest of a few causal strips would set the
-// duration.  Backward, head size 64: 1024 workgroups 189 and 146 causal, 63 and 50 without a mask, 512 38 and 38.5, 256 20.5 and
-// 21.1; head size 128 (a wavefront per SIMD, 420 registers): 845 and 988, so not built.
+// duration.  Backward, head size 64: 1024 workgroups 165 and 141 causal, 59.4 and 47.8 without a mask, 512 35 and 38, 256 18 and 21;
+// head size 128 (a wavefront per SIMD, 420 registers) 845 and 988 when both roles worked the scores out, 761 now, so not built.
 static bool own_rows(bool causal, bool bwd, int64_t n) {
     const int64_t cus = compute_units();
     return bwd ? n >= 3 * cus : !causal || n >= 5 * cus / 2;
