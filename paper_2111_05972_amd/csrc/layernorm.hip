@@ -88,12 +88,12 @@ __global__ __launch_bounds__(THREADS) void ln_fwd_kernel(int64_t M, int64_t H, c
         for (int i = 0; i < MAXC; ++i) {
             const int64_t col = ((int64_t)t + THREADS * i) * 8;
             if (col < H) {
-                if (!EARLY) ra[i].load(a + row * H + col);
-                ra[i].get(v[i]);
+                if (EARLY) ra[i].get(v[i]);
+                else load8(a + row * H + col, v[i]);
                 if (b) {
                     float w[8];
-                    if (!EARLY) rb[i].load(b + row * H + col);
-                    rb[i].get(w);
+                    if (EARLY) rb[i].get(w);
+                    else load8(b + row * H + col, w);
 #pragma unroll
                     for (int e = 0; e < 8; ++e) v[i][e] += w[e];
                 }
