@@ -363,7 +363,7 @@ def bench_layer(args, cfg, dt, pkg, torch, synthetic, ckpt=False, extras=True, o
         achieved = tot_fl / (tot_ms * 1e-3) / 1e12
         traffic = None
         tpath = os.path.join(ROOT, "profiles", "traffic.json")
-        if os.path.exists(tpath):
+        if os.path.exists(tpath) and not grouped:      # counted with one GEMM per launch
             try:
                 traffic = json.load(open(tpath)).get(cfg.name, {}).get("bytes_per_launch")
             except Exception:
