@@ -1661,25 +1661,42 @@ static Plan make_plan(int64_t M, int64_t N, int64_t K, bool a_kmaj, bool b_kmaj)
     return best;
 }
 
-// Plans are computed once per (shape, layout) and kept: a launch looks its plan up (a short scan under a mutex), it
-// does not run the planner.  Entries carry the generation of the options they were planned under.
-static Plan plan_for(int64_t M, int64_t N, int64_t K, bool a_kmaj, bool b_kmaj) {
-    struct Entry { int64_t M, N, K; int layout; unsigned gen; Plan plan; };
-    constexpr int CAP = 128;
-    static Entry cache[CAP];
-    static int used = 0, next = 0;
-    static std::mutex mu;
-    const int layout = (a_kmaj ? 1 : 0) | (b_kmaj ? 2 : 0);
-    const unsigned gen = options().generation;
-    std::lock_guard<std::mutex> lock(mu);
-    for (int i = 0; i < used; ++i) {
-        const Entry& e = cache[i];
-        if (e.M == M && e.N == N && e.K == K && e.layout == layout && e.gen == gen) return e.plan;
+// Plans that were made, by a key of whole numbers, so that a call looks its plans up and does not run the planner.  A table of
+// SETS x 4 entries, the oldest of a set replaced; shared by all threads.
+template <typename Plan, int KEY, int SETS>
+class PlanCache {
+public:
+    template <typename Make>
+    Plan get(const int64_t (&key)[KEY], Make make) {
+        uint64_t h = 0;
+        for (const int64_t k : key) h = (h ^ (uint64_t)k) * 0x9E3779B97F4A7C15ull, h ^= h >> 29;
+        Set& set = sets[h % SETS];
+        {
+            std::lock_guard<std::mutex> lock(mu);
+            for (int i = 0; i < set.used; ++i)
+                if (std::equal(key, key + KEY, set.entry[i].key)) return set.entry[i].plan;
+        }
+        const Plan plan = make();                                // outside the lock: another thread's plan is the same
+        std::lock_guard<std::mutex> lock(mu);
+        Entry& e = set.entry[set.used < WAYS ? set.used++ : set.next++ % WAYS];
+        std::copy(key, key + KEY, e.key);
+        e.plan = plan;
+        return plan;
     }
-    const Plan pl = make_plan(M, N, K, a_kmaj, b_kmaj);
-    const int slot = used < CAP ? used++ : (next++ % CAP);
-    cache[slot] = Entry{M, N, K, layout, gen, pl};
-    return pl;
+
+private:
+    static constexpr int WAYS = 4;
+    struct Entry { int64_t key[KEY]; Plan plan; };
+    struct Set { Entry entry[WAYS]; int used; unsigned next; };
+    std::mutex mu;
+    Set sets[SETS] = {};
+};
+
+// Entries carry the generation of the options they were planned under.
+static Plan plan_for(int64_t M, int64_t N, int64_t K, bool a_kmaj, bool b_kmaj) {
+    static PlanCache<Plan, 5, 256> cache;
+    const int64_t key[5] = {M, N, K, (a_kmaj ? 1 : 0) | (b_kmaj ? 2 : 0), (int64_t)options().generation};
+    return cache.get(key, [&] { return make_plan(M, N, K, a_kmaj, b_kmaj); });
 }
 
 static GemmParams gemm_params(const GemmArgs& a) {
@@ -1773,53 +1790,83 @@ GroupPlan make_pp_plan(const GemmArgs* g, int n, const GroupTile& gt) {
         if (c.shares == 1) c.cut = 0;
         return c;
     };
-    auto jobs = [&](const Cut* c, PPJob* job) {                       // longest first
+    auto jobs = [&](const Cut* c, PPJob* job) {                       // longest first, else in order
         int m = 0;
+        auto add = [&](const PPJob& j) {
+            int q = m++;
+            for (; q > 0 && job[q - 1].nk < j.nk; --q) job[q] = job[q - 1];
+            job[q] = j;
+        };
         for (int i = 0; i < n; ++i) {
-            if (tiles[i] > c[i].cut) job[m++] = PPJob{i, 0, (int)(tiles[i] - c[i].cut), nk[i], 1};
-            if (c[i].cut) job[m++] = PPJob{i, (int)(tiles[i] - c[i].cut), (int)c[i].cut, c[i].nk, c[i].shares};
+            if (tiles[i] > c[i].cut) add(PPJob{i, 0, (int)(tiles[i] - c[i].cut), nk[i], 1});
+            if (c[i].cut) add(PPJob{i, (int)(tiles[i] - c[i].cut), (int)c[i].cut, c[i].nk, c[i].shares});
         }
-        std::stable_sort(job, job + m, [](const PPJob& a, const PPJob& b) { return a.nk > b.nk; });
         return m;
     };
-    auto estimate = [&](const Cut* c) {
+    auto length = [&](int i, int steps, bool whole) { return steps * gt.step_us + gt.wg_us + (whole && g[i].epi != EPI_NONE ? gt.gelu_us : 0.0); };
+    // Anything not below `limit` where the plan cannot be: the list is dealt out only if its longest job would fit, and its work, unless
+    // list_time takes whole rounds of a job at once behind longer ones (it may come out below the work then).
+    auto estimate = [&](const Cut* c, double limit) {
+        double work = 0, longest = 0, bytes = 0, many = INFINITY;
+        auto add = [&](int64_t count, double len) {
+            work += (double)count * len;
+            longest = std::max(longest, len);
+            if (count >= 3 * cus) many = std::min(many, len);
+        };
+        for (int i = 0; i < n; ++i) {
+            if (tiles[i] > c[i].cut) add(tiles[i] - c[i].cut, length(i, nk[i], true));
+            if (c[i].cut) {
+                add(c[i].cut * c[i].shares, length(i, c[i].nk, false));
+                bytes += (double)c[i].cut * tile_bytes[i] * (8.0 * c[i].shares + 2.0);
+            }
+        }
+        const double sums = bytes > 0 ? 4.2 + bytes / 8.0e6 : 0.0;
+        const double least = std::max(std::max(many < longest ? 0.0 : work / cus, longest), floor_us) + sums;
+        if (least >= limit) return least;
         PPJob job[JOB_MAX];
         int64_t count[JOB_MAX];
-        double len[JOB_MAX], bytes = 0;
+        double len[JOB_MAX];
         const int m = jobs(c, job);
         for (int q = 0; q < m; ++q) {
             count[q] = (int64_t)job[q].count * job[q].shares;
-            len[q] = job[q].nk * gt.step_us + gt.wg_us + (g[job[q].gemm].epi != EPI_NONE && job[q].shares == 1 ? gt.gelu_us : 0.0);
-            if (job[q].shares > 1) bytes += job[q].count * tile_bytes[job[q].gemm] * (8.0 * job[q].shares + 2.0);
+            len[q] = length(job[q].gemm, job[q].nk, job[q].shares == 1);
         }
-        return std::max(list_time(cus, m, count, len), floor_us) + (bytes > 0 ? 4.2 + bytes / 8.0e6 : 0.0);
+        return std::max(list_time(cus, m, count, len), floor_us) + sums;
     };
     Cut best[GROUP_MAX], now[GROUP_MAX];
     for (int i = 0; i < n; ++i) best[i] = now[i] = with_shares(i, 0, 1);
-    double best_us = estimate(best);
+    double best_us = estimate(best, INFINITY);
     const int longest = *std::max_element(nk, nk + n);
     for (int parts = 2; parts <= MAX_SHARES && longest / parts >= PP_MIN_STEPS; ++parts) {   // everything long cut to one length
         for (int i = 0; i < n; ++i) now[i] = with_shares(i, tiles[i], std::max(1, (nk[i] * parts + longest - 1) / longest));
-        const double us = estimate(now);
+        const double us = estimate(now, best_us);
         if (us < best_us) { best_us = us; std::copy(now, now + n, best); }
     }
     for (int round = 0; round < 2 * n; ++round) {
         const double before = best_us;
         Cut base[GROUP_MAX];
         std::copy(best, best + n, base);
-        for (int i = 0; i < n; ++i)
+        for (int i = 0; i < n; ++i) {
+            int64_t others = 0;
+            for (int q = 0; q < n; ++q) others += q == i ? tiles[q] : tiles[q] - base[q].cut;
+            int last_nk = 0;
             for (int want = 1; want <= MAX_SHARES && (want == 1 || nk[i] / want >= PP_MIN_STEPS); ++want) {
-                int64_t others = 0;
-                for (int q = 0; q < n; ++q) others += q == i ? tiles[q] : tiles[q] - base[q].cut;
+                const int share_nk = with_shares(i, tiles[i], want).nk;
+                if (share_nk == last_nk) continue;                // no other plan than with fewer wanted
+                last_nk = share_nk;
+                int64_t last_cut = -1;
                 for (int eighth = n == 1 ? 8 : 0; eighth <= 8; ++eighth) {   // the tiles past whole rounds, or so many eighths; one GEMM: all
                     const int64_t cut = eighth ? (tiles[i] * eighth + 7) / 8 : std::min(tiles[i], others % cus);
+                    if (cut == last_cut) continue;
+                    last_cut = cut;
                     std::copy(base, base + n, now);
                     now[i] = with_shares(i, cut, want);
-                    const double us = estimate(now);
+                    const double us = estimate(now, best_us);
                     if (us < best_us) { best_us = us; std::copy(now, now + n, best); }
                     if (want == 1) break;
                 }
             }
+        }
         if (best_us >= before) break;
     }
     GroupPlan p{};
@@ -1880,28 +1927,16 @@ GroupPlan make_group_plan(const GemmArgs* g, int n) {
     }
     return best;
 }
-// As plan_for: plans of groups are kept.
+// As plan_for.  A layer has two groups in either direction.
 GroupPlan plan_group(const GemmArgs* g, int n) {
-    struct Entry { int64_t key[GROUP_MAX][4]; int n; unsigned gen; GroupPlan plan; };
-    constexpr int CAP = 128;                                      // a layer has 4 groups, and up to 30 single GEMMs to size its workspace
-    struct Cache { Entry entry[CAP]; int used, next; };
-    static Cache caches[2];
-    static std::mutex mu;
-    Cache& c = caches[n > 1];
-    Entry e{};
-    e.n = n;
-    e.gen = options().generation;
+    static PlanCache<GroupPlan, 2 + 4 * GROUP_MAX, 256> cache;
+    int64_t key[2 + 4 * GROUP_MAX] = {n, (int64_t)options().generation};
     for (int i = 0; i < n; ++i) {
-        const int64_t k[4] = {g[i].M, g[i].N, g[i].K, (g[i].trans_a ? 1 : 0) | (g[i].trans_b ? 2 : 0) | g[i].epi << 2};
-        std::copy(k, k + 4, e.key[i]);
+        int64_t* k = key + 2 + 4 * i;
+        // a group of one is planned for its size alone (by_turns)
+        k[0] = g[i].M; k[1] = g[i].N; k[2] = g[i].K; k[3] = n == 1 ? 0 : (g[i].trans_a ? 1 : 0) | (g[i].trans_b ? 2 : 0) | g[i].epi << 2;
     }
-    std::lock_guard<std::mutex> lock(mu);
-    for (int i = 0; i < c.used; ++i)
-        if (c.entry[i].n == n && c.entry[i].gen == e.gen && std::equal(&e.key[0][0], &e.key[0][0] + 4 * GROUP_MAX, &c.entry[i].key[0][0]))
-            return c.entry[i].plan;
-    e.plan = make_group_plan(g, n);
-    c.entry[c.used < CAP ? c.used++ : c.next++ % CAP] = e;
-    return e.plan;
+    return cache.get(key, [&] { return make_group_plan(g, n); });
 }
 size_t share_bytes(const GemmArgs& a, int shares) {               // float partial sums, column sums included
     return shares > 1 ? (size_t)shares * ((size_t)a.M * a.N + (size_t)a.N) * sizeof(float) : 0;
@@ -2025,23 +2060,26 @@ hipError_t gemm_bf16_group(const GemmArgs* g, int n, void* ws, size_t ws_bytes, 
 // 2048 x 15360 x 1280 87 and 82, 2048 x 49152 x 1536 286 and 261, 2048 x 12288 x 6144 240 and 230, NT 2048 x 1536 x 49152 344 and
 // 250, 2048 x 1536 x 12288 80 and 76, TN 1280 x 15360 x 2048 88 and 82; estimates of less than 60 us: 0.98 to 1.8 times as long, the
 // 256 x 128 tile 0.8 to 1.8.  Its kernels are built for the layouts of a layer (NN, NT, TN), and the overrides are about the others.
+constexpr double BY_TURNS_MIN_US = 60.0;
 static bool by_turns(int64_t M, int64_t N, int64_t K, bool trans_a, bool trans_b, GroupPlan* plan) {
     const Options& o = options();
     if ((trans_a && trans_b) || o.gemm_tile >= 0 || o.gemm_shares > 0 || o.gemm_force[0] || o.gemm_band > 0 || o.fuse_colsum) return false;
+    const double other_us = 0.95 * plan_for(M, N, K, !trans_a, trans_b).us;
+    if (other_us <= BY_TURNS_MIN_US) return false;
     GemmArgs a{};
-    a.dtype = BF16; a.trans_a = trans_a; a.trans_b = trans_b; a.M = M; a.N = N; a.K = K; a.epi = EPI_NONE;
+    a.dtype = BF16; a.M = M; a.N = N; a.K = K; a.epi = EPI_NONE;
     *plan = plan_group(&a, 1);
-    return plan->us >= 60.0 && plan->us < 0.95 * plan_for(M, N, K, !trans_a, trans_b).us;
+    return plan->us >= BY_TURNS_MIN_US && plan->us < other_us;
 }
-size_t gemm_bf16_workspace_bytes(int64_t M, int64_t N, int64_t K) {
-    size_t need = 0;
-    for (int layout = 0; layout < 4; ++layout) {
-        const Plan pl = plan_for(M, N, K, (layout & 1) != 0, (layout & 2) != 0);
-        if (pl.shares > 1) need = std::max(need, (size_t)pl.shares * (size_t)M * (size_t)N * sizeof(float));
-        GroupPlan gp;
-        const GemmArgs a{};
-        if (by_turns(M, N, K, (layout & 1) == 0, (layout & 2) != 0, &gp)) need = std::max(need, pp_bytes(gp, &a, 1));
-    }
+size_t gemm_bf16_share_bytes(int64_t M, int64_t N, int64_t K, bool trans_a, bool trans_b) {
+    const Plan pl = plan_for(M, N, K, !trans_a, trans_b);
+    return pl.shares > 1 ? (size_t)pl.shares * (size_t)M * (size_t)N * sizeof(float) : 0;
+}
+size_t gemm_bf16_workspace_bytes(int64_t M, int64_t N, int64_t K, bool trans_a, bool trans_b) {
+    size_t need = gemm_bf16_share_bytes(M, N, K, trans_a, trans_b);
+    GroupPlan gp;
+    const GemmArgs a{};
+    if (by_turns(M, N, K, trans_a, trans_b, &gp)) need = std::max(need, pp_bytes(gp, &a, 1));
     return need;
 }
 

@@ -132,7 +132,8 @@ hipError_t attn_f32_bwd(const AttnArgs& a);
 
 // bf16 MFMA kernels for gfx950.
 bool gemm_bf16_supported(const GemmArgs& a);
-size_t gemm_bf16_workspace_bytes(int64_t M, int64_t N, int64_t K);
+size_t gemm_bf16_share_bytes(int64_t M, int64_t N, int64_t K, bool trans_a, bool trans_b);       // K shares on any but the tile by turns
+size_t gemm_bf16_workspace_bytes(int64_t M, int64_t N, int64_t K, bool trans_a, bool trans_b);   // whichever tile is taken
 hipError_t gemm_bf16(const GemmArgs& a, bool* colsum_done = nullptr);
 // Up to 4 GEMMs that do not depend on each other (layouts NN, NT, TN) as one launch; colsum_b of a TN one is always written.
 size_t gemm_bf16_group_workspace_bytes(const GemmArgs* g, int n);

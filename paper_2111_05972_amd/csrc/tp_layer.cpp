@@ -5,6 +5,7 @@
 #include <algorithm>
 #include <cstdlib>
 #include <cstring>
+#include <initializer_list>
 
 #include "kernels.h"
 
@@ -111,12 +112,14 @@ void saved_layout(const Dims& x, tp_layer_saved_layout* L) {
     L->total = off;
 }
 
-size_t gemm_ws(int dtype, int64_t M, int64_t N, int64_t K) {
-    return up(dtype == TPL_BF16 ? gemm_bf16_workspace_bytes(M, N, K) : gemm_f32_workspace_bytes(M, N, K));
+size_t gemm_ws(int dtype, int64_t M, int64_t N, int64_t K, bool trans_a, bool trans_b) {
+    return up(dtype == TPL_BF16 ? gemm_bf16_workspace_bytes(M, N, K, trans_a, trans_b) : gemm_f32_workspace_bytes(M, N, K));
 }
 
+// Forward scratch: of the GEMMs (each: one chain's; 0 where they go out in groups), then of attention.
+struct FwdWs { bool groups; size_t gemm_each, gemm_all, attn_bytes, total; };
 // Backward scratch: dU, dO, dQKV, D, and per chain (attention, MLP) column-sum partials and GEMM scratch.
-struct BwdWs { size_t du, d_o, dqkv, dsum, colsum, colsum2, gemm, gemm2, gemm3, gemm_each, gemm_all, attn, attn_bytes, total; };
+struct BwdWs { bool groups; size_t du, d_o, dqkv, dsum, colsum, colsum2, gemm, gemm2, gemm3, gemm_each, gemm_all, attn, attn_bytes, total; };
 
 // Float partials of attention strips cut into chunks: inside a layer pass only when TPL_ATTN_CHUNK forces a chunk
 // length (own_chunking stays 0: see attn_bf16.hip), so normally 0.
@@ -125,15 +128,6 @@ size_t attn_ws(const Dims& x, bool bwd) {
     a.dtype = x.dtype; a.B = (int)x.B; a.S = (int)x.S; a.nl = (int)x.nl; a.dh = (int)x.dh; a.causal = x.causal;
     if (x.dtype != BF16 || !attn_bf16_supported(a)) return 0;
     return up(attn_bf16_workspace_bytes(a, bwd));
-}
-
-size_t fwd_gemm_ws(const Dims& x) {
-    size_t g = 0;
-    g = std::max(g, gemm_ws(x.dtype, x.M, 3 * x.Hl, x.H));
-    g = std::max(g, gemm_ws(x.dtype, x.M, x.H, x.Hl));
-    g = std::max(g, gemm_ws(x.dtype, x.M, x.Il, x.H));
-    g = std::max(g, gemm_ws(x.dtype, x.M, x.H, x.Il));
-    return std::max(g, ALIGN);
 }
 
 // ---- GEMMs of a pass as groups ---------------------------------------------------------------------------------------
@@ -171,12 +165,28 @@ size_t group_ws(const Dims& x, bool bwd) {
     const auto bytes = x.dtype == BF16 ? gemm_bf16_group_workspace_bytes : gemm_f32_group_workspace_bytes;
     return up(std::max(bytes(first, n1), bytes(second, n2)));
 }
-// GEMM scratch of a pass: one region per chain, or what its groups need (the larger of both).
-size_t fwd_gemm_total(const Dims& x) { return std::max(2 * fwd_gemm_ws(x), group_ws(x, false)); }
-size_t fwd_ws_total(const Dims& x) { return fwd_gemm_total(x) + attn_ws(x, false); }
+bool use_groups(const Dims& x);
+// Largest scratch of a list of GEMMs launched one by one.
+struct GemmShape { int trans_a, trans_b; int64_t M, N, K; };
+size_t single_ws(const Dims& x, std::initializer_list<GemmShape> list, bool launched) {
+    size_t need = ALIGN;
+    for (const GemmShape& g : list)
+        need = std::max(need, launched || x.dtype != BF16 ? gemm_ws(x.dtype, g.M, g.N, g.K, g.trans_a, g.trans_b)
+                                                          : up(gemm_bf16_share_bytes(g.M, g.N, g.K, g.trans_a, g.trans_b)));
+    return need;
+}
+// Only what the pass launches is sized: a call does this before its first launch.
+void fwd_layout(const Dims& x, FwdWs* W) {
+    W->groups = use_groups(x);
+    W->gemm_each = W->groups ? 0 : single_ws(x, {{0, 0, x.M, 3 * x.Hl, x.H}, {0, 0, x.M, x.H, x.Hl}, {0, 0, x.M, x.Il, x.H}, {0, 0, x.M, x.H, x.Il}}, true);
+    W->gemm_all = W->groups ? std::max(group_ws(x, false), ALIGN) : 2 * W->gemm_each;
+    W->attn_bytes = attn_ws(x, false);
+    W->total = W->gemm_all + W->attn_bytes;
+}
 
 void bwd_layout(const Dims& x, BwdWs* W) {
     size_t off = 0;
+    W->groups = use_groups(x);
     W->du = off;   off += up((size_t)x.M * x.Il * x.esz);
     W->d_o = off;  off += up((size_t)x.M * x.Hl * x.esz);
     W->dqkv = off; off += up((size_t)x.M * 3 * x.Hl * x.esz);
@@ -184,18 +194,13 @@ void bwd_layout(const Dims& x, BwdWs* W) {
     int64_t nmax = std::max(std::max(x.Il, 3 * x.Hl), x.H);
     W->colsum = off; off += up(colsum_scratch_bytes(x.M, nmax));
     W->colsum2 = off; off += up(colsum_scratch_bytes(x.M, nmax));
-    size_t g = fwd_gemm_ws(x);   // dgrad shapes are the forward shapes with N and K swapped
-    g = std::max(g, gemm_ws(x.dtype, x.M, x.Hl, x.H));
-    g = std::max(g, gemm_ws(x.dtype, x.M, x.H, 3 * x.Hl));
-    g = std::max(g, gemm_ws(x.dtype, x.Il, x.H, x.M));
-    g = std::max(g, gemm_ws(x.dtype, x.H, x.Il, x.M));
-    g = std::max(g, gemm_ws(x.dtype, x.Hl, x.H, x.M));
-    g = std::max(g, gemm_ws(x.dtype, x.H, 3 * x.Hl, x.M));
-    W->gemm_each = g;
-    W->gemm = off; off += g;
-    W->gemm2 = off; off += g;
-    const size_t grouped = group_ws(x, true);          // spans the three regions
-    W->gemm3 = off; off += std::max(g, grouped > 2 * g ? grouped - 2 * g : 0);   // the two weight gradients that depend on nothing computed in the pass (third chain)
+    W->gemm_each = single_ws(x, {{0, 1, x.M, x.Il, x.H}, {1, 0, x.Il, x.H, x.M}, {1, 0, x.H, x.Il, x.M}, {0, 1, x.M, x.H, x.Il},
+                                 {0, 1, x.M, x.Hl, x.H}, {1, 0, x.Hl, x.H, x.M}, {1, 0, x.H, 3 * x.Hl, x.M}, {0, 1, x.M, x.H, 3 * x.Hl}}, !W->groups);
+    W->gemm = off;
+    W->gemm2 = W->gemm + W->gemm_each;
+    W->gemm3 = W->gemm2 + W->gemm_each;                // the two weight gradients that depend on nothing computed in the pass (third chain)
+    // groups: no less than two chains of single GEMMs cut on the other tiles, which callers have room for
+    off += W->groups ? std::max(group_ws(x, true), 2 * W->gemm_each) : 3 * W->gemm_each;
     W->gemm_all = off - W->gemm;
     W->attn_bytes = attn_ws(x, true);
     W->attn = off; off += W->attn_bytes;
@@ -330,20 +335,18 @@ int run_group(const GemmArgs* g, int n, const GemmScratch& sc) {
 
 // Forward kernels in order.  With row_parallel == false the two row-parallel GEMMs (whose outputs the
 // backward pass never reads) are skipped: that is the recomputation done in checkpoint mode.
-int fwd_impl(const Dims& x, const tp_layer_params* p, const void* x_attn, const void* x_mlp, void* y_attn,
-             void* y_mlp, void* saved, void* ws, size_t ws_bytes, hipStream_t s, bool row_parallel) {
+int fwd_impl(const Dims& x, const FwdWs& W, const tp_layer_params* p, const void* x_attn, const void* x_mlp, void* y_attn,
+             void* y_mlp, void* saved, void* ws, hipStream_t s, bool row_parallel) {
     int rc;
     tp_layer_saved_layout L;
     saved_layout(x, &L);
     char* sv = (char*)saved;
     void *qkv = sv + L.qkv, *o = sv + L.o, *u = sv + L.u, *g = sv + L.g;
     float* lse = (float*)(sv + L.lse);
-    // each chain has its own half of the GEMM scratch
-    const size_t half = fwd_gemm_ws(x), gemm_total = fwd_gemm_total(x);
-    const bool groups = use_groups(x);
+    const bool groups = W.groups;
     hipStream_t s2 = side_fork(s, x.side_stream && !groups);
     SideJoin sj{s, s2};
-    GemmScratch sc{ws, half, s}, sc2{(char*)ws + half, half, s2}, all{ws, gemm_total, s};
+    GemmScratch sc{ws, W.gemm_each, s}, sc2{(char*)ws + W.gemm_each, W.gemm_each, s2}, all{ws, W.gemm_all, s};
 
     // MLP block (second chain): column-parallel up-projection + GeLU, row-parallel down-projection
     GemmArgs g4 = mk(x, 0, 0, x.M, x.Il, x.H, x_mlp, p->w_up, g, sc2);
@@ -366,8 +369,8 @@ int fwd_impl(const Dims& x, const tp_layer_params* p, const void* x_attn, const 
     AttnArgs at{};
     at.dtype = x.dtype; at.B = (int)x.B; at.S = (int)x.S; at.nl = (int)x.nl; at.dh = (int)x.dh;
     at.causal = x.causal; at.qkv = qkv; at.o = o; at.lse = lse; at.stream = s;
-    at.ws_bytes = attn_ws(x, false);
-    at.ws = at.ws_bytes ? (char*)ws + gemm_total : nullptr;
+    at.ws_bytes = W.attn_bytes;
+    at.ws = at.ws_bytes ? (char*)ws + W.gemm_all : nullptr;
     if ((rc = run_attn(at, false))) return rc;
     if (row_parallel) {
         GemmArgs g3 = mk(x, 0, 0, x.M, x.H, x.Hl, o, p->w_o, y_attn, sc);
@@ -409,12 +412,10 @@ int bwd_check(const Dims& x, const tp_layer_params* p, const void* x_attn, const
 }
 
 // Backward kernels in order (arguments already checked, ws large enough).
-int bwd_impl(const Dims& x, const tp_layer_params* p, const void* x_attn, const void* x_mlp, const void* dy_attn,
+int bwd_impl(const Dims& x, const BwdWs& W, const tp_layer_params* p, const void* x_attn, const void* x_mlp, const void* dy_attn,
              const void* dy_mlp, const void* saved, const tp_layer_grads* gr, void* dx_attn, void* dx_mlp, void* ws,
              hipStream_t s) {
     int rc;
-    BwdWs W;
-    bwd_layout(x, &W);
     tp_layer_saved_layout L;
     saved_layout(x, &L);
     const char* sv = (const char*)saved;
@@ -423,7 +424,7 @@ int bwd_impl(const Dims& x, const tp_layer_params* p, const void* x_attn, const 
     char* w = (char*)ws;
     void *du = w + W.du, *d_o = w + W.d_o, *dqkv = w + W.dqkv;
     float *dsum = (float*)(w + W.dsum), *cs = (float*)(w + W.colsum), *cs2 = (float*)(w + W.colsum2);
-    const bool groups = use_groups(x), side = x.side_stream && !groups;
+    const bool groups = W.groups, side = x.side_stream && !groups;
     hipStream_t s2 = side_fork(s, side);
     SideJoin sj{s, s2};
     // dW_dn and dW_o need only the pass's inputs and saved activations: with option side_chains = 3 they are a third chain on a
@@ -509,7 +510,11 @@ int tp_layer_saved_offsets(const tp_layer_desc* desc, tp_layer_saved_layout* out
 size_t tp_layer_workspace_bytes(const tp_layer_desc* desc, int bwd) {
     Dims x;
     if (resolve(desc, &x) != TPL_OK) return 0;
-    if (!bwd) return fwd_ws_total(x);
+    if (!bwd) {
+        FwdWs F;
+        fwd_layout(x, &F);
+        return F.total;
+    }
     BwdWs W;
     bwd_layout(x, &W);
     return W.total;
@@ -524,8 +529,10 @@ int tp_layer_fwd(const tp_layer_desc* desc, const tp_layer_params* p, const void
     if ((rc = fwd_check(x, p, x_attn, x_mlp, ws, true))) return rc;
     if (!y_attn || !y_mlp || !saved) return TPL_EINVAL;
     if (misaligned(y_attn) || misaligned(y_mlp) || misaligned(saved)) return TPL_EALIGN;
-    if (ws_bytes < fwd_ws_total(x)) return TPL_EWORKSPACE;
-    return fwd_impl(x, p, x_attn, x_mlp, y_attn, y_mlp, saved, ws, ws_bytes, (hipStream_t)hip_stream, true);
+    FwdWs W;
+    fwd_layout(x, &W);
+    if (ws_bytes < W.total) return TPL_EWORKSPACE;
+    return fwd_impl(x, W, p, x_attn, x_mlp, y_attn, y_mlp, saved, ws, (hipStream_t)hip_stream, true);
 }
 
 int tp_layer_bwd(const tp_layer_desc* desc, const tp_layer_params* p, const void* x_attn,
@@ -541,7 +548,7 @@ int tp_layer_bwd(const tp_layer_desc* desc, const tp_layer_params* p, const void
     BwdWs W;
     bwd_layout(x, &W);
     if (ws_bytes < W.total) return TPL_EWORKSPACE;
-    return bwd_impl(x, p, x_attn, x_mlp, dy_attn, dy_mlp, saved, gr, dx_attn, dx_mlp, ws, (hipStream_t)hip_stream);
+    return bwd_impl(x, W, p, x_attn, x_mlp, dy_attn, dy_mlp, saved, gr, dx_attn, dx_mlp, ws, (hipStream_t)hip_stream);
 }
 
 size_t tp_layer_workspace_bytes_recompute(const tp_layer_desc* desc) {
@@ -549,9 +556,11 @@ size_t tp_layer_workspace_bytes_recompute(const tp_layer_desc* desc) {
     if (resolve(desc, &x) != TPL_OK) return 0;
     tp_layer_saved_layout L;
     saved_layout(x, &L);
+    FwdWs F;
+    fwd_layout(x, &F);
     BwdWs W;
     bwd_layout(x, &W);
-    return up(L.total) + std::max(W.total, fwd_ws_total(x));
+    return up(L.total) + std::max(W.total, F.total);
 }
 
 int tp_layer_bwd_recompute(const tp_layer_desc* desc, const tp_layer_params* p, const void* x_attn,
@@ -564,16 +573,19 @@ int tp_layer_bwd_recompute(const tp_layer_desc* desc, const tp_layer_params* p, 
     // everything either pass needs is checked before the recomputed forward is enqueued
     if ((rc = fwd_check(x, p, x_attn, x_mlp, ws, false))) return rc;
     if ((rc = bwd_check(x, p, x_attn, x_mlp, dy_attn, dy_mlp, gr, dx_attn, dx_mlp, ws))) return rc;
-    if (ws_bytes < tp_layer_workspace_bytes_recompute(desc)) return TPL_EWORKSPACE;
     tp_layer_saved_layout L;
     saved_layout(x, &L);
+    FwdWs F;
+    fwd_layout(x, &F);
+    BwdWs W;
+    bwd_layout(x, &W);
+    if (ws_bytes < up(L.total) + std::max(W.total, F.total)) return TPL_EWORKSPACE;
     char* saved = (char*)ws;
     char* rest = saved + up(L.total);
-    const size_t rest_bytes = ws_bytes - up(L.total);
     // recompute QKV, O, LSE, U, G from the block inputs, then the ordinary backward
-    rc = fwd_impl(x, p, x_attn, x_mlp, nullptr, nullptr, saved, rest, rest_bytes, (hipStream_t)hip_stream, false);
+    rc = fwd_impl(x, F, p, x_attn, x_mlp, nullptr, nullptr, saved, rest, (hipStream_t)hip_stream, false);
     if (rc != TPL_OK) return rc;
-    return bwd_impl(x, p, x_attn, x_mlp, dy_attn, dy_mlp, saved, gr, dx_attn, dx_mlp, rest, (hipStream_t)hip_stream);
+    return bwd_impl(x, W, p, x_attn, x_mlp, dy_attn, dy_mlp, saved, gr, dx_attn, dx_mlp, rest, (hipStream_t)hip_stream);
 }
 
 static int ln_check(int dtype, int64_t M, int64_t H) {
@@ -750,7 +762,9 @@ int tp_layer_slice_epilogue_bwd_static(int dtype, int act, int64_t M, int64_t N,
 
 size_t tp_layer_gemm_workspace_bytes(int dtype, int64_t M, int64_t N, int64_t K) {
     if (M <= 0 || N <= 0 || K <= 0) return 0;
-    return std::max(gemm_ws(dtype, M, N, K), ALIGN);
+    size_t need = ALIGN;                                       // whichever operands are transposed
+    for (int layout = 0; layout < 4; ++layout) need = std::max(need, gemm_ws(dtype, M, N, K, layout & 1, layout & 2));
+    return need;
 }
 
 int tp_layer_gemm(int dtype, int trans_a, int trans_b, int64_t M, int64_t N, int64_t K,
@@ -798,9 +812,9 @@ static bool items_in_one_launch(int n, const GemmArgs* g) {
 size_t tp_layer_gemm_group_workspace_bytes(int dtype, int n, const tp_layer_gemm_item* items) {
     GemmArgs g[4];
     if (group_items(dtype, n, items, g) != TPL_OK) return 0;
+    if (items_in_one_launch(n, g)) return std::max(ALIGN, up(dtype == TPL_BF16 ? gemm_bf16_group_workspace_bytes(g, n) : gemm_f32_group_workspace_bytes(g, n)));
     size_t need = ALIGN;
-    for (int i = 0; i < n; ++i) need = std::max(need, gemm_ws(dtype, g[i].M, g[i].N, g[i].K));
-    if (items_in_one_launch(n, g)) need = std::max(need, up(dtype == TPL_BF16 ? gemm_bf16_group_workspace_bytes(g, n) : gemm_f32_group_workspace_bytes(g, n)));
+    for (int i = 0; i < n; ++i) need = std::max(need, gemm_ws(dtype, g[i].M, g[i].N, g[i].K, g[i].trans_a, g[i].trans_b));
     return need;
 }
 int tp_layer_gemm_group(int dtype, int n, const tp_layer_gemm_item* items, void* ws, size_t ws_bytes, void* hip_stream) {

@@ -208,3 +208,36 @@ def test_gemm_workspace_follows_the_k_share_plan(tune):
     d = pkg.make_desc(cfg.hidden, cfg.heads, cfg.tp_degree, cfg.tp_rank, cfg.seq, cfg.micro_batch, pkg.TPL_BF16,
                       cfg.causal, cfg.row_epilogue, cfg.head_dim, cfg.intermediate)
     assert pkg.tp_layer_workspace_bytes(d, 1) >= 2 * few
+
+
+def test_layer_workspace_holds_what_its_passes_launch():
+    """Whole groups of GEMMs are launched, so no scratch of single GEMMs by turns is asked for.  GPT-3 175B TP 8: forward is the K
+    shares of one group (a single QKV projection alone would take 113 MB of them, twice)."""
+    cfg = synthetic.CONFIGS[5]
+    d = _desc(cfg)
+    acts = cfg.tokens * (cfg.local_mlp + 4 * cfg.local_attn) * 2
+    assert pkg.tp_layer_workspace_bytes(d, 0) <= 2 * cfg.tokens * (cfg.local_mlp + 3 * cfg.local_attn) * 4
+    assert pkg.tp_layer_workspace_bytes(d, 1) <= 4 * acts
+    # two chains of single GEMMs have a region each
+    one = pkg.tp_layer_gemm_workspace_bytes(pkg.TPL_BF16, cfg.tokens, 3 * cfg.local_attn, cfg.hidden)
+    pkg.tp_layer_set_option("gemm_group", "0")
+    try:
+        assert one > 1 << 20 and pkg.tp_layer_workspace_bytes(d, 0) <= 2 * one + 256
+    finally:
+        pkg.tp_layer_set_option("gemm_group", None)
+
+
+def test_plans_of_many_layer_shapes_are_kept():
+    """64 token counts of one layer in rotation: a size query that has been made before looks its plans up."""
+    import time
+    descs = [_desc(synthetic.CONFIGS[3], seq=512 + 8 * i) for i in range(64)]
+
+    def once():
+        t = time.perf_counter()
+        for d in descs:
+            pkg.tp_layer_workspace_bytes(d, 0)
+            pkg.tp_layer_workspace_bytes(d, 1)
+        return time.perf_counter() - t
+    pkg.tp_layer_set_option("gemm_group", None)      # starts a new generation of plans
+    first = once()
+    assert min(once() for _ in range(3)) < first / 4
