@@ -44,6 +44,7 @@
 // chunk order.  Strips of one chunk write their result directly, as without a workspace.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 #include <cstdlib>
 #include <type_traits>
@@ -1738,15 +1739,24 @@ size_t attn_bf16_workspace_bytes(const AttnArgs& a0, bool bwd) {
     return (cuts(a, false, ch_q) ? part_bytes_dq(a, ch_q) : 0) + (cuts(a, true, ch_kv) ? part_bytes_dkv(a, ch_kv) : 0);
 }
 
-// Whether a launch of n workgroups goes to the kernels whose wavefronts own their rows outright, measured on both sides, us with
-// keys (roles) shared by two wavefronts and with own rows.  Forward, head size 128: 768 causal workgroups 297 and 257, 320 39.5 and
-// 48.9, 192 35 and 42, 256 without a mask 17.5 and 17.2; head size 64: 256 causal 16.3 and 18.4, 512 59 and 59, 512 without a mask
-// 17.2 and 16.7.  A wavefront alone walks a strip in almost twice the time, so the longest of a few causal strips would set the
-// duration.  Backward, head size 64: 1024 workgroups 165 and 141 causal, 59.4 and 47.8 without a mask, 512 35 and 38, 256 18 and 21;
-// head size 128 (a wavefront per SIMD, 420 registers) 845 and 988 when both roles worked the scores out, 761 now, so not built.
-static bool own_rows(bool causal, bool bwd, int64_t n) {
+// Whether a launch of n workgroups, the longest of `steps` tile steps, goes to the kernels whose wavefronts own their rows outright.  A
+// wavefront alone walks a strip in up to 1.3 times the time (without a mask; 1.9 on the diagonal's half strips), so the longest strip of a
+// launch that finds its units at once would set the duration; with more workgroups than units two share one and hide each other's waits.
+// us with keys (roles) shared by two wavefronts and with own rows:
+//   forward, no mask   up to a workgroup per unit: head size 128, 64 workgroups of 256 / 384 / 2048 / 4096 tokens 10.5 and 10.2 / 12.6 and
+//                      12.8 / 35 and 41 / 63 and 79; head size 64 of 512 / 768 / 1024 / 4096 tokens 10.0 and 9.7 / 13.1 and 13.2 / 16.3 and
+//                      16.5 / 47 and 51.  Beyond: 288 workgroups of 4096 tokens 133 and 102 (64: 75 and 70), 1024 292 and 264 (168 and 158);
+//                      768 of 4096 to 8192 tokens at head size 128, three rounds of one form, level (218 and 221, 415 and 427)
+//   forward, causal    head size 128: 768 workgroups 297 and 257, 640 of 512 / 8192 tokens 35 and 27 / 203 and 194, 320 39.5 and 48.9;
+//                      head size 64: 640 of 512 / 2048 / 4096 / 8192 tokens 20 and 16 / 38.2 and 36.8 / 63.8 and 65.2 / 119.7 and 122.9, 704
+//                      of 4096 71.2 and 68.5, 512 59 and 59
+//   backward           head size 64: 1024 workgroups 165 and 141 causal, 59.4 and 47.8 without a mask, 512 35 and 38, 256 18 and 21; head
+//                      size 128 (a wavefront per SIMD, 420 registers) 845 and 988 when both roles worked the scores out, so not built
+static bool own_rows(int dh, bool causal, bool bwd, int64_t n, int steps) {
     const int64_t cus = compute_units();
-    return bwd ? n >= 3 * cus : !causal || n >= 5 * cus / 2;
+    if (bwd) return n >= 3 * cus;
+    if (causal) return 4 * n >= (dh == 64 && steps > 48 ? 11 : 10) * cus;
+    return n > cus || steps <= (dh == 64 ? 12 : 5);
 }
 
 template <int DH, bool CAUSAL, bool FLOATW>
@@ -1767,7 +1777,7 @@ static hipError_t fwd_t(const AttnArgs& a) {
     float* part = static_cast<float*>(a.ws);
     bool launched = false;
     if constexpr (!FLOATW) {
-        if (own_rows(CAUSAL, false, wgs)) {
+        if (own_rows(DH, CAUSAL, false, wgs, std::min(ch.ch, (a.S + TILE - 1) / TILE))) {
             hipLaunchKernelGGL((attn_fwd_rows_kernel<DH, CAUSAL>), dim3((unsigned)wgs), dim3(WTHREADS), LDS_ROWS, a.stream,
                                (const bf16_t*)a.qkv, (bf16_t*)a.o, a.lse, a.S, a.nl, BH, part, ch);
             launched = true;
@@ -1813,7 +1823,7 @@ static hipError_t bwd_t(const AttnArgs& a) {
                        (const bf16_t*)a.o, (const bf16_t*)a.d_o, a.dsum, a.B, a.S, a.nl, a.dh);
     bool launched = false;
     if constexpr (OWN_ROWS) {
-        if (own_rows(CAUSAL, true, wgs_kv + wgs_q)) {
+        if (own_rows(DH, CAUSAL, true, wgs_kv + wgs_q, 0)) {
             hipLaunchKernelGGL((attn_bwd_rows_kernel<DH, CAUSAL>), dim3((unsigned)(wgs_kv + wgs_q)), dim3(WTHREADS), LDS_ROWS, a.stream,
                                (const bf16_t*)a.qkv, (const bf16_t*)a.d_o, a.lse, a.dsum, (bf16_t*)a.dqkv, a.S, a.nl, BH, part_kv, part_q,
                                ch_kv, ch_q, (int)wgs_kv);

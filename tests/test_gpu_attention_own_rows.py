@@ -60,3 +60,29 @@ def test_many_workgroups(case, causal, tune):
         y[0, j, 2, 0, 3] = float("inf")
         hit = run(y.view(B * S, 3 * nl * dh))[0]
         assert torch.equal(hit.view(B, S, nl * dh)[0, :j], o.view(B, S, nl * dh)[0, :j])
+
+
+# forward without a mask: rows shared by two wavefronts where a workgroup per compute unit (256) has strips of more than 12 steps of 64
+# keys (head size 64; 5 at 128), own rows where the strips are shorter, cut, or two workgroups share a unit
+@pytest.mark.parametrize("B,S,nl,dh,chunk", [(1, 768, 3, 64, None), (1, 769, 3, 64, None), (2, 830, 18, 64, None), (1, 830, 37, 64, None), (1, 1000, 2, 64, "8"),
+                                             (1, 320, 3, 128, None), (1, 321, 3, 128, None), (2, 449, 32, 128, None), (5, 449, 13, 128, None), (1, 700, 2, 128, "5")])
+def test_forward_without_a_mask(B, S, nl, dh, chunk, tune):
+    import torch
+    import paper_2111_05972_amd as pkg
+    tune.set("attn_chunk", chunk)
+    print(f"\n[attn] {B} {S} {nl} {dh} chunk={chunk}", flush=True)
+    dt = pkg.TPL_BF16
+    nbytes = pkg.tp_layer_attn_workspace_bytes(dt, B, S, nl, dh, False, False) if chunk else 0
+    ws = torch.full((nbytes // 4,), float("nan"), dtype=torch.float32, device="cuda") if chunk else None
+    qkv = _draw(91, (B * S, 3 * nl * dh))
+    Q, K, V = (qkv.reshape(B, S, 3, nl, dh).astype(np.float64)[:, :, i].transpose(0, 2, 1, 3) for i in range(3))
+    O, _, LSE = oracle.attention_fwd(Q, K, V, False)
+    x, runs = pkg.to_device(qkv, dt), []
+    for _ in range(2):
+        o, lse = torch.full((B * S, nl * dh), 9.0, dtype=x.dtype, device="cuda"), torch.empty(B, nl, S, dtype=torch.float32, device="cuda")
+        pkg.tp_layer_attn_fwd(dt, B, S, nl, dh, False, x, o, lse, ws=ws, stream=torch.cuda.current_stream())
+        torch.cuda.synchronize()
+        runs.append((o, lse))
+    assert oracle.max_rel_err(runs[0][0].float().cpu().numpy(), O.transpose(0, 2, 1, 3).reshape(B * S, nl * dh)) <= 2e-2
+    assert np.abs(runs[0][1].cpu().numpy() - LSE).max() <= 2e-2
+    assert torch.equal(runs[0][0], runs[1][0]) and torch.equal(runs[0][1], runs[1][1])
