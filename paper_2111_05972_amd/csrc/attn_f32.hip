@@ -274,228 +274,209 @@ __global__ __launch_bounds__(256) void attn_f32_dsum_kernel(const float* __restr
     }
 }
 
-// ---- dQ: workgroup = (32 queries, batch*head); also leaves D for the dK/dV kernel unless that is given --------------
-template <int DH, int DK_D>
-__device__ __forceinline__ void attn_f32_dq(char* smem, int wg, int S, int nl, int dh, int causal, int nblk, const float* __restrict__ qkv,
-                                            const float* __restrict__ o, const float* __restrict__ lse, const float* __restrict__ d_o,
-                                            float* __restrict__ dqkv, float* dsum) {
-    constexpr int TB = xtile_bytes<DH>(), NL = xloads<DH>();
-    const int lane = threadIdx.x & 63, half = lane >> 5, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int qb = nblk - 1 - wg % nblk, bh = wg / nblk, b = bh / nl, h = bh % nl;
-    const int64_t ld = 3LL * nl * dh, ldo = (int64_t)nl * dh;
-    const float* qbase = qkv + (int64_t)b * S * ld + (int64_t)h * dh;
-    const i32x4 rk = xrsrc(qbase + (int64_t)nl * dh, ld, S, dh), rv = xrsrc(qbase + 2LL * nl * dh, ld, S, dh);
-    const int q0 = qb * XT, q = q0 + (lane & 31);
-    const float scale = 1.0f / sqrtf((float)dh);
-    char* kt_ = smem + wave * 2 * TB;
-    const unsigned lk = (unsigned)(uintptr_t)(lds_void_ptr)kt_, lv = lk + TB;
-    float qr[DH / 2], gr[DH / 2];
-    xrow<DH>(qr, qbase, ld, q, S, dh, lane);
-    const int64_t orow = (int64_t)b * S * ldo + (int64_t)h * dh;
-    xrow<DH>(gr, d_o + orow, ldo, q, S, dh, lane);
-    float D = 0.0f;
-    {
-        float orr[DH / 2];
-        xrow<DH>(orr, o + orow, ldo, q, S, dh, lane);
-#pragma unroll
-        for (int e = 0; e < DH / 2; ++e) D = fmaf(gr[e], orr[e], D);
-        D += xother(D);
-    }
-    const float L = q < S ? lse[(int64_t)bh * S + q] : 0.0f;
-    if (DK_D != D_GIVEN && wave == 0 && half == 0 && q < S) dsum[(int64_t)bh * S + q] = D;
-    f32x16 acc[DH / 32];
-#pragma unroll
-    for (int d = 0; d < DH / 32; ++d)
-#pragma unroll
-        for (int v = 0; v < 16; ++v) acc[d][v] = 0.0f;
-    const int nt = causal ? qb + 1 : (S + XT - 1) / XT;
-    unsigned off[NL];
-    xoffsets<DH>(off, ld, dh, lane);
-    // V first: it is read first
-    if (wave < nt) { xfetch<DH>(rv, lv, off, wave * XT, ld); xfetch<DH>(rk, lk, off, wave * XT, ld); }
-    for (int t = wave; t < nt; t += 4) {
-        const int nx = t + 4;
-        xwait<NL>();
-        f32x16 dp = xscores<DH>(kt_ + TB, gr, lane);              // dP^T = V dO^T
-        xreads_done();
-        xfetch<DH>(rv, lv, off, nx < nt ? nx * XT : S, ld);
-        xwait<NL>();
-        const f32x16 s = xscores<DH>(kt_, qr, lane);
-        const int k0 = t * XT;
-        const bool edge = k0 + XT > S || (causal && k0 + XT - 1 > q0);
-#pragma unroll
-        for (int v = 0; v < 16; ++v) {
-            float p = expf(s[v] * scale - L);
-            if (edge) {
-                const int k = k0 + 8 * (v >> 2) + 4 * half + (v & 3);
-                if (k >= S || (causal && k > q)) p = 0.0f;
-            }
-            dp[v] = p * (dp[v] - D);
-        }
-        xaccumulate<DH>(acc, kt_, dp, lane);                      // dQ^T += K^T dS
-        xreads_done();
-        xfetch<DH>(rk, lk, off, nx < nt ? nx * XT : S, ld);
-    }
-    xwait<0>();
-    const float f[4] = {scale, scale, scale, scale};
-    float* dqp = dqkv + ((int64_t)b * S + q) * ld + (int64_t)h * dh;
-    const float z = xcombine<DH>(smem, acc, f, wave, lane, [&](int d, int i, const float (&r)[4]) {
-        const int c = d * 32 + 8 * i + 4 * half;
-        if (q < S && c < dh) *reinterpret_cast<float4*>(dqp + c) = make_float4(r[0], r[1], r[2], r[3]);
-    });
-    if (!causal || !__any(z != 0.0f)) return;
-    rows_stored();
-    float* q_s = xrows<DH>(smem, wave);
-    for (int i = q0; i < q0 + XT && i < S; ++i) {
-        load_row(q_s, qbase + (int64_t)i * ld, dh, lane);
-        load_row(q_s + DH, d_o + orow + (int64_t)i * ldo, dh, lane);
-        row_loaded();
-        float* dqi = dqkv + ((int64_t)b * S + i) * ld + (int64_t)h * dh;
-        float Di = 0.0f;
-        for (int d = lane; d < dh; d += 64) Di = fmaf(q_s[DH + d], o[orow + (int64_t)i * ldo + d], Di);
-        attn_row_dq<(DH + 63) / 64>(q_s, q_s + DH, qbase + (int64_t)nl * dh, qbase + 2LL * nl * dh, ld, dh, 0, i + 1, scale,
-                                    lse[(int64_t)bh * S + i], row_sum(Di), lane, [&](int d, float v) { if (xmine(d, wave)) dqi[d] = v * scale; });
-        row_loaded();
-    }
-}
-
-// ---- dK, dV: workgroup = (32 keys, batch*head) -----------------------------------------------------------------------
-// D_OWN: D of the query tiles is worked out here (and stored, the same value that dQ's workgroups store), not read.
-template <int DH, int DK_D>
-__device__ __forceinline__ void attn_f32_dkv(char* smem, int wg, int S, int nl, int dh, int causal, int nblk, const float* __restrict__ qkv,
-                                             const float* __restrict__ o, const float* __restrict__ lse, const float* __restrict__ d_o,
-                                             float* __restrict__ dqkv, float* dsum) {
-    constexpr int TB = xtile_bytes<DH>(), NL = xloads<DH>();
-    const int lane = threadIdx.x & 63, half = lane >> 5, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int kb = wg % nblk, bh = wg / nblk, b = bh / nl, h = bh % nl;   // long strips first
-    const int64_t ld = 3LL * nl * dh, ldo = (int64_t)nl * dh;
-    const float* qbase = qkv + (int64_t)b * S * ld + (int64_t)h * dh;
-    const i32x4 rq = xrsrc(qbase, ld, S, dh), rg = xrsrc(d_o + (int64_t)b * S * ldo + (int64_t)h * dh, ldo, S, dh);
-    const int k0 = kb * XT, k = k0 + (lane & 31);
-    const float scale = 1.0f / sqrtf((float)dh);
-    float kr[DH / 2], vr[DH / 2];
-    xrow<DH>(kr, qbase + (int64_t)nl * dh, ld, k, S, dh, lane);
-    xrow<DH>(vr, qbase + 2LL * nl * dh, ld, k, S, dh, lane);
-    f32x16 dk[DH / 32], dv[DH / 32];
-#pragma unroll
-    for (int d = 0; d < DH / 32; ++d)
-#pragma unroll
-        for (int v = 0; v < 16; ++v) { dk[d][v] = 0.0f; dv[d][v] = 0.0f; }
-    const float* lrow = lse + (int64_t)bh * S;
-    float* drow = dsum + (int64_t)bh * S;
-    char* qt_ = smem + wave * 2 * TB;
-    const unsigned lq = (unsigned)(uintptr_t)(lds_void_ptr)qt_, lg = lq + TB;
-    float* terms = reinterpret_cast<float*>(smem + 8 * TB) + wave * 2 * XT;   // LSE, D of the tile's queries
-    const int t0 = causal ? kb : 0, nt = (S + XT - 1) / XT;
-    unsigned offq[NL], offg[NL];
-    xoffsets<DH>(offq, ld, dh, lane);
-    xoffsets<DH>(offg, ldo, dh, lane);
-    auto term = [&](int t) {                                      // lanes 0..31: LSE, lanes 32..63: D
-        const int i = t * XT + (lane & 31);
-        if constexpr (DK_D == D_OWN) {
-            float gr[DH / 2], orr[DH / 2], D = 0.0f;
-            const int64_t orow = (int64_t)b * S * ldo + (int64_t)h * dh;
-            xrow<DH>(gr, d_o + orow, ldo, i, S, dh, lane);
-            xrow<DH>(orr, o + orow, ldo, i, S, dh, lane);
-#pragma unroll
-            for (int e = 0; e < DH / 2; ++e) D = fmaf(gr[e], orr[e], D);
-            D += xother(D);
-            if (half == 0 && i < S) drow[i] = D;
-            return i < S ? (half ? D : lrow[i]) : 0.0f;
-        }
-        return i < S ? (half ? drow[i] : lrow[i]) : 0.0f;
-    };
-    float tn = 0.0f;
-    if (t0 + wave < nt) {
-        tn = term(t0 + wave);
-        xfetch<DH>(rq, lq, offq, (t0 + wave) * XT, ld);
-        xfetch<DH>(rg, lg, offg, (t0 + wave) * XT, ldo);
-    }
-    for (int t = t0 + wave; t < nt; t += 4) {
-        const int nx = t + 4;
-        terms[lane] = tn;
-        xwait<0>();
-        if (nx < nt) tn = term(nx);
-        f32x16 p = xscores<DH>(qt_, kr, lane);
-        f32x16 ds = xscores<DH>(qt_ + TB, vr, lane);              // dP = dO V^T
-        const int q0 = t * XT;
-        const bool edge = q0 + XT > S || k0 + XT > S || (causal && k0 + XT - 1 > q0);
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const float4 l4 = *reinterpret_cast<const float4*>(terms + 8 * i + 4 * half);
-            const float4 d4 = *reinterpret_cast<const float4*>(terms + XT + 8 * i + 4 * half);
-            const float lv[4] = {l4.x, l4.y, l4.z, l4.w}, dv4[4] = {d4.x, d4.y, d4.z, d4.w};
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const int v = 4 * i + j;
-                float e = expf(p[v] * scale - lv[j]);
-                if (edge) {
-                    const int q = q0 + 8 * i + 4 * half + j;
-                    if (q >= S || k >= S || (causal && k > q)) e = 0.0f;
-                }
-                p[v] = e;
-                ds[v] = e * (ds[v] - dv4[j]);
-            }
-        }
-        xaccumulate<DH>(dv, qt_ + TB, p, lane);                   // dV^T += dO^T P
-        xreads_done();
-        xfetch<DH>(rg, lg, offg, nx < nt ? nx * XT : S, ldo);
-        xaccumulate<DH>(dk, qt_, ds, lane);                       // dK^T += Q^T dS
-        xreads_done();
-        xfetch<DH>(rq, lq, offq, nx < nt ? nx * XT : S, ld);
-    }
-    xwait<0>();
-    float* kp = dqkv + ((int64_t)b * S + k) * ld + (int64_t)nl * dh + (int64_t)h * dh;
-    float* vp = kp + (int64_t)nl * dh;
-    const float fk[4] = {scale, scale, scale, scale}, fv[4] = {1.0f, 1.0f, 1.0f, 1.0f};
-    float z = xcombine<DH>(smem, dk, fk, wave, lane, [&](int d, int i, const float (&r)[4]) {
-        const int c = d * 32 + 8 * i + 4 * half;
-        if (k < S && c < dh) *reinterpret_cast<float4*>(kp + c) = make_float4(r[0], r[1], r[2], r[3]);
-    });
-    z += xcombine<DH>(smem, dv, fv, wave, lane, [&](int d, int i, const float (&r)[4]) {
-        const int c = d * 32 + 8 * i + 4 * half;
-        if (k < S && c < dh) *reinterpret_cast<float4*>(vp + c) = make_float4(r[0], r[1], r[2], r[3]);
-    });
-    if (!causal || !__any(z != 0.0f)) return;
-    rows_stored();
-    float* k_s = xrows<DH>(smem, wave);
-    for (int j = k0; j < k0 + XT && j < S; ++j) {
-        const float* kj = qbase + (int64_t)nl * dh + (int64_t)j * ld;
-        load_row(k_s, kj, dh, lane);
-        load_row(k_s + DH, kj + (int64_t)nl * dh, dh, lane);
-        row_loaded();
-        float* dkj = dqkv + ((int64_t)b * S + j) * ld + (int64_t)nl * dh + (int64_t)h * dh;
-        float* dvj = dkj + (int64_t)nl * dh;
-        attn_row_dkv<(DH + 63) / 64>(k_s, k_s + DH, qbase, ld, d_o + (int64_t)b * S * ldo + (int64_t)h * dh, ldo, lrow, drow, dh, j, S, scale,
-                                     lane, [&](int d, float a, float v) { if (xmine(d, wave)) { dkj[d] = a * scale; dvj[d] = v; } });
-        row_loaded();
-    }
-}
-
-template <int DH>
-__global__ __launch_bounds__(256) void attn_f32_dq_kernel(int S, int nl, int dh, int causal, int nblk, const float* __restrict__ qkv,
-                                                          const float* __restrict__ o, const float* __restrict__ lse,
-                                                          const float* __restrict__ d_o, float* __restrict__ dqkv, float* dsum) {
-    extern __shared__ __attribute__((aligned(16))) char smem[];
-    attn_f32_dq<DH, D_OF_DQ>(smem, blockIdx.x, S, nl, dh, causal, nblk, qkv, o, lse, d_o, dqkv, dsum);
-}
-template <int DH>
-__global__ __launch_bounds__(256) void attn_f32_dkv_kernel(int S, int nl, int dh, int causal, int nblk, const float* __restrict__ qkv,
-                                                           const float* __restrict__ lse, const float* __restrict__ d_o,
-                                                           float* __restrict__ dqkv, float* dsum) {
-    extern __shared__ __attribute__((aligned(16))) char smem[];
-    attn_f32_dkv<DH, D_OF_DQ>(smem, blockIdx.x, S, nl, dh, causal, nblk, qkv, nullptr, lse, d_o, dqkv, dsum);
-}
-// Both in one launch of n + n workgroups: dK/dV does not wait for dQ's, D is given or worked out for its query tiles as well.
-// With D given two workgroups share a compute unit (at most 256 registers).  This launch starts at workgroup wg0 of them.
-template <int DH, int DK_D>
+// ---- backward: n workgroups of (32 keys, batch*head) for dK and dV, n of (32 queries, batch*head) for dQ ------------------------------
+// KIND_BOTH: all of them in one launch, dK/dV first; this launch starts at workgroup wg0 of the 2 n.  dK/dV does not wait for dQ's: D is
+// given or worked out for its query tiles as well.  With D given two workgroups share a compute unit (at most 256 registers).  dQ leaves D
+// for dK/dV unless it is given; D_OWN: dK/dV stores the same value that dQ's workgroups store.
+// Both stand in the kernel itself: as functions called from it they spilled up to 24 scalar registers (2048 tokens, 4 heads of 80 / 128,
+// causal 213 / 326 us, so 208 / 298; heads of 32 1 to 5 % faster, of 64 between 2 % slower and 3 % faster).
+enum { KIND_DQ, KIND_DKV, KIND_BOTH };
+template <int DH, int DK_D, int KIND>
 __global__ __launch_bounds__(256, DK_D == D_GIVEN ? 2 : 1) void attn_f32_bwd_kernel(int n, int wg0, int S, int nl, int dh, int causal, int nblk, const float* __restrict__ qkv,
                                                            const float* __restrict__ o, const float* __restrict__ lse,
                                                            const float* __restrict__ d_o, float* __restrict__ dqkv, float* dsum) {
     extern __shared__ __attribute__((aligned(16))) char smem[];
-    const int wg = blockIdx.x + wg0;                              // uniform: one kind per workgroup
-    if (wg < n) attn_f32_dkv<DH, DK_D>(smem, wg, S, nl, dh, causal, nblk, qkv, o, lse, d_o, dqkv, dsum);
-    else attn_f32_dq<DH, DK_D>(smem, wg - n, S, nl, dh, causal, nblk, qkv, o, lse, d_o, dqkv, dsum);
+    const int first = blockIdx.x + wg0;                           // uniform: one kind per workgroup
+    if (KIND == KIND_DQ || (KIND == KIND_BOTH && first >= n)) {
+        const int wg = KIND == KIND_BOTH ? first - n : first;
+        constexpr int TB = xtile_bytes<DH>(), NL = xloads<DH>();
+        const int lane = threadIdx.x & 63, half = lane >> 5, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+        const int qb = nblk - 1 - wg % nblk, bh = wg / nblk, b = bh / nl, h = bh % nl;
+        const int64_t ld = 3LL * nl * dh, ldo = (int64_t)nl * dh;
+        const float* qbase = qkv + (int64_t)b * S * ld + (int64_t)h * dh;
+        const i32x4 rk = xrsrc(qbase + (int64_t)nl * dh, ld, S, dh), rv = xrsrc(qbase + 2LL * nl * dh, ld, S, dh);
+        const int q0 = qb * XT, q = q0 + (lane & 31);
+        const float scale = 1.0f / sqrtf((float)dh);
+        char* kt_ = smem + wave * 2 * TB;
+        const unsigned lk = (unsigned)(uintptr_t)(lds_void_ptr)kt_, lv = lk + TB;
+        float qr[DH / 2], gr[DH / 2];
+        xrow<DH>(qr, qbase, ld, q, S, dh, lane);
+        const int64_t orow = (int64_t)b * S * ldo + (int64_t)h * dh;
+        xrow<DH>(gr, d_o + orow, ldo, q, S, dh, lane);
+        float D = 0.0f;
+        {
+            float orr[DH / 2];
+            xrow<DH>(orr, o + orow, ldo, q, S, dh, lane);
+#pragma unroll
+            for (int e = 0; e < DH / 2; ++e) D = fmaf(gr[e], orr[e], D);
+            D += xother(D);
+        }
+        const float L = q < S ? lse[(int64_t)bh * S + q] : 0.0f;
+        if (DK_D != D_GIVEN && wave == 0 && half == 0 && q < S) dsum[(int64_t)bh * S + q] = D;
+        f32x16 acc[DH / 32];
+#pragma unroll
+        for (int d = 0; d < DH / 32; ++d)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) acc[d][v] = 0.0f;
+        const int nt = causal ? qb + 1 : (S + XT - 1) / XT;
+        unsigned off[NL];
+        xoffsets<DH>(off, ld, dh, lane);
+        // V first: it is read first
+        if (wave < nt) { xfetch<DH>(rv, lv, off, wave * XT, ld); xfetch<DH>(rk, lk, off, wave * XT, ld); }
+        for (int t = wave; t < nt; t += 4) {
+            const int nx = t + 4;
+            xwait<NL>();
+            f32x16 dp = xscores<DH>(kt_ + TB, gr, lane);              // dP^T = V dO^T
+            xreads_done();
+            xfetch<DH>(rv, lv, off, nx < nt ? nx * XT : S, ld);
+            xwait<NL>();
+            const f32x16 s = xscores<DH>(kt_, qr, lane);
+            const int k0 = t * XT;
+            const bool edge = k0 + XT > S || (causal && k0 + XT - 1 > q0);
+#pragma unroll
+            for (int v = 0; v < 16; ++v) {
+                float p = expf(s[v] * scale - L);
+                if (edge) {
+                    const int k = k0 + 8 * (v >> 2) + 4 * half + (v & 3);
+                    if (k >= S || (causal && k > q)) p = 0.0f;
+                }
+                dp[v] = p * (dp[v] - D);
+            }
+            xaccumulate<DH>(acc, kt_, dp, lane);                      // dQ^T += K^T dS
+            xreads_done();
+            xfetch<DH>(rk, lk, off, nx < nt ? nx * XT : S, ld);
+        }
+        xwait<0>();
+        const float f[4] = {scale, scale, scale, scale};
+        float* dqp = dqkv + ((int64_t)b * S + q) * ld + (int64_t)h * dh;
+        const float z = xcombine<DH>(smem, acc, f, wave, lane, [&](int d, int i, const float (&r)[4]) {
+            const int c = d * 32 + 8 * i + 4 * half;
+            if (q < S && c < dh) *reinterpret_cast<float4*>(dqp + c) = make_float4(r[0], r[1], r[2], r[3]);
+        });
+        if (!causal || !__any(z != 0.0f)) return;
+        rows_stored();
+        float* q_s = xrows<DH>(smem, wave);
+        for (int i = q0; i < q0 + XT && i < S; ++i) {
+            load_row(q_s, qbase + (int64_t)i * ld, dh, lane);
+            load_row(q_s + DH, d_o + orow + (int64_t)i * ldo, dh, lane);
+            row_loaded();
+            float* dqi = dqkv + ((int64_t)b * S + i) * ld + (int64_t)h * dh;
+            float Di = 0.0f;
+            for (int d = lane; d < dh; d += 64) Di = fmaf(q_s[DH + d], o[orow + (int64_t)i * ldo + d], Di);
+            attn_row_dq<(DH + 63) / 64>(q_s, q_s + DH, qbase + (int64_t)nl * dh, qbase + 2LL * nl * dh, ld, dh, 0, i + 1, scale,
+                                        lse[(int64_t)bh * S + i], row_sum(Di), lane, [&](int d, float v) { if (xmine(d, wave)) dqi[d] = v * scale; });
+            row_loaded();
+        }
+        return;
+    }
+    if constexpr (KIND != KIND_DQ) {
+        const int wg = first;
+        constexpr int TB = xtile_bytes<DH>(), NL = xloads<DH>();
+        const int lane = threadIdx.x & 63, half = lane >> 5, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+        const int kb = wg % nblk, bh = wg / nblk, b = bh / nl, h = bh % nl;   // long strips first
+        const int64_t ld = 3LL * nl * dh, ldo = (int64_t)nl * dh;
+        const float* qbase = qkv + (int64_t)b * S * ld + (int64_t)h * dh;
+        const i32x4 rq = xrsrc(qbase, ld, S, dh), rg = xrsrc(d_o + (int64_t)b * S * ldo + (int64_t)h * dh, ldo, S, dh);
+        const int k0 = kb * XT, k = k0 + (lane & 31);
+        const float scale = 1.0f / sqrtf((float)dh);
+        float kr[DH / 2], vr[DH / 2];
+        xrow<DH>(kr, qbase + (int64_t)nl * dh, ld, k, S, dh, lane);
+        xrow<DH>(vr, qbase + 2LL * nl * dh, ld, k, S, dh, lane);
+        f32x16 dk[DH / 32], dv[DH / 32];
+#pragma unroll
+        for (int d = 0; d < DH / 32; ++d)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) { dk[d][v] = 0.0f; dv[d][v] = 0.0f; }
+        const float* lrow = lse + (int64_t)bh * S;
+        float* drow = dsum + (int64_t)bh * S;
+        char* qt_ = smem + wave * 2 * TB;
+        const unsigned lq = (unsigned)(uintptr_t)(lds_void_ptr)qt_, lg = lq + TB;
+        float* terms = reinterpret_cast<float*>(smem + 8 * TB) + wave * 2 * XT;   // LSE, D of the tile's queries
+        const int t0 = causal ? kb : 0, nt = (S + XT - 1) / XT;
+        unsigned offq[NL], offg[NL];
+        xoffsets<DH>(offq, ld, dh, lane);
+        xoffsets<DH>(offg, ldo, dh, lane);
+        auto term = [&](int t) {                                      // lanes 0..31: LSE, lanes 32..63: D
+            const int i = t * XT + (lane & 31);
+            if constexpr (DK_D == D_OWN) {
+                float gr[DH / 2], orr[DH / 2], D = 0.0f;
+                const int64_t orow = (int64_t)b * S * ldo + (int64_t)h * dh;
+                xrow<DH>(gr, d_o + orow, ldo, i, S, dh, lane);
+                xrow<DH>(orr, o + orow, ldo, i, S, dh, lane);
+#pragma unroll
+                for (int e = 0; e < DH / 2; ++e) D = fmaf(gr[e], orr[e], D);
+                D += xother(D);
+                if (half == 0 && i < S) drow[i] = D;
+                return i < S ? (half ? D : lrow[i]) : 0.0f;
+            }
+            return i < S ? (half ? drow[i] : lrow[i]) : 0.0f;
+        };
+        float tn = 0.0f;
+        if (t0 + wave < nt) {
+            tn = term(t0 + wave);
+            xfetch<DH>(rq, lq, offq, (t0 + wave) * XT, ld);
+            xfetch<DH>(rg, lg, offg, (t0 + wave) * XT, ldo);
+        }
+        for (int t = t0 + wave; t < nt; t += 4) {
+            const int nx = t + 4;
+            terms[lane] = tn;
+            xwait<0>();
+            if (nx < nt) tn = term(nx);
+            f32x16 p = xscores<DH>(qt_, kr, lane);
+            f32x16 ds = xscores<DH>(qt_ + TB, vr, lane);              // dP = dO V^T
+            const int q0 = t * XT;
+            const bool edge = q0 + XT > S || k0 + XT > S || (causal && k0 + XT - 1 > q0);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const float4 l4 = *reinterpret_cast<const float4*>(terms + 8 * i + 4 * half);
+                const float4 d4 = *reinterpret_cast<const float4*>(terms + XT + 8 * i + 4 * half);
+                const float lv[4] = {l4.x, l4.y, l4.z, l4.w}, dv4[4] = {d4.x, d4.y, d4.z, d4.w};
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    const int v = 4 * i + j;
+                    float e = expf(p[v] * scale - lv[j]);
+                    if (edge) {
+                        const int q = q0 + 8 * i + 4 * half + j;
+                        if (q >= S || k >= S || (causal && k > q)) e = 0.0f;
+                    }
+                    p[v] = e;
+                    ds[v] = e * (ds[v] - dv4[j]);
+                }
+            }
+            xaccumulate<DH>(dv, qt_ + TB, p, lane);                   // dV^T += dO^T P
+            xreads_done();
+            xfetch<DH>(rg, lg, offg, nx < nt ? nx * XT : S, ldo);
+            xaccumulate<DH>(dk, qt_, ds, lane);                       // dK^T += Q^T dS
+            xreads_done();
+            xfetch<DH>(rq, lq, offq, nx < nt ? nx * XT : S, ld);
+        }
+        xwait<0>();
+        float* kp = dqkv + ((int64_t)b * S + k) * ld + (int64_t)nl * dh + (int64_t)h * dh;
+        float* vp = kp + (int64_t)nl * dh;
+        const float fk[4] = {scale, scale, scale, scale}, fv[4] = {1.0f, 1.0f, 1.0f, 1.0f};
+        float z = xcombine<DH>(smem, dk, fk, wave, lane, [&](int d, int i, const float (&r)[4]) {
+            const int c = d * 32 + 8 * i + 4 * half;
+            if (k < S && c < dh) *reinterpret_cast<float4*>(kp + c) = make_float4(r[0], r[1], r[2], r[3]);
+        });
+        z += xcombine<DH>(smem, dv, fv, wave, lane, [&](int d, int i, const float (&r)[4]) {
+            const int c = d * 32 + 8 * i + 4 * half;
+            if (k < S && c < dh) *reinterpret_cast<float4*>(vp + c) = make_float4(r[0], r[1], r[2], r[3]);
+        });
+        if (!causal || !__any(z != 0.0f)) return;
+        rows_stored();
+        float* k_s = xrows<DH>(smem, wave);
+        for (int j = k0; j < k0 + XT && j < S; ++j) {
+            const float* kj = qbase + (int64_t)nl * dh + (int64_t)j * ld;
+            load_row(k_s, kj, dh, lane);
+            load_row(k_s + DH, kj + (int64_t)nl * dh, dh, lane);
+            row_loaded();
+            float* dkj = dqkv + ((int64_t)b * S + j) * ld + (int64_t)nl * dh + (int64_t)h * dh;
+            float* dvj = dkj + (int64_t)nl * dh;
+            attn_row_dkv<(DH + 63) / 64>(k_s, k_s + DH, qbase, ld, d_o + (int64_t)b * S * ldo + (int64_t)h * dh, ldo, lrow, drow, dh, j, S, scale,
+                                         lane, [&](int d, float a, float v) { if (xmine(d, wave)) { dkj[d] = a * scale; dvj[d] = v; } });
+            row_loaded();
+        }
+    }
 }
 
 // ---- host ----------------------------------------------------------------------------------------------------------------
@@ -515,12 +496,12 @@ static hipError_t set_lds() {
     hipError_t e = hipSuccess;
     auto set = [&](const void* k) { if (e == hipSuccess) e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, xlds_bytes<DH>()); };
     set(reinterpret_cast<const void*>(&attn_f32_fwd_kernel<DH>));
-    set(reinterpret_cast<const void*>(&attn_f32_bwd_kernel<DH, D_OWN>));
+    set(reinterpret_cast<const void*>(&attn_f32_bwd_kernel<DH, D_OWN, KIND_BOTH>));
     if constexpr (pairs<DH>()) {
-        set(reinterpret_cast<const void*>(&attn_f32_bwd_kernel<DH, D_GIVEN>));
+        set(reinterpret_cast<const void*>(&attn_f32_bwd_kernel<DH, D_GIVEN, KIND_BOTH>));
     } else {
-        set(reinterpret_cast<const void*>(&attn_f32_dq_kernel<DH>));
-        set(reinterpret_cast<const void*>(&attn_f32_dkv_kernel<DH>));
+        set(reinterpret_cast<const void*>(&attn_f32_bwd_kernel<DH, D_OF_DQ, KIND_DQ>));
+        set(reinterpret_cast<const void*>(&attn_f32_bwd_kernel<DH, D_OF_DQ, KIND_DKV>));
     }
     return e;
 }
@@ -542,7 +523,7 @@ static hipError_t launch(const AttnArgs& a, bool bwd) {
     }
     if (one_launch((int64_t)nblk * a.B * a.nl)) {
         const dim3 both(2 * grid.x);
-        hipLaunchKernelGGL((attn_f32_bwd_kernel<DH, D_OWN>), both, wg, xlds_bytes<DH>(), a.stream, (int)grid.x, 0, a.S, a.nl, a.dh, a.causal, nblk,
+        hipLaunchKernelGGL((attn_f32_bwd_kernel<DH, D_OWN, KIND_BOTH>), both, wg, xlds_bytes<DH>(), a.stream, (int)grid.x, 0, a.S, a.nl, a.dh, a.causal, nblk,
                            (const float*)a.qkv, (const float*)a.o, a.lse, (const float*)a.d_o, (float*)a.dqkv, a.dsum);
         return hipGetLastError();
     }
@@ -552,14 +533,14 @@ static hipError_t launch(const AttnArgs& a, bool bwd) {
                            (const float*)a.d_o, a.dsum, a.B, a.S, a.nl, a.dh);
         const bool fits = 2LL * grid.x * wg.x < 1LL << 32;            // a launch has fewer than 2^32 threads
         for (unsigned wg0 = 0; wg0 < 2 * grid.x; wg0 += fits ? 2 * grid.x : grid.x)
-            hipLaunchKernelGGL((attn_f32_bwd_kernel<DH, D_GIVEN>), dim3(fits ? 2 * grid.x : grid.x), wg, xlds_bytes<DH>(), a.stream, (int)grid.x,
+            hipLaunchKernelGGL((attn_f32_bwd_kernel<DH, D_GIVEN, KIND_BOTH>), dim3(fits ? 2 * grid.x : grid.x), wg, xlds_bytes<DH>(), a.stream, (int)grid.x,
                                (int)wg0, a.S, a.nl, a.dh, a.causal, nblk, (const float*)a.qkv, (const float*)a.o, a.lse, (const float*)a.d_o,
                                (float*)a.dqkv, a.dsum);
     } else {
-        hipLaunchKernelGGL(attn_f32_dq_kernel<DH>, grid, wg, xlds_bytes<DH>(), a.stream, a.S, a.nl, a.dh, a.causal, nblk,
+        hipLaunchKernelGGL((attn_f32_bwd_kernel<DH, D_OF_DQ, KIND_DQ>), grid, wg, xlds_bytes<DH>(), a.stream, (int)grid.x, 0, a.S, a.nl, a.dh, a.causal, nblk,
                            (const float*)a.qkv, (const float*)a.o, a.lse, (const float*)a.d_o, (float*)a.dqkv, a.dsum);
-        hipLaunchKernelGGL(attn_f32_dkv_kernel<DH>, grid, wg, xlds_bytes<DH>(), a.stream, a.S, a.nl, a.dh, a.causal, nblk,
-                           (const float*)a.qkv, a.lse, (const float*)a.d_o, (float*)a.dqkv, a.dsum);
+        hipLaunchKernelGGL((attn_f32_bwd_kernel<DH, D_OF_DQ, KIND_DKV>), grid, wg, xlds_bytes<DH>(), a.stream, (int)grid.x, 0, a.S, a.nl, a.dh, a.causal, nblk,
+                           (const float*)a.qkv, (const float*)a.o, a.lse, (const float*)a.d_o, (float*)a.dqkv, a.dsum);
     }
     return hipGetLastError();
 }
