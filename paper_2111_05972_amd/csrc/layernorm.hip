@@ -563,12 +563,15 @@ static hipError_t launch_fwd(const LnArgs& a) {
                        (const T*)a.gamma, (const T*)a.beta, a.eps, (T*)a.z, (T*)a.y, a.mean, a.rstd);
     return hipGetLastError();
 }
-// Few wide rows: all loads first, on 512 threads.  us, bfloat16, a row on 256 threads chunk by chunk and so: 500 x 16384 15.8 and 13.2;
-// many rows the other way round: 2000 x 5120 17.0 and 18.7, 2048 x 12288 33.6 and 38.1.  Narrower rows are level (launch-bound).
+// Few wide rows: all loads first, on 512 threads: up to two rows per compute unit, one of float rows of more than 8192.  us, a row on 256
+// threads chunk by chunk and so: bfloat16 500 x 16384 15.8 and 13.2, 300 x 12288 8.8 and 8.0; float 200 x 12288 10.1 and 9.5, 257 / 300 /
+// 512 x 16384 15.2 and 18.0 / 17.0 and 19.6 / 23.8 and 26.6, 300 x 12288 13.7 and 14.6, 512 x 8192 14.2 and 13.1, 300 x 8192 9.6 and 9.9;
+// many rows the other way round in bfloat16 too: 2000 x 5120 17.0 and 18.7, 2048 x 12288 33.6 and 38.1.  Narrower rows are level
+// (launch-bound).
 template <typename T, int MAXC>
 static hipError_t fwd_t(const LnArgs& a) {
     if constexpr (MAXC > 2)
-        if (a.M <= 2 * compute_units()) return launch_fwd<T, MAXC / 2, 512, true>(a);
+        if (a.M <= (sizeof(T) == 4 && MAXC > 4 ? 1 : 2) * compute_units()) return launch_fwd<T, MAXC / 2, 512, true>(a);
     return launch_fwd<T, MAXC, LN_THREADS, false>(a);
 }
 template <typename T>
