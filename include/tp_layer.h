@@ -307,7 +307,7 @@ int tp_layer_profile_read(float* ms_out, int capacity, int* count);
 
 /* Tuning overrides, for tests (which run every kernel variant through them) and for tuning; process-wide, not
  * thread-safe, and they must not change between a workspace-size query and the call it sizes.  name:
- *   "gemm_tile"   force one GEMM tile variant (0..7) for every bf16 GEMM
+ *   "gemm_tile"   force one GEMM tile variant (0..8) for every bf16 GEMM (8: not where both operands are transposed)
  *   "gemm_shares" force the number of K shares of every bf16 GEMM
  *   "gemm_band"   force the band height of the GEMM tile order
  *   "gemm_force"  "MxNxK@ab=v[:shares];..." plans for single shapes (a, b = 1 where A, B has K contiguous)

@@ -2094,15 +2094,24 @@ hipError_t gemm_bf16_group(const GemmArgs* g, int n, void* ws, size_t ws_bytes, 
 // 250, 2048 x 1536 x 12288 80 and 76, TN 1280 x 15360 x 2048 88 and 82; estimates of less than 60 us: 0.98 to 1.8 times as long, the
 // 256 x 128 tile 0.8 to 1.8.  Its kernels are built for the layouts of a layer (NN, NT, TN), and the overrides are about the others.
 constexpr double BY_TURNS_MIN_US = 60.0;
+constexpr int TURNS_VARIANT = NVARIANTS;       // option gemm_tile: this tile for every GEMM in those layouts
 static bool by_turns(int64_t M, int64_t N, int64_t K, bool trans_a, bool trans_b, GroupPlan* plan) {
     const Options& o = options();
-    if ((trans_a && trans_b) || o.gemm_tile >= 0 || o.gemm_shares > 0 || o.gemm_force[0] || o.gemm_band > 0 || o.fuse_colsum) return false;
+    if (trans_a && trans_b) return false;
+    if (o.gemm_tile == TURNS_VARIANT && o.gemm_shares > 0) {
+        const int nk = (int)((K + DK - 1) / DK), per = ((nk + o.gemm_shares - 1) / o.gemm_shares + 1) & ~1;   // two k-steps at a time
+        *plan = GroupPlan{};
+        plan->njobs = 1;
+        plan->job[0] = PPJob{0, 0, (int)(((M + 255) / 256) * ((N + 255) / 256)), per < nk ? per : nk, per < nk ? (nk + per - 1) / per : 1};
+        return true;
+    }
+    if (o.gemm_tile != TURNS_VARIANT && (o.gemm_tile >= 0 || o.gemm_shares > 0 || o.gemm_force[0] || o.gemm_band > 0 || o.fuse_colsum)) return false;
     const double other_us = 0.95 * plan_for(M, N, K, !trans_a, trans_b).us;
-    if (other_us <= BY_TURNS_MIN_US) return false;
+    if (o.gemm_tile != TURNS_VARIANT && other_us <= BY_TURNS_MIN_US) return false;
     GemmArgs a{};
     a.dtype = BF16; a.M = M; a.N = N; a.K = K; a.epi = EPI_NONE;
     *plan = plan_group(&a, 1);
-    return plan->us >= BY_TURNS_MIN_US && plan->us < other_us;
+    return o.gemm_tile == TURNS_VARIANT || (plan->us >= BY_TURNS_MIN_US && plan->us < other_us);
 }
 size_t gemm_bf16_share_bytes(int64_t M, int64_t N, int64_t K, bool trans_a, bool trans_b) {
     const Plan pl = plan_for(M, N, K, !trans_a, trans_b);

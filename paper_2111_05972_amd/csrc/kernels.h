@@ -13,7 +13,7 @@ enum Dtype { F32 = 0, BF16 = 1 };
 // TPL_GEMM_FORCE, TPL_ATTN_CHUNK); afterwards only tp_layer_set_option changes them.  Nothing on a launch path
 // reads the environment.  `generation` increases with every change: plans cached per shape carry it.
 struct Options {
-    int gemm_tile = -1;        // force one tile variant (0 .. number of variants - 1); -1: the planner chooses
+    int gemm_tile = -1;        // force one tile variant (0 .. number of variants - 1; 8: 256 x 256 by turns); -1: the planner chooses
     int gemm_shares = 0;       // force a K split; 0: the planner chooses
     int gemm_band = 0;         // force the band height of the tile order; 0: choose_band
     int attn_chunk = -1;       // force the chunk length of attention strips in 64-row tile steps (0: never cut); -1: unset

@@ -19,7 +19,7 @@ CASES = [
                                       tp_degree=2, tp_rank=1, seq=256, micro_batch=2, causal=True, row_epilogue=True), True, None),
     ("f32-one-stream", small_variant(synthetic.CONFIGS[1], name="graph-f32", seq=64), False, None),
 ]
-# launched one by one (option gemm_group 0), as layers too wide for groups are: two chains fork from and join the captured stream
+# launched one by one (option gemm_group 0), as layers with an operand of 2 GiB are: two chains fork from and join the captured stream
 CASES += [("bf16-two-chains", CASES[1][1], True, "0"), ("f32-two-chains", CASES[2][1], True, "0"), ("f32-one-by-one", CASES[2][1], False, "0")]
 
 

@@ -61,10 +61,10 @@ def test_named_configs_full_size(cid):
     _run(C[cid])
 
 
-@pytest.mark.parametrize("cid,group", [(2, None), (2, "0"), (3, None), (3, "0"), (4, None), (5, None)])
+@pytest.mark.parametrize("cid,group", [(2, None), (2, "0"), (3, None), (3, "0"), (4, None), (5, None), (4, "0"), (5, "0")])
 def test_two_chain_schedule_at_full_size(cid, group, tune):
     """The launch configuration bench.py times (TPL_SIDE_STREAM): the attention block and the MLP block of a pass on two
-    streams where GEMMs are launched one by one (configs 4 and 5, and option gemm_group 0), groups on one stream otherwise.
+    streams where GEMMs are launched one by one (option gemm_group 0), groups on one stream otherwise.
     Element by element against the oracle, and bit-identical to the call without the flag (the kernels and their order
     within a chain are the same; only what runs beside what changes)."""
     tune.set("gemm_group", group)
