@@ -1740,37 +1740,52 @@ struct GroupPlan { int tile, nk[GROUP_MAX], shares[GROUP_MAX]; double us; int nj
 
 int64_t group_tiles(const GemmArgs& a, const GroupTile& t) { return ((a.M + t.bm - 1) / t.bm) * ((a.N + t.bn - 1) / t.bn); }
 
-// How long `units` machines take for a list of jobs dealt out in order, count[i] of length len[i] each (longest first).
-double list_time(int units, int n, const int64_t* count, const double* len) {
-    struct { double t; int64_t c; } free_at[64];                  // units by the time at which they are free, earliest first
+// How long `units` machines take for a list of jobs dealt out in order, count[i] of length len[i] each (longest first); at least
+// `limit`, not to the end, where it is not below that.
+double list_time(int units, int n, const int64_t* count, const double* len, double limit) {
+    struct Free { double t; int64_t c; } old[64], now[64];         // units by the time at which they are free, earliest first
     int m = 1;
-    free_at[0] = {0.0, units};
+    old[0] = {0.0, units};
     double end = 0.0;
     for (int i = 0; i < n; ++i) {
         int64_t left = count[i];
         const int64_t rounds = left / units;                      // whole rounds move every unit alike
         if (rounds > 2) {
-            for (int q = 0; q < m; ++q) free_at[q].t += (double)(rounds - 2) * len[i];
+            for (int q = 0; q < m; ++q) old[q].t += (double)(rounds - 2) * len[i];
             left -= (rounds - 2) * units;
         }
+        // Units that take one are free len[i] later, in the order in which they took it: a queue beside that of the others.
+        int o = 0, h = 0, r = 0;                                  // heads of `old` and `now` (a ring), entries of `now`
         while (left > 0) {
-            const int64_t c = std::min(left, free_at[0].c);
-            const double t = free_at[0].t + len[i];
+            Free& f = r == 0 || (o < m && old[o].t <= now[h & 63].t) ? old[o] : now[h & 63];
+            const bool from_old = &f >= old && &f < old + 64;
+            const int64_t c = std::min(left, f.c);
+            const double t = f.t + len[i];
+            if (t >= limit) return t;
             end = std::max(end, t);
             left -= c;
-            if (c < free_at[0].c && m < 64) free_at[0].c -= c;
-            else { for (int q = 1; q < m; ++q) free_at[q - 1] = free_at[q]; --m; }
-            int q = m++;
-            for (; q > 0 && free_at[q - 1].t > t; --q) free_at[q] = free_at[q - 1];
-            free_at[q] = {t, c};
+            if (c < f.c && m - o + r < 64) f.c -= c;
+            else if (from_old) ++o;
+            else { ++h; --r; }
+            now[(h + r++) & 63] = {t, c};
         }
+        if (i + 1 == n) break;
+        Free both[64];
+        int k = 0;
+        while (o < m || r > 0) {
+            if (r == 0 || (o < m && old[o].t <= now[h & 63].t)) both[k++] = old[o++];
+            else { both[k++] = now[h++ & 63]; --r; }
+        }
+        std::copy(both, both + k, old);
+        m = k;
     }
     return end;
 }
 
 // Tiles of gemm_bf16_pp.h, one workgroup per compute unit: the last round of a list that does not fill it is cut.  Of each GEMM `cut`
-// tiles, its last ones, go out in `shares` K shares each; the plan is the best found by changing one GEMM at a time.
-GroupPlan make_pp_plan(const GemmArgs* g, int n, const GroupTile& gt) {
+// tiles, its last ones, go out in `shares` K shares each; the plan is the best found by changing one GEMM at a time.  Not searched for
+// (us infinite) where the work of the uncut list alone, which no cut takes down, is not below `limit`.
+GroupPlan make_pp_plan(const GemmArgs* g, int n, const GroupTile& gt, double limit) {
     const int cus = compute_units();
     struct Cut { int64_t cut; int shares, nk; };
     int64_t tiles[GROUP_MAX];
@@ -1805,25 +1820,30 @@ GroupPlan make_pp_plan(const GemmArgs* g, int n, const GroupTile& gt) {
         return m;
     };
     auto length = [&](int i, int steps, bool whole) { return steps * gt.step_us + gt.wg_us + (whole && g[i].epi != EPI_NONE ? gt.gelu_us : 0.0); };
-    // Anything not below `limit` where the plan cannot be: the list is dealt out only if its longest job would fit, and its work, unless
-    // list_time takes whole rounds of a job at once behind longer ones (it may come out below the work then).
-    auto estimate = [&](const Cut* c, double limit) {
+    // What a plan cannot take less than, GEMM by GEMM: its longest job and its work over all units, unless list_time takes whole rounds of a
+    // job at once behind longer ones (it may come out below the work then), and the sums of the shares.
+    struct Bound {
         double work = 0, longest = 0, bytes = 0, many = INFINITY;
-        auto add = [&](int64_t count, double len) {
+        void add(int64_t count, double len, int units) {
             work += (double)count * len;
             longest = std::max(longest, len);
-            if (count >= 3 * cus) many = std::min(many, len);
-        };
-        for (int i = 0; i < n; ++i) {
-            if (tiles[i] > c[i].cut) add(tiles[i] - c[i].cut, length(i, nk[i], true));
-            if (c[i].cut) {
-                add(c[i].cut * c[i].shares, length(i, c[i].nk, false));
-                bytes += (double)c[i].cut * tile_bytes[i] * (8.0 * c[i].shares + 2.0);
-            }
+            if (count >= 3 * units) many = std::min(many, len);
         }
-        const double sums = bytes > 0 ? 4.2 + bytes / 8.0e6 : 0.0;
-        const double least = std::max(std::max(many < longest ? 0.0 : work / cus, longest), floor_us) + sums;
-        if (least >= limit) return least;
+    };
+    auto add_gemm = [&](Bound& b, int i, const Cut& c) {
+        if (tiles[i] > c.cut) b.add(tiles[i] - c.cut, length(i, nk[i], true), cus);
+        if (!c.cut) return;
+        b.add(c.cut * c.shares, length(i, c.nk, false), cus);
+        b.bytes += (double)c.cut * tile_bytes[i] * (8.0 * c.shares + 2.0);
+    };
+    auto sums = [&](const Bound& b) { return b.bytes > 0 ? 4.2 + b.bytes / 8.0e6 : 0.0; };
+    auto least = [&](const Bound& b) {
+        return (std::max(std::max(b.many < b.longest ? 0.0 : b.work / cus, b.longest), floor_us) + sums(b)) * (1 - 1e-12);
+    };
+    // The list dealt out; where that is not below `limit`, anything that is not either.
+    auto estimate = [&](const Cut* c, double limit) {
+        Bound b;
+        for (int i = 0; i < n; ++i) add_gemm(b, i, c[i]);
         PPJob job[JOB_MAX];
         int64_t count[JOB_MAX];
         double len[JOB_MAX];
@@ -1832,10 +1852,20 @@ GroupPlan make_pp_plan(const GemmArgs* g, int n, const GroupTile& gt) {
             count[q] = (int64_t)job[q].count * job[q].shares;
             len[q] = length(job[q].gemm, job[q].nk, job[q].shares == 1);
         }
-        return std::max(list_time(cus, m, count, len), floor_us) + sums;
+        return std::max(list_time(cus, m, count, len, limit - sums(b) + 1e-6), floor_us) + sums(b);
     };
     Cut best[GROUP_MAX], now[GROUP_MAX];
-    for (int i = 0; i < n; ++i) best[i] = now[i] = with_shares(i, 0, 1);
+    Bound uncut;
+    for (int i = 0; i < n; ++i) {
+        best[i] = now[i] = with_shares(i, 0, 1);
+        add_gemm(uncut, i, best[i]);
+    }
+    // list_time may come out a little below the work, and far below where long jobs are followed by rounds of much shorter ones
+    if (std::max(uncut.many < 0.4 * uncut.longest ? 0.0 : 0.98 * uncut.work / cus, floor_us) >= limit) {
+        GroupPlan none{};
+        none.us = INFINITY;
+        return none;
+    }
     double best_us = estimate(best, INFINITY);
     const int longest = *std::max_element(nk, nk + n);
     for (int parts = 2; parts <= MAX_SHARES && longest / parts >= PP_MIN_STEPS; ++parts) {   // everything long cut to one length
@@ -1843,32 +1873,53 @@ GroupPlan make_pp_plan(const GemmArgs* g, int n, const GroupTile& gt) {
         const double us = estimate(now, best_us);
         if (us < best_us) { best_us = us; std::copy(now, now + n, best); }
     }
-    for (int round = 0; round < 2 * n; ++round) {
-        const double before = best_us;
-        Cut base[GROUP_MAX];
-        std::copy(best, best + n, base);
+    struct Try { int gemm; Cut c; double least; };
+    Try tries[GROUP_MAX * MAX_SHARES * 9];
+    for (int round = 0; round < 2 * n; ++round) {                 // the best change of one GEMM, the first of equals
+        int m = 0, first = 0, chosen = -1;
         for (int i = 0; i < n; ++i) {
             int64_t others = 0;
-            for (int q = 0; q < n; ++q) others += q == i ? tiles[q] : tiles[q] - base[q].cut;
+            Bound rest;
+            for (int q = 0; q < n; ++q) {
+                others += q == i ? tiles[q] : tiles[q] - best[q].cut;
+                if (q != i) add_gemm(rest, q, best[q]);
+            }
             int last_nk = 0;
             for (int want = 1; want <= MAX_SHARES && (want == 1 || nk[i] / want >= PP_MIN_STEPS); ++want) {
-                const int share_nk = with_shares(i, tiles[i], want).nk;
-                if (share_nk == last_nk) continue;                // no other plan than with fewer wanted
-                last_nk = share_nk;
+                Cut c = with_shares(i, tiles[i], want);
+                if (c.nk == last_nk) continue;                    // no other plan than with fewer wanted
+                last_nk = c.nk;
                 int64_t last_cut = -1;
                 for (int eighth = n == 1 ? 8 : 0; eighth <= 8; ++eighth) {   // the tiles past whole rounds, or so many eighths; one GEMM: all
                     const int64_t cut = eighth ? (tiles[i] * eighth + 7) / 8 : std::min(tiles[i], others % cus);
                     if (cut == last_cut) continue;
                     last_cut = cut;
-                    std::copy(base, base + n, now);
-                    now[i] = with_shares(i, cut, want);
-                    const double us = estimate(now, best_us);
-                    if (us < best_us) { best_us = us; std::copy(now, now + n, best); }
+                    c.cut = c.shares > 1 ? cut : 0;
+                    Bound b = rest;
+                    add_gemm(b, i, c);
+                    tries[m] = Try{i, c, least(b)};
+                    if (tries[m].least < best_us) {
+                        if (tries[m].least < tries[first].least) first = m;
+                        ++m;
+                    }
                     if (want == 1) break;
                 }
             }
         }
-        if (best_us >= before) break;
+        std::copy(best, best + n, now);
+        double us = best_us;
+        auto consider = [&](int t) {
+            if (tries[t].least > us) return;
+            now[tries[t].gemm] = tries[t].c;
+            const double it = estimate(now, us * (1 + 1e-12));
+            if (it < us || (it == us && t < chosen)) { us = it; chosen = t; }
+            now[tries[t].gemm] = best[tries[t].gemm];
+        };
+        if (m) consider(first);                                   // most of the others can then be left out
+        for (int t = 0; t < m; ++t) if (t != first) consider(t);
+        if (chosen < 0) break;
+        best_us = us;
+        best[tries[chosen].gemm] = tries[chosen].c;
     }
     GroupPlan p{};
     p.us = best_us;
@@ -1955,7 +2006,7 @@ GroupPlan make_group_plan(const GemmArgs* g, int n) {
     for (int t = 0; t < GROUP_TILE_COUNT; ++t) {
         const GroupTile& gt = GROUP_TILES[t];
         if (!gt.turns || (forced > 0 && forced != gt.option)) continue;
-        const GroupPlan p = make_pp_plan(g, n, gt);
+        const GroupPlan p = make_pp_plan(g, n, gt, us);
         if (p.us < us) { best = p; best.tile = t; us = p.us; }
     }
     return best;
