@@ -1734,6 +1734,12 @@ constexpr int GROUP_TILE_COUNT = sizeof(GROUP_TILES) / sizeof(GROUP_TILES[0]);
 // Operands and results of a launch of few rows, streamed: 100 tokens through the forward of a 12288 / 1536 shard (453 MB) take
 // 150 us on 128 x 128 tiles, 137 on 256 x 256, which have twice the loads in flight.
 constexpr double MEM_BYTES_PER_US = 4.2e6, MEM_BYTES_PER_US_SMALL = 3.5e6;
+// Up to FEW_ROWS rows there is one row of tiles on any tile, and every column of tiles reads A again beside the weights that stream; that
+// ranks the small tiles, not their K shares.  By the k-steps alone narrow tiles were chosen at 33 to 64 rows: forward with weights from
+// memory, us, 4096 / 1024 33 / 48 / 64 tokens 51.8 / 56.4 / 61.1, now 46.3 / 49.0 / 48.1; 4992 / 1248 56 / 59 / 63 and 54.5 / 56.3 / 58.8; 8192 /
+// 1024 70 / 71 / 77 and 60 / 62 / 69.  The rate is the highest with which the choice at 33 tokens of 4096 / 1024 is right.
+constexpr double AGAIN_BYTES_PER_US = 4.7e6;
+constexpr int FEW_ROWS = 64;
 constexpr int PP_MIN_STEPS = 12;               // k-steps of a K share
 struct PPJob { int gemm, tile0, count, nk, shares; };
 struct GroupPlan { int tile, nk[GROUP_MAX], shares[GROUP_MAX]; double us; int njobs; PPJob job[JOB_MAX]; };   // jobs: tile 256 only
@@ -1940,6 +1946,7 @@ GroupPlan make_small_plan(const GemmArgs* g, int n, int forced, double* beside) 
     for (int i = 0; i < n; ++i) operands += 2.0 * ((double)g[i].M * g[i].K + (double)g[i].N * g[i].K + (double)g[i].M * g[i].N);
     GroupPlan best{};
     best.us = -1;
+    double best_rank = 0;
     for (int t = 0; t < GROUP_TILE_COUNT; ++t) {
         const GroupTile& gt = GROUP_TILES[t];
         if (gt.turns || (forced > 0 && forced != gt.option)) continue;
@@ -1952,6 +1959,8 @@ GroupPlan make_small_plan(const GemmArgs* g, int n, int forced, double* beside) 
             nk[i] = p.nk[i] = (int)((g[i].K + DK - 1) / DK);
             p.shares[i] = 1;
         }
+        double again_us = 0;
+        for (int i = 0; i < n; ++i) again_us = g[i].M <= FEW_ROWS ? again_us + 2.0 * g[i].M * g[i].K * (tiles[i] - 1) / AGAIN_BYTES_PER_US : -INFINITY;
         double at_once = 0;                                       // estimate of a launch whose workgroups all run at once, see below
         auto estimate = [&]() {
             double work = 0, wgs = 0, longest = 0, bytes = 0;
@@ -1978,10 +1987,13 @@ GroupPlan make_small_plan(const GemmArgs* g, int n, int forced, double* beside) 
             }
             return us + sums + bytes / 1.6e7;
         };
+        GroupPlan mine{};                                         // the best on this tile
+        mine.us = -1;
+        double mine_beside = 0;
         auto keep = [&]() {
-            if (best.us >= 0 && p.us >= best.us) return;
-            best = p;
-            *beside = at_once > 0 ? std::min(at_once, p.us) : p.us;
+            if (mine.us >= 0 && p.us >= mine.us) return;
+            mine = p;
+            mine_beside = at_once > 0 ? std::min(at_once, p.us) : p.us;
         };
         p.us = estimate();
         for (int cuts = 0; cuts < 16; ++cuts) {                   // cut the longest again while that helps
@@ -1995,6 +2007,11 @@ GroupPlan make_small_plan(const GemmArgs* g, int n, int forced, double* beside) 
             p.us = estimate();
         }
         keep();
+        const double rank = std::max(mine.us, operands / MEM_BYTES_PER_US_SMALL + again_us);
+        if (best.us >= 0 && rank >= best_rank) continue;
+        best = mine;
+        best_rank = rank;
+        *beside = mine_beside;
     }
     return best;
 }
