@@ -1740,6 +1740,13 @@ constexpr double MEM_BYTES_PER_US = 4.2e6, MEM_BYTES_PER_US_SMALL = 3.5e6;
 // 1024 70 / 71 / 77 and 60 / 62 / 69.  The rate is the highest with which the choice at 33 tokens of 4096 / 1024 is right.
 constexpr double AGAIN_BYTES_PER_US = 4.7e6;
 constexpr int FEW_ROWS = 64;
+// Groups with weight gradients go to the tiles by turns where these are estimated this much faster, unless the list goes out uncut, one
+// workgroup to a unit.  Few tokens make tiles of few k-steps that are all start and epilogue, and small groups many K shares; where a
+// workgroup has its unit to itself nothing covers those: the estimate of 256 x 256 is 3 to 9 % short there, those of 128 and 192 3 to 14 %
+// long (forward: level).  Over 480 launches of 240 layers (16 to 8192 tokens, weights in cache and from memory) the chosen tile took 3.5 %
+// longer than the fastest, and 5 % or more longer than the fastest small tile on 102; with this 1.4 %, and on 36.  Backward of 273 tokens of
+// 2688 / 672 85 us, now 73; 476 of 1632 / 1632 133 and 126.
+constexpr double TURNS_LEAD = 1.12;
 constexpr int PP_MIN_STEPS = 12;               // k-steps of a K share
 struct PPJob { int gemm, tile0, count, nk, shares; };
 struct GroupPlan { int tile, nk[GROUP_MAX], shares[GROUP_MAX]; double us; int njobs; PPJob job[JOB_MAX]; };   // jobs: tile 256 only
@@ -2020,11 +2027,17 @@ GroupPlan make_group_plan(const GemmArgs* g, int n) {
     const int forced = n == 1 ? 256 : options().gemm_group;       // one GEMM: see by_turns
     double us = INFINITY;
     GroupPlan best = make_small_plan(g, n, forced, &us);
+    const bool weight_grads = std::any_of(g, g + n, [](const GemmArgs& a) { return a.trans_a != 0; });
     for (int t = 0; t < GROUP_TILE_COUNT; ++t) {
         const GroupTile& gt = GROUP_TILES[t];
         if (!gt.turns || (forced > 0 && forced != gt.option)) continue;
         const GroupPlan p = make_pp_plan(g, n, gt, us);
-        if (p.us < us) { best = p; best.tile = t; us = p.us; }
+        int64_t workgroups = 0;
+        for (int i = 0; i < p.njobs; ++i) workgroups += (int64_t)p.job[i].count * p.job[i].shares;
+        bool at_once = workgroups <= compute_units();             // uncut, one to a unit
+        for (int i = 0; i < p.njobs; ++i) at_once &= p.job[i].shares == 1;
+        const double put_at = p.us * (weight_grads && !at_once ? TURNS_LEAD : 1.0);
+        if (put_at < us) { best = p; best.tile = t; us = put_at; }
     }
     return best;
 }
