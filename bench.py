@@ -237,7 +237,7 @@ def _rms_rel(got, ref):
 def bench_layer(args, cfg, dt, pkg, torch, synthetic, ckpt=False, extras=True, oracle_limit=3.0e12, graph=False):
     """tp_layer_fwd + tp_layer_bwd (or tp_layer_bwd_recompute) on one config; returns the result as a dict.
 
-    extras: also time the plain single-stream schedule, the row-epilogue variant and each GEMM launch (headline run).
+    extras: also time the schedule of single GEMMs, the row-epilogue variant and each GEMM launch (headline run).
     oracle_limit: the oracle runs on the full workload when its model flops are below this, else on a quarter of
     the tokens (timing only, no error figure).  graph: also capture fwd + bwd into a HIP graph and time replays."""
     peak = F32_PEAK_TFLOPS if cfg.dtype == "f32" else BF16_PEAK_TFLOPS
@@ -306,15 +306,17 @@ def bench_layer(args, cfg, dt, pkg, torch, synthetic, ckpt=False, extras=True, o
                    "params": "shard generated directly" if not cfg.global_params else "sliced from unsharded"},
     }
 
-    # A/B of the schedule: the same step with every kernel on the caller's stream
-    if extras and not args.single_stream:
-        lay1 = mk_layer(False)
+    # A/B of the schedule: the same step with its GEMMs one by one, on two chains
+    if extras and not ckpt and not args.single_stream:
+        pkg.tp_layer_set_option("gemm_group", "0")
+        lay1 = mk_layer(True)
         s1 = make_step(lay1)
         s1(); s1()
         one_ms = timed(s1, n_split)
-        out["single_stream"] = {"ms_per_step": round(one_ms, 4), "value": round((f_fwd + f_bwd) / (one_ms * 1e-3) / 1e12, 2),
-                                "steps": n_split, "what": "the same step without TPL_SIDE_STREAM (every kernel on the caller's stream)"}
+        out["single_gemms"] = {"ms_per_step": round(one_ms, 4), "value": round((f_fwd + f_bwd) / (one_ms * 1e-3) / 1e12, 2),
+                               "steps": n_split, "what": "the same step, every GEMM a launch of its own, on two chains (TPL_SIDE_STREAM)"}
         del lay1
+        pkg.tp_layer_set_option("gemm_group", "")
     # the same shard with the row-parallel epilogue on (bias + residual in the two row-parallel GEMMs, residual
     # gradients in the two input-gradient GEMMs, db_o and db_dn): the headline rank runs with it off
     if extras and not cfg.row_epilogue and not ckpt and not args.no_row_epilogue_variant:
@@ -363,9 +365,9 @@ def bench_layer(args, cfg, dt, pkg, torch, synthetic, ckpt=False, extras=True, o
         achieved = tot_fl / (tot_ms * 1e-3) / 1e12
         traffic = None
         tpath = os.path.join(ROOT, "profiles", "traffic.json")
-        if os.path.exists(tpath) and not grouped:      # counted with one GEMM per launch
+        if os.path.exists(tpath) and not ckpt:
             try:
-                traffic = json.load(open(tpath)).get(cfg.name, {}).get("bytes_per_launch")
+                traffic = json.load(open(tpath)).get(cfg.name, {}).get("bytes_per_group_launch" if grouped else "bytes_per_launch")
             except Exception:
                 traffic = None
         kind = "bf16 MFMA GEMM kernels of gemm_bf16.hip" if cfg.dtype == "bf16" else "float MFMA GEMM kernels of gemm_f32.hip"
@@ -630,7 +632,7 @@ def bench_gemms(args, cfg, dt, pkg, torch, synthetic):
 def _brief(r):
     """One workload's result cut down to what the `other_workloads` block carries."""
     keep = ("metric", "value", "unit", "ms_per_step", "dtype", "pct_of_peak", "fwd_ms", "bwd_ms", "max_rel_err_vs_oracle",
-            "rms_rel_err_vs_oracle", "single_stream", "graph_replay")
+            "rms_rel_err_vs_oracle", "single_gemms", "graph_replay")
     b = {k: r[k] for k in keep if k in r and r[k] is not None}
     b["workload"] = r["config"]["workload"]
     if r.get("roofline"):
