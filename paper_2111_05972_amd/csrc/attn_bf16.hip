@@ -1654,9 +1654,10 @@ static bool forced_chunk(const AttnArgs& a, int* ch) {
         *ch = v > 0 && v < (1 << 16) ? v : NEVER_CUT;
         return true;
     }
-    // Inside a layer pass the attention kernels share the chip with the GEMMs of the other chain, which take the
-    // compute units that short strips free early: cutting strips there measured 1.2 % slower per step (more
-    // workgroups holding units, plus the combine kernel), so the layer leaves the strips whole.
+    // A layer pass leaves its strips whole.  With its GEMMs one by one on two chains attention shares the chip with those of the
+    // other chain, and cutting measured 1.2 % slower per step.  Where they go out in groups it has the chip to itself; forward
+    // of one sequence, us, whole and cut to the best of 8 to 24 steps: 12 heads of 2048 tokens (12288 / 1536) 734 and 734, 10
+    // (5120 / 1280) 308 and 304, 4 of 4096 tokens (4096 / 512) 232 and 213.  A cut would need room in the pass's workspace.
     if (!a.own_chunking) { *ch = NEVER_CUT; return true; }
     return false;
 }
@@ -1747,7 +1748,7 @@ size_t attn_bf16_workspace_bytes(const AttnArgs& a0, bool bwd) {
 //                      12.8 / 35 and 41 / 63 and 79; head size 64 of 512 / 768 / 1024 / 4096 tokens 10.0 and 9.7 / 13.1 and 13.2 / 16.3 and
 //                      16.5 / 47 and 51.  Beyond: 288 workgroups of 4096 tokens 133 and 102 (64: 75 and 70), 1024 292 and 264 (168 and 158);
 //                      768 of 4096 to 8192 tokens at head size 128, three rounds of one form, level (218 and 221, 415 and 427)
-//   forward, causal    head size 128: 768 workgroups 297 and 257, 640 of 512 / 8192 tokens 35 and 27 / 203 and 194, 320 39.5 and 48.9;
+//   forward, causal    head size 128: 768 workgroups 297 and 220, 640 of 512 / 8192 tokens 35 and 27 / 203 and 194, 320 39.5 and 48.9;
 //                      head size 64: 640 of 512 / 2048 / 4096 / 8192 tokens 20 and 16 / 38.2 and 36.8 / 63.8 and 65.2 / 119.7 and 122.9, 704
 //                      of 4096 71.2 and 68.5, 512 59 and 59
 //   backward           head size 64: 1024 workgroups 165 and 141 causal, 59.4 and 47.8 without a mask, 512 35 and 38, 256 18 and 21; head

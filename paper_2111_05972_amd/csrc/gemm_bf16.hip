@@ -1651,9 +1651,9 @@ static Plan make_plan(int64_t M, int64_t N, int64_t K, bool a_kmaj, bool b_kmaj)
             const double per_cu = (double)((tiles * shares + cus - 1) / cus);
             double c = per_cu * per * us_per_stage[v] + fixed_us[v] * (wgs_per_cu[v] == 1 ? per_cu : 1.0);
             if (shares > 1) c += 6.0 + (double)M * N * (8.0 * shares + 2.0) / 3.0e6;   // second pass at ~3 TB/s
-            // a split GEMM that takes (nearly) every compute unit leaves none to the kernels of the other chain:
-            // measured inside the whole step, the out-projection data gradient is fastest with 3 shares (192
-            // workgroups), 0.8 % of the step ahead of 4 (256 workgroups)
+            // single GEMMs of a pass run on two chains, and one that takes (nearly) every compute unit leaves none to the kernels
+            // of the other: inside such a step the out-projection data gradient is fastest with 3 shares (192 workgroups), 0.8 %
+            // of the step ahead of 4 (256 workgroups)
             if (shares > 1 && tiles * shares * 4 > (int64_t)cus * 3) c *= 1.10;
             if (best_c < 0 || c < best_c) { best = Plan{v, shares, per, c}; best_c = c; }
         }

@@ -6,7 +6,8 @@
 // 1337, 1360 and 1359 (fetch and math wavefronts NT, the 256 x 256 tile of four wavefronts NN and TN); at 4096^3, one tile per
 // compute unit, 100 us (NT) and 103 us (TN) against 116 and 110.
 //
-// Turns.  Wavefronts w and w + 4 share a SIMD.  The product of a step is cut into clusters (a unit of A times a unit of B); for
+// Turns (the schedule publicly described as ping-pong for this family of chips; fragments, units and waits are worked out here).
+// Wavefronts w and w + 4 share a SIMD.  The product of a step is cut into clusters (a unit of A times a unit of B); for
 // each a wavefront first reads what is missing of its fragments and issues loads (memory phase), then runs 16 matrix
 // instructions on them (matrix phase), with a workgroup barrier behind either phase.  Wavefronts 4..7 are one phase behind, so
 // of the two on a SIMD one always has matrix instructions to issue while the other waits for LDS.  The fragments of a cluster
