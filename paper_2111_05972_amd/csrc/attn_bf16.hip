@@ -27,9 +27,9 @@
 // dimension contiguous (V in forward, Q and dO in dK/dV, K in dQ) are read from LDS with the
 // transposing ds_read_b64_tr_b16.
 //
-// Backward is a row-dot kernel (D = rowsum(dO * O)) and one launch whose workgroups are dK/dV workgroups (per key
-// block) or dQ workgroups (per query block), each accumulating in registers in a fixed order: no atomics, results
-// are run-to-run identical.
+// Backward is one launch whose workgroups are dK/dV workgroups (per key block) or dQ workgroups (per query block), each
+// accumulating in registers in a fixed order: no atomics, results are run-to-run identical.  D = rowsum(dO * O) comes from a
+// kernel before it, or where strips are short from the workgroups themselves (own_dsum).
 //
 // Streaming.  K/V (or Q/dO) tiles of 64 rows go from global memory straight into a ring of two or three LDS stages (buffer
 // loads with the LDS flag), the tile of step t+1 requested at the start of step t; fragments are read from LDS a
@@ -167,6 +167,25 @@ __device__ __forceinline__ bf16x8 frag_k_global(const bf16_t* base, int64_t ld, 
     for (int e = 0; e < 8; ++e) z[e] = (bf16_t)0.0f;
     if (row >= nrows || 16 * ks + 8 * (lane >> 5) >= dh) return z;
     return *reinterpret_cast<const bf16x8*>(base + (int64_t)row * ld + 16 * ks + 8 * (lane >> 5));
+}
+// c + the products of two runs of eight elements (float accumulation)
+__device__ __forceinline__ float dot8(const bf16x8& x, const bf16x8& y, float c) {
+    typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
+#pragma unroll
+    for (int e = 0; e < 8; e += 2) {
+        bf16x2 u, v;
+        u[0] = x[e]; u[1] = x[e + 1];
+        v[0] = y[e]; v[1] = y[e + 1];
+        c = __builtin_amdgcn_fdot2_f32_bf16(u, v, c, false);
+    }
+    return c;
+}
+// The sum of v over each aligned group of eight lanes, in all of them.
+__device__ __forceinline__ float sum_of_8_lanes(float v) {
+    auto step = [](float x, auto ctrl) { return x + __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(x), decltype(ctrl)::value, 0xf, 0xf, true)); };
+    v = step(v, std::integral_constant<int, 0xB1>{});      // lane ^ 1
+    v = step(v, std::integral_constant<int, 0x4E>{});      // lane ^ 2
+    return step(v, std::integral_constant<int, 0x141>{});  // 7 - lane: the other four
 }
 #define MFMA(a, b, c) __builtin_amdgcn_mfma_f32_32x32x16_bf16((a), (b), (c), 0, 0, 0)
 __device__ __forceinline__ bf16x8 pack_regs(const f32x16& a, int first) {
@@ -645,8 +664,8 @@ constexpr int DKV_P_BYTES = 32 * 32 * 4;                  // P of a sub-tile and
 template <int DH> constexpr int dkv_lds_bytes() { return 3 * (2 * tile_bytes<DH>() + 2 * TILE * 4) + 2 * 4 * DKV_P_BYTES; }
 template <int DH, bool CAUSAL, bool FLOATW, bool DK_ROLE>
 __device__ __forceinline__ void attn_dkv_body(char* smem, const bf16_t* __restrict__ qkv,
-                                              const bf16_t* __restrict__ d_o, const float* __restrict__ lse,
-                                              const float* __restrict__ dsum, bf16_t* __restrict__ dqkv,
+                                              const bf16_t* __restrict__ o, const bf16_t* __restrict__ d_o,
+                                              const float* __restrict__ lse, const float* __restrict__ dsum, bf16_t* __restrict__ dqkv,
                                               int S, int nl, int dh, float c2f, int bh, const Chunk& ck, float* __restrict__ pslot) {
     constexpr int TB = tile_bytes<DH>(), NF = DH / 16, NT = DH / 32, HALF = 32 * DH * 2;
     constexpr int NCH = NCHUNKS<DH, FTHREADS>;
@@ -661,6 +680,7 @@ __device__ __forceinline__ void attn_dkv_body(char* smem, const bf16_t* __restri
     const bf16_t* dobase = d_o + (int64_t)b * S * ldo + (int64_t)h * dh;
     const float* lrow = lse + ((int64_t)b * nl + h) * S;
     const float* drow = dsum + ((int64_t)b * nl + h) * S;
+    const bf16_t* obase = o ? o + (int64_t)b * S * ldo + (int64_t)h * dh : nullptr;   // null: D has been summed
     const int k0 = kb * BLK + (wave & 3) * 32;
     const int kv = k0 + (lane & 31);
     const float scale = 1.0f / sqrtf((float)dh);
@@ -680,22 +700,46 @@ __device__ __forceinline__ void attn_dkv_body(char* smem, const bf16_t* __restri
     unsigned off_q[NCH], off_do[NCH];
     dma_offsets<DH, FTHREADS>(off_q, ld, dh, t);
     dma_offsets<DH, FTHREADS>(off_do, ldo, dh, t);
+    // Q and dO rows of tile qt straight into LDS; LSE and D of its rows through registers (r2s stores them), or D from the rows of O,
+    // which eight threads a row keep in registers until dO has landed.
+    constexpr int OCH = (DH / 8 + 7) / 8;
+    const int orow = t >> 3, oc = t & 7;
     float rl = 0.0f, rd = 0.0f;
-    // Q and dO rows of tile qt straight into LDS; LSE and D of its rows through registers (r2s stores them)
+    bf16x8 of[OCH];
+    auto fetch_o = [&](int qt) __attribute__((always_inline)) {
+        const int qi = qt * TILE + orow;
+#pragma unroll
+        for (int i = 0; i < OCH; ++i) {
+            const int c = (oc + 8 * i) * 8;
+#pragma unroll
+            for (int e = 0; e < 8; ++e) of[i][e] = (bf16_t)0.0f;
+            if (qi < S && c < dh) of[i] = *reinterpret_cast<const bf16x8*>(obase + (int64_t)qi * ldo + c);
+        }
+    };
+    auto write_d = [&](auto stg) __attribute__((always_inline)) {
+        constexpr int STG = decltype(stg)::value;
+        float d = 0.0f;
+#pragma unroll
+        for (int i = 0; i < OCH; ++i)
+            if (DH % 64 == 0 || oc + 8 * i < DH / 8)
+                d = dot8(of[i], lds_frag_k<(3 + STG) * TB>(lds0 + orow * (DH * 2) + (((oc + 8 * i) ^ swz<DH>(orow)) << 4)), d);
+        d = sum_of_8_lanes(d);
+        if (oc == 0) reinterpret_cast<float*>(smem + TERMS)[STG * 2 * TILE + TILE + orow] = d;
+    };
     auto g2r = [&](int qt, int stage) {
         tile_dma<DH, FTHREADS>(desc_q, lds0 + stage * TB, off_q, (unsigned)qt * TILE * (unsigned)(ld * 2), wave_u);
         tile_dma<DH, FTHREADS>(desc_do, lds0 + (3 + stage) * TB, off_do, (unsigned)qt * TILE * (unsigned)(ldo * 2), wave_u);
         if (t < TILE) {
             int qi = qt * TILE + t;
             rl = qi < S ? lrow[qi] * LOG2E : 0.0f;
-            rd = qi < S ? drow[qi] : 0.0f;
+            if (!o) rd = qi < S ? drow[qi] : 0.0f;
         }
     };
     auto r2s = [&](int stage) {
         if (t < TILE) {
             float* st = reinterpret_cast<float*>(smem + TERMS) + stage * 2 * TILE;
             st[t] = rl;
-            st[TILE + t] = rd;
+            if (!o) st[TILE + t] = rd;
         }
     };
     // LDS addresses in stage 0: rows as they are (scores: Q, dP: dO), transposed (dV: dO, dK: Q), LSE or D, P
@@ -711,7 +755,9 @@ __device__ __forceinline__ void attn_dkv_body(char* smem, const bf16_t* __restri
         }
     unsigned terms = lds0 + TERMS + (DK_ROLE ? TILE * 4 : 0) + half * 16;
     char* pbuf = smem + PS + (wave_u & 3) * DKV_P_BYTES + lane * 16;
-    if (qt0 < ntiles) { g2r(qt0, 0); r2s(0); }
+    if (qt0 < ntiles) { g2r(qt0, 0); r2s(0); if (o) fetch_o(qt0); }
+#pragma unroll
+    for (int i = 0; i < OCH; ++i) settle(of[i]);
 #pragma unroll
     for (int ks = 0; ks < NF; ++ks) settle(own[ks]);
     dma_wait();
@@ -797,6 +843,10 @@ __device__ __forceinline__ void attn_dkv_body(char* smem, const bf16_t* __restri
     auto step = [&](int qt, auto stg, auto next, auto before) __attribute__((always_inline)) {
         const bool more = qt + 1 < ntiles;
         if (more) g2r(qt + 1, decltype(next)::value);     // read for the last time before the barrier before last
+        if (o) {
+            write_d(stg);                                 // read from the next barrier on
+            if (more) fetch_o(qt + 1);
+        }
         slot(qt, stg, C0{}, before);
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // P; the next tile stays in flight
         __builtin_amdgcn_s_barrier();
@@ -804,6 +854,8 @@ __device__ __forceinline__ void attn_dkv_body(char* smem, const bf16_t* __restri
         __builtin_amdgcn_sched_barrier(0);
         slot(qt, stg, C1{}, stg);
         if (more) r2s(decltype(next)::value);
+#pragma unroll
+        for (int i = 0; i < OCH; ++i) settle(of[i]);
         dma_wait();
         __syncthreads();
     };
@@ -856,7 +908,13 @@ __device__ __forceinline__ void attn_dkv_body(char* smem, const bf16_t* __restri
         row_loaded();
         bf16_t* outp = dqkv + ((int64_t)b * S + j) * ld + (int64_t)(DK_ROLE ? 1 : 2) * nl * dh + (int64_t)h * dh;
         float* pp = pslot + (DK_ROLE ? 0 : BLK * DH) + (j - kb * BLK) * DH;
-        attn_row_dkv<(DH + 63) / 64>(k_s, k_s + DH, qbase, ld, dobase, ldo, lrow, drow, dh, max(CAUSAL ? j : 0, qt0 * TILE), min(S, ntiles * TILE),
+        auto d_of = [&](int i) {
+            if (!o) return drow[i];
+            float d = 0.0f;
+            for (int c = 0; c < dh; ++c) d = fmaf((float)dobase[(int64_t)i * ldo + c], (float)obase[(int64_t)i * ldo + c], d);
+            return d;
+        };
+        attn_row_dkv<(DH + 63) / 64>(k_s, k_s + DH, qbase, ld, dobase, ldo, lrow, d_of, dh, max(CAUSAL ? j : 0, qt0 * TILE), min(S, ntiles * TILE),
                                scale, lane, [&](int d, float dk, float dv) {
                                    const float v = DK_ROLE ? dk : dv;
                                    if (ck.nch > 1) pp[d] = v;
@@ -868,16 +926,16 @@ __device__ __forceinline__ void attn_dkv_body(char* smem, const bf16_t* __restri
 
 // dK/dV workgroup number wg (head fastest, then slot)
 template <int DH, bool CAUSAL, bool FLOATW>
-__device__ __forceinline__ void attn_dkv_wg(char* smem, const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ d_o,
-                                            const float* __restrict__ lse, const float* __restrict__ dsum,
+__device__ __forceinline__ void attn_dkv_wg(char* smem, const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ o,
+                                            const bf16_t* __restrict__ d_o, const float* __restrict__ lse, const float* __restrict__ dsum,
                                             bf16_t* __restrict__ dqkv, int S, int nl, int dh, float c2f, int BH,
                                             float* __restrict__ part, ChunkLen ch, int wg) {
     const int bh = wg % BH, slot = wg / BH;
     const Chunk ck = find_chunk(CAUSAL, true, S, ch, slot, 0);
     float* pslot = part + ((int64_t)slot * BH + bh) * (2 * BLK * DH);
     // the role is uniform per wavefront; both bodies run the same loop and the same barriers
-    if ((threadIdx.x >> 6) < 4) attn_dkv_body<DH, CAUSAL, FLOATW, false>(smem, qkv, d_o, lse, dsum, dqkv, S, nl, dh, c2f, bh, ck, pslot);
-    else attn_dkv_body<DH, CAUSAL, FLOATW, true>(smem, qkv, d_o, lse, dsum, dqkv, S, nl, dh, c2f, bh, ck, pslot);
+    if ((threadIdx.x >> 6) < 4) attn_dkv_body<DH, CAUSAL, FLOATW, false>(smem, qkv, o, d_o, lse, dsum, dqkv, S, nl, dh, c2f, bh, ck, pslot);
+    else attn_dkv_body<DH, CAUSAL, FLOATW, true>(smem, qkv, o, d_o, lse, dsum, dqkv, S, nl, dh, c2f, bh, ck, pslot);
 }
 
 // =================================================================================================
@@ -893,8 +951,8 @@ template <int DH> constexpr int dq_lds_bytes() {
 
 // dQ workgroup number wg (head fastest, then slot)
 template <int DH, bool CAUSAL, bool FLOATW>
-__device__ __forceinline__ void attn_dq_wg(char* smem, const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ d_o,
-                                           const float* __restrict__ lse, const float* __restrict__ dsum,
+__device__ __forceinline__ void attn_dq_wg(char* smem, const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ o,
+                                           const bf16_t* __restrict__ d_o, const float* __restrict__ lse, float* __restrict__ dsum,
                                            bf16_t* __restrict__ dqkv, int S, int nl, int dh, float c2f, int BH,
                                            float* __restrict__ part, ChunkLen ch, int wg) {
     constexpr int TB = tile_bytes<DH>();
@@ -915,13 +973,21 @@ __device__ __forceinline__ void attn_dq_wg(char* smem, const bf16_t* __restrict_
     const float scale = 1.0f / sqrtf((float)dh);
     const float c2 = FLOATW ? c2f : LOG2E * scale;
     const float l2 = q < S ? lse[((int64_t)b * nl + h) * S + q] * LOG2E : 0.0f;
-    const float dq_d = q < S ? dsum[((int64_t)b * nl + h) * S + q] : 0.0f;
-
     bf16x8 qf[DH / 16], dof[DH / 16];
+    float dq_d = 0.0f;                                     // D of the query: half of the row in either lane half
 #pragma unroll
     for (int ks = 0; ks < DH / 16; ++ks) {
         qf[ks] = frag_k_global(qbase, ld, q, S, dh, ks, lane);
         dof[ks] = frag_k_global(dobase, ldo, q, S, dh, ks, lane);
+    }
+    if (o) {
+#pragma unroll
+        for (int ks = 0; ks < DH / 16; ++ks)
+            dq_d = dot8(frag_k_global(o + (int64_t)b * S * ldo + (int64_t)h * dh, ldo, q, S, dh, ks, lane), dof[ks], dq_d);
+        dq_d += __shfl_xor(dq_d, 32, 64);
+        if (kvh == 0 && half == 0 && q < S) dsum[((int64_t)b * nl + h) * S + q] = dq_d;
+    } else if (q < S) {
+        dq_d = dsum[((int64_t)b * nl + h) * S + q];
     }
     f32x16 dq[DH / 32];
 #pragma unroll
@@ -1061,10 +1127,11 @@ __device__ __forceinline__ void attn_dq_wg(char* smem, const bf16_t* __restrict_
         load_row(q_s + DH, dobase + (int64_t)i * ldo, dh, lane);
         row_loaded();
         const int64_t row = ((int64_t)b * nl + h) * S + i;
+        const float d_row = __shfl(dq_d, i - q0, 64);
         bf16_t* dqp = dqkv + ((int64_t)b * S + i) * ld + (int64_t)h * dh;
         float* pp = part + ((int64_t)slot * BH + bh) * (BLK * DH) + (i - qb * BLK) * DH;
         attn_row_dq<(DH + 63) / 64>(q_s, q_s + DH, kbase, vbase, ld, dh, tile0 * TILE, min(CAUSAL ? i + 1 : S, ntiles * TILE), scale, lse[row],
-                              dsum[row], lane, [&](int d, float v) { if (ck.nch > 1) pp[d] = v; else dqp[d] = (bf16_t)(v * scale); });
+                              d_row, lane, [&](int d, float v) { if (ck.nch > 1) pp[d] = v; else dqp[d] = (bf16_t)(v * scale); });
         row_loaded();
     }
 }
@@ -1077,16 +1144,17 @@ __device__ __forceinline__ void attn_dq_wg(char* smem, const bf16_t* __restrict_
 // =================================================================================================
 template <int DH, bool CAUSAL, bool FLOATW>
 __global__ __launch_bounds__(FTHREADS, 2) void attn_bwd_kernel(const bf16_t* __restrict__ qkv,
+                                                               const bf16_t* __restrict__ o,
                                                                const bf16_t* __restrict__ d_o,
                                                                const float* __restrict__ lse,
-                                                               const float* __restrict__ dsum,
+                                                               float* __restrict__ dsum,
                                                                bf16_t* __restrict__ dqkv, int S, int nl, int dh, float c2f, int BH,
                                                                float* __restrict__ part_kv, float* __restrict__ part_q,
                                                                ChunkLen ch_kv, ChunkLen ch_q, int wgs_kv) {
     extern __shared__ __attribute__((aligned(16))) char smem[];
     const int wg = blockIdx.x;                               // uniform: one kind per workgroup, its own barriers
-    if (wg < wgs_kv) attn_dkv_wg<DH, CAUSAL, FLOATW>(smem, qkv, d_o, lse, dsum, dqkv, S, nl, dh, c2f, BH, part_kv, ch_kv, wg);
-    else attn_dq_wg<DH, CAUSAL, FLOATW>(smem, qkv, d_o, lse, dsum, dqkv, S, nl, dh, c2f, BH, part_q, ch_q, wg - wgs_kv);
+    if (wg < wgs_kv) attn_dkv_wg<DH, CAUSAL, FLOATW>(smem, qkv, o, d_o, lse, dsum, dqkv, S, nl, dh, c2f, BH, part_kv, ch_kv, wg);
+    else attn_dq_wg<DH, CAUSAL, FLOATW>(smem, qkv, o, d_o, lse, dsum, dqkv, S, nl, dh, c2f, BH, part_q, ch_q, wg - wgs_kv);
 }
 
 // =================================================================================================
@@ -1760,6 +1828,19 @@ static bool own_rows(int dh, bool causal, bool bwd, int64_t n, int steps) {
     return n > cus || steps <= (dh == 64 ? 12 : 5);
 }
 
+// Whether the workgroups of attn_bwd_kernel work D out for themselves, so that the row-dot kernel and its 2 to 3 us are not launched.  A
+// dQ workgroup does it once; one of dK/dV for every tile, between the barrier that hands the tile over and the first product: 0.3 us a
+// tile step at head size 128, next to nothing at 64.  Whole calls, us, kernel of its own and without: head size 64 4 heads of 512 tokens
+// x 8 in a step 167.3 and 164.9, 5 of 3507 x 2 279.3 and 278.1, 3 of 777 x 4 alone 36.2 and 34.6; 128: 2 of 505 x 10 in a step 153.4 and
+// 150.7, 6 of 127 x 2 alone 23.6 and 21.8, 19 of 337 x 8 (11 steps a unit) level, 22 of 1004 x 5 causal (29) 233.7 and 238.1, 12 of 8192
+// causal (198) 958 and 1011; 96: 8 of 1001 x 3 (16) in a step 453.3 and 451.7.
+static bool own_dsum(int DH, bool causal, int S, int BH, ChunkLen ch) {
+    if (DH <= 64) return true;
+    int64_t steps = 0;
+    for (int blk = 0; blk < (S + BLK - 1) / BLK; ++blk) steps += strip_tiles(causal, true, S, blk);
+    return std::max((int64_t)std::min(ch.ch, (S + TILE - 1) / TILE), steps * BH / compute_units()) <= 16;
+}
+
 template <int DH, bool CAUSAL, bool FLOATW>
 static hipError_t fwd_t(const AttnArgs& a) {
     constexpr int LDS = fwd_lds_bytes<DH>(), LDS_ROWS = 4 * tile_bytes<DH>();
@@ -1819,12 +1900,16 @@ static hipError_t bwd_t(const AttnArgs& a) {
     if (wgs_q + wgs_kv > 0x7fffffffLL) return hipErrorInvalidValue;
     float* part_q = static_cast<float*>(a.ws);
     float* part_kv = a.ws ? reinterpret_cast<float*>(static_cast<char*>(a.ws) + bytes_q) : nullptr;
-    const int64_t lanes = (int64_t)a.B * a.S * a.nl * (DH <= 32 ? 4 : DH == 64 ? 8 : 16);
-    hipLaunchKernelGGL((attn_dsum_kernel<DH>), dim3((unsigned)((lanes + 255) / 256)), dim3(256), 0, a.stream,
-                       (const bf16_t*)a.o, (const bf16_t*)a.d_o, a.dsum, a.B, a.S, a.nl, a.dh);
+    const bool rows = OWN_ROWS && own_rows(DH, CAUSAL, true, wgs_kv + wgs_q, 0);
+    const bool own_d = !rows && own_dsum(DH, CAUSAL, a.S, BH, ch_kv);
+    if (!own_d) {
+        const int64_t lanes = (int64_t)a.B * a.S * a.nl * (DH <= 32 ? 4 : DH == 64 ? 8 : 16);
+        hipLaunchKernelGGL((attn_dsum_kernel<DH>), dim3((unsigned)((lanes + 255) / 256)), dim3(256), 0, a.stream,
+                           (const bf16_t*)a.o, (const bf16_t*)a.d_o, a.dsum, a.B, a.S, a.nl, a.dh);
+    }
     bool launched = false;
     if constexpr (OWN_ROWS) {
-        if (own_rows(DH, CAUSAL, true, wgs_kv + wgs_q, 0)) {
+        if (rows) {
             hipLaunchKernelGGL((attn_bwd_rows_kernel<DH, CAUSAL>), dim3((unsigned)(wgs_kv + wgs_q)), dim3(WTHREADS), LDS_ROWS, a.stream,
                                (const bf16_t*)a.qkv, (const bf16_t*)a.d_o, a.lse, a.dsum, (bf16_t*)a.dqkv, a.S, a.nl, BH, part_kv, part_q,
                                ch_kv, ch_q, (int)wgs_kv);
@@ -1833,8 +1918,8 @@ static hipError_t bwd_t(const AttnArgs& a) {
     }
     if (!launched)
         hipLaunchKernelGGL((attn_bwd_kernel<DH, CAUSAL, FLOATW>), dim3((unsigned)(wgs_kv + wgs_q)), dim3(FTHREADS), LDS, a.stream,
-                           (const bf16_t*)a.qkv, (const bf16_t*)a.d_o, a.lse, a.dsum, (bf16_t*)a.dqkv, a.S, a.nl, a.dh, scale_log2(a.dh), BH,
-                           part_kv, part_q, ch_kv, ch_q, (int)wgs_kv);
+                           (const bf16_t*)a.qkv, own_d ? (const bf16_t*)a.o : nullptr, (const bf16_t*)a.d_o, a.lse, a.dsum, (bf16_t*)a.dqkv, a.S, a.nl, a.dh,
+                           scale_log2(a.dh), BH, part_kv, part_q, ch_kv, ch_q, (int)wgs_kv);
     int blk0_q = 0, ncut_q = 0, blk0_kv = 0, ncut_kv = 0;
     cut_range(a, false, ch_q, &blk0_q, &ncut_q);
     cut_range(a, true, ch_kv, &blk0_kv, &ncut_kv);

@@ -472,7 +472,7 @@ __global__ __launch_bounds__(256, DK_D == D_GIVEN ? 2 : 1) void attn_f32_bwd_ker
             row_loaded();
             float* dkj = dqkv + ((int64_t)b * S + j) * ld + (int64_t)nl * dh + (int64_t)h * dh;
             float* dvj = dkj + (int64_t)nl * dh;
-            attn_row_dkv<(DH + 63) / 64>(k_s, k_s + DH, qbase, ld, d_o + (int64_t)b * S * ldo + (int64_t)h * dh, ldo, lrow, drow, dh, j, S, scale,
+            attn_row_dkv<(DH + 63) / 64>(k_s, k_s + DH, qbase, ld, d_o + (int64_t)b * S * ldo + (int64_t)h * dh, ldo, lrow, [&](int i) { return drow[i]; }, dh, j, S, scale,
                                          lane, [&](int d, float a, float v) { if (xmine(d, wave)) { dkj[d] = a * scale; dvj[d] = v; } });
             row_loaded();
         }

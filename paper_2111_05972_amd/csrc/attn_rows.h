@@ -117,10 +117,10 @@ __device__ __forceinline__ void attn_row_dq(const float* q_s, const float* do_s,
 }
 
 // dK (not scaled) and dV over queries [ibeg, iend): store(d, sum_i dS_i Q_i[d], sum_i P_i dO_i[d]).  k_s, v_s: the rows in
-// LDS; lrow, drow: log-sum-exp and D of the queries.
-template <int NA, typename T, typename Store>
+// LDS; lrow, d_of: log-sum-exp and D of the queries.
+template <int NA, typename T, typename DOf, typename Store>
 __device__ __forceinline__ void attn_row_dkv(const float* k_s, const float* v_s, const T* qbase, int64_t ld, const T* dobase, int64_t ldo,
-                                             const float* lrow, const float* drow, int dh, int ibeg, int iend, float scale, int lane,
+                                             const float* lrow, DOf d_of, int dh, int ibeg, int iend, float scale, int lane,
                                              Store store) {
     float dk[NA] = {}, dv[NA] = {};
     for (int i0 = ibeg; i0 < iend; i0 += 64) {
@@ -135,7 +135,7 @@ __device__ __forceinline__ void attn_row_dkv(const float* k_s, const float* v_s,
                 dp = fmaf(to_f32(dop[d]), v_s[d], dp);
             }
             p = expf(s * scale - lrow[i]);
-            ds = p * (dp - drow[i]);
+            ds = p * (dp - d_of(i));
         }
         int cnt = min(64, iend - i0);
         for (int ii = 0; ii < cnt; ++ii) {

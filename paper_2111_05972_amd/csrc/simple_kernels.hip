@@ -177,7 +177,8 @@ __global__ __launch_bounds__(64 * AT_WAVES) void attn_simple_dkv_kernel(
     const float scale = 1.0f / sqrtf((float)dh);
     T* dkp = dqkv + ((int64_t)b * S + j) * ld + (int64_t)nl * dh + (int64_t)h * dh;
     T* dvp = dkp + (int64_t)nl * dh;
-    attn_row_dkv<AT_MAXDH / 64>(k_s[w], v_s[w], qbase, ld, dobase, ldo, lse + ((int64_t)b * nl + h) * S, dsum + ((int64_t)b * nl + h) * S, dh,
+    const float* drow = dsum + ((int64_t)b * nl + h) * S;
+    attn_row_dkv<AT_MAXDH / 64>(k_s[w], v_s[w], qbase, ld, dobase, ldo, lse + ((int64_t)b * nl + h) * S, [&](int i) { return drow[i]; }, dh,
                                 causal ? j : 0, S, scale, lane, [&](int d, float dk, float dv) {
                                     if (valid) { dkp[d] = from_f32<T>(dk * scale); dvp[d] = from_f32<T>(dv); }
                                 });
