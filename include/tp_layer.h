@@ -315,8 +315,8 @@ int tp_layer_profile_read(float* ms_out, int capacity, int* count);
  *   "side_chains" 2 or 3: chains of a backward pass under TPL_SIDE_STREAM (3: the two weight gradients that depend on
  *                 nothing computed in the pass, dW_dn and dW_o, on a second library stream), its GEMMs one by one; unset: 2
  *                 where they are
- *   "gemm_group"  0, 64, 128, 192, 256, 384: the GEMMs of a pass that do not depend on each other in one launch: never, or
- *                 always on tiles of that size (384: 256 x 128; float layers: 192 stands for 32, 256 and 384 for unset); unset: every layer,
+ *   "gemm_group"  0, 64, 128, 192, 256, 384, 512: the GEMMs of a pass that do not depend on each other in one launch: never, or
+ *                 always on tiles of that size (384: 256 x 128, 512: 128 x 256; float layers: 192 stands for 32, 256 and above for unset); unset: every layer,
  *                 on the tile that is estimated fastest, unless an option about single GEMMs or chains is set.  Operands of 2 GiB or more: never
  *   "fuse_colsum" 1: the bias gradients db_qkv, db_up are one more output row of the weight-gradient GEMM whenever
  *                 its kernel supports that; 0 (default): they come from the column-sum kernels (measured inside the

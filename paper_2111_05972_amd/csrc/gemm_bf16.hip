@@ -1729,7 +1729,16 @@ static GemmParams gemm_params(const GemmArgs& a) {
 namespace {
 struct GroupTile { int option, bm, bn; bool turns; double step_us, wg_us, base_us, alone_us, alone_base_us, gelu_us; };
 constexpr GroupTile GROUP_TILES[] = {{256, 256, 256, true, 0.72, 8.0, 0, 0, 0, 4.5}, {384, 256, 128, true, 0.42, 7.5, 0, 0, 0, 2.5},
+                                     {512, 128, 256, true, 0.55, 7.5, 0, 0, 0, 2.5},
                                      {192, 192, 192, false, 0.60, 2.6, 13.0, 0.77, 4.5, 0}, {128, 128, 128, false, 0.355, 1.0, 7.5, 0.38, 4.5, 0}, {64, 64, 64, false, 0.143, 0.92, 4.5, 0.35, 2.1, 0}};
+// Of the two half tiles by turns a group is planned on one: 128 x 256 where no GEMM of it has more than 128 rows (the forward of few tokens),
+// so that no row of tiles is multiplied that does not exist and twice the weights are in flight per unit, 256 x 128 elsewhere.  100 tokens of
+// 12288 / 1536, weights from memory, {up, qkv} and {down, out} without the sums of their shares: 256 x 128 69 and 68 us, 256 x 256 65 and
+// 51, 128 x 256 61 and 43 (126, 168, 210 and 252 workgroups for {up, qkv}: 73, 61, 57 and 57, 5.4 TB/s, where a k-step of the tile takes
+// 1.0 us and more per 64 k: step_us); forward of 12 tokens of 6848 / 6848 237 -> 205, 16 of 6240 / 6240 202 -> 187; more than 128 rows, as
+// the only half tile: 860 tokens of 3456 / 1728 recomputed 512 -> 551, 572 of 5120 / 1280 374 -> 386.
+constexpr int HALF_TILE = 1;                   // 256 x 128 in GROUP_TILES, before 128 x 256
+constexpr int FEW_TOKENS = 128;
 constexpr int GROUP_TILE_COUNT = sizeof(GROUP_TILES) / sizeof(GROUP_TILES[0]);
 // Operands and results of a launch of few rows, streamed: 100 tokens through the forward of a 12288 / 1536 shard (453 MB) take
 // 150 us on 128 x 128 tiles, 137 on 256 x 256, which have twice the loads in flight.
@@ -2028,9 +2037,11 @@ GroupPlan make_group_plan(const GemmArgs* g, int n) {
     double us = INFINITY;
     GroupPlan best = make_small_plan(g, n, forced, &us);
     const bool weight_grads = std::any_of(g, g + n, [](const GemmArgs& a) { return a.trans_a != 0; });
+    const bool few_rows = std::all_of(g, g + n, [](const GemmArgs& a) { return a.M <= FEW_TOKENS && !a.trans_a; });
+    const int left_out = few_rows ? HALF_TILE : HALF_TILE + 1;
     for (int t = 0; t < GROUP_TILE_COUNT; ++t) {
         const GroupTile& gt = GROUP_TILES[t];
-        if (!gt.turns || (forced > 0 && forced != gt.option)) continue;
+        if (!gt.turns || (forced > 0 ? forced != gt.option : t == left_out)) continue;
         const GroupPlan p = make_pp_plan(g, n, gt, us);
         int64_t workgroups = 0;
         for (int i = 0; i < p.njobs; ++i) workgroups += (int64_t)p.job[i].count * p.job[i].shares;
@@ -2120,7 +2131,10 @@ static hipError_t launch_pp_jobs(const GroupPlan& pl, const GemmArgs* g, int n, 
 }
 
 static hipError_t launch_pp(const GroupPlan& pl, const GemmArgs* g, int n, void* ws, size_t ws_bytes, hipStream_t stream) {
-    return GROUP_TILES[pl.tile].bn == 256 ? launch_pp_jobs<PPTile<2>>(pl, g, n, ws, ws_bytes, stream) : launch_pp_jobs<PPTile<4>>(pl, g, n, ws, ws_bytes, stream);
+    const GroupTile& t = GROUP_TILES[pl.tile];
+    return t.bn == 128   ? launch_pp_jobs<PPTile<4, 1>>(pl, g, n, ws, ws_bytes, stream)
+           : t.bm == 128 ? launch_pp_jobs<PPTile<2, 1>>(pl, g, n, ws, ws_bytes, stream)
+                         : launch_pp_jobs<PPTile<2, 2>>(pl, g, n, ws, ws_bytes, stream);
 }
 
 hipError_t gemm_bf16_group(const GemmArgs* g, int n, void* ws, size_t ws_bytes, hipStream_t stream) {

@@ -1,4 +1,5 @@
-// bf16 GEMM tiles for gfx950 on eight wavefronts that take turns at the matrix cores: 256 x 256 and 256 x 128, K in steps of 64.
+// bf16 GEMM tiles for gfx950 on eight wavefronts that take turns at the matrix cores: 256 x 256, 256 x 128 and 128 x 256, K in
+// steps of 64.
 //
 // What bounds them.  On random operands board power (see gemm_bf16.hip): per flop the large tile moves the fewest bytes through
 // LDS and L2 of the kernels here, and its matrix instruction (16x16x32) is the cheap one.  On zeros 1880 (NT), 1900 (NN) and
@@ -19,6 +20,8 @@
 //              each, eight clusters before their unit is read: 12 to 14 KiB per wavefront in flight
 //   256 x 128: wavefronts 4 x 2, three stages of A (256 rows), B0, B1 (64 columns each); two clusters per step; loads five
 //              clusters ahead.  Half the columns are for GEMMs of few tiles.
+//   128 x 256: wavefronts 2 x 4, three stages of A (128 rows), B0, B1 (128 columns each), else as 256 x 128.  For GEMMs of at most 128
+//              rows, which stream B: a step takes 1.0 us, and 168 workgroups of it 4.8 TB/s, 210 5.4.
 //
 // Which rows and columns a wavefront owns: rows 64 wm .. + 63 of each unit of A, columns 32 wn .. + 31 of each unit of B.  The
 // blocks of C are computed transposed, and the two blocks of such 32 columns take turns at groups of four columns, so that a
@@ -29,10 +32,10 @@
 
 namespace tpl {
 
-template <int WM_>
+template <int WM_, int UA_>
 struct PPTile {
     static constexpr int WM = WM_, WN = 8 / WM_;                          // wavefronts by rows and columns
-    static constexpr int UA = WM == 2 ? 2 : 1, STAGES = WM == 2 ? 2 : 3;  // units of A in a stage
+    static constexpr int UA = UA_, STAGES = UA == 2 ? 2 : 3;              // units of A in a stage
     static constexpr int A_ROWS = 64 * WM, B_COLS = 32 * WN;              // rows (columns) of a unit
     static constexpr int BM = UA * A_ROWS, BN = 2 * B_COLS;
     static constexpr int A_UNIT = A_ROWS * 128, B_UNIT = B_COLS * 128;    // bytes
@@ -443,7 +446,8 @@ __device__ __forceinline__ void pp_products(const GemmParams& p, const PPWork& w
             arrived(W{});                                                 // A0(s+1)
             mul(C1{}, C0{}, fb0[P], csc);
         } else {
-            // loads in issue order: B1(s+2), B0(s+3), one each, and A(s+3), four; newer than what is read next: 2 + 4 + 2 + 4
+            // loads in issue order: B1(s+2), B0(s+3), LB each, and A(s+3), LA; newer than what is read next: two pairs and two of A
+            static_assert(4 * TL::LB + 2 * TL::LA == 12, "12 loads stay in flight");
             using W = std::integral_constant<int, 12>;
             read_a(C0{}, pc);
             load_b(C1{}, s + 2, (P + 2) % 3);

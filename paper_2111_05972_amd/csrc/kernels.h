@@ -18,7 +18,7 @@ struct Options {
     int gemm_band = 0;         // force the band height of the tile order; 0: choose_band
     int attn_chunk = -1;       // force the chunk length of attention strips in 64-row tile steps (0: never cut); -1: unset
     int side_chains = 0;       // 3: under TPL_SIDE_STREAM the backward pass has a third chain, dW_dn and dW_o on a stream of their own
-    int gemm_group = -1;       // independent GEMMs of a layer pass in one launch: 0 never; 64, 128, 192, 256, 384 (256 x 128): always, on that tile (float: 192 stands for 32, 256 and 384 for -1); -1: by size
+    int gemm_group = -1;       // independent GEMMs of a layer pass in one launch: 0 never; 64, 128, 192, 256, 384 (256 x 128), 512 (128 x 256): always, on that tile (float: 192 stands for 32, 256 and above for -1); -1: by size
     int fuse_colsum = 0;       // 1: bias gradients as one more output row of the weight-gradient GEMM where its kernel can
     char gemm_force[1024] = "";   // "MxNxK@ab=v[:shares];..." plans of single shapes (a, b = 1: A, B K-major)
     unsigned generation = 0;

@@ -46,7 +46,7 @@ bool set_option(const char* name, const char* value) {
     else if (!strcmp(name, "attn_chunk")) ok = parse_int(value, -1, 0, 1 << 16, &o.attn_chunk);
     else if (!strcmp(name, "gemm_group")) {
         int v;
-        ok = parse_int(value, -1, 0, 384, &v) && (v <= 0 || v == 64 || v == 128 || v == 192 || v == 256 || v == 384);
+        ok = parse_int(value, -1, 0, 512, &v) && (v <= 0 || v == 64 || v == 128 || v == 192 || v == 256 || v == 384 || v == 512);
         if (ok) o.gemm_group = v;
     }
     else if (!strcmp(name, "fuse_colsum")) ok = parse_int(value, 0, 0, 1, &o.fuse_colsum);
