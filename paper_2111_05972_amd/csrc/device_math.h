@@ -62,5 +62,26 @@ __device__ __forceinline__ void store8(bf16_t* p, const float (&v)[8]) {
     }
     *reinterpret_cast<uint4*>(p) = make_uint4(u[0], u[1], u[2], u[3]);
 }
+// The same with the non-temporal hint: the lines leave for memory as they are written, and not when the kernel ends.
+typedef unsigned u32x4_t __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ void store8_nt(float* p, const float (&v)[8]) {
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        u32x4_t u;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) u[e] = __float_as_uint(v[4 * h + e]);
+        __builtin_nontemporal_store(u, reinterpret_cast<u32x4_t*>(p) + h);
+    }
+}
+__device__ __forceinline__ void store8_nt(bf16_t* p, const float (&v)[8]) {
+    u32x4_t u;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        bf16_t lo = (bf16_t)v[2 * i], hi = (bf16_t)v[2 * i + 1];
+        u[i] = (unsigned)__builtin_bit_cast(unsigned short, lo) |
+               ((unsigned)__builtin_bit_cast(unsigned short, hi) << 16);
+    }
+    __builtin_nontemporal_store(u, reinterpret_cast<u32x4_t*>(p));
+}
 
 }  // namespace tpl

@@ -58,9 +58,20 @@ template <> struct Raw8<bf16_t> {
     }
 };
 
+// y and dz are not read again by these kernels.  With the non-temporal hint their lines go to memory while rows are still being worked on;
+// without it the last few MB per L2 stay until the kernel's end has to wait for them.  Forward and backward, us, without and with: bf16
+// 2048 x 12288 79.7 and 78.5, 16384 x 1024 57.8 and 54.0, 1673 x 4256 34.5 and 30.3, 2400 x 16384 138 and 129.5, float 5623 x 552 27.4
+// and 25.6, 3000 x 8192 (98 MB a tensor) 148 and 141, but 4096 x 8192 (134 MB) 196 and 201, 8192 x 4096 185.6 and 187: only up to 100 MB.
+// z, which backward reads back, is faster kept: 78.5 and 82.2 at 2048 x 12288.
+template <typename T> static bool streams(const LnArgs& a) { return a.M * a.H * (int64_t)sizeof(T) <= 100000000; }
+template <bool NT, typename T> __device__ __forceinline__ void store_row(T* p, const float (&v)[8]) {
+    if (NT) store8_nt(p, v);
+    else store8(p, v);
+}
+
 // EARLY: every load of a row is requested before the first sum.  That takes the latency of a launch of few rows down, and costs
 // registers, i.e. rows in flight, where there are many (see fwd_t).
-template <typename T, int MAXC, int THREADS, bool EARLY>
+template <typename T, int MAXC, int THREADS, bool EARLY, bool NT>
 __global__ __launch_bounds__(THREADS) void ln_fwd_kernel(int64_t M, int64_t H, const T* __restrict__ a, const T* __restrict__ b,
                                                          const T* __restrict__ gamma, const T* __restrict__ beta, float eps,
                                                          T* __restrict__ z, T* __restrict__ y, float* __restrict__ mean,
@@ -122,7 +133,7 @@ __global__ __launch_bounds__(THREADS) void ln_fwd_kernel(int64_t M, int64_t H, c
                 load8(beta + col, bt);
 #pragma unroll
                 for (int e = 0; e < 8; ++e) v[i][e] = fmaf(v[i][e] * rs, g[e], bt[e]);
-                store8(y + row * H + col, v[i]);
+                store_row<NT>(y + row * H + col, v[i]);
             }
         }
         if (t == 0) { mean[row] = mu; rstd[row] = rs; }
@@ -246,7 +257,7 @@ __device__ __forceinline__ void block_sum2(float& a, float& b, float (*red)[NW])
 // dy and z are always in flight (unconverted, in a ring of registers: the kernel is bound by how many bytes a CU
 // keeps outstanding, not by arithmetic).  partials[g][0][:] = dgamma, partials[g][1][:] = dbeta of its rows.
 constexpr int LN_BWD_GROUPS = 256;     // most workgroups of the backward kernel = rows of its partial sums
-template <typename T, int MAXC, int THREADS, int DEPTH>
+template <typename T, int MAXC, int THREADS, int DEPTH, bool NT>
 __global__ __launch_bounds__(THREADS) void ln_bwd_fused_kernel(int64_t M, int64_t H, const T* __restrict__ dy,
                                                                   const T* __restrict__ z,
                                                                   const float* __restrict__ mean,
@@ -315,7 +326,7 @@ __global__ __launch_bounds__(THREADS) void ln_bwd_fused_kernel(int64_t M, int64_
                             dgam[i][e] = fmaf(g[i][e], zz[i][e], dgam[i][e]);
                             o[e] = (g[i][e] * gm[i][e] - c1 - zz[i][e] * c2) * rs;
                         }
-                        store8(dz + row * H + col, o);
+                        store_row<NT>(dz + row * H + col, o);
                     }
                 }
             }
@@ -343,7 +354,7 @@ __device__ __forceinline__ float sum8(const float (&v)[8]) { return ((v[0] + v[1
 
 // Narrow rows (H <= 512 * MAXC, MAXC <= 2): one wavefront holds a row, so the row sums need no barrier and no lane is
 // idle where a 256-thread workgroup would give most of its threads no column.
-template <typename T, int MAXC>
+template <typename T, int MAXC, bool NT>
 __global__ __launch_bounds__(LN_THREADS) void ln_fwd_wave_kernel(int64_t M, int64_t H, const T* __restrict__ a,
                                                                  const T* __restrict__ b, const T* __restrict__ gamma,
                                                                  const T* __restrict__ beta, float eps, T* __restrict__ z,
@@ -391,7 +402,7 @@ __global__ __launch_bounds__(LN_THREADS) void ln_fwd_wave_kernel(int64_t M, int6
                 load8(beta + col, bt);
 #pragma unroll
                 for (int e = 0; e < 8; ++e) v[i][e] = fmaf(v[i][e] * rs, g[e], bt[e]);
-                store8(y + row * H + col, v[i]);
+                store_row<NT>(y + row * H + col, v[i]);
             }
         }
         if (lane == 0) { mean[row] = mu; rstd[row] = rs; }
@@ -407,7 +418,7 @@ __global__ __launch_bounds__(LN_THREADS) void ln_fwd_wave_kernel(int64_t M, int6
 // Forward and backward together, before and now: bfloat16 16384 x 512 86 -> 34 us, 8192 x 1024 54 -> 34, 4096 x 768 29 -> 19;
 // float 8192 x 1024 66 -> 56.
 constexpr int LN_WAVE_ROWS = 8;        // wavefronts of a workgroup = its rows at a time
-template <typename T, int MAXC, int DEPTH>
+template <typename T, int MAXC, int DEPTH, bool NT>
 __global__ __launch_bounds__(64 * LN_WAVE_ROWS) void ln_bwd_wave_kernel(int64_t M, int64_t H, const T* __restrict__ dy,
                                                                         const T* __restrict__ z,
                                                                         const float* __restrict__ mean,
@@ -475,7 +486,7 @@ __global__ __launch_bounds__(64 * LN_WAVE_ROWS) void ln_bwd_wave_kernel(int64_t 
                             dgam[i][e] = fmaf(g[i][e], zz[i][e], dgam[i][e]);
                             o[e] = (g[i][e] * gm[i][e] - c1 - zz[i][e] * c2) * rs;
                         }
-                        store8(dz + row * H + col, o);
+                        store_row<NT>(dz + row * H + col, o);
                     }
                 }
             }
@@ -559,7 +570,8 @@ size_t ln_scratch_bytes(int64_t M, int64_t H) { return (size_t)ln_bwd_groups(M) 
 template <typename T, int C, int THREADS, bool EARLY>
 static hipError_t launch_fwd(const LnArgs& a) {
     const unsigned grid = (unsigned)(a.M < 65535 * 16 ? a.M : 65535 * 16);
-    hipLaunchKernelGGL((ln_fwd_kernel<T, C, THREADS, EARLY>), dim3(grid), dim3(THREADS), 0, a.stream, a.M, a.H, (const T*)a.a, (const T*)a.b,
+    const auto kernel = streams<T>(a) ? &ln_fwd_kernel<T, C, THREADS, EARLY, true> : &ln_fwd_kernel<T, C, THREADS, EARLY, false>;
+    hipLaunchKernelGGL(kernel, dim3(grid), dim3(THREADS), 0, a.stream, a.M, a.H, (const T*)a.a, (const T*)a.b,
                        (const T*)a.gamma, (const T*)a.beta, a.eps, (T*)a.z, (T*)a.y, a.mean, a.rstd);
     return hipGetLastError();
 }
@@ -589,13 +601,10 @@ static hipError_t bwd_t(const LnArgs& a) {
     // Rows in flight per workgroup beyond the one being worked on.  Measured at [2048, 12288] bfloat16: 1 -> 47 us,
     // 2 -> 41 us, 3 and 4 -> 42 us for both kernels together (the compiler drains the whole ring once per DEPTH rows).
     constexpr int DEPTH = (sizeof(T) == 2 && MAXC <= 6) ? 2 : 1;   // the widest rows have no registers left for two
-    if constexpr (MAXC > 2)
-        hipLaunchKernelGGL((ln_bwd_fused_kernel<T, MAXC / 2, 512, DEPTH>), dim3((unsigned)groups), dim3(512), 0, a.stream,
-                           a.M, a.H, (const T*)a.dy, (const T*)a.z, a.mean, a.rstd, (const T*)a.gamma, (T*)a.dz, part);
-    else
-        hipLaunchKernelGGL((ln_bwd_fused_kernel<T, MAXC, LN_THREADS, DEPTH>), dim3((unsigned)groups), dim3(LN_THREADS), 0,
-                           a.stream, a.M, a.H, (const T*)a.dy, (const T*)a.z, a.mean, a.rstd, (const T*)a.gamma,
-                           (T*)a.dz, part);
+    constexpr int THREADS = MAXC > 2 ? 512 : LN_THREADS, CHUNKS = MAXC > 2 ? MAXC / 2 : MAXC;
+    const auto kernel = streams<T>(a) ? &ln_bwd_fused_kernel<T, CHUNKS, THREADS, DEPTH, true> : &ln_bwd_fused_kernel<T, CHUNKS, THREADS, DEPTH, false>;
+    hipLaunchKernelGGL(kernel, dim3((unsigned)groups), dim3(THREADS), 0, a.stream, a.M, a.H, (const T*)a.dy, (const T*)a.z, a.mean, a.rstd,
+                       (const T*)a.gamma, (T*)a.dz, part);
     hipError_t e = hipGetLastError();
     return e != hipSuccess ? e : sum_groups<T>(groups, a.H, a.partials, a.dgamma, a.dbeta, a.stream);
 }
@@ -612,7 +621,8 @@ static hipError_t fwd_wave_t(const LnArgs& a) {
     constexpr int64_t ROWS = LN_THREADS / 64;
     const int64_t want = (a.M + ROWS - 1) / ROWS;
     const unsigned grid = (unsigned)(want < 65535 * 16 ? want : 65535 * 16);
-    hipLaunchKernelGGL((ln_fwd_wave_kernel<T, MAXC>), dim3(grid), dim3(LN_THREADS), 0, a.stream, a.M, a.H,
+    const auto kernel = streams<T>(a) ? &ln_fwd_wave_kernel<T, MAXC, true> : &ln_fwd_wave_kernel<T, MAXC, false>;
+    hipLaunchKernelGGL(kernel, dim3(grid), dim3(LN_THREADS), 0, a.stream, a.M, a.H,
                        (const T*)a.a, (const T*)a.b, (const T*)a.gamma, (const T*)a.beta, a.eps, (T*)a.z, (T*)a.y, a.mean,
                        a.rstd);
     return hipGetLastError();
@@ -622,7 +632,8 @@ static hipError_t bwd_wave_t(const LnArgs& a) {
     const int64_t want = (a.M + LN_WAVE_ROWS - 1) / LN_WAVE_ROWS;
     const int64_t groups = want < LN_BWD_GROUPS ? want : LN_BWD_GROUPS;      // at most the rows of the partial sums
     constexpr int DEPTH = MAXC * sizeof(T) <= 4 ? 4 : 2;                     // 32 to 64 registers of rows in flight
-    hipLaunchKernelGGL((ln_bwd_wave_kernel<T, MAXC, DEPTH>), dim3((unsigned)groups), dim3(64 * LN_WAVE_ROWS), 0, a.stream, a.M,
+    const auto kernel = streams<T>(a) ? &ln_bwd_wave_kernel<T, MAXC, DEPTH, true> : &ln_bwd_wave_kernel<T, MAXC, DEPTH, false>;
+    hipLaunchKernelGGL(kernel, dim3((unsigned)groups), dim3(64 * LN_WAVE_ROWS), 0, a.stream, a.M,
                        a.H, (const T*)a.dy, (const T*)a.z, a.mean, a.rstd, (const T*)a.gamma, (T*)a.dz, a.partials);
     hipError_t e = hipGetLastError();
     return e != hipSuccess ? e : sum_groups<T>(groups, a.H, a.partials, a.dgamma, a.dbeta, a.stream);
