@@ -464,6 +464,12 @@ hipError_t gemm_f32(const GemmArgs& a) {
 using F32Tile128 = F32Tile<2, 2, 2, 2, 1, 2>;
 using F32Tile64 = F32Tile<2, 2, 1, 1, 1, 3>;
 using F32Tile32 = F32Tile<1, 1, 1, 1, 4, 4>;
+// The 64-wide tile with two stages instead of three: four workgroups share a unit instead of three (32 KB of LDS instead of 48), so that with
+// at least six to a unit one's start, barriers and epilogue have three others beside them.  Whole steps, us, three stages and two: 6864 tokens
+// of 1024 / 256 1774 and 1732, 7997 of 768 / 192 995 and 960, 2755 of 1664 / 416 1297 and 1259, 4304 of 512 / 256 841 and 828; with fewer
+// the last of a unit runs at a lone workgroup's pace on half the loads: 3563 of 448 / 224 (3.1 to 5.5 to a unit) 363 and 368 on two stages.
+using F32Tile64Four = F32Tile<2, 2, 1, 1, 1, 2>;
+constexpr int F32_FOUR_MIN = 6;                 // workgroups per unit
 namespace {
 struct F32GroupTile { int bm; double step_us, wg_us, alone_us; };
 constexpr F32GroupTile F32_GROUP_TILES[] = {{128, 1.95, 3.0, 2.2}, {64, 0.50, 1.0, 0.65}, {32, 0.15, 0.5, 0.45}};
@@ -568,7 +574,7 @@ hipError_t gemm_f32_group(const GemmArgs* g, int n, void* ws, size_t ws_bytes, h
         gp.first[q + 1] = gp.first[q] + p.tiles_m * p.tiles_n * shares;
     }
     hipError_t e = pl.tile == 0   ? launch_f32_group<F32Tile128>(gp, stream)
-                   : pl.tile == 1 ? launch_f32_group<F32Tile64>(gp, stream)
+                   : pl.tile == 1 ? (gp.first[n] >= F32_FOUR_MIN * compute_units() ? launch_f32_group<F32Tile64Four>(gp, stream) : launch_f32_group<F32Tile64>(gp, stream))
                                   : launch_f32_group<F32Tile32>(gp, stream);
     if (e != hipSuccess || sp.n == 0) return e;
     hipLaunchKernelGGL(gemm_f32_group_sum_kernel, dim3((unsigned)sp.first[sp.n]), dim3(256), 0, stream, sp);
