@@ -1818,15 +1818,13 @@ size_t attn_bf16_workspace_bytes(const AttnArgs& a0, bool bwd) {
 //                      768 of 4096 to 8192 tokens at head size 128, three rounds of one form, level (218 and 221, 415 and 427)
 //   forward, causal    head size 128: 768 workgroups 297 and 220, 640 of 512 / 8192 tokens 35 and 27 / 203 and 194, 320 39.5 and 48.9;
 //                      head size 64: 640 of 512 / 2048 / 4096 / 8192 tokens 20 and 16 / 38.2 and 36.8 / 63.8 and 65.2 / 119.7 and 122.9, 704
-//                      of 4096 71.2 and 68.5, 512 59 and 59; up to a workgroup per unit only strips of 3 steps: 4 to 64 workgroups of 64 / 128 /
-//                      192 / 256 / 512 tokens at head size 128 6.0 and 5.5 / 8.4 and 8.1 / 8.5 and 8.2 / 10.2 and 10.3 / 13.4 and 14.9, at 64 5.6
-//                      and 5.3 / 6.0 and 5.9 / 6.1 and 6.0 / 7.3 and 7.3 / 9.8 and 10.1
+//                      of 4096 71.2 and 68.5, 512 59 and 59
 //   backward           head size 64: 1024 workgroups 165 and 141 causal, 59.4 and 47.8 without a mask, 512 35 and 38, 256 18 and 21; head
 //                      size 128 (a wavefront per SIMD, 420 registers) 845 and 988 when both roles worked the scores out, so not built
 static bool own_rows(int dh, bool causal, bool bwd, int64_t n, int steps) {
     const int64_t cus = compute_units();
     if (bwd) return n >= 3 * cus;
-    if (causal) return 4 * n >= (dh == 64 && steps > 48 ? 11 : 10) * cus || steps <= 3;
+    if (causal) return 4 * n >= (dh == 64 && steps > 48 ? 11 : 10) * cus;
     return n > cus || steps <= (dh == 64 ? 12 : 5);
 }
 
