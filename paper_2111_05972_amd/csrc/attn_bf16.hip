@@ -168,9 +168,11 @@ __device__ __forceinline__ bf16x8 frag_k_global(const bf16_t* base, int64_t ld, 
     if (row >= nrows || 16 * ks + 8 * (lane >> 5) >= dh) return z;
     return *reinterpret_cast<const bf16x8*>(base + (int64_t)row * ld + 16 * ks + 8 * (lane >> 5));
 }
-// c + the products of two runs of eight elements (float accumulation)
-__device__ __forceinline__ float dot8(const bf16x8& x, const bf16x8& y, float c) {
+// The sum of the products of two runs of eight elements (float accumulation).  Runs are added to each other in pairs: one after another the
+// sums of 64 lost a tenth more to rounding than the row-dot kernel's.
+__device__ __forceinline__ float dot8(const bf16x8& x, const bf16x8& y) {
     typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
+    float c = 0.0f;
 #pragma unroll
     for (int e = 0; e < 8; e += 2) {
         bf16x2 u, v;
@@ -722,7 +724,7 @@ __device__ __forceinline__ void attn_dkv_body(char* smem, const bf16_t* __restri
 #pragma unroll
         for (int i = 0; i < OCH; ++i)
             if (DH % 64 == 0 || oc + 8 * i < DH / 8)
-                d = dot8(of[i], lds_frag_k<(3 + STG) * TB>(lds0 + orow * (DH * 2) + (((oc + 8 * i) ^ swz<DH>(orow)) << 4)), d);
+                d += dot8(of[i], lds_frag_k<(3 + STG) * TB>(lds0 + orow * (DH * 2) + (((oc + 8 * i) ^ swz<DH>(orow)) << 4)));
         d = sum_of_8_lanes(d);
         if (oc == 0) reinterpret_cast<float*>(smem + TERMS)[STG * 2 * TILE + TILE + orow] = d;
     };
@@ -981,10 +983,15 @@ __device__ __forceinline__ void attn_dq_wg(char* smem, const bf16_t* __restrict_
         dof[ks] = frag_k_global(dobase, ldo, q, S, dh, ks, lane);
     }
     if (o) {
+        float part[DH / 16];
 #pragma unroll
         for (int ks = 0; ks < DH / 16; ++ks)
-            dq_d = dot8(frag_k_global(o + (int64_t)b * S * ldo + (int64_t)h * dh, ldo, q, S, dh, ks, lane), dof[ks], dq_d);
-        dq_d += __shfl_xor(dq_d, 32, 64);
+            part[ks] = dot8(frag_k_global(o + (int64_t)b * S * ldo + (int64_t)h * dh, ldo, q, S, dh, ks, lane), dof[ks]);
+#pragma unroll
+        for (int gap = 1; gap < DH / 16; gap *= 2)
+#pragma unroll
+            for (int ks = 0; ks + gap < DH / 16; ks += 2 * gap) part[ks] += part[ks + gap];
+        dq_d = part[0] + __shfl_xor(part[0], 32, 64);
         if (kvh == 0 && half == 0 && q < S) dsum[((int64_t)b * nl + h) * S + q] = dq_d;
     } else if (q < S) {
         dq_d = dsum[((int64_t)b * nl + h) * S + q];
