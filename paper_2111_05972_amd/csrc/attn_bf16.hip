@@ -1836,16 +1836,16 @@ static bool own_rows(int dh, bool causal, bool bwd, int64_t n, int steps) {
 }
 
 // Whether the workgroups of attn_bwd_kernel work D out for themselves, so that the row-dot kernel and its 2 to 3 us are not launched.  A
-// dQ workgroup does it once; one of dK/dV for every tile, between the barrier that hands the tile over and the first product: 0.3 us a
-// tile step at head size 128, next to nothing at 64.  Whole calls, us, kernel of its own and without: head size 64 4 heads of 512 tokens
-// x 8 in a step 167.3 and 164.9, 5 of 3507 x 2 279.3 and 278.1, 3 of 777 x 4 alone 36.2 and 34.6; 128: 2 of 505 x 10 in a step 153.4 and
-// 150.7, 6 of 127 x 2 alone 23.6 and 21.8, 19 of 337 x 8 (11 steps a unit) level, 22 of 1004 x 5 causal (29) 233.7 and 238.1, 12 of 8192
-// causal (198) 958 and 1011; 96: 8 of 1001 x 3 (16) in a step 453.3 and 451.7.
+// dQ workgroup does it once; one of dK/dV for every tile, between the barrier that hands the tile over and the first product: 0.1 to 0.2 us a
+// tile step at head size 64, 0.3 at 128.  So up to 16 steps to a unit, 12 above head size 64.  Whole calls (attention alone, forward included,
+// unless in a step), us, kernel of its own and without: head size 64 causal 12 heads of 512 x 4 / 1024 / 2048 33.3 and 31.7 / 40.9 and 39.6 /
+// 72.4 and 74.0, 8 of 4096 135 and 140; 4 of 512 x 8 in a step 167.3 and 164.9; 80: 12 of 512 x 4 53.4 and 52.3, 1024 (16 steps) 66.9 and
+// 66.8, 1024 x 2 83.1 and 83.6; 128: 6 of 127 x 2 23.6 and 21.8, 2 of 505 x 10 in a step 153.4 and 150.7, 19 of 337 x 8 (11 steps) level, 22
+// of 1004 x 5 causal (29) 233.7 and 238.1, 12 of 8192 causal (198) 958 and 1011.
 static bool own_dsum(int DH, bool causal, int S, int BH, ChunkLen ch) {
-    if (DH <= 64) return true;
     int64_t steps = 0;
     for (int blk = 0; blk < (S + BLK - 1) / BLK; ++blk) steps += strip_tiles(causal, true, S, blk);
-    return std::max((int64_t)std::min(ch.ch, (S + TILE - 1) / TILE), steps * BH / compute_units()) <= 16;
+    return std::max((int64_t)std::min(ch.ch, (S + TILE - 1) / TILE), steps * BH / compute_units()) <= (DH <= 64 ? 16 : 12);
 }
 
 template <int DH, bool CAUSAL, bool FLOATW>
