@@ -664,7 +664,7 @@ __global__ __launch_bounds__(256) void attn_dsum_kernel(const bf16_t* __restrict
 // =================================================================================================
 constexpr int DKV_P_BYTES = 32 * 32 * 4;                  // P of a sub-tile and sub-block of keys
 template <int DH> constexpr int dkv_lds_bytes() { return 3 * (2 * tile_bytes<DH>() + 2 * TILE * 4) + 2 * 4 * DKV_P_BYTES; }
-template <int DH, bool CAUSAL, bool FLOATW, bool DK_ROLE>
+template <int DH, bool CAUSAL, bool FLOATW, bool OWN_D, bool DK_ROLE>
 __device__ __forceinline__ void attn_dkv_body(char* smem, const bf16_t* __restrict__ qkv,
                                               const bf16_t* __restrict__ o, const bf16_t* __restrict__ d_o,
                                               const float* __restrict__ lse, const float* __restrict__ dsum, bf16_t* __restrict__ dqkv,
@@ -682,7 +682,7 @@ __device__ __forceinline__ void attn_dkv_body(char* smem, const bf16_t* __restri
     const bf16_t* dobase = d_o + (int64_t)b * S * ldo + (int64_t)h * dh;
     const float* lrow = lse + ((int64_t)b * nl + h) * S;
     const float* drow = dsum + ((int64_t)b * nl + h) * S;
-    const bf16_t* obase = o ? o + (int64_t)b * S * ldo + (int64_t)h * dh : nullptr;   // null: D has been summed
+    const bf16_t* obase = OWN_D ? o + (int64_t)b * S * ldo + (int64_t)h * dh : nullptr;   // not OWN_D: D has been summed
     const int k0 = kb * BLK + (wave & 3) * 32;
     const int kv = k0 + (lane & 31);
     const float scale = 1.0f / sqrtf((float)dh);
@@ -734,14 +734,14 @@ __device__ __forceinline__ void attn_dkv_body(char* smem, const bf16_t* __restri
         if (t < TILE) {
             int qi = qt * TILE + t;
             rl = qi < S ? lrow[qi] * LOG2E : 0.0f;
-            if (!o) rd = qi < S ? drow[qi] : 0.0f;
+            if (!OWN_D) rd = qi < S ? drow[qi] : 0.0f;
         }
     };
     auto r2s = [&](int stage) {
         if (t < TILE) {
             float* st = reinterpret_cast<float*>(smem + TERMS) + stage * 2 * TILE;
             st[t] = rl;
-            if (!o) st[TILE + t] = rd;
+            if (!OWN_D) st[TILE + t] = rd;
         }
     };
     // LDS addresses in stage 0: rows as they are (scores: Q, dP: dO), transposed (dV: dO, dK: Q), LSE or D, P
@@ -757,9 +757,11 @@ __device__ __forceinline__ void attn_dkv_body(char* smem, const bf16_t* __restri
         }
     unsigned terms = lds0 + TERMS + (DK_ROLE ? TILE * 4 : 0) + half * 16;
     char* pbuf = smem + PS + (wave_u & 3) * DKV_P_BYTES + lane * 16;
-    if (qt0 < ntiles) { g2r(qt0, 0); r2s(0); if (o) fetch_o(qt0); }
+    if (qt0 < ntiles) { g2r(qt0, 0); r2s(0); if (OWN_D) fetch_o(qt0); }
+    if (OWN_D) {
 #pragma unroll
-    for (int i = 0; i < OCH; ++i) settle(of[i]);
+        for (int i = 0; i < OCH; ++i) settle(of[i]);
+    }
 #pragma unroll
     for (int ks = 0; ks < NF; ++ks) settle(own[ks]);
     dma_wait();
@@ -845,7 +847,7 @@ __device__ __forceinline__ void attn_dkv_body(char* smem, const bf16_t* __restri
     auto step = [&](int qt, auto stg, auto next, auto before) __attribute__((always_inline)) {
         const bool more = qt + 1 < ntiles;
         if (more) g2r(qt + 1, decltype(next)::value);     // read for the last time before the barrier before last
-        if (o) {
+        if (OWN_D) {
             write_d(stg);                                 // read from the next barrier on
             if (more) fetch_o(qt + 1);
         }
@@ -856,8 +858,10 @@ __device__ __forceinline__ void attn_dkv_body(char* smem, const bf16_t* __restri
         __builtin_amdgcn_sched_barrier(0);
         slot(qt, stg, C1{}, stg);
         if (more) r2s(decltype(next)::value);
+        if (OWN_D) {
 #pragma unroll
-        for (int i = 0; i < OCH; ++i) settle(of[i]);
+            for (int i = 0; i < OCH; ++i) settle(of[i]);
+        }
         dma_wait();
         __syncthreads();
     };
@@ -911,7 +915,7 @@ __device__ __forceinline__ void attn_dkv_body(char* smem, const bf16_t* __restri
         bf16_t* outp = dqkv + ((int64_t)b * S + j) * ld + (int64_t)(DK_ROLE ? 1 : 2) * nl * dh + (int64_t)h * dh;
         float* pp = pslot + (DK_ROLE ? 0 : BLK * DH) + (j - kb * BLK) * DH;
         auto d_of = [&](int i) {
-            if (!o) return drow[i];
+            if (!OWN_D) return drow[i];
             float d = 0.0f;
             for (int c = 0; c < dh; ++c) d = fmaf((float)dobase[(int64_t)i * ldo + c], (float)obase[(int64_t)i * ldo + c], d);
             return d;
@@ -927,7 +931,7 @@ __device__ __forceinline__ void attn_dkv_body(char* smem, const bf16_t* __restri
 }
 
 // dK/dV workgroup number wg (head fastest, then slot)
-template <int DH, bool CAUSAL, bool FLOATW>
+template <int DH, bool CAUSAL, bool FLOATW, bool OWN_D>
 __device__ __forceinline__ void attn_dkv_wg(char* smem, const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ o,
                                             const bf16_t* __restrict__ d_o, const float* __restrict__ lse, const float* __restrict__ dsum,
                                             bf16_t* __restrict__ dqkv, int S, int nl, int dh, float c2f, int BH,
@@ -936,8 +940,8 @@ __device__ __forceinline__ void attn_dkv_wg(char* smem, const bf16_t* __restrict
     const Chunk ck = find_chunk(CAUSAL, true, S, ch, slot, 0);
     float* pslot = part + ((int64_t)slot * BH + bh) * (2 * BLK * DH);
     // the role is uniform per wavefront; both bodies run the same loop and the same barriers
-    if ((threadIdx.x >> 6) < 4) attn_dkv_body<DH, CAUSAL, FLOATW, false>(smem, qkv, o, d_o, lse, dsum, dqkv, S, nl, dh, c2f, bh, ck, pslot);
-    else attn_dkv_body<DH, CAUSAL, FLOATW, true>(smem, qkv, o, d_o, lse, dsum, dqkv, S, nl, dh, c2f, bh, ck, pslot);
+    if ((threadIdx.x >> 6) < 4) attn_dkv_body<DH, CAUSAL, FLOATW, OWN_D, false>(smem, qkv, o, d_o, lse, dsum, dqkv, S, nl, dh, c2f, bh, ck, pslot);
+    else attn_dkv_body<DH, CAUSAL, FLOATW, OWN_D, true>(smem, qkv, o, d_o, lse, dsum, dqkv, S, nl, dh, c2f, bh, ck, pslot);
 }
 
 // =================================================================================================
@@ -952,7 +956,7 @@ template <int DH> constexpr int dq_lds_bytes() {
 }
 
 // dQ workgroup number wg (head fastest, then slot)
-template <int DH, bool CAUSAL, bool FLOATW>
+template <int DH, bool CAUSAL, bool FLOATW, bool OWN_D>
 __device__ __forceinline__ void attn_dq_wg(char* smem, const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ o,
                                            const bf16_t* __restrict__ d_o, const float* __restrict__ lse, float* __restrict__ dsum,
                                            bf16_t* __restrict__ dqkv, int S, int nl, int dh, float c2f, int BH,
@@ -982,7 +986,7 @@ __device__ __forceinline__ void attn_dq_wg(char* smem, const bf16_t* __restrict_
         qf[ks] = frag_k_global(qbase, ld, q, S, dh, ks, lane);
         dof[ks] = frag_k_global(dobase, ldo, q, S, dh, ks, lane);
     }
-    if (o) {
+    if (OWN_D) {
         float part[DH / 16];
 #pragma unroll
         for (int ks = 0; ks < DH / 16; ++ks)
@@ -1149,7 +1153,7 @@ __device__ __forceinline__ void attn_dq_wg(char* smem, const bf16_t* __restrict_
 // workgroup at a time: in one launch the units that finish the short chunks of one kind pick up chunks of the other
 // instead of idling until the launch ends.  dK/dV first: its steps are the longer ones.
 // =================================================================================================
-template <int DH, bool CAUSAL, bool FLOATW>
+template <int DH, bool CAUSAL, bool FLOATW, bool OWN_D>
 __global__ __launch_bounds__(FTHREADS, 2) void attn_bwd_kernel(const bf16_t* __restrict__ qkv,
                                                                const bf16_t* __restrict__ o,
                                                                const bf16_t* __restrict__ d_o,
@@ -1160,8 +1164,8 @@ __global__ __launch_bounds__(FTHREADS, 2) void attn_bwd_kernel(const bf16_t* __r
                                                                ChunkLen ch_kv, ChunkLen ch_q, int wgs_kv) {
     extern __shared__ __attribute__((aligned(16))) char smem[];
     const int wg = blockIdx.x;                               // uniform: one kind per workgroup, its own barriers
-    if (wg < wgs_kv) attn_dkv_wg<DH, CAUSAL, FLOATW>(smem, qkv, o, d_o, lse, dsum, dqkv, S, nl, dh, c2f, BH, part_kv, ch_kv, wg);
-    else attn_dq_wg<DH, CAUSAL, FLOATW>(smem, qkv, o, d_o, lse, dsum, dqkv, S, nl, dh, c2f, BH, part_q, ch_q, wg - wgs_kv);
+    if (wg < wgs_kv) attn_dkv_wg<DH, CAUSAL, FLOATW, OWN_D>(smem, qkv, o, d_o, lse, dsum, dqkv, S, nl, dh, c2f, BH, part_kv, ch_kv, wg);
+    else attn_dq_wg<DH, CAUSAL, FLOATW, OWN_D>(smem, qkv, o, d_o, lse, dsum, dqkv, S, nl, dh, c2f, BH, part_q, ch_q, wg - wgs_kv);
 }
 
 // =================================================================================================
@@ -1892,7 +1896,8 @@ static hipError_t bwd_t(const AttnArgs& a) {
     constexpr int LDS_ROWS = 3 * (2 * tile_bytes<DH>() + 2 * TILE * 4);
     static bool once = false;
     if (!once) {
-        hipError_t e = set_lds(&attn_bwd_kernel<DH, CAUSAL, FLOATW>, LDS);
+        hipError_t e = set_lds(&attn_bwd_kernel<DH, CAUSAL, FLOATW, false>, LDS);
+        if (e == hipSuccess) e = set_lds(&attn_bwd_kernel<DH, CAUSAL, FLOATW, true>, LDS);
         if constexpr (OWN_ROWS) if (e == hipSuccess) e = set_lds(&attn_bwd_rows_kernel<DH, CAUSAL>, LDS_ROWS);
         if (e != hipSuccess) return e;
         once = true;
@@ -1923,9 +1928,10 @@ static hipError_t bwd_t(const AttnArgs& a) {
             launched = true;
         }
     }
+    const auto kernel = own_d ? &attn_bwd_kernel<DH, CAUSAL, FLOATW, true> : &attn_bwd_kernel<DH, CAUSAL, FLOATW, false>;
     if (!launched)
-        hipLaunchKernelGGL((attn_bwd_kernel<DH, CAUSAL, FLOATW>), dim3((unsigned)(wgs_kv + wgs_q)), dim3(FTHREADS), LDS, a.stream,
-                           (const bf16_t*)a.qkv, own_d ? (const bf16_t*)a.o : nullptr, (const bf16_t*)a.d_o, a.lse, a.dsum, (bf16_t*)a.dqkv, a.S, a.nl, a.dh,
+        hipLaunchKernelGGL(kernel, dim3((unsigned)(wgs_kv + wgs_q)), dim3(FTHREADS), LDS, a.stream,
+                           (const bf16_t*)a.qkv, (const bf16_t*)a.o, (const bf16_t*)a.d_o, a.lse, a.dsum, (bf16_t*)a.dqkv, a.S, a.nl, a.dh,
                            scale_log2(a.dh), BH, part_kv, part_q, ch_kv, ch_q, (int)wgs_kv);
     int blk0_q = 0, ncut_q = 0, blk0_kv = 0, ncut_kv = 0;
     cut_range(a, false, ch_q, &blk0_q, &ncut_q);
