@@ -1731,14 +1731,11 @@ struct GroupTile { int option, bm, bn; bool turns; double step_us, wg_us, base_u
 constexpr GroupTile GROUP_TILES[] = {{256, 256, 256, true, 0.72, 8.0, 0, 0, 0, 4.5}, {384, 256, 128, true, 0.42, 7.5, 0, 0, 0, 2.5},
                                      {512, 128, 256, true, 0.55, 7.5, 0, 0, 0, 2.5},
                                      {192, 192, 192, false, 0.60, 2.6, 13.0, 0.77, 4.5, 0}, {128, 128, 128, false, 0.355, 1.0, 7.5, 0.38, 4.5, 0}, {64, 64, 64, false, 0.143, 0.92, 4.5, 0.35, 2.1, 0}};
-// Of the two half tiles by turns a group is planned on one: 128 x 256 where no GEMM of it has more than 128 rows (the forward of few tokens),
-// so that no row of tiles is multiplied that does not exist and twice the weights are in flight per unit, 256 x 128 elsewhere.  100 tokens of
-// 12288 / 1536, weights from memory, {up, qkv} and {down, out} without the sums of their shares: 256 x 128 69 and 68 us, 256 x 256 65 and
-// 51, 128 x 256 61 and 43 (126, 168, 210 and 252 workgroups for {up, qkv}: 73, 61, 57 and 57, 5.4 TB/s, where a k-step of the tile takes
-// 1.0 us and more per 64 k: step_us); forward of 12 tokens of 6848 / 6848 237 -> 205, 16 of 6240 / 6240 202 -> 187; more than 128 rows, as
-// the only half tile: 860 tokens of 3456 / 1728 recomputed 512 -> 551, 572 of 5120 / 1280 374 -> 386.
-constexpr int HALF_TILE = 1;                   // 256 x 128 in GROUP_TILES, before 128 x 256
-constexpr int FEW_TOKENS = 128;
+// 128 x 256 by turns is for groups of at most 128 rows and no weight gradient (the forward of few tokens): no row of tiles is multiplied that
+// does not exist, and twice the weights of 256 x 128 are in flight per unit; on more rows it is the slower half tile (860 tokens of 3456 / 1728
+// recomputed 512 -> 551, 572 of 5120 / 1280 374 -> 386).  It takes the place of the tile that is chosen otherwise where it leads it, see takes_wide_tile.
+constexpr int WIDE_TILE = 2, FEW_TOKENS = 128;
+static_assert(GROUP_TILES[WIDE_TILE].turns && GROUP_TILES[WIDE_TILE].bm == FEW_TOKENS && GROUP_TILES[WIDE_TILE].bn == 256, "the tile of few rows");
 constexpr int GROUP_TILE_COUNT = sizeof(GROUP_TILES) / sizeof(GROUP_TILES[0]);
 // Operands and results of a launch of few rows, streamed: 100 tokens through the forward of a 12288 / 1536 shard (453 MB) take
 // 150 us on 128 x 128 tiles, 137 on 256 x 256, which have twice the loads in flight.
@@ -1758,7 +1755,7 @@ constexpr int FEW_ROWS = 64;
 constexpr double TURNS_LEAD = 1.12;
 constexpr int PP_MIN_STEPS = 12;               // k-steps of a K share
 struct PPJob { int gemm, tile0, count, nk, shares; };
-struct GroupPlan { int tile, nk[GROUP_MAX], shares[GROUP_MAX]; double us; int njobs; PPJob job[JOB_MAX]; };   // jobs: tile 256 only
+struct GroupPlan { int tile, nk[GROUP_MAX], shares[GROUP_MAX]; double us; int njobs; PPJob job[JOB_MAX]; };   // jobs: tiles by turns only
 
 int64_t group_tiles(const GemmArgs& a, const GroupTile& t) { return ((a.M + t.bm - 1) / t.bm) * ((a.N + t.bn - 1) / t.bn); }
 
@@ -1912,7 +1909,8 @@ GroupPlan make_pp_plan(const GemmArgs* g, int n, const GroupTile& gt, double lim
                 if (c.nk == last_nk) continue;                    // no other plan than with fewer wanted
                 last_nk = c.nk;
                 int64_t last_cut = -1;
-                for (int eighth = n == 1 ? 8 : 0; eighth <= 8; ++eighth) {   // the tiles past whole rounds, or so many eighths; one GEMM: all
+                // the tiles past whole rounds, or so many eighths; all of one GEMM, and of 128 x 256, whose lists go out in one round
+                for (int eighth = n == 1 || gt.bm == FEW_TOKENS ? 8 : 0; eighth <= 8; ++eighth) {
                     const int64_t cut = eighth ? (tiles[i] * eighth + 7) / 8 : std::min(tiles[i], others % cus);
                     if (cut == last_cut) continue;
                     last_cut = cut;
@@ -2032,16 +2030,53 @@ GroupPlan make_small_plan(const GemmArgs* g, int n, int forced, double* beside) 
     return best;
 }
 
+// Time of a group of few rows on a plan of a tile by turns, weights from memory.  A k-step is as long as its rows take and as its bytes do:
+// {us of a k-step without rows, what 128 rows add, bytes per us of the chip}; the two do not quite hide each other, hence the fourth powers.  The
+// sums read share after share.  Fitted to 847 launches of 280 groups (8 to 128 rows, 256 / 32 to 12288 / 12288): 4.5 % root mean square off,
+// where the estimate of make_pp_plan, which ranks the plans of a tile, is 9 to 11.
+double few_rows_us(const GemmArgs* g, int n, const GroupPlan& p) {
+    struct Rate { double step_us, rows_us, bytes_per_us; };
+    constexpr Rate RATES[] = {{0.37, 0.19, 6.0e6}, {0.23, 0.11, 5.5e6}, {0.235, 0.175, 5.9e6}};
+    static_assert(sizeof(RATES) / sizeof(RATES[0]) == WIDE_TILE + 1, "in the order of GROUP_TILES");
+    constexpr double WG_US = 11.2, START_US = 6.6, SHARE_US = 0.25, SUM_BYTES_PER_US = 3.6e6;
+    const Rate& r = RATES[p.tile];
+    double mem_us = START_US, sums_us = 0, len[JOB_MAX];
+    int64_t count[JOB_MAX];
+    int shares = 0;
+    for (int i = 0; i < n; ++i) mem_us += 2.0 * ((double)g[i].M * g[i].K + (double)g[i].N * g[i].K + (double)g[i].M * g[i].N) / r.bytes_per_us;
+    for (int j = 0; j < p.njobs; ++j) {
+        const PPJob& job = p.job[j];
+        const int64_t rows = g[job.gemm].M;
+        count[j] = (int64_t)job.count * job.shares;
+        len[j] = job.nk * (r.step_us + r.rows_us * (double)rows / FEW_TOKENS) + WG_US;
+        if (job.shares == 1) continue;
+        shares = std::max(shares, job.shares);
+        sums_us += (double)count[j] * (4.0 * ((rows + 15) / 16 * 16) * GROUP_TILES[p.tile].bn) / SUM_BYTES_PER_US;
+    }
+    const double list_us = list_time(compute_units(), p.njobs, count, len, INFINITY);
+    return std::sqrt(std::sqrt(std::pow(list_us, 4) + std::pow(mem_us, 4))) + sums_us + shares * SHARE_US;
+}
+// Whether a group goes out on `wide` (128 x 256) instead of `other`, put at `other_us` by the estimates that chose it.  Only in one round: the
+// few workgroups of a second one request little of what memory could give (8 rows of {up, qkv} of 11840 / 11840, 324 workgroups, 349 us on 256 x 256
+// and 380).  Against tiles by turns a lead of 3 %; the small tiles, put at up to 25 % more than they take where rows are few, need one of 25 %.
+// Over 207 groups of 14 us and more, weights from memory / in cache: 2.4 / 3.2 % less time than without the tile, two / three groups more than 2 % slower;
+// by make_pp_plan's estimates alone, in place of 256 x 128, it was 1.9 / 1.7 %, and 26 / 28 up to 12 / 19 % slower (8 rows of {down, out} of 3136 / 3136
+// 26.9 and 30.2 us, forward of 2 tokens of 3648 / 1824 52 and 58).  100 tokens of 12288 / 1536, {up, qkv} and {down, out} without the sums of
+// their shares: 256 x 128 69 and 68 us, 256 x 256 65 and 51, this 61 and 43.
+bool takes_wide_tile(const GemmArgs* g, int n, const GroupPlan& wide, const GroupPlan& other, double other_us) {
+    int64_t workgroups = 0;
+    for (int j = 0; j < wide.njobs; ++j) workgroups += (int64_t)wide.job[j].count * wide.job[j].shares;
+    return workgroups <= compute_units() && few_rows_us(g, n, wide) < (GROUP_TILES[other.tile].turns ? few_rows_us(g, n, other) / 1.03 : other_us / 1.25);
+}
+
 GroupPlan make_group_plan(const GemmArgs* g, int n) {
     const int forced = n == 1 ? 256 : options().gemm_group;       // one GEMM: see by_turns
     double us = INFINITY;
     GroupPlan best = make_small_plan(g, n, forced, &us);
     const bool weight_grads = std::any_of(g, g + n, [](const GemmArgs& a) { return a.trans_a != 0; });
-    const bool few_rows = std::all_of(g, g + n, [](const GemmArgs& a) { return a.M <= FEW_TOKENS && !a.trans_a; });
-    const int left_out = few_rows ? HALF_TILE : HALF_TILE + 1;
     for (int t = 0; t < GROUP_TILE_COUNT; ++t) {
         const GroupTile& gt = GROUP_TILES[t];
-        if (!gt.turns || (forced > 0 ? forced != gt.option : t == left_out)) continue;
+        if (!gt.turns || (forced > 0 ? forced != gt.option : t == WIDE_TILE)) continue;
         const GroupPlan p = make_pp_plan(g, n, gt, us);
         int64_t workgroups = 0;
         for (int i = 0; i < p.njobs; ++i) workgroups += (int64_t)p.job[i].count * p.job[i].shares;
@@ -2049,6 +2084,11 @@ GroupPlan make_group_plan(const GemmArgs* g, int n) {
         for (int i = 0; i < p.njobs; ++i) at_once &= p.job[i].shares == 1;
         const double put_at = p.us * (weight_grads && !at_once ? TURNS_LEAD : 1.0);
         if (put_at < us) { best = p; best.tile = t; us = put_at; }
+    }
+    if (forced <= 0 && std::all_of(g, g + n, [](const GemmArgs& a) { return a.M <= FEW_TOKENS && !a.trans_a; })) {
+        GroupPlan p = make_pp_plan(g, n, GROUP_TILES[WIDE_TILE], INFINITY);
+        p.tile = WIDE_TILE;
+        if (takes_wide_tile(g, n, p, best, us)) best = p;
     }
     return best;
 }
