@@ -916,9 +916,17 @@ __device__ __forceinline__ void attn_dkv_body(char* smem, const bf16_t* __restri
         float* pp = pslot + (DK_ROLE ? 0 : BLK * DH) + (j - kb * BLK) * DH;
         auto d_of = [&](int i) {
             if (!OWN_D) return drow[i];
-            float d = 0.0f;
-            for (int c = 0; c < dh; ++c) d = fmaf((float)dobase[(int64_t)i * ldo + c], (float)obase[(int64_t)i * ldo + c], d);
-            return d;
+            float d[8];                                   // added in the order of write_d: the same D as in the tiles
+#pragma unroll
+            for (int c = 0; c < 8; ++c) {
+                d[c] = 0.0f;
+#pragma unroll
+                for (int q = 0; q < OCH; ++q) {
+                    const int64_t at = (int64_t)i * ldo + (c + 8 * q) * 8;
+                    if ((c + 8 * q) * 8 < dh) d[c] += dot8(*reinterpret_cast<const bf16x8*>(obase + at), *reinterpret_cast<const bf16x8*>(dobase + at));
+                }
+            }
+            return ((d[0] + d[1]) + (d[2] + d[3])) + ((d[4] + d[5]) + (d[6] + d[7]));
         };
         attn_row_dkv<(DH + 63) / 64>(k_s, k_s + DH, qbase, ld, dobase, ldo, lrow, d_of, dh, max(CAUSAL ? j : 0, qt0 * TILE), min(S, ntiles * TILE),
                                scale, lane, [&](int d, float dk, float dv) {
