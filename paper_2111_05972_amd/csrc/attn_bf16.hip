@@ -1847,17 +1847,26 @@ static bool own_rows(int dh, bool causal, bool bwd, int64_t n, int steps) {
     return n > cus || steps <= (dh == 64 ? 12 : 5);
 }
 
-// Whether the workgroups of attn_bwd_kernel work D out for themselves, so that the row-dot kernel and its 2 to 3 us are not launched.  A
-// dQ workgroup does it once; one of dK/dV for every tile, between the barrier that hands the tile over and the first product: 0.1 to 0.2 us a
-// tile step at head size 64, 0.3 at 128.  So up to 16 steps to a unit, 12 above head size 64.  Whole calls (attention alone, forward included,
-// unless in a step), us, kernel of its own and without: head size 64 causal 12 heads of 512 x 4 / 1024 / 2048 33.3 and 31.7 / 40.9 and 39.6 /
-// 72.4 and 74.0, 8 of 4096 135 and 140; 4 of 512 x 8 in a step 167.3 and 164.9; 80: 12 of 512 x 4 53.4 and 52.3, 1024 (16 steps) 66.9 and
-// 66.8, 1024 x 2 83.1 and 83.6; 128: 6 of 127 x 2 23.6 and 21.8, 2 of 505 x 10 in a step 153.4 and 150.7, 19 of 337 x 8 (11 steps) level, 22
-// of 1004 x 5 causal (29) 233.7 and 238.1, 12 of 8192 causal (198) 958 and 1011.
-static bool own_dsum(int DH, bool causal, int S, int BH, ChunkLen ch) {
+// Whether the workgroups (n) of attn_bwd_kernel work D out for themselves, so that the row-dot kernel and its 2 us are not launched.  A dQ
+// workgroup does it once, one of dK/dV for every tile, between the barrier that hands the tile over and the first product: 0.1 to 0.2 us a
+// tile step at head size 64, 0.3 at 128.  Lines, each with both sides measured, us, kernel of its own and without:
+// - up to 16 steps to a unit, 12 above head size 64.  Forward and backward, 40: 25 heads of 810 80.7 and 79.5, 8 of 1467 85.7 and 86.6; 64: 23 of
+//   1002 causal 53.4 and 48.6; 8: 18 of 1746 106.4 and 107.5; 128: 5 of 685 47.5 and 45.9, 20 of 1268 108.0 and 109.8; 96: 28 of 805 101.3 and 102.0.
+// - up to 4 workgroups to a unit, 6 up to head size 64, 16 up to 32: a workgroup of few tiles is mostly its start, which D makes longer, and many of
+//   them share the kernel's launch.  Backward alone, 128: heads of 64 tokens 512 / 1024 / 4096 37.6 and 36.8 / 70.1 and 72.2 / 294 and 320, 192 of
+//   256 causal 53.8 and 51.9, 768 of 192 causal 153 and 160; 40: of 64 causal 512 / 1024 / 4096 26.5 and 25.9 / 52.6 and 53.4 / 185 and 195; 32: of 32
+//   2048 / 4096 37.6 and 37.0 / 68.4 and 70.1.
+// - above head size 64, where strips of 7 tiles and more stay whole, no last round up to a third full, which the lone workgroups' longer steps
+//   make longer, and without a mask no third round.  Backward alone, 128: 512 tokens, 32 / 40 / 48 heads 28.0 and 26.4 / 35.9 and 37.4 / 44.0 and
+//   42.9, causal 40 / 48 30.0 and 31.8 / 34.1 and 33.3, 576 tokens 48 / 56 48.8 and 48.2 / 64.5 and 65.6.
+static bool own_dsum(int DH, bool causal, int S, int BH, ChunkLen ch, int64_t n) {
+    const int cus = compute_units(), tiles = (S + TILE - 1) / TILE;
     int64_t steps = 0;
     for (int blk = 0; blk < (S + BLK - 1) / BLK; ++blk) steps += strip_tiles(causal, true, S, blk);
-    return std::max((int64_t)std::min(ch.ch, (S + TILE - 1) / TILE), steps * BH / compute_units()) <= (DH <= 64 ? 16 : 12);
+    if (std::max((int64_t)std::min(ch.ch, tiles), steps * BH / cus) > (DH <= 64 ? 16 : 12)) return false;
+    if (n > (int64_t)(DH <= 32 ? 16 : DH <= 64 ? 6 : 4) * cus) return false;
+    if (DH <= 64 || n <= cus || tiles < 7 || ch.ch < tiles) return true;
+    return (n - 1) % cus >= cus / 3 && (causal || n <= 2 * cus);
 }
 
 template <int DH, bool CAUSAL, bool FLOATW>
@@ -1921,7 +1930,7 @@ static hipError_t bwd_t(const AttnArgs& a) {
     float* part_q = static_cast<float*>(a.ws);
     float* part_kv = a.ws ? reinterpret_cast<float*>(static_cast<char*>(a.ws) + bytes_q) : nullptr;
     const bool rows = OWN_ROWS && own_rows(DH, CAUSAL, true, wgs_kv + wgs_q, 0);
-    const bool own_d = !rows && own_dsum(DH, CAUSAL, a.S, BH, ch_kv);
+    const bool own_d = !rows && own_dsum(DH, CAUSAL, a.S, BH, ch_kv, wgs_kv + wgs_q);
     if (!own_d) {
         const int64_t lanes = (int64_t)a.B * a.S * a.nl * (DH <= 32 ? 4 : DH == 64 ? 8 : 16);
         hipLaunchKernelGGL((attn_dsum_kernel<DH>), dim3((unsigned)((lanes + 255) / 256)), dim3(256), 0, a.stream,
