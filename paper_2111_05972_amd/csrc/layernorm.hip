@@ -59,11 +59,22 @@ template <> struct Raw8<bf16_t> {
 };
 
 // y and dz are not read again by these kernels.  With the non-temporal hint their lines go to memory while rows are still being worked on;
-// without it the last few MB per L2 stay until the kernel's end has to wait for them.  Forward and backward, us, without and with: bf16
-// 2048 x 12288 79.7 and 78.5, 16384 x 1024 57.8 and 54.0, 1673 x 4256 34.5 and 30.3, 2400 x 16384 138 and 129.5, float 5623 x 552 27.4
-// and 25.6, 3000 x 8192 (98 MB a tensor) 148 and 141, but 4096 x 8192 (134 MB) 196 and 201, 8192 x 4096 185.6 and 187: only up to 100 MB.
+// without it the last few MB per L2 stay until the kernel's end has to wait for them.  The GEMM that reads y or dz next then finds less of it in
+// cache, so that the hint is for tensors where a call gains more than the GEMM loses.  Forward and backward alone, us, without and with: bf16
+// 2048 x 12288 79.7 and 78.5, 16384 x 1024 57.8 and 54.0, 2400 x 16384 138 and 129.5, float 5623 x 552 27.4 and 25.6, 3000 x 8192 (98 MB a
+// tensor) 148 and 141, but 4096 x 8192 (134 MB) 196 and 201, 8192 x 4096 185.6 and 187: only up to 100 MB.  Below 8 MB in bf16, 2 MB in float a
+// call alone gains nothing (312 x 4096 16.9 and 16.8).  With the shard's forward behind y, backward behind dz, us:
+//   bf16 5520 x 1024 / 8 71.6 and 70.1, 117.5 and 116.4; 3020 x 1024 / 8 (6.2 MB) 54.3 and 55.8, 93.8 and 95.0; 312 x 4096 / 8 61.7 and 63.0, 88.7
+//   and 90.2; float 4436 x 512 / 8 89.5 and 88.5, 177.2 and 175.7; 1396 x 512 / 8 (2.9 MB) 44.6 and 44.3, 75.9 and 75.5
+//   y of fewer rows in bf16, whose GEMMs are too short to make up for their first reads: 1035 x 4096 / 8 106.5 and 112.5, 825 x 8192 / 8 215.6 and
+//   221.9, 1886 x 5120 / 8 192 and 197; from 2048 rows on level: 2048 x 4096 / 8 143.1 and 142.9, 2048 x 12288 / 8 762 and 761
+//   dz of them: 933 x 7680 / 8 386.5 and 387.9, 1040 x 4096 / 2 and 1244 x 4096 / 8 level
 // z, which backward reads back, is faster kept: 78.5 and 82.2 at 2048 x 12288.
-template <typename T> static bool streams(const LnArgs& a) { return a.M * a.H * (int64_t)sizeof(T) <= 100000000; }
+template <typename T> static bool streams(const LnArgs& a, bool fwd) {
+    const int64_t bytes = a.M * a.H * (int64_t)sizeof(T);
+    if (bytes > 100000000) return false;
+    return sizeof(T) == 4 ? bytes >= 2000000 : bytes >= 8000000 && (!fwd || a.M >= 2048);
+}
 template <bool NT, typename T> __device__ __forceinline__ void store_row(T* p, const float (&v)[8]) {
     if (NT) store8_nt(p, v);
     else store8(p, v);
@@ -570,7 +581,7 @@ size_t ln_scratch_bytes(int64_t M, int64_t H) { return (size_t)ln_bwd_groups(M) 
 template <typename T, int C, int THREADS, bool EARLY>
 static hipError_t launch_fwd(const LnArgs& a) {
     const unsigned grid = (unsigned)(a.M < 65535 * 16 ? a.M : 65535 * 16);
-    const auto kernel = streams<T>(a) ? &ln_fwd_kernel<T, C, THREADS, EARLY, true> : &ln_fwd_kernel<T, C, THREADS, EARLY, false>;
+    const auto kernel = streams<T>(a, true) ? &ln_fwd_kernel<T, C, THREADS, EARLY, true> : &ln_fwd_kernel<T, C, THREADS, EARLY, false>;
     hipLaunchKernelGGL(kernel, dim3(grid), dim3(THREADS), 0, a.stream, a.M, a.H, (const T*)a.a, (const T*)a.b,
                        (const T*)a.gamma, (const T*)a.beta, a.eps, (T*)a.z, (T*)a.y, a.mean, a.rstd);
     return hipGetLastError();
@@ -602,7 +613,7 @@ static hipError_t bwd_t(const LnArgs& a) {
     // 2 -> 41 us, 3 and 4 -> 42 us for both kernels together (the compiler drains the whole ring once per DEPTH rows).
     constexpr int DEPTH = (sizeof(T) == 2 && MAXC <= 6) ? 2 : 1;   // the widest rows have no registers left for two
     constexpr int THREADS = MAXC > 2 ? 512 : LN_THREADS, CHUNKS = MAXC > 2 ? MAXC / 2 : MAXC;
-    const auto kernel = streams<T>(a) ? &ln_bwd_fused_kernel<T, CHUNKS, THREADS, DEPTH, true> : &ln_bwd_fused_kernel<T, CHUNKS, THREADS, DEPTH, false>;
+    const auto kernel = streams<T>(a, false) ? &ln_bwd_fused_kernel<T, CHUNKS, THREADS, DEPTH, true> : &ln_bwd_fused_kernel<T, CHUNKS, THREADS, DEPTH, false>;
     hipLaunchKernelGGL(kernel, dim3((unsigned)groups), dim3(THREADS), 0, a.stream, a.M, a.H, (const T*)a.dy, (const T*)a.z, a.mean, a.rstd,
                        (const T*)a.gamma, (T*)a.dz, part);
     hipError_t e = hipGetLastError();
@@ -621,7 +632,7 @@ static hipError_t fwd_wave_t(const LnArgs& a) {
     constexpr int64_t ROWS = LN_THREADS / 64;
     const int64_t want = (a.M + ROWS - 1) / ROWS;
     const unsigned grid = (unsigned)(want < 65535 * 16 ? want : 65535 * 16);
-    const auto kernel = streams<T>(a) ? &ln_fwd_wave_kernel<T, MAXC, true> : &ln_fwd_wave_kernel<T, MAXC, false>;
+    const auto kernel = streams<T>(a, true) ? &ln_fwd_wave_kernel<T, MAXC, true> : &ln_fwd_wave_kernel<T, MAXC, false>;
     hipLaunchKernelGGL(kernel, dim3(grid), dim3(LN_THREADS), 0, a.stream, a.M, a.H,
                        (const T*)a.a, (const T*)a.b, (const T*)a.gamma, (const T*)a.beta, a.eps, (T*)a.z, (T*)a.y, a.mean,
                        a.rstd);
@@ -632,7 +643,7 @@ static hipError_t bwd_wave_t(const LnArgs& a) {
     const int64_t want = (a.M + LN_WAVE_ROWS - 1) / LN_WAVE_ROWS;
     const int64_t groups = want < LN_BWD_GROUPS ? want : LN_BWD_GROUPS;      // at most the rows of the partial sums
     constexpr int DEPTH = MAXC * sizeof(T) <= 4 ? 4 : 2;                     // 32 to 64 registers of rows in flight
-    const auto kernel = streams<T>(a) ? &ln_bwd_wave_kernel<T, MAXC, DEPTH, true> : &ln_bwd_wave_kernel<T, MAXC, DEPTH, false>;
+    const auto kernel = streams<T>(a, false) ? &ln_bwd_wave_kernel<T, MAXC, DEPTH, true> : &ln_bwd_wave_kernel<T, MAXC, DEPTH, false>;
     hipLaunchKernelGGL(kernel, dim3((unsigned)groups), dim3(64 * LN_WAVE_ROWS), 0, a.stream, a.M,
                        a.H, (const T*)a.dy, (const T*)a.z, a.mean, a.rstd, (const T*)a.gamma, (T*)a.dz, a.partials);
     hipError_t e = hipGetLastError();
