@@ -159,15 +159,18 @@ def bench_memopt(args, cfg, dt, pkg, torch, synthetic):
         torch.cuda.synchronize()
         tms = pkg.tp_layer_profile_read()
         pkg.tp_layer_profile(0)
-        assert len(tms) == 12 * reps, len(tms)
-        per = [sum(tms[i::12]) / reps for i in range(12)]
-        fl = [2.0 * g[1] * g[2] * g[3] for g in gl]
+        # in backward a linear's data and weight gradient go out as one group, with one record
+        out = [gl[i:i + 1] for i in range(4)] + [gl[i:i + 2] for i in range(4, 12, 2)]
+        n = len(out)
+        assert len(tms) == n * reps, len(tms)
+        per = [sum(tms[i::n]) / reps for i in range(n)]
+        fl = [sum(2.0 * g[1] * g[2] * g[3] for g in gs) for gs in out]
         ach = sum(fl) / (sum(per) * 1e-3) / 1e12
-        roofline = {"kernel": "gemm_bf16 kernels (12 launches per step)", "bound": "mfma", "achieved": round(ach, 2),
+        roofline = {"kernel": f"gemm_bf16 kernels ({n} launches per step)", "bound": "mfma", "achieved": round(ach, 2),
                     "peak": BF16_PEAK_TFLOPS, "unit": "TFLOP/s", "frac": round(ach / BF16_PEAK_TFLOPS, 4), "traffic": None,
                     "gemm_ms_per_step": round(sum(per), 4),
-                    "launches": {g[0]: {"M": g[1], "N": g[2], "K": g[3], "ms": round(t, 4),
-                                        "tflops": round(f / t / 1e9, 1)} for g, t, f in zip(gl, per, fl)}}
+                    "launches": {"+".join(g[0] for g in gs): {"MxNxK": ["x".join(map(str, g[1:])) for g in gs], "ms": round(t, 4),
+                                                              "tflops": round(f / t / 1e9, 1)} for gs, t, f in zip(out, per, fl)}}
     cpu_baseline, err = None, None
     if not args.no_cpu_baseline:
         step()
