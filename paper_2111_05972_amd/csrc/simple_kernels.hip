@@ -282,12 +282,13 @@ __global__ __launch_bounds__(256) void colsum_stage2(int64_t slabs, int64_t N, c
     if (gl == 0 && n < N) out[n] = from_f32<T>(((red[0][cl] + red[1][cl]) + red[2][cl]) + red[3][cl]);
 }
 
-// Both stages in one launch where a matrix is small: a workgroup sums 32 columns over all rows, four threads a row, 128 rows at a time, eight
-// rows of a thread in flight; the 128 row lanes are combined through LDS in a fixed tree.  What bounds such a launch is its start and end, two
-// to three us whatever it computes, and what a unit reads by itself: up to 1024 rows and 8 MB.  A call of both stages takes 10.5 us one after
-// another from a host that enqueues them one by one, this 7.5 (64 x 512 to 2048 x 3840); local compute of a rank with five such sums, us, both
-// stages and this: 432 tokens of 512 / 4 239 and 217, 256 of 1536 / 4 240 and 219, 144 of 7680 / 4 657 and 644.  More rows: 3184 of 512 / 2 270
-// and 274; more bytes: 2048 x 8192 (33 MB) 10.3 and 12.2 a call.
+// Both stages in one launch where a matrix is small: a workgroup sums 32 columns over all rows, four threads a row, 128 rows at a time; a thread
+// adds its rows one after another, with eight of them requested at once only where it has eight (from 897 rows on).  The 128 row lanes are combined
+// through LDS in a fixed tree.  What bounds such a launch is its start and end, two to three us whatever it computes, and what a unit reads by
+// itself: up to 1024 rows and 8 MB.  Back to back, matrix in cache, us, both stages and this: 100 x 1024 5.2 and 3.3, 512 x 3840 5.5 and 3.8,
+// 1024 x 3840 5.6 and 4.0, but 1280 x 8192 (21 MB) 6.1 and 9.1; local compute of a rank with five such sums: 72 tokens of 1024 / 4 147.4 and 139.8, 520 of
+// 5120 / 8 383 and 375, 832 of 640 / 2 209.9 and 205.0.  The line is on the safe side: beyond it 1376 of 512 / 8 200.2 and 195.2, 1560 of 1024 / 8 230.7
+// and 227.0, 2048 of 1024 / 4 265.5 and 264.4, 2048 of 5120 / 4 1149 and 1152, 3384 of 1024 / 8 283.5 and 287.3, 3912 of 256 / 4 235.0 and 240.3.
 constexpr int CO_COLS = 32, CO_ROWS = 128;
 template <typename T>
 __global__ __launch_bounds__(512) void colsum_once(int64_t M, int64_t N, const T* __restrict__ X, T* __restrict__ out) {
