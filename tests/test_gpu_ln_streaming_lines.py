@@ -42,3 +42,28 @@ def test_hint(dtype, M, H, fwd, bwd):
     ref = (dx - dx.mean(1, keepdim=True) - xh * (dx * xh).mean(1, keepdim=True)) / (zz.var(1, unbiased=False, keepdim=True) + 1e-5).sqrt()
     for got, want in ((y, xh * gm + beta.double()), (dz, ref), (dgamma, (d * xh).sum(0)), (dbeta, d.sum(0))):
         assert ((got.double() - want).abs().max() / want.abs().max()).item() <= tol
+
+
+@pytest.mark.parametrize("M,H", [(7900, 512), (4000, 1024), (2500, 4104)])
+def test_rows_are_the_same_on_both_sides(M, H):
+    import torch
+    import paper_2111_05972_amd as pkg
+    td, st = torch.bfloat16, torch.cuda.current_stream()
+    assert M * H * 2 >= 8_000_000 and M >= 2048
+    print(f"\n[ln] bf16 {M} x {H}", flush=True)
+    g = torch.Generator(device="cuda").manual_seed(6)
+    a, b, dy = (torch.randn(M, H, generator=g, device="cuda").to(td) for _ in range(3))
+    gamma, beta = (torch.randn(H, generator=g, device="cuda").to(td) for _ in range(2))
+    got = []
+    for rows in (M, 1600):                          # with the hint on y, and without
+        z, y, dz = (torch.full((rows, H), float("nan"), dtype=td, device="cuda") for _ in range(3))
+        mean, rstd = (torch.empty(rows, device="cuda") for _ in range(2))
+        dgamma, dbeta = torch.empty_like(gamma), torch.empty_like(beta)
+        ws = torch.empty(pkg.tp_layer_ln_workspace_bytes(rows, H), dtype=torch.uint8, device="cuda")
+        pkg.tp_layer_ln_fwd(pkg.TPL_BF16, rows, H, a[:rows], b[:rows], gamma, beta, 1e-5, z, y, mean, rstd, stream=st)
+        pkg.tp_layer_ln_bwd(pkg.TPL_BF16, rows, H, dy[:rows], z, mean, rstd, gamma, dz, dgamma, dbeta, ws, stream=st)
+        torch.cuda.synchronize()
+        assert not torch.isnan(y).any() and not torch.isnan(dz).any()
+        got.append((z, y, dz, mean, rstd))
+    for whole, part in zip(*got):
+        assert torch.equal(whole[:1600], part)
