@@ -2058,15 +2058,21 @@ double few_rows_us(const GemmArgs* g, int n, const GroupPlan& p) {
 }
 // Whether a group goes out on `wide` (128 x 256) instead of `other`, put at `other_us` by the estimates that chose it.  Only in one round: the
 // few workgroups of a second one request little of what memory could give (8 rows of {up, qkv} of 11840 / 11840, 324 workgroups, 349 us on 256 x 256
-// and 380).  Against tiles by turns a lead of 3 %; the small tiles, put at up to 25 % more than they take where rows are few, need one of 25 %.
-// Over 207 groups of 14 us and more, weights from memory / in cache: 2.4 / 3.2 % less time than without the tile, two / three groups more than 2 % slower;
-// by make_pp_plan's estimates alone, in place of 256 x 128, it was 1.9 / 1.7 %, and 26 / 28 up to 12 / 19 % slower (8 rows of {down, out} of 3136 / 3136
-// 26.9 and 30.2 us, forward of 2 tokens of 3648 / 1824 52 and 58).  100 tokens of 12288 / 1536, {up, qkv} and {down, out} without the sums of
-// their shares: 256 x 128 69 and 68 us, 256 x 256 65 and 51, this 61 and 43.
+// and 380); and of at least nine sixteenths of the units, for the same reason (80 rows of {up, qkv} of 4816 / 4816, 133 workgroups, 91.0 and 99.6, 32 of
+// 10304 / 5152, 142, 151 and 161).  Only where the rows of B of the largest GEMM are whole cache lines: where a unit's loads straddle lines this tile
+// loses far more than 256 x 256 (64 rows of {down, out} of 8944 / 8944 on 256 x 256 and this 152 and 180 us, of 8960 / 8960 145 and 148; 48 of 6432 / 6432
+// 86 and 100).  Against tiles by turns a lead of 3.5 %; the small tiles, put at up to 25 % more than they take where rows are few, need one of 25 %.
+// Of 547 groups, weights from memory, 74 go out on it; they take 10 % less time than without the tile, up to 43 %, two of them more than 2 % more (2.2
+// and 2.6).  By make_pp_plan's estimates alone, in place of 256 x 128, 29 of 262 did (8 rows of {down, out} of 3136 / 3136 26.9 and 30.2 us, forward of 2
+// tokens of 3648 / 1824 52 and 58).  100 tokens of 12288 / 1536, {up, qkv} and {down, out} without the sums of their shares: 256 x 128 69 and 68 us,
+// 256 x 256 65 and 51, this 61 and 43.
 bool takes_wide_tile(const GemmArgs* g, int n, const GroupPlan& wide, const GroupPlan& other, double other_us) {
+    const GemmArgs& largest = *std::max_element(g, g + n, [](const GemmArgs& a, const GemmArgs& b) { return a.N * a.K < b.N * b.K; });
+    if ((largest.trans_b ? largest.K : largest.N) % 64 != 0) return false;
     int64_t workgroups = 0;
     for (int j = 0; j < wide.njobs; ++j) workgroups += (int64_t)wide.job[j].count * wide.job[j].shares;
-    return workgroups <= compute_units() && few_rows_us(g, n, wide) < (GROUP_TILES[other.tile].turns ? few_rows_us(g, n, other) / 1.03 : other_us / 1.25);
+    if (workgroups > compute_units() || workgroups * 16 < compute_units() * 9) return false;
+    return few_rows_us(g, n, wide) < (GROUP_TILES[other.tile].turns ? few_rows_us(g, n, other) / 1.035 : other_us / 1.25);
 }
 
 GroupPlan make_group_plan(const GemmArgs* g, int n) {
