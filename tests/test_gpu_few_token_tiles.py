@@ -31,7 +31,7 @@ def _on_wide_tiles(items, tune):
     return need[None] == need["512"] and need["512"] not in [need[o] for o in ("256", "384", "128", "64")]
 
 
-@pytest.mark.parametrize("hidden,seq", [(3072, 8), (3584, 64)])
+@pytest.mark.parametrize("hidden,seq", [(3712, 32), (3584, 64)])
 def test_forward_that_takes_them(hidden, seq, tune):
     assert all(_on_wide_tiles(g, tune) for g in _groups(seq, hidden, hidden, 4 * hidden).values())
     print(f"\n[case] {seq} tokens of {hidden}", flush=True)
