@@ -465,13 +465,14 @@ using F32Tile128 = F32Tile<2, 2, 2, 2, 1, 2>;
 using F32Tile64 = F32Tile<2, 2, 1, 1, 1, 3>;
 using F32Tile32 = F32Tile<1, 1, 1, 1, 4, 4>;
 // The 64-wide tile with two stages instead of three: four workgroups share a unit instead of three (32 KB of LDS instead of 48), so that with
-// at least six and a half to a unit one's start, barriers and epilogue have three others beside them.  Whole steps, us, three stages and two: 4115
-// tokens of 1024 / 512 1662 and 1613, 3260 of 768 / 384 725 and 687, 6349 of 512 / 64 266.9 and 262.2, 1136 of 1792 / 1792 2315 and 2242; with
-// fewer the last of a unit runs at a lone workgroup's pace on half the loads: 3563 of 448 / 224 (3.1 to 5.5 to a unit) 363 and 368 on two stages.  At six
-// to a unit three at a time leave no rest and four leave two: launches of 6.04 and 6.25 to a unit 61.4 and 63.8, 90.2 and 91.2, though 6.09 to 6.48
-// with longer K are 3 to 10 % faster on two stages; from 6.5 on, 58 launches 0.3 % slower to 9.6 % faster.
+// at least six to a unit one's start, barriers and epilogue have three others beside them.  Whole steps, us, three stages and two: 4115 tokens
+// of 1024 / 512 1662 and 1613, 3260 of 768 / 384 725 and 687, 6349 of 512 / 64 266.9 and 262.2, 1136 of 1792 / 1792 2315 and 2242; with fewer
+// the last of a unit runs at a lone workgroup's pace on half the loads: 3563 of 448 / 224 (3.1 to 5.5 to a unit) 363 and 368 on two stages.  Launches of
+// 6 to 6.5 to a unit: 33 without weight gradients 3 to 9 % faster on two stages; of 53 with them, long beside short, 42 up to 9 % faster and 11 up to
+// 3.7 % slower, as the last workgroups of a unit happen to fall (2700 tokens of 1024 / 128 314.6 and 317.1 a step); from 6.5 on, one of 61
+// launches 2.9 % slower, the others 0.3 % slower to 9.6 % faster.
 using F32Tile64Four = F32Tile<2, 2, 1, 1, 1, 2>;
-constexpr double F32_FOUR_MIN = 6.5;            // workgroups per unit
+constexpr int F32_FOUR_MIN = 6;                 // workgroups per unit
 namespace {
 struct F32GroupTile { int bm; double step_us, wg_us, alone_us; };
 constexpr F32GroupTile F32_GROUP_TILES[] = {{128, 1.95, 3.0, 2.2}, {64, 0.50, 1.0, 0.65}, {32, 0.15, 0.5, 0.45}};
